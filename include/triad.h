@@ -16,7 +16,11 @@
  * this edge (v < w, or u < w < v with w not adjacent to u); the edge adds
  * n - |N(u) u N(v)| triads to 012 (asymmetric u-v) or 102 (mutual u-v)
  * (steps 2.1.2-2.1.3); 003 = C(n,3) minus the rest (steps 3-5). All counts
- * are exact integers; the kernels are hand-written HIP for gfx950.
+ * are exact integers; the kernels are hand-written HIP for gfx950. Where no
+ * option asks for the merge's work queue (a schedule, cycle or span recording,
+ * a launch shape), the same sums are formed without visiting the w that are
+ * adjacent to only one of u, v: these follow from each vertex's counts of
+ * out-, in- and mutual neighbours, and only the triangles are listed.
  *
  * Input graph (compact CSR of Sec. 6 / Fig. 7, direction bits kept in a
  * separate packed array):
@@ -82,14 +86,15 @@ enum triad_schedule {
 /* Device time of each stage of one census call, in milliseconds (HIP events
  * on the call's stream). */
 typedef struct triad_timing {
-  float prep_ms;     /* pack ids with direction bits + validation */
-  float tasks_ms;    /* task enumeration (scan) and scheduling */
-  float census_ms;   /* the merge/classify kernel */
+  float prep_ms;     /* validation; ids packed with direction bits, or edges directed by degree */
+  float tasks_ms;    /* task enumeration (scan) and scheduling, or sorting and work items */
+  float census_ms;   /* the merge/classify kernel, or the triangle kernels */
   float finalize_ms; /* reduction and the null count */
   int64_t tasks;     /* number of (u,v) tasks, u < v = symmetric edges */
-  int64_t hub_tasks; /* tasks split across several wavefronts */
+  int64_t hub_tasks; /* tasks split across several wavefronts (0 where triangles are listed) */
   int64_t items;     /* work items after splitting */
-  int64_t waves;     /* wavefronts of the persistent census launch */
+  int64_t waves;     /* wavefronts of the persistent merge launch: a later call that records
+                        wave spans with the same options writes that many */
 } triad_timing;
 
 /* Options (a zeroed struct gives the defaults). */

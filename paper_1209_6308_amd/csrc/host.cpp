@@ -26,6 +26,8 @@ bool take_injected_fault() {
   return false;
 }
 
+bool injected_fault_pending() { return g_inject.load() > 0; }
+
 // Held device blocks (see held_take): per device, free blocks by size. The
 // table is never destroyed, so that nothing calls into HIP during static
 // destruction at process exit (the blocks die with the process).

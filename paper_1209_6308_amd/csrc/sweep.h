@@ -1,0 +1,42 @@
+// The triangle-listing form of the census sweep (sweep.hip). Internal; not
+// part of the public ABI.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "triad_internal.h"
+
+namespace triad {
+
+// Device counters of one sweep (64-bit words, zeroed by sweep_begin):
+// acc[0..15] the 16 classes as signed sums (triangle classes exact, the open
+// and dyadic classes before the triangles' share is taken out), then
+constexpr int SW_MUT = 16;    // entries with both arcs (each mutual edge twice)
+constexpr int SW_ABOVE = 17;  // entries above their row's own id
+constexpr int SW_WORDS = 32;
+constexpr int SW_COPIES = 64;
+// err[0]: raised by the row checks, err[1]: by the entry checks, err[2]: later
+constexpr int SW_ERRS = 4;
+
+struct SweepIn {
+  int64_t n, nnz;
+  const int64_t* off;
+  const int32_t* nbr;
+  const uint8_t* flg;
+};
+
+// Enqueues the whole sweep of one graph on s: validation, orientation,
+// triangle counts and per-row sums. *acc (SW_COPIES copies of SW_WORDS words, to be summed) and *err (SW_ERRS
+// words) are its counters, in scratch memory. validate: also check symmetry.
+// ev (may be NULL): events 1, 2, 3 are recorded after the orientation, the
+// sorting and listing, and the counting.
+int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc, uint32_t** err, Scratch& scratch,
+                 hipEvent_t* ev, hipStream_t s);
+// The 16 counts and the high word of 003 into d_out unless an error is set;
+// status (device) gets the same 17 words and in word 17 the error bits.
+constexpr int SW_STATUS = 18;
+void sweep_finish(const unsigned long long* acc, uint32_t* err, int64_t nnz, int64_t n, uint64_t* d_out,
+                  uint64_t* status, hipStream_t s);
+
+}  // namespace triad

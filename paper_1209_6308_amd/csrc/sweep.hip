@@ -1,0 +1,1181 @@
+// The census by triangle listing: the Batagelj-Mrvar sums with the one-list
+// third vertices counted from row totals instead of visited.
+//
+// For every edge {u, v} the sweep of Fig. 5 visits N(u) u N(v). A third vertex
+// w adjacent to only one of u, v closes no triangle; over all edges these add
+// up to the open wedges, which follow from each vertex's counts of out-, in-
+// and mutual neighbours alone (an open wedge is a pair of neighbours of its
+// centre, less the pairs that are adjacent, which are the triangles'). Only
+// the third vertices adjacent to both are visited, each triangle once: edges
+// are directed from the vertex of lower to the one of higher degree (rank 0 =
+// highest degree), and for a vertex y the list N+(x) of every x below y is
+// streamed against the set N+(y). The merge reads sum_x d(x)^2 list entries
+// (3.57e12 at R-MAT scale 24), this reads sum_x d+(x)^2 / 2 (4.2e10). A whole
+// call took 1,560 ms there by the merge and takes 60 ms; 37.0 and 2.9 ms at
+// R-MAT scale 20, 472 and 16.7 ms on the Chung-Lu graph of 2^22 vertices, 575
+// and 140 us at R-MAT scale 10.
+//
+// Pipeline (one stream, no host synchronisation inside):
+//   k_sw_rows    per row: offset checks, row starts, degree histogram
+//   k_sw_rank    rank of each vertex by a counting sort on its degree
+//   k_sw_orient  per tile of 4,096 entries: entry checks; each row split in
+//                place into N+(x) (ranks and flags) and its in-list (the x
+//                below it, ids and flags); per-row flag counts turned into
+//                wedge and dyad sums
+//   k_sw_cross   the rows that cross tile boundaries
+//   k_sw_sort_*  N+(x) sorted by rank where it is longer than one wavefront
+//   k_sw_items   work items of the next two
+//   k_sw_hubs    vertices with long in-lists: a workgroup holds N+(y) as a
+//                byte table over the ranks and streams the N+(x)
+//   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
+//   k_sw_rest    all others: one wavefront and a small table in LDS
+//   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "sweep.h"
+
+namespace triad {
+namespace {
+
+constexpr int OT = 4096;  // entries of one orientation tile
+constexpr int OTHREADS = 256, OPER = OT / OTHREADS;
+constexpr int ROWS_THREADS = 1024, ROWS_PER = 16;
+constexpr int BUCKETS = 1024;          // degree buckets of the ranking
+constexpr int64_t DIRECT_N = 16384;    // graphs up to here index their tables by vertex id
+constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover
+constexpr int HUB_THREADS = 768;
+constexpr int64_t HUB_MIN_IN = 256;    // in-lists from here on: k_sw_hubs (ranks in its table)
+constexpr int MID_THREADS = 256;
+constexpr int64_t MID_MIN_IN = 32;     // in-lists from here on: k_sw_mids
+constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
+constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
+constexpr int TAB_WORDS = 1024;        // its slots; k_sw_rest<false>: words of 16 ids
+constexpr int REST_WAVES = 4;
+constexpr int64_t LIST_PAD = 4;        // list words read past a list's end
+constexpr uint32_t SORT_MIN = 64, SORT_MID = 256, SORT_MAX = 4096;
+
+// List words: id or rank in the low 30 bits, the direction flag in the top two.
+constexpr uint32_t ID_MASK = 0x3FFFFFFFu;
+constexpr uint32_t SLOT_FREE = 0xFFFFFFFFu;  // no id is 2^30 - 1
+// Row words: first entry << 24 | length of N+; the top bit of the length marks
+// a list that is not in rank order.
+constexpr uint32_t LEN_MASK = 0x7FFFFFu, UNSORTED = 0x800000u;
+
+__device__ __forceinline__ uint32_t rl(uint32_t x, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+__device__ __forceinline__ uint64_t rl64(uint64_t x, int lane) {
+  return ((uint64_t)rl((uint32_t)(x >> 32), lane) << 32) | rl((uint32_t)x, lane);
+}
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+__device__ __forceinline__ uint64_t sum64(uint64_t x) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+// Atomics on one cache line run one after another (88 ns each, measured with
+// 9,216 of them): the counters are kept in SW_COPIES copies, summed at the end.
+__device__ __forceinline__ unsigned long long* copy_of(unsigned long long* acc) {
+  return acc + (blockIdx.x % SW_COPIES) * SW_WORDS;
+}
+
+// Bucket of a degree, rising with it: exact below 32, then 32 steps an octave.
+__device__ __forceinline__ uint32_t degree_bucket(uint32_t d) {
+  if (d < 32) return d;
+  const uint32_t e = 31 - (uint32_t)__builtin_clz(d);
+  return ((e - 4) << 5) | ((d >> (e - 5)) & 31u);
+}
+
+__global__ void k_sw_zero(uint32_t* __restrict__ p, int64_t m) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) p[i] = 0;
+}
+
+// ------------------------------------------------------------ rows and ranks
+
+struct RowArgs {
+  int64_t n, nnz;
+  const int64_t* off;
+  uint32_t* deg;       // by id: the degree (tables indexed by id), or NULL
+  uint32_t* hist;      // degree buckets, highest degree first, or NULL
+  uint64_t* info;      // row words, N+ still empty
+  uint32_t* list;      // the first word of each row that has one: its id
+  uint32_t* mark;      // bit per entry: a row starts here
+  uint32_t* tile_row;  // row that holds each tile's first entry
+  uint32_t* err;
+};
+
+__global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
+  __shared__ uint32_t h[BUCKETS];
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * (ROWS_THREADS * ROWS_PER);
+  for (int i = 0; i < ROWS_PER; ++i) {
+    const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
+    if (u >= a.n) break;
+    const int64_t b = a.off[u], e = a.off[u + 1];
+    bool ok = true;
+    if ((u == 0 && b != 0) || (u == a.n - 1 && e != a.nnz)) ok = false;
+    if (e < b || b < 0 || e > a.nnz || e - b >= ((int64_t)1 << 31)) ok = false;
+    const uint32_t d = ok ? (uint32_t)(e - b) : 0;
+    if (!ok) atomicOr(a.err, ERR_RANGE);
+    a.info[u] = ok ? (uint64_t)b << 24 : 0;
+    if (a.deg) a.deg[u] = d;
+    if (a.hist) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
+    if (d) {
+      a.list[b] = (uint32_t)u;
+      atomicOr(&a.mark[b >> 5], 1u << (b & 31));
+      for (int64_t t = (b + OT - 1) / OT; t * OT < e; ++t) a.tile_row[t] = (uint32_t)u;
+    }
+  }
+  if (!a.hist) return;
+  __syncthreads();
+  if (h[threadIdx.x]) atomicAdd(&a.hist[threadIdx.x], h[threadIdx.x]);
+}
+
+// Ranks by a counting sort on the degree bucket, highest first; the order
+// within a bucket is free (any total order lists each triangle once).
+__global__ void __launch_bounds__(ROWS_THREADS) k_sw_rank(int64_t n, const int64_t* __restrict__ off,
+                                                          const uint32_t* __restrict__ hist,
+                                                          uint32_t* __restrict__ cursor, uint32_t* __restrict__ rank,
+                                                          const uint32_t* __restrict__ err) {
+  __shared__ uint32_t start[BUCKETS], cnt[BUCKETS], wsum[ROWS_THREADS / 64];
+  if (err[0]) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // exclusive prefix of the bucket counts
+  const uint32_t v = hist[threadIdx.x];
+  uint32_t x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  cnt[threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t add = 0;
+  for (int i = 0; i < w; ++i) add += wsum[i];
+  start[threadIdx.x] = x - v + add;
+  const int64_t base = (int64_t)blockIdx.x * (ROWS_THREADS * ROWS_PER);
+  uint32_t bk[ROWS_PER];
+  for (int i = 0; i < ROWS_PER; ++i) {
+    const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
+    bk[i] = BUCKETS;
+    if (u < n) {
+      bk[i] = BUCKETS - 1 - degree_bucket((uint32_t)(off[u + 1] - off[u]));
+      atomicAdd(&cnt[bk[i]], 1u);
+    }
+  }
+  __syncthreads();
+  if (cnt[threadIdx.x]) start[threadIdx.x] += atomicAdd(&cursor[threadIdx.x], cnt[threadIdx.x]);
+  __syncthreads();
+  for (int i = 0; i < ROWS_PER; ++i) {
+    const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
+    if (u < n) {
+      rank[u] = atomicAdd(&start[bk[i]], 1u);
+    }
+  }
+}
+
+// --------------------------------------------------------------- orientation
+
+// Sums of one row's neighbour counts (o: arcs out only, i: in only, m: both)
+// into class sums: pairs of neighbours by centre, and n - d(u) - d(v) per
+// edge (the n of a one-way edge taken at its tail, of a mutual one at the end).
+struct RowSums {
+  uint64_t c[9] = {};  // 012 102 021D 021U 021C 111D 111U 201, entries with both arcs
+  __device__ __forceinline__ void row(uint64_t n, uint64_t o, uint64_t i, uint64_t m) {
+    const uint64_t d = o + i + m;
+    c[0] += n * o - d * (o + i);
+    c[1] -= d * m;
+    c[2] += o * (o - 1) / 2;  // (o = 0: 0 * ... = 0)
+    c[3] += i * (i - 1) / 2;
+    c[4] += o * i;
+    c[5] += i * m;
+    c[6] += o * m;
+    c[7] += m * (m - 1) / 2;
+    c[8] += m;
+  }
+  static __device__ __forceinline__ int slot(int k) {
+    return k == 0 ? 1 : k == 1 ? 2 : k == 7 ? 10 : k == 8 ? SW_MUT : k + 1;
+  }
+  __device__ __forceinline__ void add_to(unsigned long long* acc, int lane) {
+    for (int k = 0; k < 9; ++k) {
+      const uint64_t s = sum64(c[k]);
+      if (lane == 0 && s) atomicAdd(&acc[slot(k)], (unsigned long long)s);
+    }
+  }
+};
+
+// Counters of a row that crosses tile boundaries, at the first tile that it
+// reaches into: entries placed so far, and the neighbour counts.
+struct Cross {
+  uint32_t f, b, o, i, m, pad[3];
+};
+
+struct OrientArgs {
+  int64_t n, nnz, ntiles;
+  const int64_t* off;
+  const int32_t* nbr;
+  const uint8_t* flg;
+  const uint32_t* key;  // rank (RANK) or degree, by row
+  const uint32_t* mark;
+  const uint32_t* tile_row;
+  uint32_t* list;
+  uint64_t* info;
+  Cross* cross;
+  uint32_t* mid;  // rows with N+ longer than SORT_MIN, than SORT_MID
+  uint32_t* lng;
+  uint32_t* counts;  // [0] of mid, [1] of lng
+  unsigned long long* acc;
+  uint32_t* err;
+};
+
+__device__ __forceinline__ uint64_t below(int k) { return (1ull << k) - 1; }  // k in [0, 63]
+
+template <bool RANK>
+__global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
+  __shared__ uint32_t at[OT];  // at a row start: the row, later its N+ length in the tile
+  __shared__ uint64_t heads[OT / 64 + 1], fwd[OT / 64 + 1], b0[OT / 64 + 1], b1[OT / 64 + 1];
+  __shared__ uint32_t pre[OT / 64 + 1];  // N+ entries before each 64-entry word
+  __shared__ uint16_t last[OT / 64];     // last row start before each word
+  __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last of the tile): where their entries go
+  __shared__ uint32_t lastc;             // start of the last segment if its row crosses the tile's end
+  __shared__ uint32_t mids[64], lngs[64], nlist[2], lbase[2];
+  if (a.err[0]) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t bad = 0;
+  uint64_t above = 0;
+  RowSums sums;
+  for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    const int64_t t0 = t * OT;
+    const int len = (int)min((int64_t)OT, a.nnz - t0);
+    __syncthreads();
+    if (tid < OT / 64) {
+      heads[tid] = ((const uint64_t*)a.mark)[t * (OT / 64) + tid] | (tid == 0 ? 1ull : 0ull);
+      if (tid == 0) {
+        heads[OT / 64] = 0;
+        lastc = OT;
+        nlist[0] = nlist[1] = 0;
+      }
+    }
+    __syncthreads();
+    const int32_t* nb = a.nbr + t0;
+    int32_t y[OPER];
+    uint32_t wd[OPER];
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid;
+      y[i] = p < len ? nb[p] : 0;
+      wd[i] = p < len ? (uint32_t)(a.flg[(t0 + p) >> 2] >> (2 * (p & 3))) & 3u : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid;
+      if ((heads[i * 4 + w] >> lane) & 1ull) at[p] = a.list[t0 + p];
+    }
+    if (w == 0) {  // last row start before each word: an exclusive running maximum
+      const uint64_t h = heads[lane];
+      int v = h ? lane * 64 + 63 - __builtin_clzll(h) : 0;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int q = __shfl_up(v, o, 64);
+        if (lane >= o) v = max(v, q);
+      }
+      const int q = __shfl_up(v, 1, 64);
+      last[lane] = (uint16_t)(lane ? q : 0);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      // rows that cross a boundary: another tile may already have placed
+      // entries over their start, so their ids come from the tile starts
+      at[0] = a.tile_row[t];
+      if (t + 1 < a.ntiles) {
+        const uint32_t x = a.tile_row[t + 1];
+        const int64_t o = a.off[x];
+        if (o < t0 + OT) {
+          lastc = o > t0 ? (uint32_t)(o - t0) : 0u;
+          at[lastc] = x;
+        }
+      }
+    }
+    __syncthreads();
+    // entry checks, direction of each edge
+    uint16_t hd[OPER];
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid, wi = i * 4 + w;
+      const bool in = p < len;
+      const uint64_t hw = heads[wi];
+      const uint64_t m = hw & (~0ull >> (63 - lane));
+      const int h = m ? wi * 64 + 63 - __builtin_clzll(m) : last[wi];
+      hd[i] = (uint16_t)h;
+      const uint32_t x = at[h];
+      int32_t pv = __shfl_up(y[i], 1, 64);
+      const bool start = (hw >> lane) & 1ull;
+      if (lane == 0 && in && t0 + p > 0) pv = nb[p - 1];
+      // (the tile's first entry carries a start bit of its own: look at the row)
+      const bool first = p == 0 ? a.off[x] == t0 : start;
+      bool f = false;
+      if (in) {
+        if (!first && pv >= y[i]) bad |= ERR_UNSORTED;
+        if (y[i] == (int32_t)x) bad |= ERR_SELFLOOP;
+        if (wd[i] == 0) bad |= ERR_RANGE;
+        if (y[i] < 0 || y[i] >= a.n) {
+          bad |= ERR_RANGE;
+          y[i] = 0;
+        }
+        const uint32_t kx = a.key[x], ky = a.key[y[i]];
+        f = RANK ? ky < kx : (ky > kx || (ky == kx && y[i] > (int32_t)x));
+        const uint32_t g = wd[i];
+        // N+ words carry f_xy and the rank (id) of y; in-list words of row x
+        // the id of y and f_yx, the flag seen from y
+        wd[i] = f ? (g << 30 | (RANK ? ky : (uint32_t)y[i])) : (((g & 1u) << 31) | ((g >> 1) << 30) | (uint32_t)y[i]);
+        const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1), ma = __ballot(y[i] > (int32_t)x);
+        if (lane == 0) {
+          above += (uint64_t)__popcll(ma);
+          fwd[wi] = mf;
+          b0[wi] = m0;
+          b1[wi] = m1;
+        }
+      } else if (lane == 0) {
+        fwd[wi] = b0[wi] = b1[wi] = 0;
+      }
+    }
+    __syncthreads();
+    if (w == 0) {
+      const uint32_t c = (uint32_t)__popcll(fwd[lane]);
+      uint32_t s = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t q = __shfl_up(s, o, 64);
+        if (lane >= o) s += q;
+      }
+      pre[lane] = s - c;
+      if (lane == 63) {
+        pre[64] = s;
+        fwd[64] = 0;
+      }
+    }
+    __syncthreads();
+    // per row segment: its counts
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid;
+      if (p >= len || !((heads[p >> 6] >> lane) & 1ull)) continue;
+      int e = len;
+      {
+        int wi = p >> 6;
+        uint64_t m = lane == 63 ? 0ull : heads[wi] & (~0ull << (lane + 1));
+        while (!m && ++wi < OT / 64) m = heads[wi];
+        if (m) e = min(len, wi * 64 + __builtin_ctzll(m));
+      }
+      const uint32_t x = at[p];
+      const uint32_t nf = pre[e >> 6] + (uint32_t)__popcll(fwd[e >> 6] & below(e & 63)) - pre[p >> 6] -
+                          (uint32_t)__popcll(fwd[p >> 6] & below(p & 63));
+      uint32_t o = 0, in = 0, mu = 0;
+      for (int wi = p >> 6; wi <= (e - 1) >> 6; ++wi) {
+        uint64_t m = ~0ull;
+        if (wi == p >> 6) m &= ~below(p & 63);
+        if (wi == e >> 6) m &= below(e & 63);
+        o += (uint32_t)__popcll(b0[wi] & ~b1[wi] & m);
+        in += (uint32_t)__popcll(b1[wi] & ~b0[wi] & m);
+        mu += (uint32_t)__popcll(b0[wi] & b1[wi] & m);
+      }
+      const int64_t ox = a.off[x], ex = a.off[x + 1];
+      if (ox >= t0 && ex <= t0 + len) {
+        const uint32_t fl = nf > SORT_MAX ? UNSORTED : 0u;
+        a.info[x] = (uint64_t)ox << 24 | (min(nf, LEN_MASK) | (RANK ? fl : 0u));
+        at[p] = nf;
+        sums.row((uint64_t)a.n, o, in, mu);
+        if (RANK && nf > SORT_MIN && nf <= SORT_MAX) {
+          const uint32_t k = nf > SORT_MID;
+          (k ? lngs : mids)[atomicAdd(&nlist[k], 1u)] = x;
+        }
+      } else {
+        Cross* c = &a.cross[ox / OT + 1];
+        const int k = p == 0 ? 0 : 1;
+        cF[k] = ox + atomicAdd(&c->f, nf);
+        cB[k] = ex - 1 - (int64_t)atomicAdd(&c->b, (uint32_t)(e - p) - nf);
+        atomicAdd(&c->o, o);
+        atomicAdd(&c->i, in);
+        atomicAdd(&c->m, mu);
+        if (p == 0) at[0] = 0xFFFFFFFFu;  // marks the crossing first segment
+      }
+    }
+    __syncthreads();
+    if (RANK && tid < 2 && nlist[tid]) lbase[tid] = atomicAdd(&a.counts[tid], nlist[tid]);
+    __syncthreads();
+    if (RANK) {
+      if (tid < (int)nlist[0]) a.mid[lbase[0] + tid] = mids[tid];
+      if (tid < (int)nlist[1]) a.lng[lbase[1] + tid] = lngs[tid];
+    }
+    // place the entries
+    const bool cross0 = at[0] == 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid, wi = i * 4 + w;
+      if (p >= len) continue;
+      const int h = hd[i];
+      const uint64_t fm = fwd[wi];
+      const uint32_t c = pre[wi] + (uint32_t)__popcll(fm & below(lane)) - pre[h >> 6] -
+                         (uint32_t)__popcll(fwd[h >> 6] & below(h & 63));
+      const bool f = (fm >> lane) & 1ull;
+      const uint32_t q = (uint32_t)(p - h) - c;  // in-list entries of the segment before this one
+      int64_t to;
+      if ((h == 0 && cross0) || (uint32_t)h == lastc) {
+        const int k = h == 0 ? 0 : 1;
+        to = f ? cF[k] + c : cB[k] - q;
+      } else {
+        to = t0 + h + (f ? c : at[h] + q);
+      }
+      a.list[to] = wd[i];
+    }
+  }
+  if (bad) atomicOr(&a.err[1], bad);
+  above = sum64(above);
+  if (lane == 0 && above) atomicAdd(&copy_of(a.acc)[SW_ABOVE], (unsigned long long)above);
+  sums.add_to(copy_of(a.acc), lane);
+}
+
+// Rows that cross tile boundaries, at the first boundary inside each.
+template <bool RANK>
+__global__ void k_sw_cross(OrientArgs a) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  RowSums sums;
+  if (!(a.err[0] | a.err[1])) {
+    for (int64_t t = 1 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.ntiles; t += stride) {
+      const uint32_t x = a.tile_row[t];
+      const int64_t ox = a.off[x];
+      if (ox >= t * OT || ox / OT + 1 != t) continue;
+      const Cross c = a.cross[t];
+      const uint32_t fl = RANK && c.f > SORT_MAX ? UNSORTED : 0u;
+      a.info[x] = (uint64_t)ox << 24 | (min(c.f, LEN_MASK) | fl);
+      sums.row((uint64_t)a.n, c.o, c.i, c.m);
+      if (RANK && c.f > SORT_MIN && c.f <= SORT_MAX) {
+        const uint32_t k = c.f > SORT_MID;
+        (k ? a.lng : a.mid)[atomicAdd(&a.counts[k], 1u)] = x;
+      }
+    }
+  }
+  sums.add_to(copy_of(a.acc), threadIdx.x & 63);
+}
+
+// ------------------------------------------------------------------- sorting
+
+// Sort keys: the rank in the high bits (a list word rotated by two).
+__device__ __forceinline__ uint32_t to_key(uint32_t w) { return w << 2 | w >> 30; }
+__device__ __forceinline__ uint32_t of_key(uint32_t k) { return k >> 2 | k << 30; }
+
+// N+ lists of 65 to 256 entries, one wavefront each: a bitonic network over
+// four registers a lane.
+__global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict__ rows,
+                                                     const uint32_t* __restrict__ count,
+                                                     const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
+                                                     const uint32_t* __restrict__ err) {
+  if (err[0] | err[1]) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t nw = gridDim.x * 4, cnt = *count;
+  for (uint32_t r = blockIdx.x * 4 + (threadIdx.x >> 6); r < cnt; r += nw) {
+    const uint64_t in = info[rows[r]];
+    const uint32_t len = (uint32_t)in & LEN_MASK;
+    uint32_t* p = list + (in >> 24);
+    uint32_t k[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) k[e] = (uint32_t)(e * 64 + lane) < len ? to_key(p[e * 64 + lane]) : 0xFFFFFFFFu;
+    // element lane * 4 + e
+#pragma unroll
+    for (int sz = 2; sz <= 256; sz <<= 1) {
+#pragma unroll
+      for (int j = sz >> 1; j > 0; j >>= 1) {
+        if (j >= 4) {
+          const int lm = j >> 2;
+          const bool up = ((lane * 4) & sz) == 0, lo = (lane & lm) == 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t o = __shfl_xor(k[e], lm, 64);
+            k[e] = (lo == up) ? min(k[e], o) : max(k[e], o);
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (e & j) continue;
+            const bool up = ((lane * 4 + e) & sz) == 0;
+            const uint32_t x = k[e], y = k[e | j];
+            k[e] = up ? min(x, y) : max(x, y);
+            k[e | j] = up ? max(x, y) : min(x, y);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if ((uint32_t)(lane * 4 + e) < len) p[lane * 4 + e] = of_key(k[e]);
+  }
+}
+
+// N+ lists of 257 to 4,096 entries, one workgroup each, in LDS.
+__global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict__ rows,
+                                                      const uint32_t* __restrict__ count,
+                                                      const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
+                                                      const uint32_t* __restrict__ err) {
+  __shared__ uint32_t k[SORT_MAX];
+  if (err[0] | err[1]) return;
+  const uint32_t cnt = *count;
+  for (uint32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
+    const uint64_t in = info[rows[r]];
+    const uint32_t len = min((uint32_t)in & LEN_MASK, SORT_MAX);
+    uint32_t* p = list + (in >> 24);
+    uint32_t N = 512;
+    while (N < len) N <<= 1;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < N; i += 256) k[i] = i < len ? to_key(p[i]) : 0xFFFFFFFFu;
+    __syncthreads();
+    for (uint32_t sz = 2; sz <= N; sz <<= 1)
+      for (uint32_t j = sz >> 1; j > 0; j >>= 1) {
+        for (uint32_t q = threadIdx.x; q < N / 2; q += 256) {
+          const uint32_t i = ((q & ~(j - 1)) << 1) | (q & (j - 1));
+          const bool up = (i & sz) == 0;
+          const uint32_t x = k[i], y = k[i | j];
+          if ((x > y) == up) {
+            k[i] = y;
+            k[i | j] = x;
+          }
+        }
+        __syncthreads();
+      }
+    for (uint32_t i = threadIdx.x; i < len; i += 256) p[i] = of_key(k[i]);
+  }
+}
+
+// ------------------------------------------------------------------ triangles
+
+// Flags of 16 candidate triangles a lane, two bits each: X = f_xz, Y = f_yz
+// (0: z is not in N+(y)), G = f_xy; counted by class 16 at a time.
+struct Tri {
+  uint32_t X = 0, Y = 0, G = 0;
+  uint32_t c[7] = {};  // all, 030C, 120D, 120U, 120C, 210, 300
+
+  __device__ __forceinline__ void count() {
+    constexpr uint32_t L = 0x55555555u;
+    const uint32_t xl = X & L, xh = (X >> 1) & L, yl = Y & L, yh = (Y >> 1) & L, gl = G & L, gh = (G >> 1) & L;
+    const uint32_t x1 = xl & ~xh, x2 = xh & ~xl, x3 = xl & xh;
+    const uint32_t y1 = yl & ~yh, y2 = yh & ~yl, y3 = yl & yh;
+    const uint32_t g1 = gl & ~gh, g2 = gh & ~gl, g3 = gl & gh;
+    const uint32_t hit = (xl | xh) & (yl | yh);
+    // the vertex outside the mutual pair (z, y or x) sends both, receives both
+    const uint32_t d = (g3 & x2 & y2) | (x3 & g2 & y1) | (y3 & g1 & x1);
+    const uint32_t u = (g3 & x1 & y1) | (x3 & g1 & y2) | (y3 & g2 & x2);
+    const uint32_t p = (g3 & ((x1 & y2) | (x2 & y1))) | (x3 & ((g1 & y1) | (g2 & y2))) | (y3 & ((g1 & x2) | (g2 & x1)));
+    const uint32_t two = (g3 & x3 & (y1 | y2)) | (g3 & (x1 | x2) & y3) | ((g1 | g2) & x3 & y3);
+    c[0] += __popc(hit);
+    c[1] += __popc((g1 & x2 & y1) | (g2 & x1 & y2));
+    c[2] += __popc(d);
+    c[3] += __popc(u);
+    c[4] += __popc(p);
+    c[5] += __popc(two);
+    c[6] += __popc(g3 & x3 & y3);
+  }
+  // Four candidates of one x: x holds f_xz in the top two bits, y f_yz in the
+  // top (TOP) or the low ones; all but the first left of them (left may be
+  // negative) are dropped. g8: f_xy in each field of a byte.
+  template <bool TOP>
+  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int left, uint32_t g8) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      X = __builtin_amdgcn_alignbit(X, x[e], 30);
+      Y = TOP ? __builtin_amdgcn_alignbit(Y, y[e], 30) : (Y << 2 | y[e]);
+    }
+    X &= ~0u << (8 - 2 * max(0, min(left, 4)));
+    G = G << 8 | g8;
+  }
+  __device__ __forceinline__ void flush(unsigned long long* acc, int lane) {
+    uint64_t s[7];
+    for (int k = 0; k < 7; ++k) {
+      s[k] = sum64(c[k]);
+      c[k] = 0;
+    }
+    if (lane == 0 && s[0]) {
+      s[0] -= s[1] + s[2] + s[3] + s[4] + s[5] + s[6];
+      const int slot[7] = {8, 9, 11, 12, 13, 14, 15};
+      for (int k = 0; k < 7; ++k)
+        if (s[k]) atomicAdd(&acc[slot[k]], (unsigned long long)s[k]);
+    }
+  }
+};
+
+// Two-bit table: id z in word z / 16, the fields from the top down. Ids past
+// the last of W words read that word, which the caller keeps zero if it can
+// meet such ids.
+template <int W>
+__device__ __forceinline__ uint32_t probe_bits(const uint32_t* tab, uint32_t w) {
+  return tab[min((w & ID_MASK) >> 4, (uint32_t)W - 1)] << ((w << 1) & 31u);
+}
+__device__ __forceinline__ void set_bits(uint32_t* tab, uint32_t w) {
+  atomicOr(&tab[(w & ID_MASK) >> 4], (w >> 30) << (30 - 2 * (w & 15u)));
+}
+
+// Hash table of list words, open addressing on the low bits of the id; at most
+// TAB_MAX of its TAB_WORDS slots are taken, so every search ends.
+__device__ __forceinline__ uint32_t probe_hash(const uint32_t* tab, uint32_t w) {
+  const uint32_t key = w & ID_MASK;
+  uint32_t h = key & (TAB_WORDS - 1), v = tab[h];
+  while (v != SLOT_FREE && (v & ID_MASK) != key) {
+    h = (h + 1) & (TAB_WORDS - 1);
+    v = tab[h];
+  }
+  return (v & ID_MASK) == key ? v : 0u;
+}
+__device__ __forceinline__ void set_hash(uint32_t* tab, uint32_t w) {
+  uint32_t h = w & (TAB_WORDS - 1);
+  while (atomicCAS(&tab[h], SLOT_FREE, w) != SLOT_FREE) h = (h + 1) & (TAB_WORDS - 1);
+}
+
+// The in-list vertices x of one batch: first entry of N+(x); its length, the
+// unsorted mark, and f_xy on top. Offsets take 32 bits where the byte offsets
+// of the whole list do (a load then adds them to a scalar base).
+template <bool WIDE>
+struct XList {
+  typename std::conditional<WIDE, uint64_t, uint32_t>::type p[64];
+  uint32_t m[64];
+};
+
+// Lists the vertices of up to `cnt` in-list words g (one a lane) whose N+ has
+// at least two entries (y is one of them).
+template <bool WIDE>
+__device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict__ in, int cnt,
+                                      const uint64_t* __restrict__ info, int lane) {
+  uint64_t xi = 0;
+  uint32_t g = 0;
+  if (lane < cnt) {
+    g = in[lane];
+    xi = info[g & ID_MASK];
+  }
+  const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
+  const uint64_t m = __ballot(has);
+  if (has) {
+    const int k = __popcll(m & below(lane));
+    L.p[k] = xi >> 24;
+    L.m[k] = (g & ~ID_MASK) | ((uint32_t)xi & (LEN_MASK | UNSORTED));
+  }
+  return __popcll(m);
+}
+
+// Streams the cnt listed N+(x) against the table of y: four lists at a time,
+// one per 16 lanes and four entries a lane, in two such sets in turn, so that
+// one set's loads are in flight while the other is counted (loads are never
+// skipped, an idle lane rereads the list's first words: the wait for a set is
+// then for its own loads only). A list in rank order ends with the 64 entries
+// that reach y's rank.
+template <bool SORTED, bool TOP, bool WIDE, class Probe>
+__device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const XList<WIDE>& L, int cnt,
+                                       uint32_t yrank, int lane, Tri& tri, Probe probe) {
+  constexpr uint64_t G0 = 0x0001000100010001ull;  // the first lane of each 16
+  const int l4 = (lane & 15) * 4;
+  const uint64_t before = below(lane & 48);
+  struct Slot {
+    typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // the lane's next entries
+    int left;      // entries of the list from there on (0 or less: none)
+    uint32_t g8, lim;
+    uint32_t w[4];
+  } sl[2];
+  auto load = [&](Slot& s) {
+    const auto o = s.left > 0 ? s.o : 0;
+    if constexpr (WIDE)
+      __builtin_memcpy(s.w, list + o, 16);
+    else
+      __builtin_memcpy(s.w, (const char*)list + (o << 2), 16);
+  };
+  auto take = [&](Slot& s, int k) {
+    s.left = 0;
+    if (k < cnt) {
+      const uint32_t m = L.m[k];
+      s.o = L.p[k] + l4;
+      s.left = (int)(m & LEN_MASK) - l4;
+      s.g8 = (m >> 30) * 0x55u;
+      s.lim = (m & UNSORTED) ? ~0u : yrank;
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    sl[i].o = 0;
+    sl[i].g8 = sl[i].lim = 0;
+    take(sl[i], i * 4 + (lane >> 4));
+    load(sl[i]);
+  }
+  int next = 8;
+  auto step = [&](Slot& s) {
+    uint32_t y[4];
+    probe(s.w, y);
+    tri.add4<TOP>(s.w, y, s.left, s.g8);
+    // lists that end here: the first lane of their 16 has at most 64 left, or
+    // the last entry read has reached y
+    uint64_t d = __ballot(s.left <= 64) & G0;
+    if (SORTED) d |= (__ballot((s.w[3] & ID_MASK) >= s.lim) >> 15) & G0;
+    s.o += 64;
+    s.left -= 64;
+    if (d) {
+      const uint64_t all = (d << 16) - d;
+      if (__builtin_amdgcn_inverse_ballot_w64(all)) take(s, next + __popcll(d & before));
+      next += __popcll(d);
+    }
+    load(s);
+  };
+  for (;;) {
+    if (!__ballot(sl[0].left > 0 || sl[1].left > 0)) break;
+    step(sl[0]);
+    step(sl[1]);
+    step(sl[0]);
+    step(sl[1]);
+    tri.count();
+  }
+}
+
+struct CountArgs {
+  int64_t n, nnz, ntiles;
+  const int64_t* off;
+  const uint32_t* list;
+  const uint64_t* info;
+  const uint32_t* rank;
+  const uint32_t* tile_row;
+  uint64_t* items[2];  // of k_sw_hubs, k_sw_mids: y << 32 | chunk
+  uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken
+  int64_t range;       // k_sw_rest: entries of one wavefront
+  unsigned long long* acc;
+  const uint32_t* err;
+};
+
+// Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
+// k_sw_rest, 3 none.
+__device__ __forceinline__ uint32_t route(uint32_t rank, uint32_t plus, int64_t minus) {
+  if (plus == 0 || minus == 0) return 3;
+  if (rank < HUB_RANKS && minus >= HUB_MIN_IN) return 0;
+  return minus >= MID_MIN_IN || plus > TAB_MAX ? 1 : 2;
+}
+
+__global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
+  __shared__ uint32_t cnt[2], base[2];
+  if (a.err[0] | a.err[1]) return;
+  for (int64_t x0 = (int64_t)blockIdx.x * 4096; x0 < a.n; x0 += (int64_t)gridDim.x * 4096) {
+    __syncthreads();
+    if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t at[16], num[16], kind = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int64_t x = x0 + i * 256 + threadIdx.x;
+      num[i] = 0;
+      if (x < a.n) {
+        const uint64_t in = a.info[x];
+        const uint32_t plus = (uint32_t)in & LEN_MASK;
+        const int64_t minus = a.off[x + 1] - (int64_t)(in >> 24) - plus;
+        if (plus && minus >= MID_MIN_IN) {
+          const uint32_t r = route(a.rank[x], plus, minus);
+          kind |= r << (2 * i);
+          num[i] = (uint32_t)((minus + CHUNK - 1) / CHUNK);
+        } else if (plus > TAB_MAX && minus) {
+          kind |= 1u << (2 * i);
+          num[i] = 1;
+        }
+        if (num[i]) at[i] = atomicAdd(&cnt[(kind >> (2 * i)) & 1u], num[i]);
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&a.counts[2 + threadIdx.x], cnt[threadIdx.x]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t r = (kind >> (2 * i)) & 1u;
+      for (uint32_t c = 0; c < num[i]; ++c)
+        a.items[r][base[r] + at[i] + c] = (uint64_t)(x0 + i * 256 + threadIdx.x) << 32 | c;
+    }
+  }
+}
+
+// Vertices with long in-lists: a workgroup takes up to CHUNK of one's in-list
+// and holds N+(y) as a byte per rank (z of N+(y) has a lower rank than y).
+template <bool WIDE>
+__global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
+  __shared__ __align__(16) uint8_t tab[HUB_RANKS + 16];  // f_yz by rank of z; past the ranks: 0
+  __shared__ XList<WIDE> xl[HUB_THREADS / 64];
+  __shared__ uint32_t item, next;
+  if (a.err[0] | a.err[1]) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < (int)sizeof(tab) / 4; i += HUB_THREADS) ((uint32_t*)tab)[i] = 0;
+  const uint32_t nitems = a.counts[2];
+  XList<WIDE>& L = xl[tid >> 6];
+  Tri tri;
+  for (;;) {
+    if (tid == 0) {
+      item = atomicAdd(&a.counts[4], 1u);
+      next = 0;
+    }
+    __syncthreads();
+    const uint32_t it = item;
+    if (it >= nitems) break;
+    const uint64_t q = a.items[0][it];
+    const uint32_t y = (uint32_t)(q >> 32);
+    const uint64_t in = a.info[y];
+    const uint32_t plus = (uint32_t)in & LEN_MASK, yr = a.rank[y];
+    const int64_t s = (int64_t)(in >> 24), b = s + plus + (int64_t)(uint32_t)q * CHUNK;
+    const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
+    for (uint32_t i = tid; i < plus; i += HUB_THREADS) {
+      const uint32_t z = a.list[s + i];
+      tab[z & ID_MASK] = (uint8_t)(z >> 30);
+    }
+    // wavefronts claim up to 64 in-list entries at a time
+    const int claim = cnt >= 1024 ? 64 : cnt >= 512 ? 32 : 16;
+    __syncthreads();
+    for (;;) {
+      int k = 0;
+      if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
+      k = __builtin_amdgcn_readfirstlane(k);
+      if (k >= cnt) break;
+      const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+      wave_sync();
+      stream<true, false, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & ID_MASK, (uint32_t)HUB_RANKS)];
+      });
+      wave_sync();
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < plus; i += HUB_THREADS) tab[a.list[s + i] & ID_MASK] = 0;
+  }
+  tri.flush(copy_of(a.acc), lane);
+}
+
+// Vertices with in-lists of middling length, of any rank: a smaller workgroup,
+// N+(y) as two bits per rank up to HUB_RANKS and a hash table beyond.
+template <bool WIDE>
+__global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
+  constexpr int W = HUB_RANKS / 16 + 1;
+  __shared__ uint32_t tab[W], high[TAB_WORDS];
+  __shared__ XList<WIDE> xl[MID_THREADS / 64];
+  __shared__ uint32_t item, next;
+  if (a.err[0] | a.err[1]) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < W; i += MID_THREADS) tab[i] = 0;
+  for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
+  const uint32_t nitems = a.counts[3];
+  XList<WIDE>& L = xl[tid >> 6];
+  Tri tri;
+  for (;;) {
+    if (tid == 0) item = atomicAdd(&a.counts[5], 1u);
+    __syncthreads();
+    const uint32_t it = item;
+    if (it >= nitems) break;
+    const uint64_t q = a.items[1][it];
+    const uint32_t y = (uint32_t)(q >> 32);
+    const uint64_t in = a.info[y];
+    const uint32_t plus = (uint32_t)in & LEN_MASK, yr = a.rank[y];
+    const int64_t s = (int64_t)(in >> 24), b = s + plus + (int64_t)(uint32_t)q * CHUNK;
+    const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
+    const int claim = cnt >= 256 ? 64 : cnt >= 128 ? 32 : 16;
+    const bool far = yr > HUB_RANKS;  // N+(y) may reach past the bits
+    // TAB_MAX entries of N+(y) at a time fit the hash table whatever their ranks
+    for (uint32_t f = 0; f < plus; f += TAB_MAX) {
+      const uint32_t fe = min(f + TAB_MAX, plus);
+      for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
+        const uint32_t z = a.list[s + i];
+        if ((z & ID_MASK) < HUB_RANKS) set_bits(tab, z); else set_hash(high, z);
+      }
+      if (tid == 0) next = 0;
+      __syncthreads();
+      for (;;) {
+        int k = 0;
+        if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
+        k = __builtin_amdgcn_readfirstlane(k);
+        if (k >= cnt) break;
+        const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+        wave_sync();
+        stream<true, true, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4]) {
+          uint32_t top = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            g[e] = probe_bits<W>(tab, w[e]);
+            top = max(top, w[e] & ID_MASK);
+          }
+          if (far && __ballot(top >= HUB_RANKS)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if ((w[e] & ID_MASK) >= HUB_RANKS) g[e] = probe_hash(high, w[e]);
+          }
+        });
+        wave_sync();
+      }
+      __syncthreads();
+      for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
+        const uint32_t z = a.list[s + i] & ID_MASK;
+        if (z < HUB_RANKS) tab[z >> 4] = 0;
+      }
+      if (far)
+        for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
+      if (fe < plus) __syncthreads();
+    }
+  }
+  tri.flush(copy_of(a.acc), lane);
+}
+
+// The other vertices: a wavefront takes a range of entries and the rows whose
+// in-lists lie in it, one row at a time. RANK: hash table of N+(y); else all
+// vertices, whose ids are below DIRECT_N and index a two-bit table.
+template <bool RANK, bool WIDE>
+__global__ void __launch_bounds__(REST_WAVES * 64, RANK ? 4 : 5) k_sw_rest(CountArgs a) {
+  __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
+  __shared__ XList<WIDE> xl[REST_WAVES];
+  if (a.err[0] | a.err[1]) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t* tab = tabs[w];
+  XList<WIDE>& L = xl[w];
+  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = RANK ? SLOT_FREE : 0u;
+  Tri tri;
+  const int64_t nw = (int64_t)gridDim.x * REST_WAVES;
+  for (int64_t j0 = ((int64_t)blockIdx.x * REST_WAVES + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
+    const int64_t j1 = min(j0 + a.range, a.nnz);
+    // the row that holds entry j0, by a 64-way search between tile starts
+    const int64_t t = j0 / OT;
+    int64_t r = a.tile_row[t];
+    {
+      int64_t span = (t + 1 < a.ntiles ? (int64_t)a.tile_row[t + 1] : a.n - 1) - r + 1;
+      while (span > 1) {
+        const int64_t step = (span + 63) / 64;
+        const bool le = lane * step < span && a.off[r + lane * step] <= j0;
+        const int k = __popcll(__ballot(le)) - 1;
+        r += k * step;
+        span = min(step, span - k * step);
+      }
+    }
+    for (;; r += 64) {
+      int64_t lo = 0, hi = 0, e = a.nnz;
+      uint64_t in = 0;
+      uint32_t yr = 0;
+      if (r + lane < a.n) {
+        in = a.info[r + lane];
+        e = a.off[r + lane + 1];
+        const uint32_t plus = (uint32_t)in & LEN_MASK;
+        const int64_t bs = (int64_t)(in >> 24) + plus;
+        lo = max(bs, j0);
+        hi = min(e, j1);
+        if (plus == 0) hi = lo;
+        if (RANK && hi > lo) {
+          yr = a.rank[r + lane];
+          if (route(yr, plus, e - bs) != 2) hi = lo;
+        }
+      }
+      uint64_t todo = __ballot(hi > lo);
+      while (todo) {
+        const int s = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const uint64_t yi = rl64(in, s);
+        const int64_t f0 = (int64_t)(yi >> 24), l0 = (int64_t)rl64((uint64_t)lo, s), l1 = (int64_t)rl64((uint64_t)hi, s);
+        const uint32_t plus = (uint32_t)yi & LEN_MASK, rk = rl(yr, s);
+        for (uint32_t i = lane; i < plus; i += 64) {
+          const uint32_t z = a.list[f0 + i];
+          if (RANK) set_hash(tab, z); else set_bits(tab, z);
+        }
+        wave_sync();
+        for (int64_t k = l0; k < l1; k += 64) {
+          const int nx = list_x<WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), a.info, lane);
+          wave_sync();
+          stream<RANK, true, WIDE>(a.list, L, nx, rk, lane, tri, [&](const uint32_t (&q)[4], uint32_t (&g)[4]) {
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2) g[e2] = RANK ? probe_hash(tab, q[e2]) : probe_bits<TAB_WORDS>(tab, q[e2]);
+          });
+          wave_sync();
+        }
+        if (RANK) {
+          for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
+        } else {
+          for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & ID_MASK) >> 4] = 0;
+        }
+        wave_sync();
+      }
+      if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
+    }
+  }
+  tri.flush(copy_of(a.acc), lane);
+}
+
+// ------------------------------------------------------------------- results
+
+// Open wedges: a triangle's three pairs of neighbours are adjacent, so each
+// class of triangle takes its own pairs out of the pair sums. 012 and 102 get
+// the common neighbours that n - d(u) - d(v) subtracted twice.
+__device__ __forceinline__ void open_wedges(uint64_t* c) {
+  c[3] -= c[8] + c[11];
+  c[4] -= c[8] + c[12];
+  c[5] -= c[8] + 3 * c[9] + c[13];
+  c[6] -= 2 * c[11] + c[13] + c[14];
+  c[7] -= 2 * c[12] + c[13] + c[14];
+  c[10] -= c[14] + 3 * c[15];
+  const uint64_t one = c[11] + c[12] + c[13];
+  c[1] += 3 * (c[8] + c[9]) + 2 * one + c[14];
+  c[2] += one + 2 * c[14] + 3 * c[15];
+}
+
+__global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t* __restrict__ err, int64_t nnz,
+                            uint64_t n, uint64_t clo, uint64_t chi, uint64_t* __restrict__ out,
+                            uint64_t* __restrict__ status) {
+  __shared__ uint64_t sum[SW_WORDS];
+  if (threadIdx.x < SW_WORDS) {
+    uint64_t t = 0;
+    for (int k = 0; k < SW_COPIES; ++k) t += acc[k * SW_WORDS + threadIdx.x];
+    sum[threadIdx.x] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  uint32_t e = err[0] | err[1] | err[2];
+  if (!e && (int64_t)sum[SW_ABOVE] * 2 != nnz) e = ERR_ASYM;
+  status[17] = e;
+  if (e) return;  // an error writes no output
+  uint64_t c[16];
+  for (int k = 0; k < 16; ++k) c[k] = sum[k];
+  c[2] += n * (sum[SW_MUT] / 2);
+  open_wedges(c);
+  uint64_t s = 0;
+  for (int k = 1; k < 16; ++k) {
+    status[k] = out[k] = c[k];
+    s += c[k];
+  }
+  status[0] = out[0] = clo - s;
+  status[16] = out[16] = chi - (clo < s ? 1u : 0u);
+}
+
+// Symmetry check: every entry's mirror with swapped direction bits.
+__global__ void k_sw_symmetry(int64_t n, int64_t nnz, const int64_t* __restrict__ off, const int32_t* __restrict__ nbr,
+                              const uint8_t* __restrict__ flg, uint32_t* __restrict__ err) {
+  if (err[0]) return;
+  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+  const int lane = threadIdx.x & 63;
+  bool bad = false;
+  for (int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); x < n; x += nw) {
+    const int64_t b = off[x], e = off[x + 1];
+    for (int64_t j = b + lane; j < e; j += 64) {
+      const int32_t y = nbr[j];
+      if (y < 0 || y >= n) continue;  // an entry check reports it
+      const uint32_t f = (flg[j >> 2] >> (2 * (j & 3))) & 3u;
+      int64_t lo = off[y], hi = off[y + 1];
+      const int64_t end = hi;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (nbr[mid] < (int32_t)x) lo = mid + 1; else hi = mid;
+      }
+      if (lo >= end || nbr[lo] != (int32_t)x ||
+          ((flg[lo >> 2] >> (2 * (lo & 3))) & 3u) != (((f & 1u) << 1) | (f >> 1)))
+        bad = true;
+    }
+  }
+  if (bad) atomicOr(&err[2], ERR_ASYM);
+}
+
+unsigned grid_of_work(int64_t work, int per, int64_t cap) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((work + per - 1) / per, cap));
+}
+
+}  // namespace
+
+int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out, uint32_t** err_out, Scratch& scratch,
+                 hipEvent_t* ev, hipStream_t s) {
+  auto rec = [&](int i) {
+    if (ev) (void)hipEventRecord(ev[i], s);
+  };
+  const int64_t n = in.n, nnz = in.nnz;
+  DeviceInfo di;
+  if (int st = device_info(&di)) return st;
+  const bool rank = n > DIRECT_N;
+  const int64_t ntiles = (nnz + OT - 1) / OT;
+  // everything that starts at zero, in one block
+  int64_t words = 0;
+  auto place = [&](int64_t w) {
+    const int64_t at = words;
+    words += (w + 1) & ~(int64_t)1;
+    return at;
+  };
+  const int64_t w_acc = place(2 * SW_WORDS * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(6);
+  const int64_t w_hist = place(rank ? 2 * BUCKETS : 0);
+  const int64_t w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
+  const int64_t w_mark = place(ntiles * (OT / 32));
+  uint32_t* zero = nullptr;
+  ALLOC(zero, words);
+  unsigned long long* acc = (unsigned long long*)(zero + w_acc);
+  uint32_t* err = zero + w_err;
+  *acc_out = acc;
+  *err_out = err;
+  k_sw_zero<<<grid_of_work(words, 1024, 2048), 256, 0, s>>>(zero, words);
+  if (n == 0 || nnz == 0) {
+    for (int i = 1; i <= 3; ++i) rec(i);
+    if (n == 0) return TRIAD_OK;
+  }
+  uint32_t *key = nullptr, *list = nullptr, *tile_row = nullptr, *mid = nullptr, *lng = nullptr;
+  uint64_t *info = nullptr, *hub_items = nullptr, *mid_items = nullptr;
+  ALLOC(key, n);
+  ALLOC(info, n);
+  ALLOC(list, nnz + LIST_PAD);
+  ALLOC(tile_row, ntiles);
+  if (rank) {
+    ALLOC(mid, nnz / SORT_MIN + 1);
+    ALLOC(lng, nnz / SORT_MID + 1);
+    // an in-list of `minus` entries makes at most minus / CHUNK + 1 items, and
+    // only in-lists of MID_MIN_IN entries or N+ of more than TAB_MAX make any
+    ALLOC(hub_items, std::min(n, HUB_RANKS) + nnz / CHUNK + 1);
+    ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
+  }
+  const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
+                   tile_row, err};
+  const unsigned rgrid = grid_of_work(n, ROWS_THREADS * ROWS_PER, INT32_MAX);
+  k_sw_rows<<<rgrid, ROWS_THREADS, 0, s>>>(ra);
+  if (nnz == 0) return TRIAD_OK;
+  if (rank)
+    k_sw_rank<<<rgrid, ROWS_THREADS, 0, s>>>(n, in.off, zero + w_hist, zero + w_hist + BUCKETS, key, err);
+  if (validate)
+    k_sw_symmetry<<<grid_of_work(n, 4, 65536), 256, 0, s>>>(n, nnz, in.off, in.nbr, in.flg, err);
+  const OrientArgs oa{n,        nnz,  ntiles, in.off, in.nbr, in.flg, key, zero + w_mark, tile_row, list, info,
+                      (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err};
+  const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 5);
+  const unsigned cgrid = grid_of_work(ntiles, 256, 256);
+  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, zero + w_cnt, 0, acc, err};
+  // a wavefront's range: small graphs spread over the chip, large ones in
+  // ranges that spread the row search over more entries
+  const int64_t waves = (int64_t)di.cus * 32;
+  ca.range = std::max<int64_t>(64, std::min<int64_t>(1024, (nnz / waves + 63) & ~(int64_t)63));
+  const unsigned wgrid = grid_of_work((nnz + ca.range - 1) / ca.range, REST_WAVES, (int64_t)di.cus * 8);
+  if (rank) {
+    k_sw_orient<true><<<ogrid, OTHREADS, 0, s>>>(oa);
+    k_sw_cross<true><<<cgrid, 256, 0, s>>>(oa);
+    rec(1);
+    k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err);
+    k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err);
+    k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+    rec(2);
+    auto count = [&](auto wide) {
+      constexpr bool W = decltype(wide)::value;
+      k_sw_hubs<W><<<(unsigned)(di.cus * 2), HUB_THREADS, 0, s>>>(ca);
+      k_sw_mids<W><<<(unsigned)(di.cus * 6), MID_THREADS, 0, s>>>(ca);
+      k_sw_rest<true, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+    };
+    if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
+  } else {
+    // (n <= DIRECT_N: fewer than 2^28 entries)
+    k_sw_orient<false><<<ogrid, OTHREADS, 0, s>>>(oa);
+    k_sw_cross<false><<<cgrid, 256, 0, s>>>(oa);
+    rec(1);
+    rec(2);
+    k_sw_rest<false, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+  }
+  rec(3);
+  HIPCHK(hipGetLastError());
+  return TRIAD_OK;
+}
+
+void sweep_finish(const unsigned long long* acc, uint32_t* err, int64_t nnz, int64_t n, uint64_t* d_out,
+                  uint64_t* status, hipStream_t s) {
+  uint64_t clo, chi;
+  choose3(n, &clo, &chi);
+  k_sw_finish<<<1, 64, 0, s>>>(acc, err, nnz, (uint64_t)n, clo, chi, d_out, status);
+}
+
+}  // namespace triad

@@ -81,6 +81,7 @@ inline bool within_cap(size_t total) {
 // Test hook: true (once per injected fault) when the calling census should
 // raise ERR_DEVICE after its census kernel; set by triad_test_inject_device_error.
 bool take_injected_fault();
+bool injected_fault_pending();
 
 // Device blocks the library keeps between calls, per device. A call that
 // drains its stream before it returns can take its scratch from here and give

@@ -1,0 +1,120 @@
+"""The triangle-listing census (the default call) where its kernels change
+path: tile and table edges, rows that cross tiles, list lengths around the
+sorted sizes, ranks past the workgroup tables. Against the oracle, closed forms
+of disjoint cliques, and the merge kernel (which an explicit chunk selects).
+Every count is a whole number: equality."""
+from math import comb
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1209_6308_amd import graphs, triad
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = pytest.importorskip("torch")
+    if not t.cuda.is_available():
+        pytest.skip("no HIP device")
+    return t
+
+
+def _census(n, d, **kw):
+    return triad.triad_census_device(n, int(d[1].numel()), *d, **kw)[0]
+
+
+@pytest.mark.parametrize("edges", [1, 2, 2047, 2048, 2049, 4096, 6145])
+def test_tile_edges(torch, edges):
+    """A hub and a path: 2 * edges entries around multiples of the 4,096-entry
+    tile, the hub's row ending in, at and past tile boundaries, first or last."""
+    rng = np.random.default_rng(edges)
+    for hub_first in (True, False):
+        n = edges + 2
+        hub = 0 if hub_first else n - 1
+        k = max(1, edges * 2 // 3)
+        leaf = (np.arange(k) + 1) % n if hub_first else np.arange(k)
+        rest = edges - k
+        s = np.concatenate([np.full(k, hub), (np.arange(rest) + 1) % (n - 1)]).astype(np.int32)
+        t = np.concatenate([leaf, (np.arange(rest) + 2) % (n - 1)]).astype(np.int32)
+        flip = rng.random(edges) < 0.4
+        g = graphs.build_csr(n, np.where(flip, t, s), np.where(flip, s, t), recip_p=0.3, recip_seed=3)
+        assert _census(n, triad.to_device(g)) == oracle.census(g)
+
+
+@pytest.mark.parametrize("n", [16383, 16384, 16385, 65536, 65537])
+def test_table_edges(torch, n):
+    """Around the largest graph whose tables are indexed by id, and around the
+    ranks of the workgroup tables; ids at both ends carry the dense part."""
+    rng = np.random.default_rng(n)
+    core = np.concatenate([np.arange(150), np.arange(n - 150, n)])
+    s = np.concatenate([rng.choice(core, 30000), rng.integers(0, n, 60000)]).astype(np.int32)
+    t = np.concatenate([rng.choice(core, 30000), rng.choice(core, 60000)]).astype(np.int32)
+    g = graphs.build_csr(n, s, t, recip_p=0.2, recip_seed=1)
+    d = triad.to_device(g)
+    got = _census(n, d)
+    assert got == oracle.census_mt(g)
+    assert got == _census(n, d, chunk=32768)
+
+
+def _cliques(torch, sizes, mutual):
+    """Disjoint cliques: complete, or transitive (arcs to the higher id)."""
+    off, nbr, flg, base = [], [], [], 0
+    for k in sizes:
+        i = torch.arange(k, device="cuda", dtype=torch.int32)
+        y = i[None, :].expand(k, k)[~torch.eye(k, dtype=torch.bool, device="cuda")].view(k, k - 1)
+        up = y > i[:, None]
+        nbr.append((y + base).reshape(-1))
+        flg.append((torch.where(up, 1, 2) if not mutual else torch.full_like(y, 3)).to(torch.uint8).reshape(-1))
+        off.append(torch.full((k,), k - 1, dtype=torch.int64, device="cuda"))
+        base += k
+    deg = torch.cat(off)
+    offs = torch.zeros(base + 1, dtype=torch.int64, device="cuda")
+    offs[1:] = torch.cumsum(deg, 0)
+    f = torch.cat(flg)
+    f = torch.nn.functional.pad(f, (0, -f.numel() % 4)).view(-1, 4)
+    return base, (offs, torch.cat(nbr), f[:, 0] | (f[:, 1] << 2) | (f[:, 2] << 4) | (f[:, 3] << 6))
+
+
+@pytest.mark.parametrize("mutual", [True, False])
+@pytest.mark.parametrize("sizes", [
+    [64, 65, 66, 67, 256, 257, 258, 514, 515] + [3] * 6000,  # lists around 64, 256 and 512 entries
+    [4097, 4098, 200] + [2] * 5000,                          # lists past the sorted length (4,096)
+    [600] * 130,                                             # 78,000 ranks, lists of up to 599
+    [40] * 3000 + [300] * 10,
+])
+def test_cliques(torch, sizes, mutual):
+    n, d = _cliques(torch, sizes, mutual)
+    c = [0] * 16
+    c[15 if mutual else 8] = sum(comb(k, 3) for k in sizes)
+    c[2 if mutual else 1] = sum(comb(k, 2) * (n - k) for k in sizes)
+    c[0] = comb(n, 3) - sum(c)
+    assert _census(n, d) == c
+
+
+@pytest.mark.parametrize("case", [("rmat", 15, 12), ("rmat", 17, 8), ("chung_lu", 90001, 20), ("chung_lu", 300007, 9)])
+def test_against_the_merge(torch, case):
+    kind, a, b = case
+    g = graphs.rmat(a, b, seed=4, recip_p=0.25) if kind == "rmat" else graphs.chung_lu(a, 2.1, float(b), a / 16.0, seed=2)
+    d = triad.to_device(g)
+    want = _census(g.n, d, chunk=32768)
+    for _ in range(2):  # ranks of equal degrees fall differently from run to run
+        assert _census(g.n, d) == want
+    assert _census(g.n, d, validate=1) == want
+
+
+@pytest.mark.parametrize("n", [900, 40000])
+def test_one_sided_csr_is_refused(torch, n):
+    """Entries above and below the diagonal that do not pair up."""
+    off = np.zeros(n + 1, np.int64)
+    off[1:] = 2
+    off[n // 2:] = 4
+    nbr = np.array([3, 5, 7, n - 1], np.int32)
+    flg = np.array([0b01010101], np.uint8)
+    d = [torch.from_numpy(a).cuda() for a in (off, nbr, flg)]
+    for kw in ({}, {"validate": 1}, {"chunk": 32768}):
+        with pytest.raises(triad.TriadError) as e:
+            triad.triad_census_device(n, 4, *d, **kw)
+        assert e.value.status == triad.EASYM
