@@ -112,7 +112,8 @@ typedef struct triad_opts {
   triad_timing *timing;    /* optional host output */
   int32_t waves_per_group; /* wavefronts per workgroup (1, 2 or 4); 0 = default */
   int32_t grid_groups;     /* persistent grid size in workgroups; 0 = default */
-  int32_t kernel_variant;  /* census kernel variant (LDS window and counter layout),
+  int32_t kernel_variant;  /* census kernel variant (LDS window and counter layout of the
+                              merge; entries per wavefront and turn of a batch),
                               set by triad_batch_autotune; 0 = the default */
   uint64_t *wave_span;     /* optional device buffer [waves][2]: real-time clock
                               (s_memrealtime, 100 MHz) at each census wavefront's
@@ -123,9 +124,8 @@ typedef struct triad_opts {
                               mean of the last 32,768 by tail_share / 10,000 of one
                               wavefront's share of the whole census; 0 = default
                               (30, i.e. 0.3%), < 0 = always */
-  int32_t short_tasks;     /* batched census: 0 = tasks whose two merged lists are short
-                              run several to a round (default), < 0 = every task through
-                              the per-task merge rounds */
+  int32_t short_tasks;     /* batched census: 0 = triangles are listed (default), < 0 = every
+                              task through the per-task merge rounds */
 } triad_opts;
 
 /* Census of one graph given by HOST pointers (copied to the device; the call
@@ -334,7 +334,9 @@ int triad_version(void);
  * outputs. bytes < 0: TRIAD_EINVAL. Needs no device. */
 int triad_set_memory_cap(int64_t bytes);
 
-/* Held device memory. The census entry points that allocate
+/* Held device memory. A batch plan's scratch is one such block, given back when
+ * the plan is destroyed (after its last launch has finished). The census entry
+ * points that allocate
  * (triad_census_device, triad_labelled_census_device), triad_csr_from_arcs
  * and triad_census_update wait for their stream before they return. When the
  * stream belongs to the current device, their scratch blocks are then kept by

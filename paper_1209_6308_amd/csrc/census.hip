@@ -21,8 +21,8 @@
 //   k_finalize  the common-neighbour part of 012 and 102 from the triangle
 //               classes; 003 = C(n,3) - sum of the rest, in two 64-bit words
 // The batched census (many graphs in one captured launch) and the labelled
-// (64-state) census use the same kernels; short tasks of a batch run several
-// to a round in k_census_grouped.
+// (64-state) census can use the same kernels; by default graphs and batches
+// take the triangle listing of sweep.hip instead.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -370,10 +370,6 @@ static void launch_emit_entries(const EmitArgs& e, int64_t nnz, hipStream_t s) {
 
 // ------------------------------------------------------------ the census
 
-// Longest list (entries) of a task merged by the grouped-task kernel (one
-// LDS window of it per list).
-constexpr int GROUP_W = 448;
-
 struct CensusArgs {
   int64_t n;
   const int64_t* off;
@@ -383,7 +379,6 @@ struct CensusArgs {
   const uint64_t* tasks;   // the task queue
   const uint64_t* htasks;  // the task words the hub list indexes
   const int64_t* order;    // optional: queue position -> index into tasks
-  const int64_t* ntasks_dev;  // batched census: queue length read on the device
   int64_t ntasks;
   const uint64_t* hub_task;
   const int64_t* hub_pre;  // [nhub+1] exclusive prefix of chunk counts
@@ -536,10 +531,7 @@ __device__ bool fetch_batch(const CensusArgs& g, int lane, int& phase, Batch& bt
   const int64_t hub_items = g.nhub ? g.hub_pre[g.nhub] : 0;
   for (;;) {
     const int q = phase == 0 ? 0 : 1;
-    int64_t limit = phase == 0 ? hub_items : g.ntasks;
-    if constexpr (BAT) {
-      if (phase == 1 && g.ntasks_dev) limit = *g.ntasks_dev;
-    }
+    const int64_t limit = phase == 0 ? hub_items : g.ntasks;
     uint64_t base = 0;
     if (lane == 0) base = atomicAdd(&g.qctr[q], (unsigned long long)BATCH);
     base = bcast64(base, 0);
@@ -1151,254 +1143,6 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_census(CensusArgs g) {
   if (lane == 0 && g.wave_span) g.wave_span[2 * wave_id + 1] = __builtin_amdgcn_s_memrealtime();
 }
 
-// ------------------------------------------------- short tasks, grouped
-// A task whose two merged lists (N(u) above u, N(v) from u) are short costs
-// little merging but a whole round of the item path. Such tasks run GT to a
-// round instead: the wavefront's two LDS windows are cut into GT slots of
-// GROUP_W / GT entries, one per task and list (the last entry of a slot holds
-// the sentinel), and each task gets 64 / GT lanes, each walking its merge-path
-// share of that task's merge (Fig. 8) and classifying every w in situ exactly
-// as the item path does. A wavefront claims GROUP_CLAIM consecutive tasks (CSR
-// order) at a time and takes them 64 at a time: every task is sized, the ones
-// whose longer list fits a slot for GT = 8, 4, 2 or 1 are sorted by that fit
-// (bin 0..3) into an LDS list and run GT per round; bin 4 (longer, or split)
-// is appended to a list the item path takes afterwards.
-constexpr int GROUP_WAVES = 2;
-constexpr int GROUP_CLAIM = 1024;  // tasks per claim: claims of a shared counter must stay rare
-__host__ __device__ constexpr int group_tasks(int bin) { return 8 >> bin; }  // tasks per round of bins 0..3
-
-struct GroupTask {  // one task of a round
-  uint32_t aoff, boff;  // first entries of the two lists (entry indices < 2^32)
-  uint32_t lens;        // la | lb << 16
-  uint32_t uq, vq;      // u << 2 | 3 and v << 2 | f_uv
-  uint32_t gid;         // graph of the task (batched census)
-};
-
-struct GroupArgs {
-  const int64_t* off;
-  const uint32_t* packed;
-  const uint32_t* ustart;
-  const uint32_t* tskip;
-  const uint64_t* tasks;
-  int64_t ntasks;
-  const uint32_t* grow;   // batched: graph of each row (else NULL)
-  const int64_t* vbase;   // batched: first row of each graph
-  int64_t n;              // single graph: vertex count
-  unsigned long long* qctr;   // claim counter
-  unsigned long long* nlong;  // tasks handed to the item path
-  int64_t* order4;            // their task indices
-  unsigned long long* acc;    // single graph: [16]
-  unsigned long long* gout;   // batched: [graphs][16]
-  const uint32_t* err;
-  ClassSlices cls;
-};
-
-struct GroupLds {
-  uint32_t a[GROUP_W];
-  uint32_t b[GROUP_W];
-  uint32_t hist[16 * 64];  // [class][lane]
-  GroupTask rec[64];       // this sub-batch's grouped tasks, by bin
-};
-
-__device__ void group_flush(GroupLds& L, int lane, unsigned long long* acc) {
-  wave_lds_sync();
-  for (int c = 1; c < 16; ++c) {
-    const uint64_t sum = wave_sum64((uint64_t)(int64_t)(int32_t)L.hist[c * 64 + lane]);
-    if (lane == 0 && sum) atomicAdd(&acc[c], (unsigned long long)sum);
-    L.hist[c * 64 + lane] = 0;
-  }
-  wave_lds_sync();
-}
-
-// One round: GT tasks (records x of lanes' tasks, slots of GROUP_W / GT).
-template <bool BAT, int GT>
-__device__ __forceinline__ void group_round(const GroupArgs& g, GroupLds& L, int lane, const GroupTask& x, bool valid,
-                                            uint32_t& wg, uint32_t& steps) {
-  constexpr int LPT = 64 / GT, STRIDE = GROUP_W / GT, NL = (STRIDE + LPT - 1) / LPT;
-  const int t = lane / LPT, sl = lane % LPT;
-  uint32_t* const A = L.a + t * STRIDE;
-  uint32_t* const B = L.b + t * STRIDE;
-  const uint32_t la = valid ? x.lens & 0xFFFFu : 0u, lb = valid ? x.lens >> 16 : 0u;
-  uint32_t ra[NL], rb[NL];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const uint32_t j = (uint32_t)(sl + k * LPT);
-    ra[k] = j < la ? g.packed[(uint64_t)x.aoff + j] : 0u;
-    rb[k] = j < lb ? g.packed[(uint64_t)x.boff + j] : 0u;
-  }
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const uint32_t j = (uint32_t)(sl + k * LPT);
-    if (j < la) A[j] = ra[k];
-    if (j < lb) B[j] = rb[k];
-  }
-  if (sl == 0) {
-    A[la] = KEY_INF;
-    B[lb] = KEY_INF;
-  }
-  wave_lds_sync();
-  bool mixed = false;
-  if constexpr (BAT) {
-    const uint32_t g0 = bcast32(x.gid, 0);
-    mixed = __ballot(valid && x.gid != g0) != 0;
-    if (wg != 0xFFFFFFFFu && (mixed || g0 != wg)) {
-      group_flush(L, lane, g.gout + 16 * (uint64_t)wg);
-      steps = 0;
-    }
-    wg = mixed ? 0xFFFFFFFFu : g0;
-  }
-  // this lane's merge-path share of its task's merge (A before B on equal ids)
-  const uint32_t D = la + lb;
-  const uint32_t d0 = (sl * D) / LPT, d1 = ((sl + 1) * D) / LPT;
-  uint32_t lo = d0 > lb ? d0 - lb : 0, hi = d0 < la ? d0 : la;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (key_of(A[mid]) <= key_of(B[d0 - mid - 1])) lo = mid + 1; else hi = mid;
-  }
-  uint32_t i = lo, k = d0 - lo;
-  if (i > 0 && k < lb && key_of(A[i - 1]) == key_of(B[k])) ++k;  // consumed with A[i-1]
-  const uint32_t f = x.vq & 3u, vq = x.vq | 3u;  // v itself (in N(u)) is never counted
-  const uint64_t slice = f == 3u ? g.cls.s[3] : (f == 2u ? g.cls.s[2] : g.cls.s[1]);
-  for (uint32_t pos = i + k; pos < d1; pos = i + k) {
-    const uint32_t a = A[i], b = B[k];
-    const uint32_t ea = a | 3u, eb = b | 3u;
-    const bool ta = ea <= eb, tb = eb <= ea;
-    // canonical selection (Fig. 5 step 2.1.4), as in the item path
-    const bool cA = ta & (ea > vq);
-    const bool cB = (tb & cA) | (!ta & (eb > x.uq));
-    const uint32_t fa = cA ? a & 3u : 0u, sb = cB ? b : 0u;
-    const uint32_t cls = (uint32_t)(slice >> ((((sb << 2) | fa) << 2) & 63u)) & 15u;
-    atomicAdd(&L.hist[cls * 64 + lane], 1u);
-    i += (uint32_t)ta;
-    k += (uint32_t)tb;
-  }
-  wave_lds_sync();
-  if constexpr (BAT) {
-    if (mixed) {
-      // a round over several graphs: each lane's column to its own task's graph
-      for (int c = 1; c < 16; ++c) {
-        const uint32_t v = L.hist[c * 64 + lane];
-        if (valid && v) atomicAdd(&g.gout[16 * (uint64_t)x.gid + c], (unsigned long long)v);
-        L.hist[c * 64 + lane] = 0;
-      }
-      wave_lds_sync();
-    }
-  }
-  steps += 2 * STRIDE / LPT + 2;
-}
-
-template <bool BAT>
-__global__ void __launch_bounds__(GROUP_WAVES * 64) k_census_grouped(GroupArgs g) {
-  __shared__ GroupLds lds[GROUP_WAVES];
-  if (*g.err) return;
-  const int lane = threadIdx.x & 63;
-  GroupLds& L = lds[threadIdx.x >> 6];
-  for (int c = 0; c < 16; ++c) L.hist[c * 64 + lane] = 0;
-  wave_lds_sync();
-  const uint64_t below = (1ull << lane) - 1;
-  uint32_t wg = 0xFFFFFFFFu;  // graph whose counts the LDS columns hold (batched)
-  uint32_t steps = 0;
-  for (;;) {
-    uint64_t base = 0;
-    if (lane == 0) base = atomicAdd(g.qctr, (unsigned long long)GROUP_CLAIM);
-    base = bcast64(base, 0);
-    if ((int64_t)base >= g.ntasks) break;
-    const int64_t cend = min((int64_t)base + GROUP_CLAIM, g.ntasks);
-    for (int64_t s0 = (int64_t)base; s0 < cend; s0 += 64) {
-      // size this lane's task
-      const int64_t tid = s0 + lane;
-      int bin = -1;
-      GroupTask x{};
-      int32_t dyad = 0;
-      if (tid < cend) {
-        const uint64_t tk = g.tasks[tid];
-        if (!(tk & HUB_BIT)) {  // split tasks are merged from the hub list
-          const uint32_t u = (uint32_t)(tk >> 32) & 0x3FFFFFFFu;
-          const int64_t au0 = g.off[u], au1 = g.off[u + 1];
-          const uint32_t pv = g.packed[au0 + (uint32_t)tk];
-          const int64_t bv0 = g.off[pv >> 2], bv1 = g.off[(pv >> 2) + 1];
-          const uint32_t sv = min(g.tskip[tid], (uint32_t)(bv1 - bv0));
-          const uint32_t su = g.ustart[u];
-          const uint32_t la = (uint32_t)(au1 - au0) - su, lb = (uint32_t)(bv1 - bv0) - sv;
-          const uint32_t m = max(la, lb);
-          bin = m < (uint32_t)(GROUP_W / 8) ? 0 : m < (uint32_t)(GROUP_W / 4) ? 1 : m < (uint32_t)(GROUP_W / 2) ? 2
-              : m < (uint32_t)GROUP_W ? 3 : 4;
-          x.aoff = (uint32_t)(au0 + su);
-          x.boff = (uint32_t)(bv0 + sv);
-          x.lens = la | lb << 16;
-          x.uq = (u << 2) | 3u;
-          x.vq = pv;
-          int64_t nn = g.n;
-          if (BAT) {
-            x.gid = g.grow[u];
-            nn = g.vbase[x.gid + 1] - g.vbase[x.gid];
-          }
-          if (bin < 4) dyad = (int32_t)(nn - (int64_t)(au1 - au0) - (int64_t)(bv1 - bv0));
-        }
-      }
-      // tasks for the item path: appended to its list
-      if (g.order4) {
-        const uint64_t m4 = __ballot(bin == 4);
-        if (m4) {
-          uint64_t at = 0;
-          if (lane == 0) at = atomicAdd(g.nlong, (unsigned long long)__popcll(m4));
-          at = bcast64(at, 0);
-          if (bin == 4) g.order4[at + __popcll(m4 & below)] = tid;
-        }
-      }
-      // the dyadic terms n - d(u) - d(v) of the grouped tasks (Fig. 5 step
-      // 2.1.3; the common-neighbour part is added at the end)
-      {
-        const bool mut = (x.vq & 3u) == 3u;
-        const uint32_t g0 = bcast32(x.gid, 0);
-        if (!BAT || __ballot(dyad != 0 && x.gid != g0) == 0) {
-          const uint64_t sa = wave_sum64(mut ? 0 : (uint64_t)(int64_t)dyad);
-          const uint64_t sm = wave_sum64(mut ? (uint64_t)(int64_t)dyad : 0);
-          unsigned long long* tgt = BAT ? g.gout + 16 * (uint64_t)g0 : g.acc;
-          if (lane == 0) {
-            if (sa) atomicAdd(&tgt[1], (unsigned long long)sa);
-            if (sm) atomicAdd(&tgt[2], (unsigned long long)sm);
-          }
-        } else if (dyad != 0) {
-          atomicAdd(&g.gout[16 * (uint64_t)x.gid + (mut ? 2 : 1)], (unsigned long long)(int64_t)dyad);
-        }
-      }
-      // the grouped tasks into LDS, bin by bin
-      uint32_t nb[4], sb[4];
-      uint32_t run = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint64_t mq = __ballot(bin == q);
-        if (bin == q) L.rec[run + __popcll(mq & below)] = x;
-        nb[q] = (uint32_t)__popcll(mq);
-        sb[q] = run;
-        run += nb[q];
-      }
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int GTq = 8 >> q;
-        for (uint32_t r = 0; r < nb[q]; r += (uint32_t)GTq) {
-          const uint32_t slot = (uint32_t)(lane / (64 / GTq));
-          const bool valid = r + slot < nb[q];
-          GroupTask y{};
-          if (valid) y = L.rec[sb[q] + r + slot];
-          if (q == 0) group_round<BAT, 8>(g, L, lane, y, valid, wg, steps);
-          else if (q == 1) group_round<BAT, 4>(g, L, lane, y, valid, wg, steps);
-          else if (q == 2) group_round<BAT, 2>(g, L, lane, y, valid, wg, steps);
-          else group_round<BAT, 1>(g, L, lane, y, valid, wg, steps);
-        }
-      }
-      wave_lds_sync();
-      if (steps > (1u << 30)) {
-        if (!BAT || wg != 0xFFFFFFFFu) group_flush(L, lane, BAT ? g.gout + 16 * (uint64_t)wg : g.acc);
-        steps = 0;
-      }
-    }
-  }
-  if (!BAT || wg != 0xFFFFFFFFu) group_flush(L, lane, BAT ? g.gout + 16 * (uint64_t)wg : g.acc);
-}
-
 // The dyadic counts (Fig. 5 step 2.1.3) need each task's number of common
 // neighbours of u and v, added to 012 or 102 by the task's dyad. Summed over
 // the tasks of each dyad kind these follow from the triangle classes: a
@@ -1542,18 +1286,6 @@ static hipError_t launch_census(int waves, int variant, const CensusArgs& a, int
     case 2: return launch_v<2>(variant, a, cyc, groups, s);
     default: return launch_v<4>(variant, a, cyc, groups, s);
   }
-}
-
-// Persistent grid of a grouped-task kernel: every workgroup resident.
-template <bool BAT>
-static int group_grid() {
-  DeviceInfo di;
-  if (device_info(&di) != TRIAD_OK) return 1024;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census_grouped<BAT>, GROUP_WAVES * 64, 0) !=
-          hipSuccess || per_cu < 1)
-    per_cu = 1;
-  return di.cus * per_cu;
 }
 
 // The labelled census (64 state counters per column, two 16-bit counters per
@@ -1732,7 +1464,7 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     return hres[16] ? TRIAD_OK_003_WRAPPED : TRIAD_OK;
   }
   uint32_t* err = nullptr;
-  // NC census counters, 2 queue counters, hub tasks, long rows, grouped-task claims
+  // NC census counters, 2 queue counters, hub tasks
   unsigned long long* acc = nullptr;
   ALLOC(err, 1);
   ALLOC(acc, NC + 5);
@@ -2069,7 +1801,11 @@ struct triad_batch_plan {
   hipGraphExec_t exec = nullptr;
   hipStream_t last = nullptr;
   int launched = 0;
+  bool drained = true;  // nothing launched since the last wait
   size_t bytes = 0;  // device memory the plan holds (counted against the memory cap)
+  void* block = nullptr;  // its one scratch block, from the held blocks of `device`
+  size_t block_bytes = 0;
+  int device = -1;
 };
 
 namespace triad {
@@ -2079,6 +1815,17 @@ static void plan_free(triad_batch_plan* p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
   for (void* b : p->bufs) (void)hipFree(b);
+  if (p->block) {
+    // hipFree would wait for the device; a kept block has to wait as well
+    // before another call may take it
+    int dev = -1;
+    (void)hipGetDevice(&dev);
+    if (dev != p->device) (void)hipSetDevice(p->device);
+    const bool idle = p->drained || hipDeviceSynchronize() == hipSuccess;
+    if (dev != p->device) (void)hipSetDevice(dev);
+    if (idle) held_give(p->block, p->block_bytes, p->device);
+    else (void)hipFree(p->block);
+  }
   delete p;
 }
 
@@ -2097,7 +1844,8 @@ static hipError_t plan_alloc(triad_batch_plan* p, T** ptr, int64_t count) {
 // Graph bases of a batch: vbase[0] = 0, non-decreasing, vbase[G] = nv, and
 // every member below BATCH_MAX_N vertices (C(n_g, 3) < 2^64).
 constexpr int64_t BATCH_MAX_N = 4801281;
-static int check_vbase(int32_t G, int64_t nv, const int64_t* hv) {
+static int check_vbase(int32_t G, int64_t nv, const int64_t* hv, int64_t* nmax = nullptr) {
+  if (nmax) *nmax = 0;
   if (hv[0] != 0) return fail(TRIAD_EINVAL, "vbase[0] must be 0");
   if (hv[G] != nv) return fail(TRIAD_EINVAL, "vbase[G] must equal the number of rows nv");
   for (int32_t g = 0; g < G; ++g) {
@@ -2105,8 +1853,15 @@ static int check_vbase(int32_t G, int64_t nv, const int64_t* hv) {
     if (hv[g + 1] - hv[g] >= BATCH_MAX_N)
       return fail(TRIAD_EINVAL, "graph " + std::to_string(g) + " has 4,801,281 or more vertices (its 003 count "
                                 "would not fit in 64 bits); census it on its own");
+    if (nmax) *nmax = std::max(*nmax, hv[g + 1] - hv[g]);
   }
   return TRIAD_OK;
+}
+
+// Entries that a wavefront of the batched triangle listing takes per turn, by
+// kernel variant (the default and every odd one: 512).
+static int64_t batch_range(int32_t variant) {
+  return variant <= 0 || variant > NUM_VARIANTS ? 512 : (int64_t)128 << (variant % 4 + 1);
 }
 
 static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, const int64_t* off, const int32_t* nbr,
@@ -2122,6 +1877,7 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
   if (waves != 1 && waves != 2 && waves != 4) return fail(TRIAD_EINVAL, "waves_per_group must be 1, 2 or 4");
   DeviceInfo di;
   if (int st = device_info(&di)) return st;
+  int64_t nmax = 0;
   // The graph bases are checked on the host before anything is captured or
   // launched: every kernel indexes rows through them, and each member's null
   // count C(n_g, 3) is formed in 64 bits.
@@ -2129,7 +1885,7 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
     std::vector<int64_t> hv((size_t)G + 1);
     HIPCHK(hipMemcpyAsync(hv.data(), vbase, sizeof(int64_t) * ((size_t)G + 1), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (int st = check_vbase(G, nv, hv.data())) return st;
+    if (int st = check_vbase(G, nv, hv.data(), &nmax)) return st;
   }
   triad_batch_plan* p = new triad_batch_plan;
   p->G = G;
@@ -2137,48 +1893,33 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
   p->nnz = nnz;
   p->vbase = vbase;
   p->out = d_out;
+  // Triangles are listed unless the caller asks for the per-task merge
+  const bool merge = o.short_tasks < 0;
   uint32_t *grow = nullptr, *ustart = nullptr, *packed = nullptr, *tskip = nullptr, *rowmark = nullptr;
   int64_t *ntask = nullptr, *tpre = nullptr, *bsum = nullptr;
   uint64_t* tasks = nullptr;
-  unsigned long long* q = nullptr;  // census queue [2], long rows, grouped bins [3]
+  unsigned long long* q = nullptr;  // census queue [2]
   const int64_t ntasks = nnz / 2;
-  // short tasks run grouped (task records hold 32-bit entry offsets)
-  const bool grouped = ntasks > 0 && nnz + PAD < ((int64_t)1 << 32) && o.short_tasks >= 0;
-  int64_t* order4 = nullptr;
   unsigned long long* gacc = nullptr;  // per-graph counters; d_out is written only by a clean finalize
-  if (plan_alloc(p, &p->err, 1) || plan_alloc(p, &q, 6) || plan_alloc(p, &gacc, (int64_t)G * 16) || plan_alloc(p, &grow, nv) || plan_alloc(p, &ustart, nv) ||
-      plan_alloc(p, &ntask, nv) || plan_alloc(p, &tpre, nv + 1) || plan_alloc(p, &bsum, nv / SCAN_B + 2) ||
-      plan_alloc(p, &packed, nnz + PAD) || plan_alloc(p, &tasks, ntasks) || plan_alloc(p, &tskip, ntasks) ||
-      plan_alloc(p, &rowmark, (nnz >> 5) + 1) ||
-      (grouped && plan_alloc(p, &order4, ntasks))) {
+  bool failed = false;
+  if (merge) {
+    failed = plan_alloc(p, &p->err, 1) || plan_alloc(p, &q, 2) || plan_alloc(p, &gacc, (int64_t)G * 16) ||
+             plan_alloc(p, &grow, nv) || plan_alloc(p, &ustart, nv) || plan_alloc(p, &ntask, nv) ||
+             plan_alloc(p, &tpre, nv + 1) || plan_alloc(p, &bsum, nv / SCAN_B + 2) ||
+             plan_alloc(p, &packed, nnz + PAD) || plan_alloc(p, &tasks, ntasks) || plan_alloc(p, &tskip, ntasks) ||
+             plan_alloc(p, &rowmark, (nnz >> 5) + 1);
+  } else {
+    p->device = di.device;
+    const size_t bytes = sweep_batch_bytes(G, nv, nnz);
+    failed = !within_cap(bytes) || held_take(&p->block, bytes, &p->block_bytes) != hipSuccess;
+    p->bytes = bytes;
+  }
+  if (failed) {
+    p->block_bytes = 0;
     plan_free(p);
     (void)hipGetLastError();
     return fail(TRIAD_ENOMEM, "device allocation for the batch plan failed");
   }
-  CensusArgs a{};
-  a.n = 0;
-  a.off = off;
-  a.packed = packed;
-  a.ustart = ustart;
-  a.tskip = tskip;
-  a.tasks = tasks;
-  a.htasks = tasks;
-  a.order = nullptr;
-  a.ntasks = ntasks;
-  a.hub_task = nullptr;
-  a.hub_pre = nullptr;
-  a.nhub = 0;
-  a.chunk = 1;
-  a.qctr = q;
-  a.acc = gacc;
-  a.cycles = nullptr;
-  a.wave_span = nullptr;
-  a.grow = grow;
-  a.vbase = vbase;
-  a.gout = gacc;
-  a.err = p->err;
-  a.cls = class_slices();
-  const int groups = census_groups(waves, variant, 2, o.grid_groups);
   // capture the whole batched census as one graph (fills instead of memsets)
   // on a private stream: the caller's stream may be the legacy null stream,
   // which cannot be captured; launches replay it on the caller's stream
@@ -2191,56 +1932,57 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
     return fail(TRIAD_EDEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
   }
   s = cs;
-  k_fill_u32<<<1, 64, 0, s>>>(p->err, 1, 0);
-  k_fill_u64<<<1, 64, 0, s>>>((uint64_t*)q, 6, 0);  // queue counters, long rows, grouped bins
-  k_fill_u64<<<grid_for((int64_t)G * 16, 256, 4096), 256, 0, s>>>((uint64_t*)gacc, (int64_t)G * 16, 0);
-  if (nv > 0) {
-    k_fill_u32<<<grid_for((nnz >> 5) + 1, 256, 4096), 256, 0, s>>>(rowmark, (nnz >> 5) + 1, 0);
-    k_rows_batch<<<grid_for(nv, 256, 65535), 256, 0, s>>>(G, nv, nnz, vbase, off, nbr, grow, ustart, ntask, rowmark,
-                                                          p->err);
-    if (nnz > 0)
-      k_entries_batch<<<grid_for(nnz, ETILE, 65536), 256, 0, s>>>(G, nnz, vbase, off, nbr, flg, rowmark, packed,
-                                                                 p->err);
-    scan_excl_pre(ntask, nv, tpre, bsum, s);
-    k_check_tasks<<<1, 64, 0, s>>>(tpre, nv, nnz, p->err);
-    if (ntasks > 0) {
-      // the ids of N(v) below u are counted (the merge starts N(v) at u) when
-      // the short tasks run grouped, where every merged entry weighs
-      const EmitArgs ea{nv, off, packed, ustart, tpre, tasks, tskip, grouped ? 1 : 0, -1, p->err, nullptr, nullptr};
-      launch_emit_entries(ea, nnz, s);
-      if (grouped) {
-        GroupArgs ga{};
-        ga.off = off;
-        ga.packed = packed;
-        ga.ustart = ustart;
-        ga.tskip = tskip;
-        ga.tasks = tasks;
-        ga.ntasks = ntasks;
-        ga.grow = grow;
-        ga.vbase = vbase;
-        ga.n = 0;
-        ga.qctr = q + 3;
-        ga.nlong = q + 4;
-        ga.order4 = order4;
-        ga.acc = nullptr;
-        ga.gout = gacc;
-        ga.err = p->err;
-        ga.cls = class_slices();
-        k_census_grouped<true><<<group_grid<true>(), GROUP_WAVES * 64, 0, s>>>(ga);
-        // the rest through the item path, in CSR order
-        a.order = order4;
-        a.ntasks_dev = (const int64_t*)(q + 4);
+  int st = TRIAD_OK;
+  if (merge) {
+    k_fill_u32<<<1, 64, 0, s>>>(p->err, 1, 0);
+    k_fill_u64<<<1, 64, 0, s>>>((uint64_t*)q, 2, 0);  // queue counters
+    k_fill_u64<<<grid_for((int64_t)G * 16, 256, 4096), 256, 0, s>>>((uint64_t*)gacc, (int64_t)G * 16, 0);
+    if (nv > 0) {
+      k_fill_u32<<<grid_for((nnz >> 5) + 1, 256, 4096), 256, 0, s>>>(rowmark, (nnz >> 5) + 1, 0);
+      k_rows_batch<<<grid_for(nv, 256, 65535), 256, 0, s>>>(G, nv, nnz, vbase, off, nbr, grow, ustart, ntask, rowmark,
+                                                            p->err);
+      if (nnz > 0)
+        k_entries_batch<<<grid_for(nnz, ETILE, 65536), 256, 0, s>>>(G, nnz, vbase, off, nbr, flg, rowmark, packed,
+                                                                   p->err);
+      scan_excl_pre(ntask, nv, tpre, bsum, s);
+      k_check_tasks<<<1, 64, 0, s>>>(tpre, nv, nnz, p->err);
+      if (ntasks > 0) {
+        const EmitArgs ea{nv, off, packed, ustart, tpre, tasks, tskip, 0, -1, p->err, nullptr, nullptr};
+        launch_emit_entries(ea, nnz, s);
+        CensusArgs a{};
+        a.off = off;
+        a.packed = packed;
+        a.ustart = ustart;
+        a.tskip = tskip;
+        a.tasks = tasks;
+        a.htasks = tasks;
+        a.ntasks = ntasks;
+        a.chunk = 1;
+        a.qctr = q;
+        a.acc = gacc;
+        a.grow = grow;
+        a.vbase = vbase;
+        a.gout = gacc;
+        a.err = p->err;
+        a.cls = class_slices();
+        (void)launch_census(waves, variant, a, census_groups(waves, variant, 2, o.grid_groups), s);
       }
-      (void)launch_census(waves, variant, a, groups, s);
     }
+    k_finalize_batch<<<(G + 255) / 256, 256, 0, s>>>(G, vbase, gacc, p->err, d_out);
+  } else {
+    Scratch arena(s, p->block, p->block_bytes);
+    const SweepIn in{nv, nnz, off, nbr, flg};
+    const int wpg = o.waves_per_group ? o.waves_per_group : 4;
+    const int groups = o.grid_groups > 0 ? o.grid_groups : sweep_batch_groups(wpg);
+    st = sweep_batch(G, nv, in, vbase, nmax, wpg, groups, batch_range(o.kernel_variant), d_out, &p->err, arena, s);
   }
-  k_finalize_batch<<<(G + 255) / 256, 256, 0, s>>>(G, vbase, gacc, p->err, d_out);
   e = hipStreamEndCapture(s, &p->graph);
   if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
   (void)hipStreamDestroy(cs);
-  if (e != hipSuccess) {
+  if (st != TRIAD_OK || e != hipSuccess) {
     plan_free(p);
-    return fail(TRIAD_EDEVICE, std::string("batch graph capture failed: ") + hipGetErrorString(e));
+    return st != TRIAD_OK ? st
+                          : fail(TRIAD_EDEVICE, std::string("batch graph capture failed: ") + hipGetErrorString(e));
   }
   *out_plan = p;
   return TRIAD_OK;
@@ -2368,15 +2110,17 @@ int triad_batch_plan_launch(triad_batch_plan* plan, void* hip_stream) {
   HIPCHK(hipGraphLaunch(plan->exec, s));
   plan->last = s;
   plan->launched = 1;
+  plan->drained = false;
   return TRIAD_OK;
 }
 
 int triad_batch_plan_status(triad_batch_plan* plan) {
   if (!plan) return fail(TRIAD_EINVAL, "invalid plan");
   if (!plan->launched) return fail(TRIAD_EINVAL, "plan not launched");
-  HIPCHK(hipStreamSynchronize(plan->last));
   uint32_t e = 0;
-  HIPCHK(hipMemcpy(&e, plan->err, sizeof(e), hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpyAsync(&e, plan->err, sizeof(e), hipMemcpyDeviceToHost, plan->last));
+  HIPCHK(hipStreamSynchronize(plan->last));
+  plan->drained = true;
   if (e) return fail(status_from_bits(e), "batch input validation failed on the device");
   return TRIAD_OK;
 }
@@ -2426,13 +2170,13 @@ int triad_batch_autotune(int32_t G, int64_t nv, int64_t nnz, const int64_t* d_vb
   snprintf(sig, sizeof sig, "%s|G=%d|nv=%lld|nnz=%lld|h=%016llx|d2=%llu", di.name.c_str(), (int)G, (long long)nv,
            (long long)nnz, hsig[0], hsig[1]);
   // the candidate launch shapes; a cached line naming any other is ignored
-  const int variants[4] = {V_W448_HH7 + 1, V_W512_HH6 + 1, V_W512 + 1, V_W512_HH + 1};
+  const int variants[4] = {1, 2, 3, 4};
   const int wavess[2] = {1, 2};
   auto candidate = [&](int kv, int wv, int gg) {
     for (int vi = 0; vi < 4; ++vi)
       for (int wi = 0; wi < 2; ++wi)
         for (int gm = 1; gm <= 2; ++gm)
-          if (kv == variants[vi] && wv == wavess[wi] && gg == census_groups(wv, kv - 1, 2, 0) * gm) return true;
+          if (kv == variants[vi] && wv == wavess[wi] && gg == sweep_batch_groups(wv) * gm) return true;
     return false;
   };
   // cache: one JSON object per line: {"sig": "...", "kernel_variant": k, "waves_per_group": w, "grid_groups": g, "ms": t}
@@ -2474,7 +2218,7 @@ int triad_batch_autotune(int32_t G, int64_t nv, int64_t nnz, const int64_t* d_vb
         triad_opts o{};
         o.kernel_variant = variants[vi];
         o.waves_per_group = wavess[wi];
-        o.grid_groups = census_groups(o.waves_per_group, variants[vi] - 1, 2, 0) * gm;
+        o.grid_groups = sweep_batch_groups(o.waves_per_group) * gm;
         triad_batch_plan* p = nullptr;
         status = triad_batch_plan_create(G, nv, nnz, d_vbase, d_offsets, d_nbrs, d_flags, out, &o, hip_stream, &p);
         if (status != TRIAD_OK) break;

@@ -39,4 +39,15 @@ constexpr int SW_STATUS = 18;
 void sweep_finish(const unsigned long long* acc, uint32_t* err, int64_t nnz, int64_t n, uint64_t* d_out,
                   uint64_t* status, hipStream_t s);
 
+// A batch (the concatenated CSR of in, nv rows, the largest member nmax
+// vertices): enqueues the whole batched census; d_out [graphs][16] is written
+// unless an error is found, *err (one word, in scratch memory) has its bits
+// afterwards. Its scratch is sweep_batch_bytes from an arena. Launch shape:
+// wavefronts per workgroup (1, 2, 4), workgroups, entries per wavefront and
+// turn (a multiple of 64). Capturable.
+size_t sweep_batch_bytes(int32_t graphs, int64_t nv, int64_t nnz);
+int sweep_batch_groups(int waves);  // default workgroups
+int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vbase, int64_t nmax, int waves,
+                int groups, int64_t range, uint64_t* d_out, uint32_t** err, Scratch& scratch, hipStream_t s);
+
 }  // namespace triad

@@ -30,6 +30,10 @@
 //   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
 //   k_sw_rest    all others: one wavefront and a small table in LDS
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
+// A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_rest
+// as one disjoint union with ids local to each graph, its counters by graph
+// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 32.9 ms a launch; 256
+// graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.57 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,6 +46,7 @@ namespace {
 
 constexpr int OT = 4096;  // entries of one orientation tile
 constexpr int OTHREADS = 256, OPER = OT / OTHREADS;
+constexpr int TILE_GRAPHS = 8;  // graphs of a batch whose sums a tile keeps in LDS
 constexpr int ROWS_THREADS = 1024, ROWS_PER = 16;
 constexpr int BUCKETS = 1024;          // degree buckets of the ranking
 constexpr int64_t DIRECT_N = 16384;    // graphs up to here index their tables by vertex id
@@ -110,6 +115,10 @@ struct RowArgs {
   uint32_t* mark;      // bit per entry: a row starts here
   uint32_t* tile_row;  // row that holds each tile's first entry
   uint32_t* err;
+  // a batch: its graphs, their first rows, and the graph of each row (out)
+  int32_t graphs;
+  const int64_t* vbase;
+  uint32_t* grow;
 };
 
 __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
@@ -127,6 +136,14 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
     const uint32_t d = ok ? (uint32_t)(e - b) : 0;
     if (!ok) atomicOr(a.err, ERR_RANGE);
     a.info[u] = ok ? (uint64_t)b << 24 : 0;
+    if (a.vbase) {
+      int32_t lo = 0, hi = a.graphs;  // the last graph with vbase[g] <= u
+      while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (a.vbase[mid] <= u) lo = mid; else hi = mid;
+      }
+      a.grow[u] = (uint32_t)lo;
+    }
     if (a.deg) a.deg[u] = d;
     if (a.hist) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
     if (d) {
@@ -205,6 +222,8 @@ struct RowSums {
   static __device__ __forceinline__ int slot(int k) {
     return k == 0 ? 1 : k == 1 ? 2 : k == 7 ? 10 : k == 8 ? SW_MUT : k + 1;
   }
+  // a graph of a batch keeps the mutual count in the place of 003
+  static __device__ __forceinline__ int batch_slot(int k) { return k == 8 ? 0 : slot(k); }
   __device__ __forceinline__ void add_to(unsigned long long* acc, int lane) {
     for (int k = 0; k < 9; ++k) {
       const uint64_t s = sum64(c[k]);
@@ -235,11 +254,16 @@ struct OrientArgs {
   uint32_t* counts;  // [0] of mid, [1] of lng
   unsigned long long* acc;
   uint32_t* err;
+  // a batch: ids are local to their graph, the class sums go to gacc[graph][16]
+  const int64_t* vbase;
+  const uint32_t* grow;
+  unsigned long long* gacc;
 };
 
 __device__ __forceinline__ uint64_t below(int k) { return (1ull << k) - 1; }  // k in [0, 63]
 
-template <bool RANK>
+// RANK: lists hold ranks, else ids. BAT: a batch (ids).
+template <bool RANK, bool BAT>
 __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
   __shared__ uint32_t at[OT];  // at a row start: the row, later its N+ length in the tile
   __shared__ uint64_t heads[OT / 64 + 1], fwd[OT / 64 + 1], b0[OT / 64 + 1], b1[OT / 64 + 1];
@@ -248,6 +272,7 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
   __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last of the tile): where their entries go
   __shared__ uint32_t lastc;             // start of the last segment if its row crosses the tile's end
   __shared__ uint32_t mids[64], lngs[64], nlist[2], lbase[2];
+  __shared__ unsigned long long gsum[BAT ? TILE_GRAPHS : 1][9];  // BAT: sums of the tile's first graphs
   if (a.err[0]) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint32_t bad = 0;
@@ -265,7 +290,9 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
         nlist[0] = nlist[1] = 0;
       }
     }
+    if (BAT && tid >= 128 && tid - 128 < TILE_GRAPHS * 9) (&gsum[0][0])[tid - 128] = 0;
     __syncthreads();
+    const uint32_t g0 = BAT ? a.grow[a.tile_row[t]] : 0u;
     const int32_t* nb = a.nbr + t0;
     int32_t y[OPER];
     uint32_t wd[OPER];
@@ -316,6 +343,13 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
       const int h = m ? wi * 64 + 63 - __builtin_clzll(m) : last[wi];
       hd[i] = (uint16_t)h;
       const uint32_t x = at[h];
+      int64_t base = 0, ng = a.n;
+      if (BAT && in) {
+        const uint32_t g = a.grow[x];
+        base = a.vbase[g];
+        ng = a.vbase[g + 1] - base;
+      }
+      const int32_t xl = (int32_t)(x - base);  // the row's id as its entries name it
       int32_t pv = __shfl_up(y[i], 1, 64);
       const bool start = (hw >> lane) & 1ull;
       if (lane == 0 && in && t0 + p > 0) pv = nb[p - 1];
@@ -324,19 +358,19 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
       bool f = false;
       if (in) {
         if (!first && pv >= y[i]) bad |= ERR_UNSORTED;
-        if (y[i] == (int32_t)x) bad |= ERR_SELFLOOP;
+        if (y[i] == xl) bad |= ERR_SELFLOOP;
         if (wd[i] == 0) bad |= ERR_RANGE;
-        if (y[i] < 0 || y[i] >= a.n) {
+        if (y[i] < 0 || y[i] >= ng) {
           bad |= ERR_RANGE;
           y[i] = 0;
         }
-        const uint32_t kx = a.key[x], ky = a.key[y[i]];
-        f = RANK ? ky < kx : (ky > kx || (ky == kx && y[i] > (int32_t)x));
+        const uint32_t kx = a.key[x], ky = a.key[base + y[i]];
+        f = RANK ? ky < kx : (ky > kx || (ky == kx && y[i] > xl));
         const uint32_t g = wd[i];
         // N+ words carry f_xy and the rank (id) of y; in-list words of row x
         // the id of y and f_yx, the flag seen from y
         wd[i] = f ? (g << 30 | (RANK ? ky : (uint32_t)y[i])) : (((g & 1u) << 31) | ((g >> 1) << 30) | (uint32_t)y[i]);
-        const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1), ma = __ballot(y[i] > (int32_t)x);
+        const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1), ma = __ballot(y[i] > xl);
         if (lane == 0) {
           above += (uint64_t)__popcll(ma);
           fwd[wi] = mf;
@@ -390,7 +424,18 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
         const uint32_t fl = nf > SORT_MAX ? UNSORTED : 0u;
         a.info[x] = (uint64_t)ox << 24 | (min(nf, LEN_MASK) | (RANK ? fl : 0u));
         at[p] = nf;
-        sums.row((uint64_t)a.n, o, in, mu);
+        if constexpr (BAT) {
+          const uint32_t g = a.grow[x];
+          RowSums one;
+          one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), o, in, mu);
+          for (int k = 0; k < 9; ++k) {
+            if (!one.c[k]) continue;
+            if (g - g0 < TILE_GRAPHS) atomicAdd(&gsum[g - g0][k], (unsigned long long)one.c[k]);
+            else atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
+          }
+        } else {
+          sums.row((uint64_t)a.n, o, in, mu);
+        }
         if (RANK && nf > SORT_MIN && nf <= SORT_MAX) {
           const uint32_t k = nf > SORT_MID;
           (k ? lngs : mids)[atomicAdd(&nlist[k], 1u)] = x;
@@ -412,6 +457,12 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
     if (RANK) {
       if (tid < (int)nlist[0]) a.mid[lbase[0] + tid] = mids[tid];
       if (tid < (int)nlist[1]) a.lng[lbase[1] + tid] = lngs[tid];
+    }
+    if constexpr (BAT) {
+      if (tid < TILE_GRAPHS * 9) {
+        const unsigned long long v = gsum[tid / 9][tid % 9];
+        if (v) atomicAdd(&a.gacc[(uint64_t)(g0 + tid / 9) * 16 + RowSums::batch_slot(tid % 9)], v);
+      }
     }
     // place the entries
     const bool cross0 = at[0] == 0xFFFFFFFFu;
@@ -442,7 +493,7 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
 }
 
 // Rows that cross tile boundaries, at the first boundary inside each.
-template <bool RANK>
+template <bool RANK, bool BAT>
 __global__ void k_sw_cross(OrientArgs a) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   RowSums sums;
@@ -454,7 +505,15 @@ __global__ void k_sw_cross(OrientArgs a) {
       const Cross c = a.cross[t];
       const uint32_t fl = RANK && c.f > SORT_MAX ? UNSORTED : 0u;
       a.info[x] = (uint64_t)ox << 24 | (min(c.f, LEN_MASK) | fl);
-      sums.row((uint64_t)a.n, c.o, c.i, c.m);
+      if constexpr (BAT) {
+        const uint32_t g = a.grow[x];
+        RowSums one;
+        one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), c.o, c.i, c.m);
+        for (int k = 0; k < 9; ++k)
+          if (one.c[k]) atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
+      } else {
+        sums.row((uint64_t)a.n, c.o, c.i, c.m);
+      }
       if (RANK && c.f > SORT_MIN && c.f <= SORT_MAX) {
         const uint32_t k = c.f > SORT_MID;
         (k ? a.lng : a.mid)[atomicAdd(&a.counts[k], 1u)] = x;
@@ -664,18 +723,18 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
   return __popcll(m);
 }
 
-// Streams the cnt listed N+(x) against the table of y: four lists at a time,
-// one per 16 lanes and four entries a lane, in two such sets in turn, so that
-// one set's loads are in flight while the other is counted (loads are never
-// skipped, an idle lane rereads the list's first words: the wait for a set is
-// then for its own loads only). A list in rank order ends with the 64 entries
-// that reach y's rank.
-template <bool SORTED, bool TOP, bool WIDE, class Probe>
+// Streams the cnt listed N+(x) against the table of y: one list per GL lanes
+// and four entries a lane, in two such sets in turn, so that one set's loads
+// are in flight while the other is counted (loads are never skipped, an idle
+// lane rereads the list's first words: the wait for a set is then for its own
+// loads only). A list in rank order ends with the step that reaches y's rank.
+template <int GL, bool SORTED, bool TOP, bool WIDE, class Probe>
 __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const XList<WIDE>& L, int cnt,
                                        uint32_t yrank, int lane, Tri& tri, Probe probe) {
-  constexpr uint64_t G0 = 0x0001000100010001ull;  // the first lane of each 16
-  const int l4 = (lane & 15) * 4;
-  const uint64_t before = below(lane & 48);
+  constexpr uint64_t G0 = GL == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;  // first lane of each group
+  constexpr int STEP = 4 * GL, SETS = 64 / GL;
+  const int l4 = (lane & (GL - 1)) * 4;
+  const uint64_t before = below(lane & (64 - GL));
   struct Slot {
     typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // the lane's next entries
     int left;      // entries of the list from there on (0 or less: none)
@@ -696,29 +755,30 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
       s.o = L.p[k] + l4;
       s.left = (int)(m & LEN_MASK) - l4;
       s.g8 = (m >> 30) * 0x55u;
-      s.lim = (m & UNSORTED) ? ~0u : yrank;
+      // (lists of up to SORT_MIN entries are not sorted)
+      s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : yrank;
     }
   };
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     sl[i].o = 0;
     sl[i].g8 = sl[i].lim = 0;
-    take(sl[i], i * 4 + (lane >> 4));
+    take(sl[i], i * SETS + lane / GL);
     load(sl[i]);
   }
-  int next = 8;
+  int next = 2 * SETS;
   auto step = [&](Slot& s) {
     uint32_t y[4];
     probe(s.w, y);
     tri.add4<TOP>(s.w, y, s.left, s.g8);
-    // lists that end here: the first lane of their 16 has at most 64 left, or
-    // the last entry read has reached y
-    uint64_t d = __ballot(s.left <= 64) & G0;
-    if (SORTED) d |= (__ballot((s.w[3] & ID_MASK) >= s.lim) >> 15) & G0;
-    s.o += 64;
-    s.left -= 64;
+    // lists that end here: their first lane has at most one step left, or the
+    // last entry read has reached y
+    uint64_t d = __ballot(s.left <= STEP) & G0;
+    if (SORTED) d |= (__ballot((s.w[3] & ID_MASK) >= s.lim) >> (GL - 1)) & G0;
+    s.o += STEP;
+    s.left -= STEP;
     if (d) {
-      const uint64_t all = (d << 16) - d;
+      const uint64_t all = (d << GL) - d;
       if (__builtin_amdgcn_inverse_ballot_w64(all)) take(s, next + __popcll(d & before));
       next += __popcll(d);
     }
@@ -746,6 +806,10 @@ struct CountArgs {
   int64_t range;       // k_sw_rest: entries of one wavefront
   unsigned long long* acc;
   const uint32_t* err;
+  // a batch (see OrientArgs)
+  const int64_t* vbase;
+  const uint32_t* grow;
+  unsigned long long* gacc;
 };
 
 // Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
@@ -836,7 +900,7 @@ __global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
       if (k >= cnt) break;
       const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
       wave_sync();
-      stream<true, false, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4]) {
+      stream<16, true, false, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4]) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & ID_MASK, (uint32_t)HUB_RANKS)];
       });
@@ -892,7 +956,7 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
         if (k >= cnt) break;
         const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
         wave_sync();
-        stream<true, true, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4]) {
+        stream<16, true, true, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4]) {
           uint32_t top = 0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -921,20 +985,23 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
 }
 
 // The other vertices: a wavefront takes a range of entries and the rows whose
-// in-lists lie in it, one row at a time. RANK: hash table of N+(y); else all
-// vertices, whose ids are below DIRECT_N and index a two-bit table.
-template <bool RANK, bool WIDE>
-__global__ void __launch_bounds__(REST_WAVES * 64, RANK ? 4 : 5) k_sw_rest(CountArgs a) {
+// in-lists lie in it, one row at a time. BITS: the ids are below DIRECT_N and
+// index a two-bit table of N+(y); else a hash table, filled TAB_MAX entries at
+// a time. RANK: lists in ranks, and only the rows that the kernels above leave;
+// else all rows. BAT: a batch, counted by graph.
+template <bool BITS, bool RANK, bool BAT, bool WIDE>
+__global__ void __launch_bounds__(REST_WAVES * 64, BITS ? 5 : 4) k_sw_rest(CountArgs a) {
   __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
   __shared__ XList<WIDE> xl[REST_WAVES];
   if (a.err[0] | a.err[1]) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   XList<WIDE>& L = xl[w];
-  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = RANK ? SLOT_FREE : 0u;
+  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = BITS ? 0u : SLOT_FREE;
   Tri tri;
-  const int64_t nw = (int64_t)gridDim.x * REST_WAVES;
-  for (int64_t j0 = ((int64_t)blockIdx.x * REST_WAVES + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
+  uint32_t graph = 0;
+  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+  for (int64_t j0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
     const int64_t j1 = min(j0 + a.range, a.nnz);
     // the row that holds entry j0, by a 64-way search between tile starts
     const int64_t t = j0 / OT;
@@ -965,6 +1032,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, RANK ? 4 : 5) k_sw_rest(Count
           yr = a.rank[r + lane];
           if (route(yr, plus, e - bs) != 2) hi = lo;
         }
+        if (BAT && hi > lo) yr = a.grow[r + lane];
       }
       uint64_t todo = __ballot(hi > lo);
       while (todo) {
@@ -973,31 +1041,44 @@ __global__ void __launch_bounds__(REST_WAVES * 64, RANK ? 4 : 5) k_sw_rest(Count
         const uint64_t yi = rl64(in, s);
         const int64_t f0 = (int64_t)(yi >> 24), l0 = (int64_t)rl64((uint64_t)lo, s), l1 = (int64_t)rl64((uint64_t)hi, s);
         const uint32_t plus = (uint32_t)yi & LEN_MASK, rk = rl(yr, s);
-        for (uint32_t i = lane; i < plus; i += 64) {
-          const uint32_t z = a.list[f0 + i];
-          if (RANK) set_hash(tab, z); else set_bits(tab, z);
+        const uint64_t* info = a.info;
+        if (BAT) {
+          if (rk != graph) {
+            tri.flush(a.gacc + (uint64_t)graph * 16, lane);
+            graph = rk;
+          }
+          info += a.vbase[graph];
         }
-        wave_sync();
-        for (int64_t k = l0; k < l1; k += 64) {
-          const int nx = list_x<WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), a.info, lane);
+        for (uint32_t f = 0; f < plus; f += TAB_MAX) {
+          const uint32_t fe = BITS ? plus : min(f + TAB_MAX, plus);
+          for (uint32_t i = f + lane; i < fe; i += 64) {
+            const uint32_t z = a.list[f0 + i];
+            if (BITS) set_bits(tab, z); else set_hash(tab, z);
+          }
           wave_sync();
-          stream<RANK, true, WIDE>(a.list, L, nx, rk, lane, tri, [&](const uint32_t (&q)[4], uint32_t (&g)[4]) {
+          for (int64_t k = l0; k < l1; k += 64) {
+            const int nx = list_x<WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), info, lane);
+            wave_sync();
+            stream<8, RANK, true, WIDE>(a.list, L, nx, rk, lane, tri, [&](const uint32_t (&q)[4], uint32_t (&g)[4]) {
 #pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) g[e2] = RANK ? probe_hash(tab, q[e2]) : probe_bits<TAB_WORDS>(tab, q[e2]);
-          });
+              for (int i = 0; i < 4; ++i) g[i] = BITS ? probe_bits<TAB_WORDS>(tab, q[i]) : probe_hash(tab, q[i]);
+            });
+            wave_sync();
+          }
+          if (BITS) {
+            for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & ID_MASK) >> 4] = 0;
+          } else {
+            for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
+          }
           wave_sync();
+          if (BITS) break;
         }
-        if (RANK) {
-          for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
-        } else {
-          for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & ID_MASK) >> 4] = 0;
-        }
-        wave_sync();
       }
       if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
     }
   }
-  tri.flush(copy_of(a.acc), lane);
+  if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
+  else tri.flush(copy_of(a.acc), lane);
 }
 
 // ------------------------------------------------------------------- results
@@ -1043,6 +1124,43 @@ __global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t
   }
   status[0] = out[0] = clo - s;
   status[16] = out[16] = chi - (clo < s ? 1u : 0u);
+}
+
+// Per graph: the classes from its sums; 003 = C(n_g, 3) less the rest (n_g <
+// 4,801,281 keeps C(n_g, 3) below 2^64). err[3] keeps the batch's error bits.
+__global__ void k_sw_finish_batch(int32_t graphs, int64_t nnz, const int64_t* __restrict__ vbase,
+                                  const unsigned long long* __restrict__ gacc,
+                                  const unsigned long long* __restrict__ acc, uint32_t* __restrict__ err,
+                                  uint64_t* __restrict__ out) {
+  uint64_t above = threadIdx.x < SW_COPIES ? acc[threadIdx.x * SW_WORDS + SW_ABOVE] : 0;
+  __shared__ uint64_t part[4];
+  above = sum64(above);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = above;
+  __syncthreads();
+  uint32_t e = err[0] | err[1];
+  if (!e && (int64_t)(part[0] + part[1] + part[2] + part[3]) * 2 != nnz) e = ERR_ASYM;
+  if (blockIdx.x == 0 && threadIdx.x == 0) err[3] = e;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= graphs || e) return;  // an error writes no output
+  const uint64_t n = (uint64_t)(vbase[g + 1] - vbase[g]);
+  uint64_t c3 = 0;
+  if (n >= 3) {
+    // n(n-1)(n-2)/6 without overflow: divide the factors first
+    uint64_t x = n, y = n - 1, z = n - 2;
+    if (x % 2 == 0) x /= 2; else y /= 2;
+    if (x % 3 == 0) x /= 3; else if (y % 3 == 0) y /= 3; else z /= 3;
+    c3 = x * y * z;
+  }
+  uint64_t c[16];
+  for (int k = 1; k < 16; ++k) c[k] = gacc[16 * (uint64_t)g + k];
+  c[2] += n * (gacc[16 * (uint64_t)g] / 2);
+  open_wedges(c);
+  uint64_t s = 0;
+  for (int k = 1; k < 16; ++k) {
+    out[16 * (uint64_t)g + k] = c[k];
+    s += c[k];
+  }
+  out[16 * (uint64_t)g] = c3 - s;
 }
 
 // Symmetry check: every entry's mirror with swapped direction bits.
@@ -1125,7 +1243,7 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
     ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
-                   tile_row, err};
+                   tile_row, err, 0, nullptr, nullptr};
   const unsigned rgrid = grid_of_work(n, ROWS_THREADS * ROWS_PER, INT32_MAX);
   k_sw_rows<<<rgrid, ROWS_THREADS, 0, s>>>(ra);
   if (nnz == 0) return TRIAD_OK;
@@ -1134,18 +1252,19 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
   if (validate)
     k_sw_symmetry<<<grid_of_work(n, 4, 65536), 256, 0, s>>>(n, nnz, in.off, in.nbr, in.flg, err);
   const OrientArgs oa{n,        nnz,  ntiles, in.off, in.nbr, in.flg, key, zero + w_mark, tile_row, list, info,
-                      (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err};
+                      (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err, nullptr, nullptr, nullptr};
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 5);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
-  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, zero + w_cnt, 0, acc, err};
+  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, zero + w_cnt, 0, acc, err,
+               nullptr, nullptr, nullptr};
   // a wavefront's range: small graphs spread over the chip, large ones in
   // ranges that spread the row search over more entries
   const int64_t waves = (int64_t)di.cus * 32;
   ca.range = std::max<int64_t>(64, std::min<int64_t>(1024, (nnz / waves + 63) & ~(int64_t)63));
   const unsigned wgrid = grid_of_work((nnz + ca.range - 1) / ca.range, REST_WAVES, (int64_t)di.cus * 8);
   if (rank) {
-    k_sw_orient<true><<<ogrid, OTHREADS, 0, s>>>(oa);
-    k_sw_cross<true><<<cgrid, 256, 0, s>>>(oa);
+    k_sw_orient<true, false><<<ogrid, OTHREADS, 0, s>>>(oa);
+    k_sw_cross<true, false><<<cgrid, 256, 0, s>>>(oa);
     rec(1);
     k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err);
     k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err);
@@ -1155,19 +1274,97 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
       constexpr bool W = decltype(wide)::value;
       k_sw_hubs<W><<<(unsigned)(di.cus * 2), HUB_THREADS, 0, s>>>(ca);
       k_sw_mids<W><<<(unsigned)(di.cus * 6), MID_THREADS, 0, s>>>(ca);
-      k_sw_rest<true, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+      k_sw_rest<false, true, false, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
     };
     if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
   } else {
     // (n <= DIRECT_N: fewer than 2^28 entries)
-    k_sw_orient<false><<<ogrid, OTHREADS, 0, s>>>(oa);
-    k_sw_cross<false><<<cgrid, 256, 0, s>>>(oa);
+    k_sw_orient<false, false><<<ogrid, OTHREADS, 0, s>>>(oa);
+    k_sw_cross<false, false><<<cgrid, 256, 0, s>>>(oa);
     rec(1);
     rec(2);
-    k_sw_rest<false, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+    k_sw_rest<true, false, false, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
   }
   rec(3);
   HIPCHK(hipGetLastError());
+  return TRIAD_OK;
+}
+
+// A batch: the pieces of its scratch block in order (sizes in bytes, rounded
+// up as Scratch hands them out).
+struct BatchSizes {
+  int64_t ntiles, zero_words, w_err, w_cnt, w_gacc, w_cross, w_mark;
+  BatchSizes(int32_t graphs, int64_t nnz) {
+    ntiles = (nnz + OT - 1) / OT;
+    zero_words = 0;
+    auto place = [&](int64_t w) {
+      const int64_t at = zero_words;
+      zero_words += (w + 1) & ~(int64_t)1;
+      return at;
+    };
+    place(2 * SW_WORDS * SW_COPIES);  // acc first
+    w_err = place(SW_ERRS);
+    w_cnt = place(6);
+    w_gacc = place(32 * (int64_t)graphs);
+    w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
+    w_mark = place(ntiles * (OT / 32));
+  }
+};
+
+size_t sweep_batch_bytes(int32_t graphs, int64_t nv, int64_t nnz) {
+  const BatchSizes z(graphs, nnz);
+  auto r = [](int64_t b) { return (size_t)((std::max<int64_t>(b, 1) + 255) & ~(int64_t)255); };
+  return r(4 * z.zero_words) + 2 * r(4 * nv) + r(8 * nv) + r(4 * (nnz + LIST_PAD)) + r(4 * z.ntiles);
+}
+
+int sweep_batch_groups(int waves) {
+  DeviceInfo di;
+  if (device_info(&di) != TRIAD_OK) return 1024;
+  return di.cus * 32 / waves;
+}
+
+int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vbase, int64_t nmax, int waves,
+                int groups, int64_t range, uint64_t* d_out, uint32_t** err_out, Scratch& scratch, hipStream_t s) {
+  const int64_t nnz = in.nnz;
+  const BatchSizes z(graphs, nnz);
+  uint32_t *zero = nullptr, *key = nullptr, *grow = nullptr, *list = nullptr, *tile_row = nullptr;
+  uint64_t* info = nullptr;
+  ALLOC(zero, z.zero_words);
+  ALLOC(key, nv);
+  ALLOC(grow, nv);
+  ALLOC(info, nv);
+  ALLOC(list, nnz + LIST_PAD);
+  ALLOC(tile_row, z.ntiles);
+  unsigned long long* acc = (unsigned long long*)zero;
+  unsigned long long* gacc = (unsigned long long*)(zero + z.w_gacc);
+  uint32_t* err = zero + z.w_err;
+  *err_out = err + 3;
+  k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words);
+  if (nv > 0) {
+    const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow};
+    k_sw_rows<<<grid_of_work(nv, ROWS_THREADS * ROWS_PER, INT32_MAX), ROWS_THREADS, 0, s>>>(ra);
+  }
+  if (nv > 0 && nnz > 0) {
+    DeviceInfo di;
+    if (int st = device_info(&di)) return st;
+    const OrientArgs oa{nv, nnz, z.ntiles, in.off, in.nbr, in.flg, key, zero + z.w_mark, tile_row, list, info,
+                        (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
+    k_sw_orient<false, true><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 5), OTHREADS, 0, s>>>(oa);
+    k_sw_cross<false, true><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
+    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, zero + z.w_cnt, range, acc,
+                 err, vbase, grow, gacc};
+    const unsigned grid = grid_of_work((nnz + range - 1) / range, waves, groups);
+    auto count = [&](auto bits, auto wide) {
+      k_sw_rest<decltype(bits)::value, false, true, decltype(wide)::value><<<grid, waves * 64, 0, s>>>(ca);
+    };
+    const bool wide = nnz + LIST_PAD >= ((int64_t)1 << 30);
+    if (nmax <= DIRECT_N) {
+      if (wide) count(std::true_type{}, std::true_type{}); else count(std::true_type{}, std::false_type{});
+    } else {
+      if (wide) count(std::false_type{}, std::true_type{}); else count(std::false_type{}, std::false_type{});
+    }
+  }
+  k_sw_finish_batch<<<grid_of_work(graphs, 256, INT32_MAX), 256, 0, s>>>(graphs, nnz, vbase, gacc, acc, err, d_out);
   return TRIAD_OK;
 }
 

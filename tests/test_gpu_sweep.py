@@ -118,3 +118,32 @@ def test_one_sided_csr_is_refused(torch, n):
         with pytest.raises(triad.TriadError) as e:
             triad.triad_census_device(n, 4, *d, **kw)
         assert e.value.status == triad.EASYM
+
+
+def test_batch_members_of_all_sizes(torch):
+    """Members around a tile and beyond the id-indexed tables (hash tables of
+    N+, filled in parts where it is longer than 512), empty and tiny ones
+    between them; the same members without the large one (id-indexed tables)."""
+    rng = np.random.default_rng(8)
+
+    def core(n, k, m):  # k vertices densely connected, m arcs into them
+        c = rng.choice(n, k, replace=False)
+        s = np.concatenate([rng.choice(c, k * k), rng.integers(0, n, m)])
+        t = np.concatenate([rng.choice(c, k * k), rng.choice(c, m)])
+        return graphs.build_csr(n, s.astype(np.int32), t.astype(np.int32), recip_p=0.2, recip_seed=2)
+
+    none = np.zeros(0, np.int32)
+    small = [graphs.rmat(6, 4, seed=s) for s in range(40)] + [graphs.build_csr(3, none, none), core(2500, 60, 9000),
+             graphs.from_arcs(2, [(1, 0)]), core(16384, 200, 20000), graphs.build_csr(0, none, none), core(70, 30, 200)]
+    for members in (small, small[:20] + [core(20011, 900, 40000)] + small[20:]):
+        B = graphs.concat_csrs(members)
+        d = triad.batch_to_device(B)
+        want = [oracle.census_mt(g) if g.n > 1000 else oracle.census(g) for g in members]
+        nv = int(B.vbase[-1])
+        assert triad.triad_census_batch(B.G, nv, B.nnz, *d) == want
+        assert triad.triad_census_batch(B.G, nv, B.nnz, *d, short_tasks=-1) == want
+        plan = triad.BatchPlan(B.G, nv, B.nnz, *d, waves_per_group=1, grid_groups=7, kernel_variant=2)
+        for _ in range(3):
+            plan.launch()
+            assert plan.result() == want
+        plan.close()
