@@ -18,7 +18,7 @@
 // Pipeline (one stream, no host synchronisation inside):
 //   k_sw_rows    per row: offset checks, row starts, degree histogram
 //   k_sw_rank    rank of each vertex by a counting sort on its degree
-//   k_sw_orient  per tile of 4,096 entries: entry checks; each row split in
+//   k_sw_orient  per tile of 2,048 entries: entry checks; each row split in
 //                place into N+(x) (ranks and flags) and its in-list (the x
 //                below it, ids and flags); per-row flag counts turned into
 //                wedge and dyad sums
@@ -44,8 +44,9 @@
 namespace triad {
 namespace {
 
-constexpr int OT = 4096;  // entries of one orientation tile
-constexpr int OTHREADS = 256, OPER = OT / OTHREADS;
+constexpr int OT = 2048;  // entries of one orientation tile
+constexpr int OTHREADS = 256, OPER = OT / OTHREADS, OWORDS = OT / 64;
+constexpr int LONG_KEEP = 256;  // rows with long N+ kept in LDS before they are listed
 constexpr int TILE_GRAPHS = 8;  // graphs of a batch whose sums a tile keeps in LDS
 constexpr int ROWS_THREADS = 1024, ROWS_PER = 16;
 constexpr int BUCKETS = 1024;          // degree buckets of the ranking
@@ -224,12 +225,6 @@ struct RowSums {
   }
   // a graph of a batch keeps the mutual count in the place of 003
   static __device__ __forceinline__ int batch_slot(int k) { return k == 8 ? 0 : slot(k); }
-  __device__ __forceinline__ void add_to(unsigned long long* acc, int lane) {
-    for (int k = 0; k < 9; ++k) {
-      const uint64_t s = sum64(c[k]);
-      if (lane == 0 && s) atomicAdd(&acc[slot(k)], (unsigned long long)s);
-    }
-  }
 };
 
 // Counters of a row that crosses tile boundaries, at the first tile that it
@@ -262,37 +257,51 @@ struct OrientArgs {
 
 __device__ __forceinline__ uint64_t below(int k) { return (1ull << k) - 1; }  // k in [0, 63]
 
+// One workgroup per tile of OT entries. The tile's row segments are compacted
+// in LDS (a row start bit per entry marks them), so that every entry finds its
+// row by two reads and a population count, and the counts of a segment are
+// taken by one thread from bit planes without touching memory again: the only
+// dependent reads of a tile are its entries, then the keys of their ends
+// (tiles of 4,096 entries with a search and three row reads per segment in
+// turn, at 2 wavefronts per SIMD: 11.4 ms at R-MAT scale 24 and 13.7 ms on the
+// 4,096-graph batch, now 9.6 and 5.9; bound by the random reads of the keys).
+// Five wavefronts per SIMD hide more of them than three without spills.
 // RANK: lists hold ranks, else ids. BAT: a batch (ids).
 template <bool RANK, bool BAT>
-__global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
-  __shared__ uint32_t at[OT];  // at a row start: the row, later its N+ length in the tile
-  __shared__ uint64_t heads[OT / 64 + 1], fwd[OT / 64 + 1], b0[OT / 64 + 1], b1[OT / 64 + 1];
-  __shared__ uint32_t pre[OT / 64 + 1];  // N+ entries before each 64-entry word
-  __shared__ uint16_t last[OT / 64];     // last row start before each word
-  __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last of the tile): where their entries go
-  __shared__ uint32_t lastc;             // start of the last segment if its row crosses the tile's end
-  __shared__ uint32_t mids[64], lngs[64], nlist[2], lbase[2];
-  __shared__ unsigned long long gsum[BAT ? TILE_GRAPHS : 1][9];  // BAT: sums of the tile's first graphs
+__global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
+  __shared__ uint32_t srow[OT], skey[OT];  // per segment: its row (BAT: within its graph), its key; later N+ entries
+  __shared__ uint16_t spos[OT + 1];        // its first entry
+  __shared__ uint16_t sgr[BAT ? OT : 1];   // BAT: its graph, from the tile's first
+  __shared__ uint64_t heads[OWORDS], fwd[OWORDS + 1], b0[OWORDS], b1[OWORDS];
+  __shared__ uint32_t hpre[OWORDS + 1];  // segments, N+ entries before each 64-entry word
+  __shared__ uint32_t pre[OWORDS + 1];
+  __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last segment): where their entries go
+  __shared__ int64_t ends[4];            // the first and the last segment's row: its entry range
+  __shared__ uint32_t longs[2][LONG_KEEP], nlong[2], lbase[2];  // rows with long N+, over several tiles
+  __shared__ unsigned long long gsum[BAT ? TILE_GRAPHS : 1][9];  // sums of the block, BAT: of the tile's first graphs
   if (a.err[0]) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  uint32_t bad = 0;
-  uint64_t above = 0;
-  RowSums sums;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t bad = 0, above = 0;
+  // the rows with long N+ kept so far, to their list (one atomic; the whole block)
+  auto put_longs = [&](int tid, int k) {
+    if (tid == 0) lbase[k] = atomicAdd(&a.counts[k], nlong[k]);
+    __syncthreads();
+    for (int i = tid; i < (int)nlong[k]; i += OTHREADS) (k ? a.lng : a.mid)[lbase[k] + i] = longs[k][i];
+    __syncthreads();
+    if (tid == 0) nlong[k] = 0;
+    __syncthreads();
+  };
+  if (!BAT && threadIdx.x < 9) gsum[0][threadIdx.x] = 0;
+  if (threadIdx.x < 2) nlong[threadIdx.x] = 0;
   for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    // (made opaque: the values derived from it are recomputed per tile instead of
+    // being hoisted out of the loop as live registers)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
     const int64_t t0 = t * OT;
     const int len = (int)min((int64_t)OT, a.nnz - t0);
-    __syncthreads();
-    if (tid < OT / 64) {
-      heads[tid] = ((const uint64_t*)a.mark)[t * (OT / 64) + tid] | (tid == 0 ? 1ull : 0ull);
-      if (tid == 0) {
-        heads[OT / 64] = 0;
-        lastc = OT;
-        nlist[0] = nlist[1] = 0;
-      }
-    }
-    if (BAT && tid >= 128 && tid - 128 < TILE_GRAPHS * 9) (&gsum[0][0])[tid - 128] = 0;
-    __syncthreads();
-    const uint32_t g0 = BAT ? a.grow[a.tile_row[t]] : 0u;
+    const uint32_t xfirst = a.tile_row[t], xlast = t + 1 < a.ntiles ? a.tile_row[t + 1] : xfirst;
     const int32_t* nb = a.nbr + t0;
     int32_t y[OPER];
     uint32_t wd[OPER];
@@ -302,112 +311,118 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
       y[i] = p < len ? nb[p] : 0;
       wd[i] = p < len ? (uint32_t)(a.flg[(t0 + p) >> 2] >> (2 * (p & 3))) & 3u : 0u;
     }
+    __syncthreads();  // the tile before is done with LDS
+    if (w == 0) {
+      uint64_t h = lane < OWORDS ? ((const uint64_t*)a.mark)[t * OWORDS + lane] | (lane == 0 ? 1ull : 0ull) : 0ull;
+      const uint32_t c = (uint32_t)__popcll(h);
+      uint32_t s = c;
+      for (int o = 1; o < OWORDS; o <<= 1) {
+        const uint32_t q = __shfl_up(s, o, 64);
+        if (lane >= o) s += q;
+      }
+      if (lane < OWORDS) {
+        heads[lane] = h;
+        hpre[lane] = s - c;
+        if (lane == OWORDS - 1) {
+          hpre[OWORDS] = s;
+          spos[s] = (uint16_t)len;
+        }
+      }
+    } else if (w == 1) {
+      // the rows that may cross a boundary: another tile may already have
+      // placed entries over their start, so their ids come from the tile starts
+      if (lane < 4) ends[lane] = a.off[(lane < 2 ? xfirst : xlast) + (lane & 1)];
+    }
+    if (BAT)
+      for (int k = tid; k < TILE_GRAPHS * 9; k += OTHREADS) (&gsum[0][0])[k] = 0;
+    __syncthreads();
+    const int nseg = (int)hpre[OWORDS];
 #pragma unroll
     for (int i = 0; i < OPER; ++i) {
-      const int p = i * OTHREADS + tid;
-      if ((heads[i * 4 + w] >> lane) & 1ull) at[p] = a.list[t0 + p];
+      const int wi = i * (OTHREADS / 64) + w;
+      if ((heads[wi] >> lane) & 1ull) spos[hpre[wi] + (uint32_t)__popcll(heads[wi] & below(lane))] = (uint16_t)(wi * 64 + lane);
     }
-    if (w == 0) {  // last row start before each word: an exclusive running maximum
-      const uint64_t h = heads[lane];
-      int v = h ? lane * 64 + 63 - __builtin_clzll(h) : 0;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int q = __shfl_up(v, o, 64);
-        if (lane >= o) v = max(v, q);
-      }
-      const int q = __shfl_up(v, 1, 64);
-      last[lane] = (uint16_t)(lane ? q : 0);
-    }
+    const bool cross0 = ends[0] < t0 || ends[1] > t0 + len;                       // the first segment's row
+    const bool cross1 = t + 1 < a.ntiles && ends[2] > t0 && ends[2] < t0 + len;  // the last one's, another row
     __syncthreads();
-    if (tid == 0) {
-      // rows that cross a boundary: another tile may already have placed
-      // entries over their start, so their ids come from the tile starts
-      at[0] = a.tile_row[t];
-      if (t + 1 < a.ntiles) {
-        const uint32_t x = a.tile_row[t + 1];
-        const int64_t o = a.off[x];
-        if (o < t0 + OT) {
-          lastc = o > t0 ? (uint32_t)(o - t0) : 0u;
-          at[lastc] = x;
-        }
+    const uint32_t g0 = BAT ? a.grow[xfirst] : 0u;
+    for (int s = tid; s < nseg; s += OTHREADS) {
+      const uint32_t x = s == 0 ? xfirst : s == nseg - 1 && cross1 ? xlast : a.list[t0 + spos[s]];
+      skey[s] = a.key[x];
+      if constexpr (BAT) {
+        const uint32_t g = a.grow[x];
+        sgr[s] = (uint16_t)(g - g0);
+        srow[s] = (uint32_t)(x - a.vbase[g]);
+      } else {
+        srow[s] = x;
       }
     }
     __syncthreads();
     // entry checks, direction of each edge
-    uint16_t hd[OPER];
+    uint16_t sg[OPER];
+    uint32_t ky[OPER];
 #pragma unroll
     for (int i = 0; i < OPER; ++i) {
-      const int p = i * OTHREADS + tid, wi = i * 4 + w;
-      const bool in = p < len;
-      const uint64_t hw = heads[wi];
-      const uint64_t m = hw & (~0ull >> (63 - lane));
-      const int h = m ? wi * 64 + 63 - __builtin_clzll(m) : last[wi];
-      hd[i] = (uint16_t)h;
-      const uint32_t x = at[h];
+      const int p = i * OTHREADS + tid, wi = i * (OTHREADS / 64) + w;
+      sg[i] = (uint16_t)(hpre[wi] + (uint32_t)__popcll(heads[wi] & (~0ull >> (63 - lane))) - 1);
       int64_t base = 0, ng = a.n;
-      if (BAT && in) {
-        const uint32_t g = a.grow[x];
+      if (BAT) {
+        const int64_t g = (int64_t)g0 + sgr[sg[i]];
         base = a.vbase[g];
         ng = a.vbase[g + 1] - base;
       }
-      const int32_t xl = (int32_t)(x - base);  // the row's id as its entries name it
+      if (p < len && (y[i] < 0 || y[i] >= ng)) {
+        bad |= ERR_RANGE;
+        y[i] = 0;
+      }
+      ky[i] = a.key[base + y[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid, wi = i * (OTHREADS / 64) + w;
+      const bool in = p < len;
+      const int32_t x = (int32_t)srow[sg[i]];
       int32_t pv = __shfl_up(y[i], 1, 64);
-      const bool start = (hw >> lane) & 1ull;
       if (lane == 0 && in && t0 + p > 0) pv = nb[p - 1];
       // (the tile's first entry carries a start bit of its own: look at the row)
-      const bool first = p == 0 ? a.off[x] == t0 : start;
-      bool f = false;
+      const bool first = p == 0 ? ends[0] == t0 : (heads[wi] >> lane) & 1ull;
       if (in) {
         if (!first && pv >= y[i]) bad |= ERR_UNSORTED;
-        if (y[i] == xl) bad |= ERR_SELFLOOP;
+        if (y[i] == x) bad |= ERR_SELFLOOP;
         if (wd[i] == 0) bad |= ERR_RANGE;
-        if (y[i] < 0 || y[i] >= ng) {
-          bad |= ERR_RANGE;
-          y[i] = 0;
-        }
-        const uint32_t kx = a.key[x], ky = a.key[base + y[i]];
-        f = RANK ? ky < kx : (ky > kx || (ky == kx && y[i] > xl));
-        const uint32_t g = wd[i];
-        // N+ words carry f_xy and the rank (id) of y; in-list words of row x
-        // the id of y and f_yx, the flag seen from y
-        wd[i] = f ? (g << 30 | (RANK ? ky : (uint32_t)y[i])) : (((g & 1u) << 31) | ((g >> 1) << 30) | (uint32_t)y[i]);
-        const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1), ma = __ballot(y[i] > xl);
-        if (lane == 0) {
-          above += (uint64_t)__popcll(ma);
-          fwd[wi] = mf;
-          b0[wi] = m0;
-          b1[wi] = m1;
-        }
-      } else if (lane == 0) {
-        fwd[wi] = b0[wi] = b1[wi] = 0;
+      }
+      const uint32_t kx = skey[sg[i]], g = wd[i];
+      const bool f = in && (RANK ? ky[i] < kx : (ky[i] > kx || (ky[i] == kx && y[i] > x)));
+      // N+ words carry f_xy and the rank (id) of y; in-list words of row x
+      // the id of y and f_yx, the flag seen from y
+      wd[i] = f ? (g << 30 | (RANK ? ky[i] : (uint32_t)y[i])) : (((g & 1u) << 31) | ((g >> 1) << 30) | (uint32_t)y[i]);
+      const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1);
+      above += (uint32_t)__popcll(__ballot(in && y[i] > x));
+      if (lane == 0) {
+        fwd[wi] = mf;
+        b0[wi] = m0;
+        b1[wi] = m1;
       }
     }
     __syncthreads();
     if (w == 0) {
-      const uint32_t c = (uint32_t)__popcll(fwd[lane]);
+      const uint32_t c = lane < OWORDS ? (uint32_t)__popcll(fwd[lane]) : 0u;
       uint32_t s = c;
-      for (int o = 1; o < 64; o <<= 1) {
+      for (int o = 1; o < OWORDS; o <<= 1) {
         const uint32_t q = __shfl_up(s, o, 64);
         if (lane >= o) s += q;
       }
-      pre[lane] = s - c;
-      if (lane == 63) {
-        pre[64] = s;
-        fwd[64] = 0;
+      if (lane < OWORDS) pre[lane] = s - c;
+      if (lane == OWORDS - 1) {
+        pre[OWORDS] = s;
+        fwd[OWORDS] = 0;
       }
     }
     __syncthreads();
-    // per row segment: its counts
-    for (int i = 0; i < OPER; ++i) {
-      const int p = i * OTHREADS + tid;
-      if (p >= len || !((heads[p >> 6] >> lane) & 1ull)) continue;
-      int e = len;
-      {
-        int wi = p >> 6;
-        uint64_t m = lane == 63 ? 0ull : heads[wi] & (~0ull << (lane + 1));
-        while (!m && ++wi < OT / 64) m = heads[wi];
-        if (m) e = min(len, wi * 64 + __builtin_ctzll(m));
-      }
-      const uint32_t x = at[p];
+    // the counts of each segment
+    RowSums sums;
+    for (int s = tid; s < nseg; s += OTHREADS) {
+      const int p = spos[s], e = spos[s + 1];
       const uint32_t nf = pre[e >> 6] + (uint32_t)__popcll(fwd[e >> 6] & below(e & 63)) - pre[p >> 6] -
                           (uint32_t)__popcll(fwd[p >> 6] & below(p & 63));
       uint32_t o = 0, in = 0, mu = 0;
@@ -415,17 +430,18 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
         uint64_t m = ~0ull;
         if (wi == p >> 6) m &= ~below(p & 63);
         if (wi == e >> 6) m &= below(e & 63);
-        o += (uint32_t)__popcll(b0[wi] & ~b1[wi] & m);
-        in += (uint32_t)__popcll(b1[wi] & ~b0[wi] & m);
-        mu += (uint32_t)__popcll(b0[wi] & b1[wi] & m);
+        const uint64_t q0 = b0[wi] & m, q1 = b1[wi] & m;
+        o += (uint32_t)__popcll(q0 & ~q1);
+        in += (uint32_t)__popcll(q1 & ~q0);
+        mu += (uint32_t)__popcll(q0 & q1);
       }
-      const int64_t ox = a.off[x], ex = a.off[x + 1];
-      if (ox >= t0 && ex <= t0 + len) {
+      const uint32_t g = BAT ? g0 + sgr[s] : 0u;
+      const uint32_t x = srow[s] + (BAT ? (uint32_t)a.vbase[g] : 0u);
+      skey[s] = nf;
+      if (!((s == 0 && cross0) || (s == nseg - 1 && cross1))) {
         const uint32_t fl = nf > SORT_MAX ? UNSORTED : 0u;
-        a.info[x] = (uint64_t)ox << 24 | (min(nf, LEN_MASK) | (RANK ? fl : 0u));
-        at[p] = nf;
+        a.info[x] = (uint64_t)(t0 + p) << 24 | (min(nf, LEN_MASK) | (RANK ? fl : 0u));
         if constexpr (BAT) {
-          const uint32_t g = a.grow[x];
           RowSums one;
           one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), o, in, mu);
           for (int k = 0; k < 9; ++k) {
@@ -438,89 +454,111 @@ __global__ void __launch_bounds__(OTHREADS) k_sw_orient(OrientArgs a) {
         }
         if (RANK && nf > SORT_MIN && nf <= SORT_MAX) {
           const uint32_t k = nf > SORT_MID;
-          (k ? lngs : mids)[atomicAdd(&nlist[k], 1u)] = x;
+          longs[k][atomicAdd(&nlong[k], 1u)] = x;
         }
       } else {
+        const int k = s == 0 ? 0 : 1;
+        const int64_t ox = ends[2 * k], ex = ends[2 * k + 1];
         Cross* c = &a.cross[ox / OT + 1];
-        const int k = p == 0 ? 0 : 1;
         cF[k] = ox + atomicAdd(&c->f, nf);
         cB[k] = ex - 1 - (int64_t)atomicAdd(&c->b, (uint32_t)(e - p) - nf);
         atomicAdd(&c->o, o);
         atomicAdd(&c->i, in);
         atomicAdd(&c->m, mu);
-        if (p == 0) at[0] = 0xFFFFFFFFu;  // marks the crossing first segment
       }
     }
-    __syncthreads();
-    if (RANK && tid < 2 && nlist[tid]) lbase[tid] = atomicAdd(&a.counts[tid], nlist[tid]);
-    __syncthreads();
-    if (RANK) {
-      if (tid < (int)nlist[0]) a.mid[lbase[0] + tid] = mids[tid];
-      if (tid < (int)nlist[1]) a.lng[lbase[1] + tid] = lngs[tid];
-    }
-    if constexpr (BAT) {
-      if (tid < TILE_GRAPHS * 9) {
-        const unsigned long long v = gsum[tid / 9][tid % 9];
-        if (v) atomicAdd(&a.gacc[(uint64_t)(g0 + tid / 9) * 16 + RowSums::batch_slot(tid % 9)], v);
+    if (!BAT && w * 64 < nseg)
+      for (int k = 0; k < 9; ++k) {
+        const uint64_t v = sum64(sums.c[k]);
+        if (lane == 0 && v) atomicAdd(&gsum[0][k], (unsigned long long)v);
       }
-    }
+    __syncthreads();
     // place the entries
-    const bool cross0 = at[0] == 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < OPER; ++i) {
-      const int p = i * OTHREADS + tid, wi = i * 4 + w;
+      const int p = i * OTHREADS + tid, wi = i * (OTHREADS / 64) + w;
       if (p >= len) continue;
-      const int h = hd[i];
+      const int s = sg[i], h = spos[s];
       const uint64_t fm = fwd[wi];
       const uint32_t c = pre[wi] + (uint32_t)__popcll(fm & below(lane)) - pre[h >> 6] -
                          (uint32_t)__popcll(fwd[h >> 6] & below(h & 63));
       const bool f = (fm >> lane) & 1ull;
       const uint32_t q = (uint32_t)(p - h) - c;  // in-list entries of the segment before this one
       int64_t to;
-      if ((h == 0 && cross0) || (uint32_t)h == lastc) {
-        const int k = h == 0 ? 0 : 1;
+      if ((s == 0 && cross0) || (s == nseg - 1 && cross1)) {
+        const int k = s == 0 ? 0 : 1;
         to = f ? cF[k] + c : cB[k] - q;
       } else {
-        to = t0 + h + (f ? c : at[h] + q);
+        to = t0 + h + (f ? c : skey[s] + q);
       }
       a.list[to] = wd[i];
     }
+    if (RANK && nlong[0] + OT / SORT_MIN > LONG_KEEP) put_longs(tid, 0);
+    if (RANK && nlong[1] + OT / SORT_MIN > LONG_KEEP) put_longs(tid, 1);
+    if (BAT)
+      for (int k = tid; k < TILE_GRAPHS * 9; k += OTHREADS) {
+        const unsigned long long v = gsum[k / 9][k % 9];
+        if (v) atomicAdd(&a.gacc[(uint64_t)(g0 + k / 9) * 16 + RowSums::batch_slot(k % 9)], v);
+      }
   }
-  if (bad) atomicOr(&a.err[1], bad);
-  above = sum64(above);
+  const int tid = threadIdx.x, lane = tid & 63;
+  __syncthreads();
+  if (RANK) {
+    put_longs(tid, 0);
+    put_longs(tid, 1);
+  }
+  for (int o = 32; o > 0; o >>= 1) bad |= __shfl_xor(bad, o, 64);
+  if (lane == 0 && bad) atomicOr(&a.err[1], bad);
   if (lane == 0 && above) atomicAdd(&copy_of(a.acc)[SW_ABOVE], (unsigned long long)above);
-  sums.add_to(copy_of(a.acc), lane);
+  __syncthreads();
+  if (!BAT && tid < 9 && gsum[0][tid]) atomicAdd(&copy_of(a.acc)[RowSums::slot(tid)], gsum[0][tid]);
 }
 
 // Rows that cross tile boundaries, at the first boundary inside each.
 template <bool RANK, bool BAT>
-__global__ void k_sw_cross(OrientArgs a) {
+__global__ void __launch_bounds__(256) k_sw_cross(OrientArgs a) {
+  if (a.err[0] | a.err[1]) return;
+  const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   RowSums sums;
-  if (!(a.err[0] | a.err[1])) {
-    for (int64_t t = 1 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.ntiles; t += stride) {
-      const uint32_t x = a.tile_row[t];
+  for (int64_t t0 = 1 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; t0 < a.ntiles; t0 += stride) {
+    const int64_t t = t0 + lane;
+    int kind = -1;  // list of long N+
+    uint32_t x = 0;
+    if (t < a.ntiles) {
+      x = a.tile_row[t];
       const int64_t ox = a.off[x];
-      if (ox >= t * OT || ox / OT + 1 != t) continue;
-      const Cross c = a.cross[t];
-      const uint32_t fl = RANK && c.f > SORT_MAX ? UNSORTED : 0u;
-      a.info[x] = (uint64_t)ox << 24 | (min(c.f, LEN_MASK) | fl);
-      if constexpr (BAT) {
-        const uint32_t g = a.grow[x];
-        RowSums one;
-        one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), c.o, c.i, c.m);
-        for (int k = 0; k < 9; ++k)
-          if (one.c[k]) atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
-      } else {
-        sums.row((uint64_t)a.n, c.o, c.i, c.m);
-      }
-      if (RANK && c.f > SORT_MIN && c.f <= SORT_MAX) {
-        const uint32_t k = c.f > SORT_MID;
-        (k ? a.lng : a.mid)[atomicAdd(&a.counts[k], 1u)] = x;
+      if (ox < t * OT && ox / OT + 1 == t) {
+        const Cross c = a.cross[t];
+        const uint32_t fl = RANK && c.f > SORT_MAX ? UNSORTED : 0u;
+        a.info[x] = (uint64_t)ox << 24 | (min(c.f, LEN_MASK) | fl);
+        if constexpr (BAT) {
+          const uint32_t g = a.grow[x];
+          RowSums one;
+          one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), c.o, c.i, c.m);
+          for (int k = 0; k < 9; ++k)
+            if (one.c[k]) atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
+        } else {
+          sums.row((uint64_t)a.n, c.o, c.i, c.m);
+        }
+        if (RANK && c.f > SORT_MIN && c.f <= SORT_MAX) kind = c.f > SORT_MID ? 1 : 0;
       }
     }
+    if (RANK)
+      for (int k = 0; k < 2; ++k) {  // one atomic a wavefront
+        const uint64_t m = __ballot(kind == k);
+        if (!m) continue;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&a.counts[k], (uint32_t)__popcll(m));
+        base = rl(base, 0);
+        if (kind == k) (k ? a.lng : a.mid)[base + __popcll(m & below(lane))] = x;
+      }
   }
-  sums.add_to(copy_of(a.acc), threadIdx.x & 63);
+  if (BAT) return;
+  for (int k = 0; k < 9; ++k) {
+    const uint64_t v = sum64(sums.c[k]);
+    if (lane == 0 && v) atomicAdd(&copy_of(a.acc)[RowSums::slot(k)], (unsigned long long)v);
+  }
 }
 
 // ------------------------------------------------------------------- sorting
@@ -1253,7 +1291,7 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
     k_sw_symmetry<<<grid_of_work(n, 4, 65536), 256, 0, s>>>(n, nnz, in.off, in.nbr, in.flg, err);
   const OrientArgs oa{n,        nnz,  ntiles, in.off, in.nbr, in.flg, key, zero + w_mark, tile_row, list, info,
                       (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err, nullptr, nullptr, nullptr};
-  const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 5);
+  const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
   CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, zero + w_cnt, 0, acc, err,
                nullptr, nullptr, nullptr};
@@ -1349,7 +1387,7 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
     if (int st = device_info(&di)) return st;
     const OrientArgs oa{nv, nnz, z.ntiles, in.off, in.nbr, in.flg, key, zero + z.w_mark, tile_row, list, info,
                         (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
-    k_sw_orient<false, true><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 5), OTHREADS, 0, s>>>(oa);
+    k_sw_orient<false, true><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
     k_sw_cross<false, true><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
     CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, zero + z.w_cnt, range, acc,
                  err, vbase, grow, gacc};
