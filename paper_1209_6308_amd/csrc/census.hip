@@ -1418,39 +1418,40 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
   // The default call lists triangles (sweep.hip). The merge below remains for
   // calls that ask for what only it has: a work queue of tasks to order
   // (schedules), to time (per-task cycles, wave spans) or to shape.
-  if (!labelled && o.schedule == TRIAD_SCHED_PLAIN && !o.task_cycles && !o.wave_span && !o.hub_threshold && !o.chunk &&
-      !o.waves_per_group && !o.grid_groups && !o.kernel_variant) {
+  if ((!labelled || n < SW_LAB_MAX_N) && o.schedule == TRIAD_SCHED_PLAIN && !o.task_cycles && !o.wave_span &&
+      !o.hub_threshold && !o.chunk && !o.waves_per_group && !o.grid_groups && !o.kernel_variant) {
     unsigned long long* acc = nullptr;
     uint32_t* err = nullptr;
     uint64_t* status = nullptr;
     ev.rec(0, s);
     ALLOC(status, SW_STATUS);
     const SweepIn in{n, nnz, off, nbr, flg};
-    if (int st = sweep_census(in, o.validate == 1, &acc, &err, scratch, ev.on ? ev.e : nullptr, s)) return st;
+    if (int st = sweep_census(in, o.validate == 1, labelled, &acc, &err, scratch, ev.on ? ev.e : nullptr, s)) return st;
     // test hook: a call that passes validation reports a device fault
     if (injected_fault_pending()) {
       uint32_t eh[SW_ERRS];
-      std::vector<unsigned long long> sums((size_t)SW_COPIES * SW_WORDS);
+      const size_t words = labelled ? SW_LAB_WORDS : SW_WORDS;
+      std::vector<unsigned long long> sums(SW_COPIES * words);
       HIPCHK(hipMemcpyAsync(eh, err, sizeof eh, hipMemcpyDeviceToHost, s));
       HIPCHK(hipMemcpyAsync(sums.data(), acc, sums.size() * sizeof sums[0], hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
       unsigned long long above = 0;
-      for (int k = 0; k < SW_COPIES; ++k) above += sums[(size_t)k * SW_WORDS + SW_ABOVE];
+      for (int k = 0; k < SW_COPIES; ++k) above += sums[k * words + (labelled ? SW_LAB_ABOVE : SW_ABOVE)];
       if (!(eh[0] | eh[1] | eh[2]) && (int64_t)above * 2 == nnz && take_injected_fault()) k_fill_u32<<<1, 64, 0, s>>>(err + 2, 1, ERR_DEVICE);
     }
-    sweep_finish(acc, err, nnz, n, d_out, status, s);
+    sweep_finish(acc, err, labelled, nnz, n, d_out, status, s);
     HIPCHK(hipGetLastError());
     ev.rec(4, s);
     uint64_t hres[SW_STATUS];
-    HIPCHK(hipMemcpyAsync(hres, status, sizeof hres, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(hres, status, (NC + 2) * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (int st = status_from_bits((uint32_t)hres[17]))
+    if (int st = status_from_bits((uint32_t)hres[NC + 1]))
       return fail(st, st == TRIAD_ERANGE      ? "neighbour id out of range, zero flag, or bad offsets"
                       : st == TRIAD_ESELFLOOP ? "self-loop in the CSR"
                       : st == TRIAD_EUNSORTED ? "row not strictly increasing"
                       : st == TRIAD_EASYM     ? "CSR not symmetric or flags not mirrored"
                                               : "the device reported a fault during the census");
-    if (h_out) std::memcpy(h_out, hres, 17 * sizeof(uint64_t));
+    if (h_out) std::memcpy(h_out, hres, (NC + 1) * sizeof(uint64_t));
     if (o.timing) {
       o.timing->prep_ms = ev.ms(0, 1);
       o.timing->tasks_ms = ev.ms(1, 2);
@@ -1459,9 +1460,10 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
       o.timing->tasks = nnz / 2;
       o.timing->hub_tasks = 0;
       o.timing->items = nnz / 2;
-      o.timing->waves = (int64_t)census_groups(waves, variant, 0, 0) * waves;
+      o.timing->waves = labelled ? (int64_t)lab_groups(0) * LAB_WAVES
+                                 : (int64_t)census_groups(waves, variant, 0, 0) * waves;
     }
-    return hres[16] ? TRIAD_OK_003_WRAPPED : TRIAD_OK;
+    return hres[NC] ? TRIAD_OK_003_WRAPPED : TRIAD_OK;
   }
   uint32_t* err = nullptr;
   // NC census counters, 2 queue counters, hub tasks

@@ -16,6 +16,8 @@ constexpr int SW_MUT = 16;    // entries with both arcs (each mutual edge twice)
 constexpr int SW_ABOVE = 17;  // entries above their row's own id
 constexpr int SW_WORDS = 32;
 constexpr int SW_COPIES = 64;
+// labelled: the 64 states, then the entries above
+constexpr int SW_LAB_ABOVE = 64, SW_LAB_WORDS = 80;
 // err[0]: raised by the row checks, err[1]: by the entry checks, err[2]: later
 constexpr int SW_ERRS = 4;
 
@@ -27,16 +29,19 @@ struct SweepIn {
 };
 
 // Enqueues the whole sweep of one graph on s: validation, orientation,
-// triangle counts and per-row sums. *acc (SW_COPIES copies of SW_WORDS words, to be summed) and *err (SW_ERRS
+// triangle counts and per-row sums. *acc (SW_COPIES copies of SW_WORDS words, to be summed; labelled: SW_LAB_WORDS) and *err (SW_ERRS
 // words) are its counters, in scratch memory. validate: also check symmetry.
 // ev (may be NULL): events 1, 2, 3 are recorded after the orientation, the
 // sorting and listing, and the counting.
-int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc, uint32_t** err, Scratch& scratch,
+int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long long** acc, uint32_t** err, Scratch& scratch,
                  hipEvent_t* ev, hipStream_t s);
-// The 16 counts and the high word of 003 into d_out unless an error is set;
-// status (device) gets the same 17 words and in word 17 the error bits.
-constexpr int SW_STATUS = 18;
-void sweep_finish(const unsigned long long* acc, uint32_t* err, int64_t nnz, int64_t n, uint64_t* d_out,
+// Labelled: the 64 states (n below SW_LAB_MAX_N).
+constexpr int64_t SW_LAB_MAX_N = (int64_t)1 << 29;
+// The 16 counts and the high word of 003 (labelled: 64 states and the high word
+// of state 0) into d_out unless an error is set; status (device, at most
+// SW_STATUS words) gets the same words and then the error bits.
+constexpr int SW_STATUS = 66;
+void sweep_finish(const unsigned long long* acc, uint32_t* err, bool labelled, int64_t nnz, int64_t n, uint64_t* d_out,
                   uint64_t* status, hipStream_t s);
 
 // A batch (the concatenated CSR of in, nv rows, the largest member nmax

@@ -33,7 +33,8 @@
 // A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_rest
 // as one disjoint union with ids local to each graph, its counters by graph
 // (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 32.9 ms a launch; 256
-// graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.57 ms).
+// graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.57 ms). The labelled
+// census adds k_lab_sums (54.9 -> 3.8 ms at R-MAT scale 20).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,19 +53,23 @@ constexpr int ROWS_THREADS = 1024, ROWS_PER = 16;
 constexpr int BUCKETS = 1024;          // degree buckets of the ranking
 constexpr int64_t DIRECT_N = 16384;    // graphs up to here index their tables by vertex id
 constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover
-constexpr int HUB_THREADS = 768;
+// two workgroups a CU: six wavefronts a SIMD, four with the labels' counters
+constexpr int hub_threads(bool lab) { return lab ? 512 : 768; }
 constexpr int64_t HUB_MIN_IN = 256;    // in-lists from here on: k_sw_hubs (ranks in its table)
 constexpr int MID_THREADS = 256;
 constexpr int64_t MID_MIN_IN = 32;     // in-lists from here on: k_sw_mids
 constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
-constexpr int TAB_WORDS = 1024;        // its slots; k_sw_rest<false>: words of 16 ids
+constexpr int TAB_WORDS = 1024;        // its slots
 constexpr int REST_WAVES = 4;
 constexpr int64_t LIST_PAD = 4;        // list words read past a list's end
 constexpr uint32_t SORT_MIN = 64, SORT_MID = 256, SORT_MAX = 4096;
 
 // List words: id or rank in the low 30 bits, the direction flag in the top two.
-constexpr uint32_t ID_MASK = 0x3FFFFFFFu;
+// Labelled (LAB): the flag is seen from the lower id of the pair, bit 29 says
+// which vertex that is, and ids take 29 bits.
+template <bool LAB>
+constexpr uint32_t IDM = LAB ? 0x1FFFFFFFu : 0x3FFFFFFFu;
 constexpr uint32_t SLOT_FREE = 0xFFFFFFFFu;  // no id is 2^30 - 1
 // Row words: first entry << 24 | length of N+; the top bit of the length marks
 // a list that is not in rank order.
@@ -88,8 +93,9 @@ __device__ __forceinline__ uint64_t sum64(uint64_t x) {
 
 // Atomics on one cache line run one after another (88 ns each, measured with
 // 9,216 of them): the counters are kept in SW_COPIES copies, summed at the end.
+template <bool LAB>
 __device__ __forceinline__ unsigned long long* copy_of(unsigned long long* acc) {
-  return acc + (blockIdx.x % SW_COPIES) * SW_WORDS;
+  return acc + (blockIdx.x % SW_COPIES) * (LAB ? SW_LAB_WORDS : SW_WORDS);
 }
 
 // Bucket of a degree, rising with it: exact below 32, then 32 steps an octave.
@@ -120,6 +126,16 @@ struct RowArgs {
   int32_t graphs;
   const int64_t* vbase;
   uint32_t* grow;
+  // labelled: the entries below the row's own id, for rows that cross tiles
+  const int32_t* nbr;
+  struct Cross* cross;
+};
+
+// Counters of a row that crosses tile boundaries, at the first tile that it
+// reaches into: entries placed so far, the neighbour counts (labelled: the
+// entries below the row's own id).
+struct Cross {
+  uint32_t f, b, o, i, m, su, pad[2];
 };
 
 __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
@@ -151,6 +167,14 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
       a.list[b] = (uint32_t)u;
       atomicOr(&a.mark[b >> 5], 1u << (b & 31));
       for (int64_t t = (b + OT - 1) / OT; t * OT < e; ++t) a.tile_row[t] = (uint32_t)u;
+      if (a.cross && b / OT != (e - 1) / OT) {
+        int64_t lo = b, hi = e;
+        while (lo < hi) {
+          const int64_t m = (lo + hi) >> 1;
+          if (a.nbr[m] < (int32_t)u) lo = m + 1; else hi = m;
+        }
+        a.cross[b / OT + 1].su = (uint32_t)(lo - b);
+      }
     }
   }
   if (!a.hist) return;
@@ -227,12 +251,6 @@ struct RowSums {
   static __device__ __forceinline__ int batch_slot(int k) { return k == 8 ? 0 : slot(k); }
 };
 
-// Counters of a row that crosses tile boundaries, at the first tile that it
-// reaches into: entries placed so far, and the neighbour counts.
-struct Cross {
-  uint32_t f, b, o, i, m, pad[3];
-};
-
 struct OrientArgs {
   int64_t n, nnz, ntiles;
   const int64_t* off;
@@ -266,8 +284,9 @@ __device__ __forceinline__ uint64_t below(int k) { return (1ull << k) - 1; }  //
 // turn, at 2 wavefronts per SIMD: 11.4 ms at R-MAT scale 24 and 13.7 ms on the
 // 4,096-graph batch, now 9.6 and 5.9; bound by the random reads of the keys).
 // Five wavefronts per SIMD hide more of them than three without spills.
-// RANK: lists hold ranks, else ids. BAT: a batch (ids).
-template <bool RANK, bool BAT>
+// RANK: lists hold ranks, else ids. BAT: a batch (ids). LAB: labelled words,
+// the sums are k_lab_sums'.
+template <bool RANK, bool BAT, bool LAB>
 __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
   __shared__ uint32_t srow[OT], skey[OT];  // per segment: its row (BAT: within its graph), its key; later N+ entries
   __shared__ uint16_t spos[OT + 1];        // its first entry
@@ -395,7 +414,11 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       const bool f = in && (RANK ? ky[i] < kx : (ky[i] > kx || (ky[i] == kx && y[i] > x)));
       // N+ words carry f_xy and the rank (id) of y; in-list words of row x
       // the id of y and f_yx, the flag seen from y
-      wd[i] = f ? (g << 30 | (RANK ? ky[i] : (uint32_t)y[i])) : (((g & 1u) << 31) | ((g >> 1) << 30) | (uint32_t)y[i]);
+      const uint32_t id = f && RANK ? ky[i] : (uint32_t)y[i], mirror = (g & 1u) << 1 | g >> 1;
+      if (LAB)
+        wd[i] = (y[i] > x ? g : mirror) << 30 | (uint32_t)(f == (y[i] < x)) << 29 | id;
+      else
+        wd[i] = (f ? g : mirror) << 30 | id;
       const uint64_t mf = __ballot(f), m0 = __ballot(g & 1u), m1 = __ballot(g >> 1);
       above += (uint32_t)__popcll(__ballot(in && y[i] > x));
       if (lane == 0) {
@@ -449,7 +472,7 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
             if (g - g0 < TILE_GRAPHS) atomicAdd(&gsum[g - g0][k], (unsigned long long)one.c[k]);
             else atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
           }
-        } else {
+        } else if constexpr (!LAB) {
           sums.row((uint64_t)a.n, o, in, mu);
         }
         if (RANK && nf > SORT_MIN && nf <= SORT_MAX) {
@@ -467,7 +490,7 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
         atomicAdd(&c->m, mu);
       }
     }
-    if (!BAT && w * 64 < nseg)
+    if (!BAT && !LAB && w * 64 < nseg)
       for (int k = 0; k < 9; ++k) {
         const uint64_t v = sum64(sums.c[k]);
         if (lane == 0 && v) atomicAdd(&gsum[0][k], (unsigned long long)v);
@@ -509,13 +532,13 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
   }
   for (int o = 32; o > 0; o >>= 1) bad |= __shfl_xor(bad, o, 64);
   if (lane == 0 && bad) atomicOr(&a.err[1], bad);
-  if (lane == 0 && above) atomicAdd(&copy_of(a.acc)[SW_ABOVE], (unsigned long long)above);
+  if (lane == 0 && above) atomicAdd(&copy_of<LAB>(a.acc)[LAB ? SW_LAB_ABOVE : SW_ABOVE], (unsigned long long)above);
   __syncthreads();
-  if (!BAT && tid < 9 && gsum[0][tid]) atomicAdd(&copy_of(a.acc)[RowSums::slot(tid)], gsum[0][tid]);
+  if (!BAT && !LAB && tid < 9 && gsum[0][tid]) atomicAdd(&copy_of<LAB>(a.acc)[RowSums::slot(tid)], gsum[0][tid]);
 }
 
 // Rows that cross tile boundaries, at the first boundary inside each.
-template <bool RANK, bool BAT>
+template <bool RANK, bool BAT, bool LAB>
 __global__ void __launch_bounds__(256) k_sw_cross(OrientArgs a) {
   if (a.err[0] | a.err[1]) return;
   const int lane = threadIdx.x & 63;
@@ -538,7 +561,7 @@ __global__ void __launch_bounds__(256) k_sw_cross(OrientArgs a) {
           one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), c.o, c.i, c.m);
           for (int k = 0; k < 9; ++k)
             if (one.c[k]) atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
-        } else {
+        } else if constexpr (!LAB) {
           sums.row((uint64_t)a.n, c.o, c.i, c.m);
         }
         if (RANK && c.f > SORT_MIN && c.f <= SORT_MAX) kind = c.f > SORT_MID ? 1 : 0;
@@ -554,25 +577,301 @@ __global__ void __launch_bounds__(256) k_sw_cross(OrientArgs a) {
         if (kind == k) (k ? a.lng : a.mid)[base + __popcll(m & below(lane))] = x;
       }
   }
-  if (BAT) return;
+  if (BAT || LAB) return;
   for (int k = 0; k < 9; ++k) {
     const uint64_t v = sum64(sums.c[k]);
-    if (lane == 0 && v) atomicAdd(&copy_of(a.acc)[RowSums::slot(k)], (unsigned long long)v);
+    if (lane == 0 && v) atomicAdd(&copy_of<LAB>(a.acc)[RowSums::slot(k)], (unsigned long long)v);
+  }
+}
+
+// ------------------------------------------------------------- labelled sums
+// The open wedges and dyads of the 64-state census in closed form (states of a
+// triple a < b < c: f_ab | f_ac << 2 | f_bc << 4; h below is a pair's flag seen
+// from its lower id). A wedge at centre x is two of its entries: both below x
+// (states h << 2 | h' << 4, in id order), one on each side (h | h' << 4), both
+// above (h | h' << 2); the counts of ordered flag pairs on one side come from
+// running counts of the flags 1 and 2 along the row. An edge u < v of flag h has
+// third vertices adjacent to neither below u (state h << 4),
+// between (h << 2) and above (h), less the common neighbours there:
+//   below  u - s_u - s_v, between (v - u - 1) - (k - s_u) - (d'_v - s_v - 1),
+//   above  (n - 1 - v) - (d_u - k - 1) - (d_v - d'_v)
+// with k the index of v in row u, s_u, d'_v the entries of rows u, v below
+// their own ids and s_v the index of u in row v, so each entry adds its own
+// row's part. (The common neighbours are added with the triangles.)
+struct SegCounts {
+  uint32_t lo[3], hi[3];  // entries below and above the row's id, by h - 1
+};
+
+struct LabArgs {
+  int64_t n, nnz, ntiles;
+  const int64_t* off;
+  const int32_t* nbr;
+  const uint8_t* flg;
+  const uint32_t* mark;
+  const uint32_t* tile_row;
+  const uint32_t* list;  // a row's id at its first entry
+  const Cross* cross;    // entries below the own id of rows that cross tiles
+  SegCounts* segs;       // [tile][2]: the counts of a crossing first, last segment
+  unsigned long long* acc;
+  const uint32_t* err;
+};
+
+// Row totals into the wedge states (hist: 64 words): pairs of unlike flags on
+// one side all in the order (higher flag, lower flag); the running counts move
+// those that come the other way round.
+template <class Add>
+__device__ __forceinline__ void lab_row(const uint64_t (&lo)[3], const uint64_t (&hi)[3], Add add) {
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) {
+      if (lo[i] && hi[j]) add((i + 1) | (j + 1) << 4, lo[i] * hi[j]);
+      if (i == j) {
+        if (lo[i] > 1) add((i + 1) << 2 | (j + 1) << 4, lo[i] * (lo[i] - 1) / 2);
+        if (hi[i] > 1) add((i + 1) | (j + 1) << 2, hi[i] * (hi[i] - 1) / 2);
+      } else if (i > j) {
+        if (lo[i] && lo[j]) add((i + 1) << 2 | (j + 1) << 4, lo[i] * lo[j]);
+        if (hi[i] && hi[j]) add((i + 1) | (j + 1) << 2, hi[i] * hi[j]);
+      }
+    }
+}
+
+// Pairs (earlier flag i, later flag j), i < j, k = 0..2 for (1,2) (1,3) (2,3):
+// moved from the state of (j, i) to that of (i, j).
+__device__ __forceinline__ void lab_move(unsigned long long* acc, int side, int k, uint64_t v) {
+  if (!v) return;
+  const int i = k == 2 ? 2 : 1, j = k == 0 ? 2 : 3;
+  const int s0 = side ? (i | j << 2) : (i << 2 | j << 4), s1 = side ? (j | i << 2) : (j << 2 | i << 4);
+  atomicAdd(&acc[s0], (unsigned long long)v);
+  atomicAdd(&acc[s1], (unsigned long long)(0 - v));
+}
+
+__global__ void __launch_bounds__(OTHREADS, 4) k_lab_sums(LabArgs a) {
+  __shared__ uint32_t srow[OT], ssu[OT];
+  __shared__ uint16_t spos[OT + 1];
+  __shared__ uint64_t heads[OWORDS];
+  __shared__ uint32_t hpre[OWORDS + 1];
+  __shared__ uint64_t pl[6][OWORDS + 1];  // planes: below 1, 2, 3; above 1, 2, 3
+  __shared__ uint32_t pp[6][OWORDS + 1];  // their counts before each word
+  __shared__ int64_t ends[4];
+  __shared__ unsigned long long hist[64];
+  if (a.err[0]) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (threadIdx.x < 64) hist[threadIdx.x] = 0;
+  uint64_t dy[3][3] = {}, pr[2][3] = {};  // dyads [below, between, above][h - 1], ordered pairs [side][k]
+  for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const int64_t t0 = t * OT;
+    const int len = (int)min((int64_t)OT, a.nnz - t0);
+    const uint32_t xfirst = a.tile_row[t], xlast = t + 1 < a.ntiles ? a.tile_row[t + 1] : xfirst;
+    int32_t y[OPER];
+    uint32_t h[OPER];
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid;
+      y[i] = p < len ? a.nbr[t0 + p] : 0;
+      h[i] = p < len ? (uint32_t)(a.flg[(t0 + p) >> 2] >> (2 * (p & 3))) & 3u : 0u;
+    }
+    __syncthreads();
+    if (w == 0) {
+      uint64_t m = lane < OWORDS ? ((const uint64_t*)a.mark)[t * OWORDS + lane] | (lane == 0 ? 1ull : 0ull) : 0ull;
+      const uint32_t c = (uint32_t)__popcll(m);
+      uint32_t s = c;
+      for (int o = 1; o < OWORDS; o <<= 1) {
+        const uint32_t q = __shfl_up(s, o, 64);
+        if (lane >= o) s += q;
+      }
+      if (lane < OWORDS) {
+        heads[lane] = m;
+        hpre[lane] = s - c;
+        if (lane == OWORDS - 1) {
+          hpre[OWORDS] = s;
+          spos[s] = (uint16_t)len;
+        }
+      }
+    } else if (w == 1 && lane < 4) {
+      ends[lane] = a.off[(lane < 2 ? xfirst : xlast) + (lane & 1)];
+    }
+    __syncthreads();
+    const int nseg = (int)hpre[OWORDS];
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int wi = i * (OTHREADS / 64) + w;
+      if ((heads[wi] >> lane) & 1ull) spos[hpre[wi] + (uint32_t)__popcll(heads[wi] & below(lane))] = (uint16_t)(wi * 64 + lane);
+    }
+    const bool cross0 = ends[0] < t0 || ends[1] > t0 + len;
+    const bool cross1 = t + 1 < a.ntiles && ends[2] > t0 && ends[2] < t0 + len;
+    __syncthreads();
+    for (int s = tid; s < nseg; s += OTHREADS)
+      srow[s] = s == 0 ? xfirst : s == nseg - 1 && cross1 ? xlast : a.list[t0 + spos[s]];
+    __syncthreads();
+    uint16_t sg[OPER];
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int wi = i * (OTHREADS / 64) + w;
+      sg[i] = (uint16_t)(hpre[wi] + (uint32_t)__popcll(heads[wi] & (~0ull >> (63 - lane))) - 1);
+      const bool up = y[i] > (int32_t)srow[sg[i]];
+      if (!up) h[i] = (h[i] & 1u) << 1 | h[i] >> 1;
+#pragma unroll
+      for (uint32_t f = 1; f <= 3; ++f) {
+        const uint64_t ml = __ballot(h[i] == f && !up), mh = __ballot(h[i] == f && up);
+        if (lane == 0) {
+          pl[f - 1][wi] = ml;
+          pl[f + 2][wi] = mh;
+        }
+      }
+    }
+    __syncthreads();
+    for (int k = w; k < 6; k += OTHREADS / 64) {
+      const uint32_t c = lane < OWORDS ? (uint32_t)__popcll(pl[k][lane]) : 0u;
+      uint32_t s = c;
+      for (int o = 1; o < OWORDS; o <<= 1) {
+        const uint32_t q = __shfl_up(s, o, 64);
+        if (lane >= o) s += q;
+      }
+      if (lane < OWORDS) pp[k][lane] = s - c;
+      if (lane == OWORDS - 1) {
+        pp[k][OWORDS] = s;
+        pl[k][OWORDS] = 0;
+      }
+    }
+    __syncthreads();
+    // entries of plane k before position p of the tile
+    auto before = [&](int k, int p) { return pp[k][p >> 6] + (uint32_t)__popcll(pl[k][p >> 6] & below(p & 63)); };
+    for (int s = tid; s < nseg; s += OTHREADS) {
+      const int p = spos[s], e = spos[s + 1];
+      uint64_t lo[3], hi[3];
+      for (int f = 0; f < 3; ++f) {
+        lo[f] = before(f, e) - before(f, p);
+        hi[f] = before(f + 3, e) - before(f + 3, p);
+      }
+      if ((s == 0 && cross0) || (s == nseg - 1 && cross1)) {
+        const int k = s == 0 ? 0 : 1;
+        SegCounts c;
+        for (int f = 0; f < 3; ++f) {
+          c.lo[f] = (uint32_t)lo[f];
+          c.hi[f] = (uint32_t)hi[f];
+        }
+        a.segs[2 * t + k] = c;
+        ssu[s] = a.cross[ends[2 * k] / OT + 1].su;
+      } else {
+        ssu[s] = (uint32_t)(lo[0] + lo[1] + lo[2]);
+        lab_row(lo, hi, [&](int st, uint64_t v) { atomicAdd(&hist[st], (unsigned long long)v); });
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < OPER; ++i) {
+      const int p = i * OTHREADS + tid, s = sg[i], p0 = spos[s];
+      if (p >= len) continue;
+      const int64_t x = srow[s], su = ssu[s];
+      int64_t k = p - p0, d = spos[s + 1] - p0;
+      if ((s == 0 && cross0) || (s == nseg - 1 && cross1)) {
+        const int q = s == 0 ? 0 : 1;
+        k = t0 + p - ends[2 * q];
+        d = ends[2 * q + 1] - ends[2 * q];
+      }
+      const bool up = y[i] > (int32_t)x;
+      const int64_t d0 = up ? x - su : -k, d1 = up ? (y[i] - x - 1) - (k - su) : -(su - k - 1),
+                    d2 = up ? (a.n - 1 - y[i]) - (d - 1 - k) : -(d - su);
+      const int side = up ? 3 : 0;
+      const uint32_t c1 = before(side, p) - before(side, p0), c2 = before(side + 1, p) - before(side + 1, p0);
+#pragma unroll
+      for (uint32_t f = 1; f <= 3; ++f) {
+        const bool me = h[i] == f;
+        dy[0][f - 1] += me ? (uint64_t)d0 : 0;
+        dy[1][f - 1] += me ? (uint64_t)d1 : 0;
+        dy[2][f - 1] += me ? (uint64_t)d2 : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const bool me = (q != 0) == up;
+        pr[q][0] += me && h[i] == 2 ? c1 : 0u;
+        pr[q][1] += me && h[i] == 3 ? c1 : 0u;
+        pr[q][2] += me && h[i] == 3 ? c2 : 0u;
+      }
+    }
+  }
+  unsigned long long* acc = copy_of<true>(a.acc);
+  const int lane = threadIdx.x & 63;
+  for (int f = 1; f <= 3; ++f)
+    for (int k = 0; k < 3; ++k) {
+      const uint64_t v = sum64(dy[k][f - 1]);
+      if (lane == 0 && v) atomicAdd(&acc[f << (4 - 2 * k)], (unsigned long long)v);
+    }
+  for (int q = 0; q < 2; ++q)
+    for (int k = 0; k < 3; ++k) {
+      const uint64_t v = sum64(pr[q][k]);
+      if (lane == 0) lab_move(acc, q, k, v);
+    }
+  __syncthreads();
+  if (threadIdx.x < 64 && hist[threadIdx.x]) atomicAdd(&acc[threadIdx.x], hist[threadIdx.x]);
+}
+
+// Rows that cross tiles, one wavefront each: their totals, and the ordered pairs
+// whose entries lie in different tiles.
+__global__ void __launch_bounds__(256) k_lab_cross(LabArgs a) {
+  if (a.err[0]) return;
+  const int lane = threadIdx.x & 63;
+  unsigned long long* acc = copy_of<true>(a.acc);
+  const int64_t nw = (int64_t)gridDim.x * 4;
+  for (int64_t t = 1 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < a.ntiles; t += nw) {
+    const uint32_t x = a.tile_row[t];
+    const int64_t ox = a.off[x], ex = a.off[x + 1];
+    if (ox >= t * OT || ox / OT + 1 != t) continue;
+    const int64_t ta = t - 1, te = (ex - 1) / OT;  // first and last tile of the row
+    uint64_t tot[6] = {}, pr[2][3] = {};
+    for (int64_t b = ta; b <= te; b += 64) {
+      uint64_t c[6] = {}, run[6];
+      const int64_t q = b + lane;
+      if (q <= te) {
+        const SegCounts g = a.segs[2 * q + (q == ta && ox > ta * OT ? 1 : 0)];
+        for (int f = 0; f < 3; ++f) {
+          c[f] = g.lo[f];
+          c[f + 3] = g.hi[f];
+        }
+      }
+      for (int k = 0; k < 6; ++k) {
+        uint64_t v = c[k];
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint64_t u = __shfl_up(v, o, 64);
+          if (lane >= o) v += u;
+        }
+        run[k] = tot[k] + v - c[k];  // in the row's tiles before this one
+        tot[k] += __shfl(v, 63, 64);
+      }
+      for (int s = 0; s < 2; ++s) {
+        pr[s][0] += run[3 * s] * c[3 * s + 1];
+        pr[s][1] += run[3 * s] * c[3 * s + 2];
+        pr[s][2] += run[3 * s + 1] * c[3 * s + 2];
+      }
+    }
+    for (int s = 0; s < 2; ++s)
+      for (int k = 0; k < 3; ++k) {
+        const uint64_t v = sum64(pr[s][k]);
+        if (lane == 0) lab_move(acc, s, k, v);
+      }
+    if (lane == 0) {
+      const uint64_t lo[3] = {tot[0], tot[1], tot[2]}, hi[3] = {tot[3], tot[4], tot[5]};
+      lab_row(lo, hi, [&](int st, uint64_t v) { atomicAdd(&acc[st], (unsigned long long)v); });
+    }
   }
 }
 
 // ------------------------------------------------------------------- sorting
 
-// Sort keys: the rank in the high bits (a list word rotated by two).
-__device__ __forceinline__ uint32_t to_key(uint32_t w) { return w << 2 | w >> 30; }
-__device__ __forceinline__ uint32_t of_key(uint32_t k) { return k >> 2 | k << 30; }
+// Sort keys: the rank in the high bits (a list word rotated left by its flag
+// bits, 2, or 3 with labels).
+__device__ __forceinline__ uint32_t to_key(uint32_t w, int r) { return __builtin_amdgcn_alignbit(w, w, 32 - r); }
+__device__ __forceinline__ uint32_t of_key(uint32_t k, int r) { return __builtin_amdgcn_alignbit(k, k, r); }
 
 // N+ lists of 65 to 256 entries, one wavefront each: a bitonic network over
 // four registers a lane.
 __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict__ rows,
                                                      const uint32_t* __restrict__ count,
                                                      const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
-                                                     const uint32_t* __restrict__ err) {
+                                                     const uint32_t* __restrict__ err,
+                                                      int rot) {
   if (err[0] | err[1]) return;
   const int lane = threadIdx.x & 63;
   const uint32_t nw = gridDim.x * 4, cnt = *count;
@@ -582,7 +881,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
     uint32_t* p = list + (in >> 24);
     uint32_t k[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) k[e] = (uint32_t)(e * 64 + lane) < len ? to_key(p[e * 64 + lane]) : 0xFFFFFFFFu;
+    for (int e = 0; e < 4; ++e) k[e] = (uint32_t)(e * 64 + lane) < len ? to_key(p[e * 64 + lane], rot) : 0xFFFFFFFFu;
     // element lane * 4 + e
 #pragma unroll
     for (int sz = 2; sz <= 256; sz <<= 1) {
@@ -610,7 +909,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if ((uint32_t)(lane * 4 + e) < len) p[lane * 4 + e] = of_key(k[e]);
+      if ((uint32_t)(lane * 4 + e) < len) p[lane * 4 + e] = of_key(k[e], rot);
   }
 }
 
@@ -618,7 +917,8 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
 __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict__ rows,
                                                       const uint32_t* __restrict__ count,
                                                       const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
-                                                      const uint32_t* __restrict__ err) {
+                                                      const uint32_t* __restrict__ err,
+                                                      int rot) {
   __shared__ uint32_t k[SORT_MAX];
   if (err[0] | err[1]) return;
   const uint32_t cnt = *count;
@@ -629,7 +929,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict
     uint32_t N = 512;
     while (N < len) N <<= 1;
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < N; i += 256) k[i] = i < len ? to_key(p[i]) : 0xFFFFFFFFu;
+    for (uint32_t i = threadIdx.x; i < N; i += 256) k[i] = i < len ? to_key(p[i], rot) : 0xFFFFFFFFu;
     __syncthreads();
     for (uint32_t sz = 2; sz <= N; sz <<= 1)
       for (uint32_t j = sz >> 1; j > 0; j >>= 1) {
@@ -644,7 +944,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict
         }
         __syncthreads();
       }
-    for (uint32_t i = threadIdx.x; i < len; i += 256) p[i] = of_key(k[i]);
+    for (uint32_t i = threadIdx.x; i < len; i += 256) p[i] = of_key(k[i], rot);
   }
 }
 
@@ -653,6 +953,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict
 // Flags of 16 candidate triangles a lane, two bits each: X = f_xz, Y = f_yz
 // (0: z is not in N+(y)), G = f_xy; counted by class 16 at a time.
 struct Tri {
+  static constexpr bool LAB = false;
   uint32_t X = 0, Y = 0, G = 0;
   uint32_t c[7] = {};  // all, 030C, 120D, 120U, 120C, 210, 300
 
@@ -704,27 +1005,89 @@ struct Tri {
   }
 };
 
-// Two-bit table: id z in word z / 16, the fields from the top down. Ids past
-// the last of W words read that word, which the caller keeps zero if it can
-// meet such ids.
-template <int W>
+// The labelled counterpart: X, Y, G hold the flags seen from the lower id of
+// each pair, LX, LY, LG (the high bit of each field) whether z < x, z < y, y <
+// x by id. The three pairs are told apart by id order (ab, ac, bc of a < b < c)
+// with masks, then each of the 27 states has its counter.
+struct TriLab {
+  static constexpr bool LAB = true;
+  uint32_t X = 0, Y = 0, G = 0, LX = 0, LY = 0, LG = 0;
+  uint32_t c[27] = {};
+
+  __device__ __forceinline__ void count() {
+    constexpr uint32_t L = 0x55555555u;
+    const uint32_t xl = X & L, xh = (X >> 1) & L, yl = Y & L, yh = (Y >> 1) & L, gl = G & L, gh = (G >> 1) & L;
+    const uint32_t lx = LX >> 1, ly = LY >> 1, lg = LG >> 1;  // (fields masked below)
+    const uint32_t hit = (xl | xh) & (yl | yh);
+    // the pair without the largest vertex is ab, the one without the smallest bc
+    const uint32_t big_x = lg & lx, big_y = ~lg & ly, big_z = ~lx & ~ly;
+    const uint32_t low_x = ~lg & ~lx, low_y = lg & ~ly, low_z = lx & ly;
+    const uint32_t abl = (big_x & yl) | (big_y & xl) | (big_z & gl), abh = (big_x & yh) | (big_y & xh) | (big_z & gh);
+    const uint32_t bcl = (low_x & yl) | (low_y & xl) | (low_z & gl), bch = (low_x & yh) | (low_y & xh) | (low_z & gh);
+    const uint32_t acl = gl ^ xl ^ yl ^ abl ^ bcl, ach = gh ^ xh ^ yh ^ abh ^ bch;
+    const uint32_t ab[3] = {abl & ~abh & hit, abh & ~abl & hit, abl & abh & hit};
+    const uint32_t ac[3] = {acl & ~ach, ach & ~acl, acl & ach};
+    const uint32_t bc[3] = {bcl & ~bch, bch & ~bcl, bcl & bch};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const uint32_t q = ab[i] & ac[j];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[i * 9 + j * 3 + k] += __popc(q & bc[k]);
+      }
+  }
+  // g8: the flag in each field of the low byte, y < x in those of the next
+  template <bool TOP>
+  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int left, uint32_t g8) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      X = __builtin_amdgcn_alignbit(X, x[e], 30);
+      LX = __builtin_amdgcn_alignbit(LX, x[e] << 2, 30);
+      Y = TOP ? __builtin_amdgcn_alignbit(Y, y[e], 30) : (Y << 2 | y[e] >> 1);
+      LY = TOP ? __builtin_amdgcn_alignbit(LY, y[e] << 2, 30) : (LY << 2 | (y[e] << 1 & 2u));
+    }
+    X &= ~0u << (8 - 2 * max(0, min(left, 4)));
+    G = G << 8 | (g8 & 0xFFu);
+    LG = LG << 8 | g8 >> 8;
+  }
+  __device__ __forceinline__ void flush(unsigned long long* acc, int lane) {
+#pragma unroll
+    for (int k = 0; k < 27; ++k) {
+      const uint64_t v = sum64(c[k]);
+      const int state = (k / 9 + 1) | (k / 3 % 3 + 1) << 2 | (k % 3 + 1) << 4;
+      if (lane == 0 && v) atomicAdd(&acc[state], (unsigned long long)v);
+      c[k] = 0;
+    }
+  }
+};
+
+// Table of two-bit (LAB: four-bit) fields: id z in word z / 16 (z / 8), the
+// fields from the top down. Ids past the last of W words read that word, which
+// the caller keeps zero if it can meet such ids.
+template <bool LAB>
+constexpr int FB = LAB ? 3 : 4;  // log2 of the fields of a word
+template <int W, bool LAB>
 __device__ __forceinline__ uint32_t probe_bits(const uint32_t* tab, uint32_t w) {
-  return tab[min((w & ID_MASK) >> 4, (uint32_t)W - 1)] << ((w << 1) & 31u);
+  return tab[min((w & IDM<LAB>) >> FB<LAB>, (uint32_t)W - 1)] << ((w << (LAB ? 2 : 1)) & 31u);
 }
+template <bool LAB>
 __device__ __forceinline__ void set_bits(uint32_t* tab, uint32_t w) {
-  atomicOr(&tab[(w & ID_MASK) >> 4], (w >> 30) << (30 - 2 * (w & 15u)));
+  const uint32_t f = LAB ? (w >> 28 & 0xEu) << (28 - 4 * (w & 7u)) : (w >> 30) << (30 - 2 * (w & 15u));
+  atomicOr(&tab[(w & IDM<LAB>) >> FB<LAB>], f);
 }
 
 // Hash table of list words, open addressing on the low bits of the id; at most
 // TAB_MAX of its TAB_WORDS slots are taken, so every search ends.
+template <bool LAB>
 __device__ __forceinline__ uint32_t probe_hash(const uint32_t* tab, uint32_t w) {
-  const uint32_t key = w & ID_MASK;
+  const uint32_t key = w & IDM<LAB>;
   uint32_t h = key & (TAB_WORDS - 1), v = tab[h];
-  while (v != SLOT_FREE && (v & ID_MASK) != key) {
+  while (v != SLOT_FREE && (v & IDM<LAB>) != key) {
     h = (h + 1) & (TAB_WORDS - 1);
     v = tab[h];
   }
-  return (v & ID_MASK) == key ? v : 0u;
+  return (v & IDM<LAB>) == key ? v : 0u;
 }
 __device__ __forceinline__ void set_hash(uint32_t* tab, uint32_t w) {
   uint32_t h = w & (TAB_WORDS - 1);
@@ -742,21 +1105,21 @@ struct XList {
 
 // Lists the vertices of up to `cnt` in-list words g (one a lane) whose N+ has
 // at least two entries (y is one of them).
-template <bool WIDE>
+template <bool LAB, bool WIDE>
 __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict__ in, int cnt,
                                       const uint64_t* __restrict__ info, int lane) {
   uint64_t xi = 0;
   uint32_t g = 0;
   if (lane < cnt) {
     g = in[lane];
-    xi = info[g & ID_MASK];
+    xi = info[g & IDM<LAB>];
   }
   const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
   const uint64_t m = __ballot(has);
   if (has) {
     const int k = __popcll(m & below(lane));
     L.p[k] = xi >> 24;
-    L.m[k] = (g & ~ID_MASK) | ((uint32_t)xi & (LEN_MASK | UNSORTED));
+    L.m[k] = (g & ~IDM<LAB>) | ((uint32_t)xi & (LEN_MASK | UNSORTED));
   }
   return __popcll(m);
 }
@@ -766,9 +1129,9 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
 // are in flight while the other is counted (loads are never skipped, an idle
 // lane rereads the list's first words: the wait for a set is then for its own
 // loads only). A list in rank order ends with the step that reaches y's rank.
-template <int GL, bool SORTED, bool TOP, bool WIDE, class Probe>
+template <int GL, bool SORTED, bool TOP, bool WIDE, class T, class Probe>
 __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const XList<WIDE>& L, int cnt,
-                                       uint32_t yrank, int lane, Tri& tri, Probe probe) {
+                                       uint32_t yrank, int lane, T& tri, Probe probe) {
   constexpr uint64_t G0 = GL == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;  // first lane of each group
   constexpr int STEP = 4 * GL, SETS = 64 / GL;
   const int l4 = (lane & (GL - 1)) * 4;
@@ -792,7 +1155,7 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
       const uint32_t m = L.m[k];
       s.o = L.p[k] + l4;
       s.left = (int)(m & LEN_MASK) - l4;
-      s.g8 = (m >> 30) * 0x55u;
+      s.g8 = (m >> 30) * 0x55u | (T::LAB ? (m >> 29 & 1u) * 0xAA00u : 0u);
       // (lists of up to SORT_MIN entries are not sorted)
       s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : yrank;
     }
@@ -808,11 +1171,11 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
   auto step = [&](Slot& s) {
     uint32_t y[4];
     probe(s.w, y);
-    tri.add4<TOP>(s.w, y, s.left, s.g8);
+    tri.template add4<TOP>(s.w, y, s.left, s.g8);
     // lists that end here: their first lane has at most one step left, or the
     // last entry read has reached y
     uint64_t d = __ballot(s.left <= STEP) & G0;
-    if (SORTED) d |= (__ballot((s.w[3] & ID_MASK) >= s.lim) >> (GL - 1)) & G0;
+    if (SORTED) d |= (__ballot((s.w[3] & IDM<T::LAB>) >= s.lim) >> (GL - 1)) & G0;
     s.o += STEP;
     s.left -= STEP;
     if (d) {
@@ -899,8 +1262,9 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
 
 // Vertices with long in-lists: a workgroup takes up to CHUNK of one's in-list
 // and holds N+(y) as a byte per rank (z of N+(y) has a lower rank than y).
-template <bool WIDE>
-__global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
+template <bool LAB, bool WIDE>
+__global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(CountArgs a) {
+  constexpr int HUB_THREADS = hub_threads(LAB);
   __shared__ __align__(16) uint8_t tab[HUB_RANKS + 16];  // f_yz by rank of z; past the ranks: 0
   __shared__ XList<WIDE> xl[HUB_THREADS / 64];
   __shared__ uint32_t item, next;
@@ -909,7 +1273,7 @@ __global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
   for (int i = tid; i < (int)sizeof(tab) / 4; i += HUB_THREADS) ((uint32_t*)tab)[i] = 0;
   const uint32_t nitems = a.counts[2];
   XList<WIDE>& L = xl[tid >> 6];
-  Tri tri;
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
   for (;;) {
     if (tid == 0) {
       item = atomicAdd(&a.counts[4], 1u);
@@ -926,7 +1290,7 @@ __global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
     const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
     for (uint32_t i = tid; i < plus; i += HUB_THREADS) {
       const uint32_t z = a.list[s + i];
-      tab[z & ID_MASK] = (uint8_t)(z >> 30);
+      tab[z & IDM<LAB>] = (uint8_t)(z >> (LAB ? 29 : 30));
     }
     // wavefronts claim up to 64 in-list entries at a time
     const int claim = cnt >= 1024 ? 64 : cnt >= 512 ? 32 : 16;
@@ -936,25 +1300,25 @@ __global__ void __launch_bounds__(HUB_THREADS, 6) k_sw_hubs(CountArgs a) {
       if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
       k = __builtin_amdgcn_readfirstlane(k);
       if (k >= cnt) break;
-      const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+      const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
       wave_sync();
       stream<16, true, false, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4]) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & ID_MASK, (uint32_t)HUB_RANKS)];
+        for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & IDM<LAB>, (uint32_t)HUB_RANKS)];
       });
       wave_sync();
     }
     __syncthreads();
-    for (uint32_t i = tid; i < plus; i += HUB_THREADS) tab[a.list[s + i] & ID_MASK] = 0;
+    for (uint32_t i = tid; i < plus; i += HUB_THREADS) tab[a.list[s + i] & IDM<LAB>] = 0;
   }
-  tri.flush(copy_of(a.acc), lane);
+  tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
 // Vertices with in-lists of middling length, of any rank: a smaller workgroup,
 // N+(y) as two bits per rank up to HUB_RANKS and a hash table beyond.
-template <bool WIDE>
-__global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
-  constexpr int W = HUB_RANKS / 16 + 1;
+template <bool LAB, bool WIDE>
+__global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs a) {
+  constexpr int W = (HUB_RANKS >> FB<LAB>) + 1;
   __shared__ uint32_t tab[W], high[TAB_WORDS];
   __shared__ XList<WIDE> xl[MID_THREADS / 64];
   __shared__ uint32_t item, next;
@@ -964,7 +1328,7 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
   for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
   const uint32_t nitems = a.counts[3];
   XList<WIDE>& L = xl[tid >> 6];
-  Tri tri;
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
   for (;;) {
     if (tid == 0) item = atomicAdd(&a.counts[5], 1u);
     __syncthreads();
@@ -983,7 +1347,7 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
       const uint32_t fe = min(f + TAB_MAX, plus);
       for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
         const uint32_t z = a.list[s + i];
-        if ((z & ID_MASK) < HUB_RANKS) set_bits(tab, z); else set_hash(high, z);
+        if ((z & IDM<LAB>) < HUB_RANKS) set_bits<LAB>(tab, z); else set_hash(high, z);
       }
       if (tid == 0) next = 0;
       __syncthreads();
@@ -992,34 +1356,34 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
         if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
         k = __builtin_amdgcn_readfirstlane(k);
         if (k >= cnt) break;
-        const int nx = list_x<WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+        const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
         wave_sync();
         stream<16, true, true, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4]) {
           uint32_t top = 0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            g[e] = probe_bits<W>(tab, w[e]);
-            top = max(top, w[e] & ID_MASK);
+            g[e] = probe_bits<W, LAB>(tab, w[e]);
+            top = max(top, w[e] & IDM<LAB>);
           }
           if (far && __ballot(top >= HUB_RANKS)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if ((w[e] & ID_MASK) >= HUB_RANKS) g[e] = probe_hash(high, w[e]);
+              if ((w[e] & IDM<LAB>) >= HUB_RANKS) g[e] = probe_hash<LAB>(high, w[e]);
           }
         });
         wave_sync();
       }
       __syncthreads();
       for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
-        const uint32_t z = a.list[s + i] & ID_MASK;
-        if (z < HUB_RANKS) tab[z >> 4] = 0;
+        const uint32_t z = a.list[s + i] & IDM<LAB>;
+        if (z < HUB_RANKS) tab[z >> FB<LAB>] = 0;
       }
       if (far)
         for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
       if (fe < plus) __syncthreads();
     }
   }
-  tri.flush(copy_of(a.acc), lane);
+  tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
 // The other vertices: a wavefront takes a range of entries and the rows whose
@@ -1027,16 +1391,17 @@ __global__ void __launch_bounds__(MID_THREADS, 5) k_sw_mids(CountArgs a) {
 // index a two-bit table of N+(y); else a hash table, filled TAB_MAX entries at
 // a time. RANK: lists in ranks, and only the rows that the kernels above leave;
 // else all rows. BAT: a batch, counted by graph.
-template <bool BITS, bool RANK, bool BAT, bool WIDE>
-__global__ void __launch_bounds__(REST_WAVES * 64, BITS ? 5 : 4) k_sw_rest(CountArgs a) {
-  __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
+template <bool BITS, bool RANK, bool BAT, bool LAB, bool WIDE>
+__global__ void __launch_bounds__(REST_WAVES * 64, BITS && !LAB ? 5 : 4) k_sw_rest(CountArgs a) {
+  constexpr int TW = BITS ? (int)(DIRECT_N >> FB<LAB>) : TAB_WORDS;
+  __shared__ uint32_t tabs[REST_WAVES][TW];
   __shared__ XList<WIDE> xl[REST_WAVES];
   if (a.err[0] | a.err[1]) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   XList<WIDE>& L = xl[w];
-  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = BITS ? 0u : SLOT_FREE;
-  Tri tri;
+  for (int i = lane; i < TW; i += 64) tab[i] = BITS ? 0u : SLOT_FREE;
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
   uint32_t graph = 0;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
   for (int64_t j0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
@@ -1091,20 +1456,20 @@ __global__ void __launch_bounds__(REST_WAVES * 64, BITS ? 5 : 4) k_sw_rest(Count
           const uint32_t fe = BITS ? plus : min(f + TAB_MAX, plus);
           for (uint32_t i = f + lane; i < fe; i += 64) {
             const uint32_t z = a.list[f0 + i];
-            if (BITS) set_bits(tab, z); else set_hash(tab, z);
+            if (BITS) set_bits<LAB>(tab, z); else set_hash(tab, z);
           }
           wave_sync();
           for (int64_t k = l0; k < l1; k += 64) {
-            const int nx = list_x<WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), info, lane);
+            const int nx = list_x<LAB, WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), info, lane);
             wave_sync();
             stream<8, RANK, true, WIDE>(a.list, L, nx, rk, lane, tri, [&](const uint32_t (&q)[4], uint32_t (&g)[4]) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i) g[i] = BITS ? probe_bits<TAB_WORDS>(tab, q[i]) : probe_hash(tab, q[i]);
+              for (int i = 0; i < 4; ++i) g[i] = BITS ? probe_bits<TW, LAB>(tab, q[i]) : probe_hash<LAB>(tab, q[i]);
             });
             wave_sync();
           }
           if (BITS) {
-            for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & ID_MASK) >> 4] = 0;
+            for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & IDM<LAB>) >> FB<LAB>] = 0;
           } else {
             for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
           }
@@ -1116,7 +1481,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, BITS ? 5 : 4) k_sw_rest(Count
     }
   }
   if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
-  else tri.flush(copy_of(a.acc), lane);
+  else tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
 // ------------------------------------------------------------------- results
@@ -1162,6 +1527,44 @@ __global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t
   }
   status[0] = out[0] = clo - s;
   status[16] = out[16] = chi - (clo < s ? 1u : 0u);
+}
+
+// Labelled: a triangle a < b < c takes its three pairs of neighbours out of the
+// wedge states and gives the common neighbour back to the dyads of its edges
+// (bc with the third vertex below, ac between, ab above).
+__global__ void k_sw_finish_lab(const unsigned long long* __restrict__ acc, uint32_t* __restrict__ err, int64_t nnz,
+                                uint64_t clo, uint64_t chi, uint64_t* __restrict__ out,
+                                uint64_t* __restrict__ status) {
+  __shared__ uint64_t c[SW_LAB_WORDS];
+  for (int i = threadIdx.x; i < SW_LAB_WORDS; i += blockDim.x) {
+    uint64_t t = 0;
+    for (int k = 0; k < SW_COPIES; ++k) t += acc[k * SW_LAB_WORDS + i];
+    c[i] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  uint32_t e = err[0] | err[1] | err[2];
+  if (!e && (int64_t)c[SW_LAB_ABOVE] * 2 != nnz) e = ERR_ASYM;
+  status[65] = e;
+  if (e) return;  // an error writes no output
+  for (uint32_t st = 21; st < 64; ++st) {
+    const uint32_t ab = st & 3u, ac = st >> 2 & 3u, bc = st >> 4;
+    if (!ab || !ac || !bc) continue;
+    const uint64_t t = c[st];
+    c[ab | ac << 2] -= t;
+    c[ab | bc << 4] -= t;
+    c[ac << 2 | bc << 4] -= t;
+    c[ab] += t;
+    c[ac << 2] += t;
+    c[bc << 4] += t;
+  }
+  uint64_t s = 0;
+  for (int k = 1; k < 64; ++k) {
+    status[k] = out[k] = c[k];
+    s += c[k];
+  }
+  status[0] = out[0] = clo - s;
+  status[64] = out[64] = chi - (clo < s ? 1u : 0u);
 }
 
 // Per graph: the classes from its sums; 003 = C(n_g, 3) less the rest (n_g <
@@ -1234,7 +1637,7 @@ unsigned grid_of_work(int64_t work, int per, int64_t cap) {
 
 }  // namespace
 
-int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out, uint32_t** err_out, Scratch& scratch,
+int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long long** acc_out, uint32_t** err_out, Scratch& scratch,
                  hipEvent_t* ev, hipStream_t s) {
   auto rec = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], s);
@@ -1251,7 +1654,7 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
     words += (w + 1) & ~(int64_t)1;
     return at;
   };
-  const int64_t w_acc = place(2 * SW_WORDS * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(6);
+  const int64_t w_acc = place(2 * (labelled ? SW_LAB_WORDS : SW_WORDS) * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(6);
   const int64_t w_hist = place(rank ? 2 * BUCKETS : 0);
   const int64_t w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
   const int64_t w_mark = place(ntiles * (OT / 32));
@@ -1268,6 +1671,8 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
   }
   uint32_t *key = nullptr, *list = nullptr, *tile_row = nullptr, *mid = nullptr, *lng = nullptr;
   uint64_t *info = nullptr, *hub_items = nullptr, *mid_items = nullptr;
+  SegCounts* segs = nullptr;
+  if (labelled) ALLOC(segs, 2 * ntiles);
   ALLOC(key, n);
   ALLOC(info, n);
   ALLOC(list, nnz + LIST_PAD);
@@ -1281,7 +1686,7 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
     ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
-                   tile_row, err, 0, nullptr, nullptr};
+                   tile_row, err, 0, nullptr, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
   const unsigned rgrid = grid_of_work(n, ROWS_THREADS * ROWS_PER, INT32_MAX);
   k_sw_rows<<<rgrid, ROWS_THREADS, 0, s>>>(ra);
   if (nnz == 0) return TRIAD_OK;
@@ -1300,29 +1705,39 @@ int sweep_census(const SweepIn& in, bool validate, unsigned long long** acc_out,
   const int64_t waves = (int64_t)di.cus * 32;
   ca.range = std::max<int64_t>(64, std::min<int64_t>(1024, (nnz / waves + 63) & ~(int64_t)63));
   const unsigned wgrid = grid_of_work((nnz + ca.range - 1) / ca.range, REST_WAVES, (int64_t)di.cus * 8);
-  if (rank) {
-    k_sw_orient<true, false><<<ogrid, OTHREADS, 0, s>>>(oa);
-    k_sw_cross<true, false><<<cgrid, 256, 0, s>>>(oa);
-    rec(1);
-    k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err);
-    k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err);
-    k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
-    rec(2);
-    auto count = [&](auto wide) {
-      constexpr bool W = decltype(wide)::value;
-      k_sw_hubs<W><<<(unsigned)(di.cus * 2), HUB_THREADS, 0, s>>>(ca);
-      k_sw_mids<W><<<(unsigned)(di.cus * 6), MID_THREADS, 0, s>>>(ca);
-      k_sw_rest<false, true, false, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
-    };
-    if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
-  } else {
-    // (n <= DIRECT_N: fewer than 2^28 entries)
-    k_sw_orient<false, false><<<ogrid, OTHREADS, 0, s>>>(oa);
-    k_sw_cross<false, false><<<cgrid, 256, 0, s>>>(oa);
-    rec(1);
-    rec(2);
-    k_sw_rest<true, false, false, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+  if (labelled) {
+    const LabArgs la{n, nnz, ntiles, in.off, in.nbr, in.flg, zero + w_mark, tile_row, list, (Cross*)(zero + w_cross),
+                     segs, acc, err};
+    k_lab_sums<<<ogrid, OTHREADS, 0, s>>>(la);
+    k_lab_cross<<<grid_of_work(ntiles, 4, 2048), 256, 0, s>>>(la);
   }
+  auto run = [&](auto lab) {
+    constexpr bool LAB = decltype(lab)::value;
+    if (rank) {
+      k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
+      k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
+      rec(1);
+      k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err, LAB ? 3 : 2);
+      k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err, LAB ? 3 : 2);
+      k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+      rec(2);
+      auto count = [&](auto wide) {
+        constexpr bool W = decltype(wide)::value;
+        k_sw_hubs<LAB, W><<<(unsigned)(di.cus * 2), hub_threads(LAB), 0, s>>>(ca);
+        k_sw_mids<LAB, W><<<(unsigned)(di.cus * (LAB ? 4 : 6)), MID_THREADS, 0, s>>>(ca);
+        k_sw_rest<false, true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+      };
+      if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
+    } else {
+      // (n <= DIRECT_N: fewer than 2^28 entries)
+      k_sw_orient<false, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
+      k_sw_cross<false, false, LAB><<<cgrid, 256, 0, s>>>(oa);
+      rec(1);
+      rec(2);
+      k_sw_rest<true, false, false, LAB, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+    }
+  };
+  if (labelled) run(std::true_type{}); else run(std::false_type{});
   rec(3);
   HIPCHK(hipGetLastError());
   return TRIAD_OK;
@@ -1379,7 +1794,8 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   *err_out = err + 3;
   k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words);
   if (nv > 0) {
-    const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow};
+    const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow,
+                     nullptr, nullptr};
     k_sw_rows<<<grid_of_work(nv, ROWS_THREADS * ROWS_PER, INT32_MAX), ROWS_THREADS, 0, s>>>(ra);
   }
   if (nv > 0 && nnz > 0) {
@@ -1387,13 +1803,13 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
     if (int st = device_info(&di)) return st;
     const OrientArgs oa{nv, nnz, z.ntiles, in.off, in.nbr, in.flg, key, zero + z.w_mark, tile_row, list, info,
                         (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
-    k_sw_orient<false, true><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
-    k_sw_cross<false, true><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
+    k_sw_orient<false, true, false><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
+    k_sw_cross<false, true, false><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
     CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, zero + z.w_cnt, range, acc,
                  err, vbase, grow, gacc};
     const unsigned grid = grid_of_work((nnz + range - 1) / range, waves, groups);
     auto count = [&](auto bits, auto wide) {
-      k_sw_rest<decltype(bits)::value, false, true, decltype(wide)::value><<<grid, waves * 64, 0, s>>>(ca);
+      k_sw_rest<decltype(bits)::value, false, true, false, decltype(wide)::value><<<grid, waves * 64, 0, s>>>(ca);
     };
     const bool wide = nnz + LIST_PAD >= ((int64_t)1 << 30);
     if (nmax <= DIRECT_N) {
@@ -1406,11 +1822,12 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   return TRIAD_OK;
 }
 
-void sweep_finish(const unsigned long long* acc, uint32_t* err, int64_t nnz, int64_t n, uint64_t* d_out,
-                  uint64_t* status, hipStream_t s) {
+void sweep_finish(const unsigned long long* acc, uint32_t* err, bool labelled, int64_t nnz, int64_t n,
+                  uint64_t* d_out, uint64_t* status, hipStream_t s) {
   uint64_t clo, chi;
   choose3(n, &clo, &chi);
-  k_sw_finish<<<1, 64, 0, s>>>(acc, err, nnz, (uint64_t)n, clo, chi, d_out, status);
+  if (labelled) k_sw_finish_lab<<<1, 128, 0, s>>>(acc, err, nnz, clo, chi, d_out, status);
+  else k_sw_finish<<<1, 64, 0, s>>>(acc, err, nnz, (uint64_t)n, clo, chi, d_out, status);
 }
 
 }  // namespace triad

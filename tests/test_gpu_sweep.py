@@ -147,3 +147,41 @@ def test_batch_members_of_all_sizes(torch):
             plan.launch()
             assert plan.result() == want
         plan.close()
+
+
+def _lab(n, d, **kw):
+    return triad.labelled_census_device(n, int(d[1].numel()), *d, **kw)[0]
+
+
+@pytest.mark.parametrize("edges", [1, 2047, 2049, 6145, 20000])
+def test_labelled_rows_across_tiles(torch, edges):
+    """Rows of one hub over several tiles, the hub's id at either end or in the
+    middle (its entries then lie below and above it), all flags mixed."""
+    rng = np.random.default_rng(edges + 1)
+    n = edges + 3
+    for hub in (0, n // 2, n - 1):
+        leaf = rng.permutation(np.delete(np.arange(n), hub))[:edges * 3 // 4 + 1]
+        extra = rng.integers(0, n, (2, edges // 4 + 1))
+        s = np.concatenate([np.full(leaf.size, hub), extra[0]]).astype(np.int32)
+        t = np.concatenate([leaf, extra[1]]).astype(np.int32)
+        flip = rng.random(s.size) < 0.5
+        g = graphs.build_csr(n, np.where(flip, t, s), np.where(flip, s, t), recip_p=0.3, recip_seed=3)
+        assert _lab(n, triad.to_device(g)) == oracle.labelled_census(g)
+
+
+@pytest.mark.parametrize("case", [("rmat", 9, 12), ("rmat", 14, 10), ("rmat", 15, 12), ("chung_lu", 90001, 20)])
+def test_labelled_against_the_merge(torch, case):
+    kind, a, b = case
+    g = graphs.rmat(a, b, seed=4, recip_p=0.25) if kind == "rmat" else graphs.chung_lu(a, 2.1, float(b), a / 16.0, seed=2)
+    d = triad.to_device(g)
+    assert _lab(g.n, d) == _lab(g.n, d, chunk=32768)
+
+
+@pytest.mark.parametrize("sizes", [[64, 257, 514, 3, 3, 700], [4100, 30] + [2] * 13000, [600] * 120])
+def test_labelled_cliques(torch, sizes):
+    n, d = _cliques(torch, sizes, False)  # transitive: every triple a < b < c has arcs a->b, a->c, b->c
+    c = _lab(n, d)
+    want = sum(comb(k, 3) for k in sizes)
+    assert c[21] == want
+    assert sum(c) == comb(n, 3)
+    assert all(c[s] == 0 for s in range(64) if s not in (0, 1, 4, 16, 21))
