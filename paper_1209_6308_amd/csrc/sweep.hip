@@ -442,8 +442,8 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       }
     }
     __syncthreads();
-    // the counts of each segment
-    RowSums sums;
+    // the counts of each segment (its sums go to LDS at once: kept in registers
+    // over the tiles they cost a wavefront per SIMD and spills)
     for (int s = tid; s < nseg; s += OTHREADS) {
       const int p = spos[s], e = spos[s + 1];
       const uint32_t nf = pre[e >> 6] + (uint32_t)__popcll(fwd[e >> 6] & below(e & 63)) - pre[p >> 6] -
@@ -464,16 +464,14 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       if (!((s == 0 && cross0) || (s == nseg - 1 && cross1))) {
         const uint32_t fl = nf > SORT_MAX ? UNSORTED : 0u;
         a.info[x] = (uint64_t)(t0 + p) << 24 | (min(nf, LEN_MASK) | (RANK ? fl : 0u));
-        if constexpr (BAT) {
+        if constexpr (!LAB) {
           RowSums one;
-          one.row((uint64_t)(a.vbase[g + 1] - a.vbase[g]), o, in, mu);
+          one.row(BAT ? (uint64_t)(a.vbase[g + 1] - a.vbase[g]) : (uint64_t)a.n, o, in, mu);
           for (int k = 0; k < 9; ++k) {
             if (!one.c[k]) continue;
-            if (g - g0 < TILE_GRAPHS) atomicAdd(&gsum[g - g0][k], (unsigned long long)one.c[k]);
+            if (!BAT || g - g0 < TILE_GRAPHS) atomicAdd(&gsum[g - g0][k], (unsigned long long)one.c[k]);
             else atomicAdd(&a.gacc[(uint64_t)g * 16 + RowSums::batch_slot(k)], (unsigned long long)one.c[k]);
           }
-        } else if constexpr (!LAB) {
-          sums.row((uint64_t)a.n, o, in, mu);
         }
         if (RANK && nf > SORT_MIN && nf <= SORT_MAX) {
           const uint32_t k = nf > SORT_MID;
@@ -490,11 +488,6 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
         atomicAdd(&c->m, mu);
       }
     }
-    if (!BAT && !LAB && w * 64 < nseg)
-      for (int k = 0; k < 9; ++k) {
-        const uint64_t v = sum64(sums.c[k]);
-        if (lane == 0 && v) atomicAdd(&gsum[0][k], (unsigned long long)v);
-      }
     __syncthreads();
     // place the entries
 #pragma unroll
