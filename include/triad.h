@@ -83,8 +83,9 @@ enum triad_schedule {
                                 predicted cycles, summed over the batch */
 };
 
-/* Device time of each stage of one census call, in milliseconds (HIP events
- * on the call's stream). */
+/* Device time of each stage of one census call, in milliseconds (HIP events on
+ * the call's stream, or the device's 100 MHz clock at the start of each stage's
+ * first kernel where triangles are listed). */
 typedef struct triad_timing {
   float prep_ms;     /* validation; ids packed with direction bits, or edges directed by degree */
   float tasks_ms;    /* task enumeration (scan) and scheduling, or sorting and work items */

@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -1244,13 +1245,18 @@ static hipError_t launch_t(const CensusArgs& a, int mode, int groups, hipStream_
 }
 template <int WAVES, int W, bool HH, int MINW>
 static int occ_t(int mode) {
+  // a property of the code object (gfx950), asked for once: every timed call
+  // reports the launch size
+  static std::atomic<int> known[3];
+  if (const int k = known[mode].load(std::memory_order_relaxed)) return k;
   int per_cu = 0;
   hipError_t e;
   if (mode == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census<WAVES, W, HH, 1, MINW>, WAVES * 64, 0);
   else if (mode == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census<WAVES, W, HH, 2, MINW>, WAVES * 64, 0);
   else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census<WAVES, W, HH, 0, MINW>, WAVES * 64, 0);
   if (e != hipSuccess) return 1;
-  return per_cu < 1 ? 1 : per_cu;
+  known[mode].store(std::max(per_cu, 1), std::memory_order_relaxed);
+  return std::max(per_cu, 1);
 }
 template <int WAVES>
 static hipError_t launch_v(int variant, const CensusArgs& a, int cyc, int groups, hipStream_t s) {
@@ -1300,10 +1306,14 @@ static int lab_groups(int requested) {
   if (requested > 0) return requested;
   DeviceInfo di;
   if (device_info(&di) != TRIAD_OK) return 1024;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census<LAB_WAVES, 448, true, 3, 5>, LAB_WAVES * 64, 0) !=
-          hipSuccess || per_cu < 1)
-    per_cu = 1;
+  static std::atomic<int> known;
+  int per_cu = known.load(std::memory_order_relaxed);
+  if (!per_cu) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_census<LAB_WAVES, 448, true, 3, 5>, LAB_WAVES * 64, 0) !=
+            hipSuccess || per_cu < 1)
+      return di.cus;
+    known.store(per_cu, std::memory_order_relaxed);
+  }
   return di.cus * per_cu;
 }
 
@@ -1412,8 +1422,6 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
       return fail(TRIAD_EINVAL, "graph too large for the no-allocation census: it needs " + std::to_string(need) +
                                     " bytes of scratch, the static scratch holds " + std::to_string(arena_bytes));
   }
-  Events ev;
-  if (o.timing) HIPCHK(ev.init());
   Scratch scratch = arena ? Scratch(s, arena, arena_bytes) : Scratch(s, allocated_before, true);
   // The default call lists triangles (sweep.hip). The merge below remains for
   // calls that ask for what only it has: a work queue of tasks to order
@@ -1423,10 +1431,9 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     unsigned long long* acc = nullptr;
     uint32_t* err = nullptr;
     uint64_t* status = nullptr;
-    ev.rec(0, s);
     ALLOC(status, SW_STATUS);
     const SweepIn in{n, nnz, off, nbr, flg};
-    if (int st = sweep_census(in, o.validate == 1, labelled, &acc, &err, scratch, ev.on ? ev.e : nullptr, s)) return st;
+    if (int st = sweep_census(in, o.validate == 1, labelled, &acc, &err, scratch, status, s)) return st;
     // test hook: a call that passes validation reports a device fault
     if (injected_fault_pending()) {
       uint32_t eh[SW_ERRS];
@@ -1441,9 +1448,8 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     }
     sweep_finish(acc, err, labelled, nnz, n, d_out, status, s);
     HIPCHK(hipGetLastError());
-    ev.rec(4, s);
     uint64_t hres[SW_STATUS];
-    HIPCHK(hipMemcpyAsync(hres, status, (NC + 2) * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(hres, status, sizeof hres, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (int st = status_from_bits((uint32_t)hres[NC + 1]))
       return fail(st, st == TRIAD_ERANGE      ? "neighbour id out of range, zero flag, or bad offsets"
@@ -1453,10 +1459,13 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
                                               : "the device reported a fault during the census");
     if (h_out) std::memcpy(h_out, hres, (NC + 1) * sizeof(uint64_t));
     if (o.timing) {
-      o.timing->prep_ms = ev.ms(0, 1);
-      o.timing->tasks_ms = ev.ms(1, 2);
-      o.timing->census_ms = ev.ms(2, 3);
-      o.timing->finalize_ms = ev.ms(3, 4);
+      const uint64_t* clk = hres + SW_CLK;
+      auto ms = [&](int i, int j) { return (float)((double)(int64_t)(clk[j] - clk[i]) / 1e5); };
+      const bool ran = nnz > 0;  // else the counting stages were not launched
+      o.timing->prep_ms = ms(0, ran ? 1 : 3);
+      o.timing->tasks_ms = ran ? ms(1, 2) : 0.0f;
+      o.timing->census_ms = ran ? ms(2, 3) : 0.0f;
+      o.timing->finalize_ms = ms(3, 4);
       o.timing->tasks = nnz / 2;
       o.timing->hub_tasks = 0;
       o.timing->items = nnz / 2;
@@ -1465,6 +1474,8 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     }
     return hres[NC] ? TRIAD_OK_003_WRAPPED : TRIAD_OK;
   }
+  Events ev;
+  if (o.timing) HIPCHK(ev.init());
   uint32_t* err = nullptr;
   // NC census counters, 2 queue counters, hub tasks
   unsigned long long* acc = nullptr;
@@ -1861,9 +1872,9 @@ static int check_vbase(int32_t G, int64_t nv, const int64_t* hv, int64_t* nmax =
 }
 
 // Entries that a wavefront of the batched triangle listing takes per turn, by
-// kernel variant (the default and every odd one: 512).
+// kernel variant (0: left to sweep_batch).
 static int64_t batch_range(int32_t variant) {
-  return variant <= 0 || variant > NUM_VARIANTS ? 512 : (int64_t)128 << (variant % 4 + 1);
+  return variant <= 0 || variant > NUM_VARIANTS ? 0 : (int64_t)128 << (variant % 4 + 1);
 }
 
 static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, const int64_t* off, const int32_t* nbr,

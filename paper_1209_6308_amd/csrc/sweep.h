@@ -21,6 +21,8 @@ constexpr int SW_LAB_ABOVE = 64, SW_LAB_WORDS = 80;
 // err[0]: raised by the row checks, err[1]: by the entry checks, err[2]: later
 constexpr int SW_ERRS = 4;
 
+constexpr int SW_CLK = 66, SW_STATUS = SW_CLK + 5;
+
 struct SweepIn {
   int64_t n, nnz;
   const int64_t* off;
@@ -31,16 +33,16 @@ struct SweepIn {
 // Enqueues the whole sweep of one graph on s: validation, orientation,
 // triangle counts and per-row sums. *acc (SW_COPIES copies of SW_WORDS words, to be summed; labelled: SW_LAB_WORDS) and *err (SW_ERRS
 // words) are its counters, in scratch memory. validate: also check symmetry.
-// ev (may be NULL): events 1, 2, 3 are recorded after the orientation, the
-// sorting and listing, and the counting.
+// status (device, SW_STATUS words): from word SW_CLK on, the device clock at
+// the start, after the orientation, after the sorting and listing, after the
+// counting, at the end (a stage that did not run leaves its word).
 int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long long** acc, uint32_t** err, Scratch& scratch,
-                 hipEvent_t* ev, hipStream_t s);
+                 uint64_t* status, hipStream_t s);
 // Labelled: the 64 states (n below SW_LAB_MAX_N).
 constexpr int64_t SW_LAB_MAX_N = (int64_t)1 << 29;
 // The 16 counts and the high word of 003 (labelled: 64 states and the high word
-// of state 0) into d_out unless an error is set; status (device, at most
-// SW_STATUS words) gets the same words and then the error bits.
-constexpr int SW_STATUS = 66;
+// of state 0) into d_out unless an error is set; status gets the same words and
+// then the error bits.
 void sweep_finish(const unsigned long long* acc, uint32_t* err, bool labelled, int64_t nnz, int64_t n, uint64_t* d_out,
                   uint64_t* status, hipStream_t s);
 
@@ -49,7 +51,7 @@ void sweep_finish(const unsigned long long* acc, uint32_t* err, bool labelled, i
 // unless an error is found, *err (one word, in scratch memory) has its bits
 // afterwards. Its scratch is sweep_batch_bytes from an arena. Launch shape:
 // wavefronts per workgroup (1, 2, 4), workgroups, entries per wavefront and
-// turn (a multiple of 64). Capturable.
+// turn (a multiple of 64; 0: chosen here). Capturable.
 size_t sweep_batch_bytes(int32_t graphs, int64_t nv, int64_t nnz);
 int sweep_batch_groups(int waves);  // default workgroups
 int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vbase, int64_t nmax, int waves,

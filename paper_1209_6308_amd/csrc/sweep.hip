@@ -28,9 +28,11 @@
 //   k_sw_hubs    vertices with long in-lists: a workgroup holds N+(y) as a
 //                byte table over the ranks and streams the N+(x)
 //   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
-//   k_sw_rest    all others: one wavefront and a small table in LDS
+//   k_sw_rest    all others: one wavefront and a hash table in LDS
+//   k_sw_small   graphs of up to 16,384 vertices instead of the last three: lists
+//                in ids, several rows a wavefront, a table field per id
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
-// A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_rest
+// A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_small
 // as one disjoint union with ids local to each graph, its counters by graph
 // (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 32.9 ms a launch; 256
 // graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.57 ms). The labelled
@@ -49,7 +51,7 @@ constexpr int OT = 2048;  // entries of one orientation tile
 constexpr int OTHREADS = 256, OPER = OT / OTHREADS, OWORDS = OT / 64;
 constexpr int LONG_KEEP = 256;  // rows with long N+ kept in LDS before they are listed
 constexpr int TILE_GRAPHS = 8;  // graphs of a batch whose sums a tile keeps in LDS
-constexpr int ROWS_THREADS = 1024, ROWS_PER = 16;
+constexpr int ROWS_THREADS = 1024;  // of the ranking kernels, 4 or 16 rows a thread
 constexpr int BUCKETS = 1024;          // degree buckets of the ranking
 constexpr int64_t DIRECT_N = 16384;    // graphs up to here index their tables by vertex id
 constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover
@@ -105,7 +107,14 @@ __device__ __forceinline__ uint32_t degree_bucket(uint32_t d) {
   return ((e - 4) << 5) | ((d >> (e - 5)) & 31u);
 }
 
-__global__ void k_sw_zero(uint32_t* __restrict__ p, int64_t m) {
+// The start of a stage by the device's 100 MHz clock: an event per stage took
+// 43 us of a 115 us call.
+__device__ __forceinline__ void stamp(uint64_t* clk, int i) {
+  if (clk && blockIdx.x == 0 && threadIdx.x == 0) clk[i] = __builtin_amdgcn_s_memrealtime();
+}
+
+__global__ void k_sw_zero(uint32_t* __restrict__ p, int64_t m, uint64_t* __restrict__ clk) {
+  stamp(clk, 0);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) p[i] = 0;
 }
@@ -138,13 +147,18 @@ struct Cross {
   uint32_t f, b, o, i, m, su, pad[2];
 };
 
-__global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
-  __shared__ uint32_t h[BUCKETS];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * (ROWS_THREADS * ROWS_PER);
-  for (int i = 0; i < ROWS_PER; ++i) {
-    const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
+// PER rows a thread; PER > 1: with the degree histogram (workgroups of BUCKETS
+// threads).
+template <int PER>
+__global__ void __launch_bounds__(PER > 1 ? ROWS_THREADS : 256) k_sw_rows(RowArgs a) {
+  __shared__ uint32_t h[PER > 1 ? BUCKETS : 1];
+  if (PER > 1) {
+    h[threadIdx.x] = 0;
+    __syncthreads();
+  }
+  const int64_t base = (int64_t)blockIdx.x * (blockDim.x * PER);
+  for (int i = 0; i < PER; ++i) {
+    const int64_t u = base + i * blockDim.x + threadIdx.x;
     if (u >= a.n) break;
     const int64_t b = a.off[u], e = a.off[u + 1];
     bool ok = true;
@@ -162,7 +176,7 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
       a.grow[u] = (uint32_t)lo;
     }
     if (a.deg) a.deg[u] = d;
-    if (a.hist) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
+    if (PER > 1) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
     if (d) {
       a.list[b] = (uint32_t)u;
       atomicOr(&a.mark[b >> 5], 1u << (b & 31));
@@ -177,13 +191,14 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rows(RowArgs a) {
       }
     }
   }
-  if (!a.hist) return;
+  if (PER == 1) return;
   __syncthreads();
   if (h[threadIdx.x]) atomicAdd(&a.hist[threadIdx.x], h[threadIdx.x]);
 }
 
 // Ranks by a counting sort on the degree bucket, highest first; the order
 // within a bucket is free (any total order lists each triangle once).
+template <int PER>
 __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rank(int64_t n, const int64_t* __restrict__ off,
                                                           const uint32_t* __restrict__ hist,
                                                           uint32_t* __restrict__ cursor, uint32_t* __restrict__ rank,
@@ -204,9 +219,9 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rank(int64_t n, const int64
   uint32_t add = 0;
   for (int i = 0; i < w; ++i) add += wsum[i];
   start[threadIdx.x] = x - v + add;
-  const int64_t base = (int64_t)blockIdx.x * (ROWS_THREADS * ROWS_PER);
-  uint32_t bk[ROWS_PER];
-  for (int i = 0; i < ROWS_PER; ++i) {
+  const int64_t base = (int64_t)blockIdx.x * (ROWS_THREADS * PER);
+  uint32_t bk[PER];
+  for (int i = 0; i < PER; ++i) {
     const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
     bk[i] = BUCKETS;
     if (u < n) {
@@ -217,7 +232,7 @@ __global__ void __launch_bounds__(ROWS_THREADS) k_sw_rank(int64_t n, const int64
   __syncthreads();
   if (cnt[threadIdx.x]) start[threadIdx.x] += atomicAdd(&cursor[threadIdx.x], cnt[threadIdx.x]);
   __syncthreads();
-  for (int i = 0; i < ROWS_PER; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int64_t u = base + i * ROWS_THREADS + threadIdx.x;
     if (u < n) {
       rank[u] = atomicAdd(&start[bk[i]], 1u);
@@ -295,6 +310,7 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
   __shared__ uint32_t hpre[OWORDS + 1];  // segments, N+ entries before each 64-entry word
   __shared__ uint32_t pre[OWORDS + 1];
   __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last segment): where their entries go
+  __shared__ int32_t edge[OWORDS + 1];   // the entry before each 64-entry word
   __shared__ int64_t ends[4];            // the first and the last segment's row: its entry range
   __shared__ uint32_t longs[2][LONG_KEEP], nlong[2], lbase[2];  // rows with long N+, over several tiles
   __shared__ unsigned long long gsum[BAT ? TILE_GRAPHS : 1][9];  // sums of the block, BAT: of the tile's first graphs
@@ -330,7 +346,12 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       y[i] = p < len ? nb[p] : 0;
       wd[i] = p < len ? (uint32_t)(a.flg[(t0 + p) >> 2] >> (2 * (p & 3))) & 3u : 0u;
     }
+    const int32_t left = tid == 0 && t > 0 ? nb[-1] : 0;
     __syncthreads();  // the tile before is done with LDS
+#pragma unroll
+    for (int i = 0; i < OPER; ++i)
+      if (lane == 63) edge[i * (OTHREADS / 64) + w + 1] = y[i];
+    if (tid == 0) edge[0] = left;
     if (w == 0) {
       uint64_t h = lane < OWORDS ? ((const uint64_t*)a.mark)[t * OWORDS + lane] | (lane == 0 ? 1ull : 0ull) : 0ull;
       const uint32_t c = (uint32_t)__popcll(h);
@@ -402,7 +423,7 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       const bool in = p < len;
       const int32_t x = (int32_t)srow[sg[i]];
       int32_t pv = __shfl_up(y[i], 1, 64);
-      if (lane == 0 && in && t0 + p > 0) pv = nb[p - 1];
+      if (lane == 0) pv = edge[wi];
       // (the tile's first entry carries a start bit of its own: look at the row)
       const bool first = p == 0 ? ends[0] == t0 : (heads[wi] >> lane) & 1ull;
       if (in) {
@@ -864,7 +885,8 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
                                                      const uint32_t* __restrict__ count,
                                                      const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
                                                      const uint32_t* __restrict__ err,
-                                                      int rot) {
+                                                      int rot, uint64_t* __restrict__ clk) {
+  stamp(clk, 1);
   if (err[0] | err[1]) return;
   const int lane = threadIdx.x & 63;
   const uint32_t nw = gridDim.x * 4, cnt = *count;
@@ -1122,7 +1144,7 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
 // are in flight while the other is counted (loads are never skipped, an idle
 // lane rereads the list's first words: the wait for a set is then for its own
 // loads only). A list in rank order ends with the step that reaches y's rank.
-template <int GL, bool SORTED, bool TOP, bool WIDE, class T, class Probe>
+template <int GL, bool SORTED, bool TOP, bool WIDE, bool MULTI, class T, class Probe>
 __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const XList<WIDE>& L, int cnt,
                                        uint32_t yrank, int lane, T& tri, Probe probe) {
   constexpr uint64_t G0 = GL == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;  // first lane of each group
@@ -1132,7 +1154,8 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
   struct Slot {
     typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // the lane's next entries
     int left;      // entries of the list from there on (0 or less: none)
-    uint32_t g8, lim;
+    uint32_t g8;
+    uint32_t lim;  // SORTED: the rank that ends the list; MULTI: the list's table
     uint32_t w[4];
   } sl[2];
   auto load = [&](Slot& s) {
@@ -1150,7 +1173,8 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
       s.left = (int)(m & LEN_MASK) - l4;
       s.g8 = (m >> 30) * 0x55u | (T::LAB ? (m >> 29 & 1u) * 0xAA00u : 0u);
       // (lists of up to SORT_MIN entries are not sorted)
-      s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : yrank;
+      if (MULTI) s.lim = m >> 24 & 15u;
+      else s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : yrank;
     }
   };
 #pragma unroll
@@ -1163,7 +1187,7 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
   int next = 2 * SETS;
   auto step = [&](Slot& s) {
     uint32_t y[4];
-    probe(s.w, y);
+    probe(s.w, y, s.lim);
     tri.template add4<TOP>(s.w, y, s.left, s.g8);
     // lists that end here: their first lane has at most one step left, or the
     // last entry read has reached y
@@ -1196,6 +1220,7 @@ struct CountArgs {
   const uint32_t* rank;
   const uint32_t* tile_row;
   uint64_t* items[2];  // of k_sw_hubs, k_sw_mids: y << 32 | chunk
+  uint64_t* clk;       // stage starts, or NULL
   uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken
   int64_t range;       // k_sw_rest: entries of one wavefront
   unsigned long long* acc;
@@ -1261,6 +1286,7 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
   __shared__ __align__(16) uint8_t tab[HUB_RANKS + 16];  // f_yz by rank of z; past the ranks: 0
   __shared__ XList<WIDE> xl[HUB_THREADS / 64];
   __shared__ uint32_t item, next;
+  stamp(a.clk, 2);
   if (a.err[0] | a.err[1]) return;
   const int tid = threadIdx.x, lane = tid & 63;
   for (int i = tid; i < (int)sizeof(tab) / 4; i += HUB_THREADS) ((uint32_t*)tab)[i] = 0;
@@ -1295,7 +1321,7 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
       if (k >= cnt) break;
       const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
       wave_sync();
-      stream<16, true, false, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4]) {
+      stream<16, true, false, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4], uint32_t) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & IDM<LAB>, (uint32_t)HUB_RANKS)];
       });
@@ -1351,7 +1377,7 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
         if (k >= cnt) break;
         const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
         wave_sync();
-        stream<16, true, true, WIDE>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4]) {
+        stream<16, true, true, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4], uint32_t) {
           uint32_t top = 0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -1379,40 +1405,47 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
   tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
-// The other vertices: a wavefront takes a range of entries and the rows whose
-// in-lists lie in it, one row at a time. BITS: the ids are below DIRECT_N and
-// index a two-bit table of N+(y); else a hash table, filled TAB_MAX entries at
-// a time. RANK: lists in ranks, and only the rows that the kernels above leave;
-// else all rows. BAT: a batch, counted by graph.
-template <bool BITS, bool RANK, bool BAT, bool LAB, bool WIDE>
-__global__ void __launch_bounds__(REST_WAVES * 64, BITS && !LAB ? 5 : 4) k_sw_rest(CountArgs a) {
-  constexpr int TW = BITS ? (int)(DIRECT_N >> FB<LAB>) : TAB_WORDS;
-  __shared__ uint32_t tabs[REST_WAVES][TW];
+// The row that holds entry j, by a 64-way search between tile starts.
+__device__ __forceinline__ int64_t row_of(const CountArgs& a, int64_t j, int lane) {
+  const int64_t t = j / OT;
+  int64_t r = a.tile_row[t];
+  int64_t span = (t + 1 < a.ntiles ? (int64_t)a.tile_row[t + 1] : a.n - 1) - r + 1;
+  while (span > 1) {
+    const int64_t step = (span + 63) / 64;
+    const bool le = lane * step < span && a.off[r + lane * step] <= j;
+    const int k = __popcll(__ballot(le)) - 1;
+    r += k * step;
+    span = min(step, span - k * step);
+  }
+  return r;
+}
+
+// Workgroups are dealt to the 8 XCDs in turn; this numbering gives each XCD
+// consecutive ones, whose ranges share lists in its L2.
+__device__ __forceinline__ uint32_t xcd_block() {
+  const uint32_t g = gridDim.x, q = g / 8, r = g % 8, x = blockIdx.x % 8;
+  return x * q + min(x, r) + blockIdx.x / 8;
+}
+
+// The other vertices of a ranked graph (RANK), and all vertices of a batch with
+// members above DIRECT_N: a wavefront takes a range of entries and the rows
+// whose in-lists lie in it, one row at a time, with a hash table of N+(y) filled
+// TAB_MAX entries at a time. BAT: a batch, counted by graph.
+template <bool RANK, bool BAT, bool LAB, bool WIDE>
+__global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
+  __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
   __shared__ XList<WIDE> xl[REST_WAVES];
   if (a.err[0] | a.err[1]) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   XList<WIDE>& L = xl[w];
-  for (int i = lane; i < TW; i += 64) tab[i] = BITS ? 0u : SLOT_FREE;
+  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   uint32_t graph = 0;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t j0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
+  for (int64_t j0 = ((int64_t)xcd_block() * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
     const int64_t j1 = min(j0 + a.range, a.nnz);
-    // the row that holds entry j0, by a 64-way search between tile starts
-    const int64_t t = j0 / OT;
-    int64_t r = a.tile_row[t];
-    {
-      int64_t span = (t + 1 < a.ntiles ? (int64_t)a.tile_row[t + 1] : a.n - 1) - r + 1;
-      while (span > 1) {
-        const int64_t step = (span + 63) / 64;
-        const bool le = lane * step < span && a.off[r + lane * step] <= j0;
-        const int k = __popcll(__ballot(le)) - 1;
-        r += k * step;
-        span = min(step, span - k * step);
-      }
-    }
-    for (;; r += 64) {
+    for (int64_t r = row_of(a, j0, lane);; r += 64) {
       int64_t lo = 0, hi = 0, e = a.nnz;
       uint64_t in = 0;
       uint32_t yr = 0;
@@ -1446,28 +1479,21 @@ __global__ void __launch_bounds__(REST_WAVES * 64, BITS && !LAB ? 5 : 4) k_sw_re
           info += a.vbase[graph];
         }
         for (uint32_t f = 0; f < plus; f += TAB_MAX) {
-          const uint32_t fe = BITS ? plus : min(f + TAB_MAX, plus);
-          for (uint32_t i = f + lane; i < fe; i += 64) {
-            const uint32_t z = a.list[f0 + i];
-            if (BITS) set_bits<LAB>(tab, z); else set_hash(tab, z);
-          }
+          const uint32_t fe = min(f + TAB_MAX, plus);
+          for (uint32_t i = f + lane; i < fe; i += 64) set_hash(tab, a.list[f0 + i]);
           wave_sync();
           for (int64_t k = l0; k < l1; k += 64) {
             const int nx = list_x<LAB, WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), info, lane);
             wave_sync();
-            stream<8, RANK, true, WIDE>(a.list, L, nx, rk, lane, tri, [&](const uint32_t (&q)[4], uint32_t (&g)[4]) {
+            stream<8, RANK, true, WIDE, false>(a.list, L, nx, rk, lane, tri,
+                                               [&](const uint32_t (&q)[4], uint32_t (&g)[4], uint32_t) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i) g[i] = BITS ? probe_bits<TW, LAB>(tab, q[i]) : probe_hash<LAB>(tab, q[i]);
+              for (int i = 0; i < 4; ++i) g[i] = probe_hash<LAB>(tab, q[i]);
             });
             wave_sync();
           }
-          if (BITS) {
-            for (uint32_t i = lane; i < plus; i += 64) tab[(a.list[f0 + i] & IDM<LAB>) >> FB<LAB>] = 0;
-          } else {
-            for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
-          }
+          for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
           wave_sync();
-          if (BITS) break;
         }
       }
       if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
@@ -1475,6 +1501,129 @@ __global__ void __launch_bounds__(REST_WAVES * 64, BITS && !LAB ? 5 : 4) k_sw_re
   }
   if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
   else tri.flush(copy_of<LAB>(a.acc), lane);
+}
+
+// Graphs and batch members of up to N vertices, lists in ids: a wavefront takes
+// a range of entries and R rows at a time, 64 / R lanes each filling that row's
+// table of N+(y) (a field per id), then the R in-lists as one list whose x carry
+// their row's table: short rows fill the steps of one stream together, and
+// their dependent reads overlap. (One row at a time: 17.3 ms on the 4,096-graph
+// batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10.
+// Bound by vector issue on the large batch, by the reads' latency on small ones.)
+template <int N, int R, bool BAT, bool LAB, bool WIDE>
+__global__ void __launch_bounds__(REST_WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_small(CountArgs a) {
+  constexpr int TW = N >> FB<LAB>, LR = 64 / R;  // words of one table, lanes of one row
+  __shared__ uint32_t tabs[REST_WAVES][R * TW];
+  __shared__ XList<WIDE> xl[REST_WAVES];
+  stamp(a.clk, 1);
+  stamp(a.clk, 2);
+  if (a.err[0] | a.err[1]) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t* tab = tabs[w];
+  uint32_t* mine = tab + lane / LR * TW;
+  XList<WIDE>& L = xl[w];
+  for (int i = lane; i < R * TW; i += 64) tab[i] = 0;
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
+  uint32_t graph = 0;
+  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+  for (int64_t j0 = ((int64_t)xcd_block() * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
+    const int64_t j1 = min(j0 + a.range, a.nnz);
+    for (int64_t r = row_of(a, j0, lane);; r += 64) {
+      // 64 rows, one a lane: N+ and the part of the in-list in the range
+      int64_t lo = 0, e = a.nnz;
+      uint64_t in = 0;
+      uint32_t num = 0, gr = 0;
+      if (r + lane < a.n) {
+        in = a.info[r + lane];
+        e = a.off[r + lane + 1];
+        const uint32_t plus = (uint32_t)in & LEN_MASK;
+        lo = max((int64_t)(in >> 24) + plus, j0);
+        const int64_t hi = min(e, j1);
+        if (plus && hi > lo) {
+          num = (uint32_t)(hi - lo);
+          if (BAT) gr = a.grow[r + lane];
+        }
+      }
+      uint64_t todo = __ballot(num > 0);
+      while (todo) {
+        const uint64_t* info = a.info;
+        if (BAT) {
+          const uint32_t g = rl(gr, __builtin_ctzll(todo));
+          if (g != graph) {
+            tri.flush(a.gacc + (uint64_t)graph * 16, lane);
+            graph = g;
+          }
+          info += a.vbase[graph];
+        }
+        // the next R rows (of one graph): lanes LR q .. take the q-th
+        int src = -1;
+        uint32_t end[R];  // in-list entries of rows 0 .. q
+        uint64_t at[R];   // list position of row q's in-list, less the entries before
+        uint32_t total = 0;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          at[q] = 0;
+          if (todo && (!BAT || q == 0 || rl(gr, __builtin_ctzll(todo)) == graph)) {
+            const int s = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            if (lane / LR == q) src = s;
+            at[q] = rl64((uint64_t)lo, s) - total;
+            total += rl(num, s);
+          }
+          end[q] = total;
+        }
+        const uint64_t yi = __shfl(in, max(src, 0), 64);
+        const uint32_t plus = src < 0 ? 0u : (uint32_t)yi & LEN_MASK;
+        const uint32_t* mylist = a.list + (yi >> 24);
+        for (uint32_t i = lane % LR; i < plus; i += LR) set_bits<LAB>(mine, mylist[i]);
+        wave_sync();
+        for (uint32_t k = 0; k < total; k += 64) {
+          const uint32_t p = k + lane;
+          uint32_t q = 0, g = 0;
+          uint64_t xi = 0, from = at[0];
+#pragma unroll
+          for (int i = 1; i < R; ++i)
+            if (p >= end[i - 1]) {
+              q = i;
+              from = at[i];
+            }
+          if (p < total) {
+            g = a.list[from + p];
+            xi = info[g & IDM<LAB>];
+          }
+          const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
+          const uint64_t m = __ballot(has);
+          if (has) {
+            const int i = __popcll(m & below(lane));
+            L.p[i] = xi >> 24;
+            L.m[i] = (g & ~IDM<LAB>) | q << 24 | ((uint32_t)xi & LEN_MASK);
+          }
+          wave_sync();
+          stream<8, false, true, WIDE, true>(a.list, L, __popcll(m), 0, lane, tri,
+                                             [&](const uint32_t (&q)[4], uint32_t (&f)[4], uint32_t t) {
+            const uint32_t* mt = tab + t * TW;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[i] = probe_bits<TW, LAB>(mt, q[i]);
+          });
+          wave_sync();
+        }
+        for (uint32_t i = lane % LR; i < plus; i += LR) mine[(mylist[i] & IDM<LAB>) >> FB<LAB>] = 0;
+        wave_sync();
+      }
+      if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
+    }
+  }
+  if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
+  else tri.flush(copy_of<LAB>(a.acc), lane);
+}
+
+// k_sw_small by the largest member: tables of 8 KB a wavefront in all (labelled
+// 16 KB), so that four workgroups fit a CU's LDS.
+template <bool BAT, bool LAB, bool WIDE>
+void launch_small(int64_t nmax, unsigned grid, int waves, const CountArgs& ca, hipStream_t s) {
+  if (nmax <= 4096) k_sw_small<4096, 4, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
+  else if (nmax <= 8192) k_sw_small<8192, 4, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
+  else k_sw_small<DIRECT_N, 2, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
 }
 
 // ------------------------------------------------------------------- results
@@ -1497,6 +1646,7 @@ __device__ __forceinline__ void open_wedges(uint64_t* c) {
 __global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t* __restrict__ err, int64_t nnz,
                             uint64_t n, uint64_t clo, uint64_t chi, uint64_t* __restrict__ out,
                             uint64_t* __restrict__ status) {
+  stamp(status + SW_CLK, 3);
   __shared__ uint64_t sum[SW_WORDS];
   if (threadIdx.x < SW_WORDS) {
     uint64_t t = 0;
@@ -1520,6 +1670,7 @@ __global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t
   }
   status[0] = out[0] = clo - s;
   status[16] = out[16] = chi - (clo < s ? 1u : 0u);
+  stamp(status + SW_CLK, 4);
 }
 
 // Labelled: a triangle a < b < c takes its three pairs of neighbours out of the
@@ -1528,6 +1679,7 @@ __global__ void k_sw_finish(const unsigned long long* __restrict__ acc, uint32_t
 __global__ void k_sw_finish_lab(const unsigned long long* __restrict__ acc, uint32_t* __restrict__ err, int64_t nnz,
                                 uint64_t clo, uint64_t chi, uint64_t* __restrict__ out,
                                 uint64_t* __restrict__ status) {
+  stamp(status + SW_CLK, 3);
   __shared__ uint64_t c[SW_LAB_WORDS];
   for (int i = threadIdx.x; i < SW_LAB_WORDS; i += blockDim.x) {
     uint64_t t = 0;
@@ -1558,6 +1710,7 @@ __global__ void k_sw_finish_lab(const unsigned long long* __restrict__ acc, uint
   }
   status[0] = out[0] = clo - s;
   status[64] = out[64] = chi - (clo < s ? 1u : 0u);
+  stamp(status + SW_CLK, 4);
 }
 
 // Per graph: the classes from its sums; 003 = C(n_g, 3) less the rest (n_g <
@@ -1631,10 +1784,8 @@ unsigned grid_of_work(int64_t work, int per, int64_t cap) {
 }  // namespace
 
 int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long long** acc_out, uint32_t** err_out, Scratch& scratch,
-                 hipEvent_t* ev, hipStream_t s) {
-  auto rec = [&](int i) {
-    if (ev) (void)hipEventRecord(ev[i], s);
-  };
+                 uint64_t* status, hipStream_t s) {
+  uint64_t* clk = status + SW_CLK;
   const int64_t n = in.n, nnz = in.nnz;
   DeviceInfo di;
   if (int st = device_info(&di)) return st;
@@ -1657,11 +1808,8 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   uint32_t* err = zero + w_err;
   *acc_out = acc;
   *err_out = err;
-  k_sw_zero<<<grid_of_work(words, 1024, 2048), 256, 0, s>>>(zero, words);
-  if (n == 0 || nnz == 0) {
-    for (int i = 1; i <= 3; ++i) rec(i);
-    if (n == 0) return TRIAD_OK;
-  }
+  k_sw_zero<<<grid_of_work(words, 1024, 2048), 256, 0, s>>>(zero, words, clk);
+  if (n == 0) return TRIAD_OK;
   uint32_t *key = nullptr, *list = nullptr, *tile_row = nullptr, *mid = nullptr, *lng = nullptr;
   uint64_t *info = nullptr, *hub_items = nullptr, *mid_items = nullptr;
   SegCounts* segs = nullptr;
@@ -1680,23 +1828,31 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
                    tile_row, err, 0, nullptr, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
-  const unsigned rgrid = grid_of_work(n, ROWS_THREADS * ROWS_PER, INT32_MAX);
-  k_sw_rows<<<rgrid, ROWS_THREADS, 0, s>>>(ra);
+  // (16 rows a thread: fewer atomics on the bucket counters; 4 while that
+  // leaves fewer workgroups than four a CU)
+  const bool many = n > (int64_t)di.cus * 4 * ROWS_THREADS * 16;
+  const unsigned rgrid = grid_of_work(n, ROWS_THREADS * (many ? 16 : 4), INT32_MAX);
+  if (!rank) k_sw_rows<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ra);
+  else if (many) k_sw_rows<16><<<rgrid, ROWS_THREADS, 0, s>>>(ra);
+  else k_sw_rows<4><<<rgrid, ROWS_THREADS, 0, s>>>(ra);
   if (nnz == 0) return TRIAD_OK;
-  if (rank)
-    k_sw_rank<<<rgrid, ROWS_THREADS, 0, s>>>(n, in.off, zero + w_hist, zero + w_hist + BUCKETS, key, err);
+  if (rank) {
+    uint32_t* hist = zero + w_hist;
+    if (many) k_sw_rank<16><<<rgrid, ROWS_THREADS, 0, s>>>(n, in.off, hist, hist + BUCKETS, key, err);
+    else k_sw_rank<4><<<rgrid, ROWS_THREADS, 0, s>>>(n, in.off, hist, hist + BUCKETS, key, err);
+  }
   if (validate)
     k_sw_symmetry<<<grid_of_work(n, 4, 65536), 256, 0, s>>>(n, nnz, in.off, in.nbr, in.flg, err);
   const OrientArgs oa{n,        nnz,  ntiles, in.off, in.nbr, in.flg, key, zero + w_mark, tile_row, list, info,
                       (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err, nullptr, nullptr, nullptr};
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
-  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, zero + w_cnt, 0, acc, err,
+  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, clk, zero + w_cnt, 0, acc, err,
                nullptr, nullptr, nullptr};
   // a wavefront's range: small graphs spread over the chip, large ones in
   // ranges that spread the row search over more entries
-  const int64_t waves = (int64_t)di.cus * 32;
-  ca.range = std::max<int64_t>(64, std::min<int64_t>(1024, (nnz / waves + 63) & ~(int64_t)63));
+  const int64_t waves = (int64_t)di.cus * (rank ? 32 : 16);
+  ca.range = std::max<int64_t>(64, std::min<int64_t>(rank ? 1024 : 512, (nnz / waves + 63) & ~(int64_t)63));
   const unsigned wgrid = grid_of_work((nnz + ca.range - 1) / ca.range, REST_WAVES, (int64_t)di.cus * 8);
   if (labelled) {
     const LabArgs la{n, nnz, ntiles, in.off, in.nbr, in.flg, zero + w_mark, tile_row, list, (Cross*)(zero + w_cross),
@@ -1709,29 +1865,24 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     if (rank) {
       k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
-      rec(1);
-      k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err, LAB ? 3 : 2);
+      k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err, LAB ? 3 : 2, clk);
       k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err, LAB ? 3 : 2);
       k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
-      rec(2);
       auto count = [&](auto wide) {
         constexpr bool W = decltype(wide)::value;
         k_sw_hubs<LAB, W><<<(unsigned)(di.cus * 2), hub_threads(LAB), 0, s>>>(ca);
         k_sw_mids<LAB, W><<<(unsigned)(di.cus * (LAB ? 4 : 6)), MID_THREADS, 0, s>>>(ca);
-        k_sw_rest<false, true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+        k_sw_rest<true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
       };
       if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
     } else {
       // (n <= DIRECT_N: fewer than 2^28 entries)
       k_sw_orient<false, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<false, false, LAB><<<cgrid, 256, 0, s>>>(oa);
-      rec(1);
-      rec(2);
-      k_sw_rest<true, false, false, LAB, false><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
+      launch_small<false, LAB, false>(n, wgrid, REST_WAVES, ca, s);
     }
   };
   if (labelled) run(std::true_type{}); else run(std::false_type{});
-  rec(3);
   HIPCHK(hipGetLastError());
   return TRIAD_OK;
 }
@@ -1785,11 +1936,11 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   unsigned long long* gacc = (unsigned long long*)(zero + z.w_gacc);
   uint32_t* err = zero + z.w_err;
   *err_out = err + 3;
-  k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words);
+  k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words, nullptr);
   if (nv > 0) {
     const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow,
                      nullptr, nullptr};
-    k_sw_rows<<<grid_of_work(nv, ROWS_THREADS * ROWS_PER, INT32_MAX), ROWS_THREADS, 0, s>>>(ra);
+    k_sw_rows<1><<<grid_of_work(nv, 256, INT32_MAX), 256, 0, s>>>(ra);
   }
   if (nv > 0 && nnz > 0) {
     DeviceInfo di;
@@ -1798,18 +1949,18 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
                         (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
     k_sw_orient<false, true, false><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
     k_sw_cross<false, true, false><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
-    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, zero + z.w_cnt, range, acc,
+    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, nullptr, zero + z.w_cnt, range, acc,
                  err, vbase, grow, gacc};
+    // (by default 512 entries a turn, fewer where that leaves wavefronts idle)
+    if (range <= 0) range = std::max<int64_t>(64, std::min<int64_t>(512, (nnz / (di.cus * 16) + 63) & ~(int64_t)63));
+    ca.range = range;
     const unsigned grid = grid_of_work((nnz + range - 1) / range, waves, groups);
-    auto count = [&](auto bits, auto wide) {
-      k_sw_rest<decltype(bits)::value, false, true, false, decltype(wide)::value><<<grid, waves * 64, 0, s>>>(ca);
+    auto count = [&](auto wide) {
+      constexpr bool W = decltype(wide)::value;
+      if (nmax <= DIRECT_N) launch_small<true, false, W>(nmax, grid, waves, ca, s);
+      else k_sw_rest<false, true, false, W><<<grid, waves * 64, 0, s>>>(ca);
     };
-    const bool wide = nnz + LIST_PAD >= ((int64_t)1 << 30);
-    if (nmax <= DIRECT_N) {
-      if (wide) count(std::true_type{}, std::true_type{}); else count(std::true_type{}, std::false_type{});
-    } else {
-      if (wide) count(std::false_type{}, std::true_type{}); else count(std::false_type{}, std::false_type{});
-    }
+    if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
   }
   k_sw_finish_batch<<<grid_of_work(graphs, 256, INT32_MAX), 256, 0, s>>>(graphs, nnz, vbase, gacc, acc, err, d_out);
   return TRIAD_OK;
