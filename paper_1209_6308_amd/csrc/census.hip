@@ -1217,7 +1217,7 @@ static int grid_for(int64_t work, int threads, int cap = 65536) {
   return (int)g;
 }
 
-static int scan_excl(const int64_t* in, int64_t m, int64_t* out, Scratch& scratch, hipStream_t s) {
+int scan_i64(const int64_t* in, int64_t m, int64_t* out, Scratch& scratch, hipStream_t s) {
   const int64_t nb = (m + SCAN_B - 1) / SCAN_B;
   int64_t* bsum = nullptr;
   ALLOC(bsum, nb + 1);
@@ -1512,7 +1512,7 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
   uint64_t* hub_task = nullptr;
   int64_t *hub_nch = nullptr, *hub_pre = nullptr;
   if (n > 0) {
-    if (int st = scan_excl(ntask, n, tpre, scratch, s)) return st;
+    if (int st = scan_i64(ntask, n, tpre, scratch, s)) return st;
     HIPCHK(hipMemcpyAsync(&ntasks, tpre + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(&errh, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -1546,7 +1546,7 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
       ALLOC(itmp, ntasks);
       ALLOC(lpre, n + 1);
       k_lower_counts<<<grid_for(n, 256), 256, 0, s>>>(n, ustart, ntask);
-      if (int st = scan_excl(ntask, n, lpre, scratch, s)) return st;
+      if (int st = scan_i64(ntask, n, lpre, scratch, s)) return st;
     }
     const EmitArgs e{n, off, packed, ustart, tpre, tasks, tskip, by_sort ? 0 : 1, hub_thr, err, items, lpre};
     launch_emit_entries(e, nnz, s);
@@ -1575,7 +1575,7 @@ int census_device(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
       HIPCHK(hipStreamSynchronize(s));
       nhub = (int64_t)hc;
       if (nhub > 0) {
-        if (int st = scan_excl(hub_nch, nhub, hub_pre, scratch, s)) return st;
+        if (int st = scan_i64(hub_nch, nhub, hub_pre, scratch, s)) return st;
       }
     }
   }

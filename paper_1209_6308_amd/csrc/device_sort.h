@@ -20,6 +20,9 @@ int radix_sort_u64(uint64_t** keys, uint64_t** tmp, int64_t N, int lo, int hi, S
 // total goes to *total (device) when total is not NULL.
 int scan_u32(const uint32_t* in, int64_t m, uint32_t* out, uint32_t* total, Scratch& scratch, hipStream_t s);
 
+// out[0..m] = exclusive prefix of m 64-bit values (out[m] = the total).
+int scan_i64(const int64_t* in, int64_t m, int64_t* out, Scratch& scratch, hipStream_t s);
+
 // Grid size for `work` items at `threads` per block, between 1 and cap.
 int grid_of(int64_t work, int threads, int cap);
 

@@ -11,8 +11,7 @@ namespace triad {
 
 // Device counters of one sweep (64-bit words, zeroed by sweep_begin):
 // acc[0..15] the 16 classes as signed sums (triangle classes exact, the open
-// and dyadic classes before the triangles' share is taken out), then
-constexpr int SW_MUT = 16;    // entries with both arcs (each mutual edge twice)
+// and dyadic classes before the triangles' share is taken out; see sums.h), then
 constexpr int SW_ABOVE = 17;  // entries above their row's own id
 constexpr int SW_WORDS = 32;
 constexpr int SW_COPIES = 64;

@@ -1,49 +1,53 @@
 // Incremental census of a graph that changes by arc insertions and deletions:
 // the census of the graph after a batch of updates, from the census before it
-// and a merge of the neighbour lists of each changed pair only (the census at
-// fixed time intervals of Sec. 3, Figs. 3-4, without a full sweep per
-// interval).
+// and the changed pairs only (the census at fixed time intervals of Sec. 3,
+// Figs. 3-4, without a full sweep per interval).
 //
 // A batch is a sequence of arc operations applied in order (insert x->y, or
-// delete it). Only its net effect on each unordered pair {a, b}, a < b,
-// matters: the pair's flag f (bit0 = a->b, bit1 = b->a, as in row a of the
-// CSR) goes from f0 to f1, each bit being set by the last operation on its arc
-// (or kept). Only triads that contain a changed pair change class, and
-//     census(after) - census(before)
-//       = sum over changed pairs {a, b}, over third vertices w, of
-//         [class after] - [class before] of the triad {a, b, w},
-// each triad counted by the smallest of its changed pairs (pair order
-// a << RB | b). For one changed pair the third vertices are
-//   - w in N(a) or N(b), before or after: the triad's code is read from the
-//     two rows (and the changed pairs of a and b), before and after;
-//   - every other w (n - 2 - |that union| of them): only the pair {a, b} has
-//     arcs, so the triad moves from the dyadic class of f0 to that of f1
-//     (Fig. 5 steps 2.1.2-2.1.3 for a single edge).
+// delete it). Only its net effect on each unordered pair {a, b} matters: the
+// pair's flag goes from f0 to f1, each bit being set by the last operation on
+// its arc (or kept). The census is a sum of row terms and triangles (see
+// sweep.hip), so its change is
+//   - for every row with a changed entry, the row's sums after less before, from
+//     its counts of out-, in- and mutual neighbours (a pass over its 2-bit flags),
+//   - for every changed pair {a, b}, a < b, the triangles {a, b, w} after less
+//     before, each counted by the smallest of its changed pairs (pair order a <<
+//     RB | b). The w adjacent to both a and b before come from the shorter of the
+//     two rows searched in the longer; the others are among the changes of a or
+//     b. (Merging both rows of every changed pair took 6.5 of 8.2 ms per 100,000
+//     updates on 112 M entries, R-MAT; row sums, pairs and parts now 1.3 ms. Bound
+//     by the latency of the searches' dependent reads.)
 // The classes come from the 64-state table of the census (Fig. 5 step
 // 2.1.4.1). The null count stays C(n,3) minus the rest.
 //
-//   k_upd_keys      one key per operation: pair, arc direction, kind
-//   radix sort      by (pair, direction), stable: operations keep their order
-//   k_run_heads     first operation of each pair
-//   k_pair_state    f0 from the CSR, f1 from the last operation on each arc
-//   k_changed_keys  two entries per changed pair (one per row), sorted
-//   k_pair_chunks   merged positions of each changed pair cut into work items
-//   k_upd_delta     one wavefront per work item: the class changes
-//   k_row_marks, k_new_offsets, k_copy_old, k_insert_new, k_pack_bytes
-//                   the CSR after the batch
+//   k_upd_small     up to UPD_SMALL operations: the next four in one workgroup
+//   k_upd_keys      two keys per operation (one a row): row, column, direction, kind
+//   radix sort      by (row, column, direction), stable: operations keep their order
+//   k_upd_state     f0 from the CSR, f1 from the last operation on each arc
+//   k_upd_emit      the changed entries E in order, their places in the old rows
+//   k_upd_rows      changed rows: their sums
+//   k_upd_pairs     changed pairs: their triangles
+//   k_new_offsets, k_upd_copy   the CSR after the batch
+// Nothing waits for the host until the end: counts stay on the device and grids
+// are sized for their bounds.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
 #include <string>
 
 #include "device_sort.h"
-#include "tile_rows.h"
+#include "sums.h"
 #include "triad_internal.h"
 
 namespace triad {
 namespace {
 
 constexpr int UT = 256;
+constexpr int UPD_SMALL = 2048;      // operations that one workgroup sorts in LDS
+constexpr int SMALL_T = 1024;
+constexpr int64_t UPD_PART = 1024;   // entries of the shorter row that one wavefront searches
+constexpr int64_t UPD_PARTS = 64;    // parts of one pair at most
+constexpr int64_t UPD_QUEUE = 1 << 18;  // parts put off to k_upd_parts
 
 __device__ __forceinline__ uint32_t mirror2(uint32_t f) { return ((f & 1u) << 1) | (f >> 1); }
 __device__ __forceinline__ uint32_t entry_flag(const uint8_t* flg, int64_t j) {
@@ -68,114 +72,287 @@ __device__ __forceinline__ int64_t lower_key(const uint64_t* keys, int64_t b, in
   return b;
 }
 
-// Operation key: (a << rb | b) << 2 | dir << 1 | insert, a < b the pair, dir =
-// 1 for the arc b -> a.
-__global__ void k_upd_keys(int64_t n, int64_t k, int rb, const int32_t* __restrict__ src,
-                           const int32_t* __restrict__ dst, const uint8_t* __restrict__ ins,
-                           uint64_t* __restrict__ keys, uint32_t* __restrict__ err) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  uint32_t bits = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride) {
-    const int32_t s = src[i], d = dst[i];
-    const uint32_t op = ins[i];
-    if (s < 0 || d < 0 || s >= n || d >= n || op > 1u) {
-      bits |= ERR_RANGE;
-      keys[i] = 0;
-      continue;
-    }
-    if (s == d) bits |= ERR_SELFLOOP;
-    const uint64_t a = (uint64_t)min(s, d), b = (uint64_t)max(s, d);
-    keys[i] = (((a << rb) | b) << 2) | ((uint64_t)(s > d) << 1) | op;
-  }
-  if (bits) atomicOr(err, bits);
-}
-
-__global__ void k_run_heads(const uint64_t* __restrict__ keys, int64_t k, int shift, uint32_t* __restrict__ head) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride)
-    head[i] = (i == 0 || (keys[i] >> shift) != (keys[i - 1] >> shift)) ? 1u : 0u;
-}
-
-// Per pair (run of operations): f0 from row a of the CSR, f1 = f0 with each
-// arc's bit set by the last operation on that arc (runs are sorted by arc
-// direction, operations in batch order within it).
-__global__ void k_pair_state(const uint64_t* __restrict__ keys, int64_t k, int rb, const uint32_t* __restrict__ head,
-                             const uint32_t* __restrict__ hpos, const int64_t* __restrict__ off,
-                             const int32_t* __restrict__ nbr, const uint8_t* __restrict__ flg,
-                             uint64_t* __restrict__ pkey, uint8_t* __restrict__ pf, uint32_t* __restrict__ chg) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const uint64_t bmask = (1ull << rb) - 1;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride) {
-    if (!head[i]) continue;
-    const uint64_t pr = keys[i] >> 2;
-    const int64_t a = (int64_t)(pr >> rb);
-    const int32_t b = (int32_t)(pr & bmask);
-    const int64_t e = off[a + 1];
-    const int64_t j = lower_id(nbr, off[a], e, b);
-    const uint32_t f0 = (j < e && nbr[j] == b) ? entry_flag(flg, j) : 0u;
-    uint32_t f1 = f0;
-    for (int64_t q = i; q < k && (keys[q] >> 2) == pr; ++q) {
-      const uint32_t bit = 1u << ((keys[q] >> 1) & 1u);
-      f1 = (keys[q] & 1u) ? (f1 | bit) : (f1 & ~bit);
-    }
-    const uint32_t r = hpos[i];
-    pkey[r] = pr;
-    pf[r] = (uint8_t)(f0 | f1 << 2);
-    chg[r] = f0 != f1 ? 1u : 0u;
-  }
-}
-
-// Two entries per changed pair, one in each row: (row << rb | col) << 4 |
-// f0 << 2 | f1, flags seen from the row (mirrored in row b).
-__global__ void k_changed_keys(const uint64_t* __restrict__ pkey, const uint8_t* __restrict__ pf,
-                               const uint32_t* __restrict__ chg, const uint32_t* __restrict__ cpos, int64_t np,
-                               int rb, uint64_t* __restrict__ E) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const uint64_t bmask = (1ull << rb) - 1;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < np; r += stride) {
-    if (!chg[r]) continue;
-    const uint64_t a = pkey[r] >> rb, b = pkey[r] & bmask;
-    const uint32_t f0 = pf[r] & 3u, f1 = pf[r] >> 2;
-    const uint32_t c = cpos[r];
-    E[2 * (int64_t)c] = (((a << rb) | b) << 4) | (f0 << 2) | f1;
-    E[2 * (int64_t)c + 1] = (((b << rb) | a) << 4) | (mirror2(f0) << 2) | mirror2(f1);
-  }
-}
-
-struct DeltaArgs {
-  int64_t n;
+struct UpdGraph {
+  int64_t n, nnz;
   const int64_t* off;
   const int32_t* nbr;
   const uint8_t* flg;
-  int rb;
-  const uint64_t* E;  // sorted change entries
-  int64_t nE;
-  uint64_t lut[4];    // class of code c: nibble c & 15 of lut[c >> 4]
-  unsigned long long* delta;  // [16], two's complement
-  // work items: item it is chunk it - ipre[q] of the pair of entry q (ipre:
-  // exclusive prefix of the chunk counts, ipre[nE] = the item count)
-  const uint32_t* ipre;
+  int rb;  // ids below 2^rb
 };
 
-// Merged positions of N(a) and N(b) per work item: a longer pair is cut into
-// chunks of about UPD_CHUNK positions (at most maxch chunks, which keeps the
-// item count below 2^32) that different wavefronts walk, so that a pair on a
-// hub row does not hold one wavefront for the whole of its merge.
-constexpr int64_t UPD_CHUNK = 8192;
+// Words the kernels share (zeroed first).
+enum { U_ERR = 0, U_NE = 1, U_PARTS = 2, U_WORDS = 4 };
 
-// Chunk count of the pair of each change entry (0 for the entry in the upper
-// row: a pair is processed from its lower row).
-__global__ void k_pair_chunks(const uint64_t* __restrict__ E, int64_t nE, int rb, const int64_t* __restrict__ off,
-                              uint32_t maxch, uint32_t* __restrict__ nch) {
+// Operation i as two keys (row << rb | column) << 2 | direction << 1 | insert,
+// direction 0 for the arc row -> column.
+__device__ __forceinline__ uint32_t op_keys(const UpdGraph& g, int32_t s, int32_t d, uint32_t op, uint64_t* k0,
+                                            uint64_t* k1) {
+  *k0 = *k1 = ~0ull;
+  if (s < 0 || d < 0 || s >= g.n || d >= g.n || op > 1u) return ERR_RANGE;
+  *k0 = ((((uint64_t)s << g.rb) | (uint64_t)d) << 2) | op;
+  *k1 = ((((uint64_t)d << g.rb) | (uint64_t)s) << 2) | 2u | op;
+  return s == d ? (uint32_t)ERR_SELFLOOP : 0u;
+}
+
+__global__ void k_upd_keys(UpdGraph g, int64_t k, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                           const uint8_t* __restrict__ ins, uint64_t* __restrict__ keys, uint32_t* __restrict__ u) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const uint64_t cmask = (1ull << rb) - 1;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nE; q += stride) {
-    const uint64_t ent = E[q];
-    const int64_t a = (int64_t)(ent >> (4 + rb)), b = (int64_t)((ent >> 4) & cmask);
-    const int64_t D = (off[a + 1] - off[a]) + (off[b + 1] - off[b]);
-    nch[q] = b < a ? 0u : (uint32_t)min((int64_t)maxch, max((int64_t)1, (D + UPD_CHUNK - 1) / UPD_CHUNK));
+  uint32_t bits = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride)
+    bits |= op_keys(g, src[i], dst[i], ins[i], &keys[2 * i], &keys[2 * i + 1]);
+  if (bits) atomicOr(&u[U_ERR], bits);
+}
+
+// The entry of key's (row, column): where it stands (or would stand) in the old
+// row, and f0 << 2 | f1, f1 = f0 with each arc's bit set by the last operation
+// on it (the run's operations are sorted by direction, in order within it).
+// key(q) is the sorted key at q < N.
+template <class Key>
+__device__ __forceinline__ uint32_t entry_state(const UpdGraph& g, int64_t i, int64_t N, Key key, int64_t* pos) {
+  const uint64_t pr = key(i) >> 2;
+  const int64_t x = (int64_t)(pr >> g.rb);
+  const int32_t y = (int32_t)(pr & ((1ull << g.rb) - 1));
+  const int64_t e = g.off[x + 1], j = lower_id(g.nbr, g.off[x], e, y);
+  const uint32_t f0 = j < e && g.nbr[j] == y ? entry_flag(g.flg, j) : 0u;
+  uint32_t f1 = f0;
+  for (int64_t q = i; q < N && (key(q) >> 2) == pr; ++q) {
+    const uint64_t kq = key(q);
+    const uint32_t bit = 1u << ((kq >> 1) & 1u);
+    f1 = (kq & 1u) ? (f1 | bit) : (f1 & ~bit);
+  }
+  *pos = j;
+  return f0 << 2 | f1;
+}
+
+__global__ void k_upd_state(UpdGraph g, const uint64_t* __restrict__ keys, int64_t N, uint32_t* __restrict__ chg,
+                            uint8_t* __restrict__ st, uint32_t* __restrict__ pos, const uint32_t* __restrict__ u) {
+  if (u[U_ERR]) return;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride) {
+    chg[i] = 0;
+    if (i > 0 && (keys[i] >> 2) == (keys[i - 1] >> 2)) continue;
+    int64_t p;
+    const uint32_t f = entry_state(g, i, N, [&](int64_t q) { return keys[q]; }, &p);
+    st[i] = (uint8_t)f;
+    pos[i] = (uint32_t)p;
+    chg[i] = (f >> 2) != (f & 3u) ? 1u : 0u;
   }
 }
+
+// Changed entries: E = (row << rb | column) << 4 | f0 << 2 | f1 in order, P their
+// places, net = +1 for an inserted entry, -1 for a deleted one.
+__device__ __forceinline__ int64_t net_of(uint32_t f) { return (f >> 2) == 0 ? 1 : (f & 3u) == 0 ? -1 : 0; }
+
+__global__ void k_upd_emit(const uint64_t* __restrict__ keys, int64_t N, const uint32_t* __restrict__ chg,
+                           const uint32_t* __restrict__ cpos, const uint8_t* __restrict__ st,
+                           const uint32_t* __restrict__ pos, uint64_t* __restrict__ E, uint32_t* __restrict__ P,
+                           int64_t* __restrict__ net, const uint32_t* __restrict__ u) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const bool bad = u[U_ERR] != 0;
+  const int64_t nE = bad ? 0 : u[U_NE];
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride) {
+    if (!bad && chg[i]) {
+      const uint32_t c = cpos[i], f = st[i];
+      E[c] = (keys[i] >> 2) << 4 | f;
+      P[c] = pos[i];
+      net[c] = net_of(f);
+    }
+    if (i >= nE) net[i] = 0;  // the scan runs over all N
+  }
+}
+
+// All of the above for at most UPD_SMALL operations, in one workgroup: keys and
+// their order of arrival sorted by a bitonic network in LDS, the changed entries
+// compacted and their shifts S (sum of net before each; S[nE] = the total)
+// scanned (36 us for 601 updates, bound by the network's barriers and the row
+// searches; as sort passes of five launches each, scans and waits for the host
+// it was most of a call of 534 us, now 143).
+__global__ void __launch_bounds__(SMALL_T) k_upd_small(UpdGraph g, int k, const int32_t* __restrict__ src,
+                                                       const int32_t* __restrict__ dst, const uint8_t* __restrict__ ins,
+                                                       uint64_t* __restrict__ E, uint32_t* __restrict__ P,
+                                                       int64_t* __restrict__ S, uint32_t* __restrict__ u) {
+  constexpr int M = 2 * UPD_SMALL, PER = M / SMALL_T;
+  __shared__ uint64_t key[M];
+  __shared__ uint16_t ord[M];
+  __shared__ uint32_t err, wsum[SMALL_T / 64][2];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int N = 2 * k;
+  int L = 64;
+  while (L < N) L <<= 1;
+  if (tid == 0) err = 0;
+  __syncthreads();
+  uint32_t bits = 0;
+  for (int i = tid; i < L / 2; i += SMALL_T) {
+    uint64_t k0 = ~0ull, k1 = ~0ull;
+    if (i < k) bits |= op_keys(g, src[i], dst[i], ins[i], &k0, &k1);
+    key[2 * i] = k0;
+    key[2 * i + 1] = k1;
+    ord[2 * i] = (uint16_t)(2 * i);
+    ord[2 * i + 1] = (uint16_t)(2 * i + 1);
+  }
+  if (bits) atomicOr(&err, bits);
+  __syncthreads();
+  if (err) {
+    if (tid == 0) u[U_ERR] = err;
+    return;
+  }
+  for (int sz = 2; sz <= L; sz <<= 1)
+    for (int j = sz >> 1; j > 0; j >>= 1) {
+      for (int q = tid; q < L / 2; q += SMALL_T) {
+        const int a = ((q & ~(j - 1)) << 1) | (q & (j - 1)), b = a | j;
+        const uint64_t ka = key[a], kb = key[b];
+        const uint16_t oa = ord[a], ob = ord[b];
+        const bool gt = (ka >> 1) != (kb >> 1) ? (ka >> 1) > (kb >> 1) : oa > ob;
+        if (gt == ((a & sz) == 0)) {
+          key[a] = kb;
+          key[b] = ka;
+          ord[a] = ob;
+          ord[b] = oa;
+        }
+      }
+      __syncthreads();
+    }
+  // each thread: PER consecutive keys
+  uint32_t f[PER], c = 0;
+  int64_t pos[PER], d = 0;
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int i = tid * PER + r;
+    f[r] = 0;
+    pos[r] = 0;
+    if (i < N && (i == 0 || (key[i] >> 2) != (key[i - 1] >> 2))) {
+      f[r] = entry_state(g, i, N, [&](int64_t q) { return key[q]; }, &pos[r]);
+      if ((f[r] >> 2) == (f[r] & 3u)) f[r] = 0;
+    }
+    if (f[r]) {
+      ++c;
+      d += net_of(f[r]);
+    }
+  }
+  // exclusive prefix of (changed entries, net) over the threads
+  uint32_t sc = c;
+  int32_t sd = (int32_t)d;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t qc = __shfl_up(sc, o, 64);
+    const int32_t qd = __shfl_up(sd, o, 64);
+    if (lane >= o) {
+      sc += qc;
+      sd += qd;
+    }
+  }
+  if (lane == 63) {
+    wsum[w][0] = sc;
+    wsum[w][1] = (uint32_t)sd;
+  }
+  __syncthreads();
+  uint32_t at = sc - c;
+  int64_t sh = sd - d;
+  for (int q = 0; q < w; ++q) {
+    at += wsum[q][0];
+    sh += (int32_t)wsum[q][1];
+  }
+#pragma unroll
+  for (int r = 0; r < PER; ++r)
+    if (f[r]) {
+      E[at] = (key[tid * PER + r] >> 2) << 4 | f[r];
+      P[at] = (uint32_t)pos[r];
+      S[at] = sh;
+      ++at;
+      sh += net_of(f[r]);
+    }
+  if (tid == SMALL_T - 1) {
+    S[at] = sh;
+    u[U_NE] = at;
+  }
+}
+
+// ----------------------------------------------------------------- row sums
+
+struct DeltaArgs {
+  UpdGraph g;
+  const uint64_t* E;  // sorted changed entries
+  uint64_t lut[4];    // class of code c: nibble c & 15 of lut[c >> 4]
+  unsigned long long* acc;  // UPD_COPIES x UPD_ACC words, two's complement
+  uint32_t* u;
+  uint64_t* queue;    // parts put off: entry << 8 | part
+};
+constexpr int UPD_COPIES = 32, UPD_ACC = 32;
+__device__ __forceinline__ unsigned long long* acc_of(const DeltaArgs& a) {
+  return a.acc + (blockIdx.x % UPD_COPIES) * UPD_ACC;
+}
+__device__ __forceinline__ uint64_t wave_sum(uint64_t x) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+__device__ __forceinline__ uint64_t lane64(uint64_t x, int l) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+}
+
+// Neighbour counts by flag of the entries [b, e), by one wavefront: 16 entries a
+// lane and read.
+__device__ __forceinline__ void flag_counts(const UpdGraph& g, int64_t b, int64_t e, int lane, uint32_t (&c)[3]) {
+  const int64_t nbytes = (g.nnz + 3) / 4;
+  uint32_t o = 0, i = 0, m = 0;
+#pragma unroll 4
+  for (int64_t p = (b >> 2) + 4 * lane; p * 4 < e; p += 256) {
+    uint32_t w = 0;
+    if (p + 4 <= nbytes) __builtin_memcpy(&w, g.flg + p, 4);
+    else
+      for (int q = 0; q < 4 && p + q < nbytes; ++q) w |= (uint32_t)g.flg[p + q] << (8 * q);
+    const int64_t at = p * 4;  // the word's first entry
+    if (at < b) w &= ~0u << (2 * (b - at));
+    if (at + 16 > e) w &= ~(~0u << (2 * (e - at)));
+    const uint32_t lo = w & 0x55555555u, hi = (w >> 1) & 0x55555555u;
+    o += __popc(lo & ~hi);
+    i += __popc(hi & ~lo);
+    m += __popc(lo & hi);
+  }
+  for (int s = 32; s > 0; s >>= 1) {
+    o += __shfl_xor(o, s, 64);
+    i += __shfl_xor(i, s, 64);
+    m += __shfl_xor(m, s, 64);
+  }
+  c[0] = o;
+  c[1] = i;
+  c[2] = m;
+}
+
+// One wavefront per changed row (at the first of its changed entries).
+__global__ void __launch_bounds__(UT) k_upd_rows(DeltaArgs a) {
+  if (a.u[U_ERR]) return;
+  const UpdGraph& g = a.g;
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = ((int64_t)gridDim.x * UT) >> 6, nE = a.u[U_NE];
+  RowSums sums;
+  for (int64_t i = ((int64_t)blockIdx.x * UT + threadIdx.x) >> 6; i < nE; i += nw) {
+    const uint64_t x = a.E[i] >> (4 + g.rb);
+    if (i > 0 && (a.E[i - 1] >> (4 + g.rb)) == x) continue;
+    uint32_t c0[3];
+    flag_counts(g, g.off[x], g.off[x + 1], lane, c0);
+    int64_t c1[3] = {c0[0], c0[1], c0[2]};
+    for (int64_t j = i;; j += 64) {
+      const uint64_t ent = j + lane < nE ? a.E[j + lane] : ~0ull;
+      const bool mine = j + lane < nE && (ent >> (4 + g.rb)) == x;
+      for (uint32_t f = 1; f <= 3; ++f)
+        c1[f - 1] += (int64_t)__popcll(__ballot(mine && (ent & 3u) == f)) -
+                     (int64_t)__popcll(__ballot(mine && (ent >> 2 & 3u) == f));
+      if (!__builtin_amdgcn_readlane(mine, 63)) break;
+    }
+    if (lane == 0) {
+      RowSums p, q;
+      p.row((uint64_t)g.n, c0[0], c0[1], c0[2]);
+      q.row((uint64_t)g.n, (uint64_t)c1[0], (uint64_t)c1[1], (uint64_t)c1[2]);
+      for (int k = 0; k < 9; ++k) sums.c[k] += q.c[k] - p.c[k];
+    }
+  }
+  // (lane 0 holds each wavefront's sums)
+  if (lane == 0)
+    for (int k = 0; k < 9; ++k)
+      if (sums.c[k]) atomicAdd(&acc_of(a)[RowSums::slot(k)], (unsigned long long)sums.c[k]);
+}
+
+// ---------------------------------------------------------------- triangles
 
 __device__ __forceinline__ uint32_t class_of(const DeltaArgs& g, uint32_t code) {
   const uint64_t w = code < 16 ? g.lut[0] : code < 32 ? g.lut[1] : code < 48 ? g.lut[2] : g.lut[3];
@@ -183,416 +360,301 @@ __device__ __forceinline__ uint32_t class_of(const DeltaArgs& g, uint32_t code) 
 }
 
 // Change entry of (x, y) in E[b, e) (the row x range): index or -1.
-__device__ __forceinline__ int64_t find_change(const DeltaArgs& g, int64_t b, int64_t e, int64_t x, int32_t y) {
-  const uint64_t k = (((uint64_t)x << g.rb) | (uint64_t)y) << 4;
-  const int64_t p = lower_key(g.E, b, e, k);
-  return (p < e && (g.E[p] >> 4) == (k >> 4)) ? p : -1;
+__device__ __forceinline__ int64_t find_change(const DeltaArgs& a, int64_t b, int64_t e, int64_t x, int32_t y) {
+  const uint64_t k = (((uint64_t)x << a.g.rb) | (uint64_t)y) << 4;
+  const int64_t p = lower_key(a.E, b, e, k);
+  return (p < e && (a.E[p] >> 4) == (k >> 4)) ? p : -1;
 }
 
-// Positions of the merged walk of N(a) and N(b) each lane takes per round.
-constexpr int UPD_S = 16;
+struct Pair {
+  int64_t a;
+  int32_t b;
+  uint32_t f0, f1;
+  int64_t oa, ea, ob, eb;      // rows a and b
+  int64_t da0, da1, db0, db1;  // their changed entries
+};
 
-// Class change of the triad {a, b, w} for the third vertex w with old flags
-// g0a (a-w), g0b (b-w) and new ones g1a, g1b (cha, chb: that pair changes),
-// counted by the triad's smallest changed pair only.
-__device__ __forceinline__ void triad_move(const DeltaArgs& g, int32_t* h, int lane, uint64_t pk, int64_t a, int32_t b,
-                                           int32_t w, uint32_t f0, uint32_t f1, uint32_t g0a, uint32_t g1a, bool cha,
-                                           uint32_t g0b, uint32_t g1b, bool chb) {
-  bool own = true;
-  if (cha) own = own && pk < ((((uint64_t)min((int64_t)w, a)) << g.rb) | (uint64_t)max((int64_t)w, a));
-  if (chb) own = own && pk < ((((uint64_t)min(w, b)) << g.rb) | (uint64_t)max(w, b));
-  if (!own) return;
-  const uint32_t oc = class_of(g, f0 | g0a << 2 | g0b << 4), nc = class_of(g, f1 | g1a << 2 | g1b << 4);
-  if (oc != nc) {
-    h[oc * 64 + lane] -= 1;
-    h[nc * 64 + lane] += 1;
+// The pair is the smallest changed one of the triad {a, b, w} (the changed ones
+// among its other two: cha, chb).
+__device__ __forceinline__ bool owns(int rb, const Pair& p, int32_t w, bool cha, bool chb) {
+  const uint64_t pk = ((uint64_t)p.a << rb) | (uint64_t)p.b;
+  const int64_t a = p.a, b = p.b;
+  return !(cha && ((((uint64_t)min((int64_t)w, a)) << rb) | (uint64_t)max((int64_t)w, a)) < pk) &&
+         !(chb && ((((uint64_t)min((int64_t)w, b)) << rb) | (uint64_t)max((int64_t)w, b)) < pk);
+}
+
+// Entries [s0, s1) of the shorter of rows a and b searched in the longer: the w
+// adjacent to both before.
+__device__ void pair_part(const DeltaArgs& A, const Pair& p, int64_t s0, int64_t s1, int lane, int32_t* h) {
+  const UpdGraph& g = A.g;
+  const bool aside = p.ea - p.oa <= p.eb - p.ob;  // row a is the shorter
+  const int64_t base = aside ? p.oa : p.ob, lb = aside ? p.ob : p.oa, le = aside ? p.eb : p.ea;
+  for (int64_t j = s0 + lane; j < s1; j += 64) {
+    const int32_t w = g.nbr[base + j];
+    const int64_t q = lower_id(g.nbr, lb, le, w);
+    if (q >= le || g.nbr[q] != w) continue;
+    const uint32_t fs = entry_flag(g.flg, base + j), fl = entry_flag(g.flg, q);
+    const uint32_t g0a = aside ? fs : fl, g0b = aside ? fl : fs;
+    const int64_t ca = p.da1 - p.da0 > 1 ? find_change(A, p.da0, p.da1, p.a, w) : -1;
+    const int64_t cb = p.db1 - p.db0 > 1 ? find_change(A, p.db0, p.db1, p.b, w) : -1;
+    if (!owns(g.rb, p, w, ca >= 0, cb >= 0)) continue;
+    const uint32_t g1a = ca >= 0 ? (uint32_t)A.E[ca] & 3u : g0a, g1b = cb >= 0 ? (uint32_t)A.E[cb] & 3u : g0b;
+    if (p.f0) h[class_of(A, p.f0 | g0a << 2 | g0b << 4) * 64 + lane] -= 1;
+    if (p.f1 && g1a && g1b) h[class_of(A, p.f1 | g1a << 2 | g1b << 4) * 64 + lane] += 1;
   }
 }
 
-// One wavefront per work item: a chunk of the merge of a changed pair {a, b}
-// (the pairs are the entries of row a in E with a < b). The third vertices are
-// the union of four sorted lists: N(a), the changes of a, N(b), the changes of
-// b. N(a) and N(b) are walked together, merged in id order (a merge path cut
-// into 16 positions per lane and round, a common id consumed once), so each
-// vertex of either row comes with both old flags; a vertex adjacent to b only
-// whose pair with a changes is left to the pass over the changes of a. The
-// pair's first item then takes the changes of a, then of b, each vertex seen
-// in an earlier list skipped.
-__global__ void __launch_bounds__(UT) k_upd_delta(DeltaArgs g) {
-  __shared__ int32_t hist[UT / 64][16][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int32_t* h = &hist[wv][0][0];
-  for (int c = 0; c < 16; ++c) h[c * 64 + lane] = 0;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+// The triangles after that need an inserted entry of a or of b.
+__device__ void pair_changes(const DeltaArgs& A, const Pair& p, int lane, int32_t* h) {
+  if (!p.f1) return;
+  const UpdGraph& g = A.g;
   const uint64_t cmask = (1ull << g.rb) - 1;
-  uint32_t steps = 0;
-  const int64_t nit = g.ipre[g.nE];
-  for (int64_t it = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; it < nit; it += nw) {
-    // the item's pair: the last entry q with ipre[q] <= it (one with chunks)
-    int64_t q = 0;
-    for (int64_t hi = g.nE; hi - q > 1;) {
-      const int64_t mid = (q + hi) >> 1;
-      if ((int64_t)g.ipre[mid] <= it) q = mid; else hi = mid;
-    }
-    const int64_t chunk = it - (int64_t)g.ipre[q];
-    const uint64_t ent = g.E[q];
-    const int64_t a = (int64_t)(ent >> (4 + g.rb));
-    const int32_t b = (int32_t)((ent >> 4) & cmask);
-    const uint32_t f0 = (ent >> 2) & 3u, f1 = ent & 3u;
-    const uint64_t pk = ((uint64_t)a << g.rb) | (uint64_t)b;
-    const int64_t oa = g.off[a], ea = g.off[a + 1], ob = g.off[b], eb = g.off[b + 1];
-    const int64_t da0 = lower_key(g.E, 0, g.nE, (uint64_t)a << (g.rb + 4));
-    const int64_t da1 = lower_key(g.E, da0, g.nE, (uint64_t)(a + 1) << (g.rb + 4));
-    const int64_t db0 = lower_key(g.E, 0, g.nE, (uint64_t)b << (g.rb + 4));
-    const int64_t db1 = lower_key(g.E, db0, g.nE, (uint64_t)(b + 1) << (g.rb + 4));
-    uint32_t ucount = 0;
-    // N(a) and N(b) merged
-    const int32_t* const A = g.nbr + oa;
-    const int32_t* const B = g.nbr + ob;
-    const int64_t la = ea - oa, lb = eb - ob, D = la + lb;
-    // this item's merged positions [c0, c1) (the pair's nq chunks cover its
-    // merge); per lane and round UPD_S of them, or fewer for a short range so
-    // that it spreads over the wavefront
-    const int64_t nq = (int64_t)g.ipre[q + 1] - (int64_t)g.ipre[q];
-    const int64_t csz = (D + nq - 1) / nq;
-    const int64_t c0 = min(D, chunk * csz), c1 = min(D, c0 + csz);
-    const int64_t S = c1 - c0 < 64 * UPD_S ? max((int64_t)1, (c1 - c0 + 63) >> 6) : (int64_t)UPD_S;
-    for (int64_t r0 = c0; r0 < c1; r0 += 64 * S) {
-      const int64_t d0 = min(c1, r0 + (int64_t)lane * S), d1 = min(c1, d0 + S);
-      // merge-path split of diagonal d0: A elements among the first d0 merged
-      int64_t lo = d0 > lb ? d0 - lb : 0, hi = min(d0, la);
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (A[mid] <= B[d0 - mid - 1]) lo = mid + 1; else hi = mid;
+  auto old_flag = [&](int64_t b, int64_t e, int32_t w) {
+    const int64_t j = lower_id(g.nbr, b, e, w);
+    return j < e && g.nbr[j] == w ? entry_flag(g.flg, j) : 0u;
+  };
+  for (int side = 0; side < 2; ++side) {
+    const int64_t L0 = side ? p.db0 : p.da0, L1 = side ? p.db1 : p.da1;
+    for (int64_t j = L0 + lane; j < L1; j += 64) {
+      const uint64_t ent = A.E[j];
+      const int32_t w = (int32_t)((ent >> 4) & cmask);
+      const uint32_t g0 = (uint32_t)(ent >> 2) & 3u, g1 = (uint32_t)ent & 3u;  // with this side
+      if (w == p.a || w == p.b || !g1) continue;
+      const int64_t q = side ? find_change(A, p.da0, p.da1, p.a, w) : find_change(A, p.db0, p.db1, p.b, w);
+      if (side && q >= 0) continue;  // taken by the changes of a
+      uint32_t h0, h1;               // with the other side
+      if (q >= 0) {
+        h0 = (uint32_t)(A.E[q] >> 2) & 3u;
+        h1 = (uint32_t)A.E[q] & 3u;
+      } else {
+        h0 = h1 = side ? old_flag(p.oa, p.ea, w) : old_flag(p.ob, p.eb, w);
       }
-      int64_t i = lo, k = d0 - lo;
-      // an id shared by A[i-1] and B[k] was taken with A[i-1] by a lane before
-      if (i > 0 && k < lb && A[i - 1] == B[k]) ++k;
-      if (i + k >= d1) continue;
-      // The lane's ids ascend, and so do the change entries of a and of b: one
-      // search each for the first change at or after the lane's first id, then
-      // cursors that only move forward. (A change list holding only the pair
-      // {a, b} itself has no entry for any w walked here.)
-      const int32_t wfirst = min(i < la ? A[i] : INT32_MAX, k < lb ? B[k] : INT32_MAX);
-      int64_t pa = da1, pb = db1;
-      if (da1 - da0 > 1) pa = lower_key(g.E, da0, da1, (((uint64_t)a << g.rb) | (uint64_t)wfirst) << 4);
-      if (db1 - db0 > 1) pb = lower_key(g.E, db0, db1, (((uint64_t)b << g.rb) | (uint64_t)wfirst) << 4);
-      int64_t ida = pa < da1 ? (int64_t)((g.E[pa] >> 4) & cmask) : INT64_MAX;
-      int64_t idb = pb < db1 ? (int64_t)((g.E[pb] >> 4) & cmask) : INT64_MAX;
-      while (i + k < d1) {
-        const int32_t x = i < la ? A[i] : INT32_MAX, y = k < lb ? B[k] : INT32_MAX;
-        const bool inA = x <= y, inB = y <= x;
-        const int32_t w = inA ? x : y;
-        const uint32_t fa = inA ? entry_flag(g.flg, oa + i) : 0u, fb = inB ? entry_flag(g.flg, ob + k) : 0u;
-        i += inA;
-        k += inB;
-        while (ida < w) {
-          ++pa;
-          ida = pa < da1 ? (int64_t)((g.E[pa] >> 4) & cmask) : INT64_MAX;
-        }
-        while (idb < w) {
-          ++pb;
-          idb = pb < db1 ? (int64_t)((g.E[pb] >> 4) & cmask) : INT64_MAX;
-        }
-        if (w == a || w == b) continue;
-        uint32_t g1a = fa;
-        bool cha = false;
-        if (ida == w) {
-          if (!inA) continue;  // a pair with a that changes: the pass over the changes of a takes w
-          cha = true;
-          g1a = (uint32_t)(g.E[pa] & 3u);
-        }
-        const bool chb = idb == w;
-        const uint32_t g1b = chb ? (uint32_t)(g.E[pb] & 3u) : fb;
-        ++ucount;
-        triad_move(g, h, lane, pk, a, b, w, f0, f1, fa, g1a, cha, fb, g1b, chb);
-      }
+      if (!h1 || (g0 && h0) || !owns(g.rb, p, w, side == 0 || q >= 0, side == 1 || q >= 0)) continue;
+      h[class_of(A, p.f1 | (side ? h1 : g1) << 2 | (side ? g1 : h1) << 4) * 64 + lane] += 1;
     }
-    // the changes of a (vertices not in N(a)), then of b (not in N(b), not
-    // seen before): the pair's first item only
-    for (int phase = 1; phase < 4 && chunk == 0; phase += 2) {
-      const int64_t L0 = phase == 1 ? da0 : db0;
-      const int64_t L1 = phase == 1 ? da1 : db1;
-      for (int64_t j0 = L0; j0 < L1; j0 += 64) {
-        const int64_t j = j0 + lane;
-        if (j >= L1) continue;
-        int32_t w;
-        uint32_t g0a = 0, g1a = 0, g0b = 0, g1b = 0;
-        bool cha = false, chb = false, keep = true;
-        {
-          const uint64_t e = g.E[j];
-          w = (int32_t)((e >> 4) & cmask);
-          if (w == a || w == b) continue;
-          if (phase == 1) {
-            g0a = (e >> 2) & 3u;
-            g1a = e & 3u;
-            cha = true;
-            keep = g0a == 0;  // otherwise w is in N(a), seen in the merged walk
-            if (keep) {
-              const int64_t jb = lower_id(g.nbr, ob, eb, w);
-              g0b = (jb < eb && g.nbr[jb] == w) ? entry_flag(g.flg, jb) : 0u;
-              const int64_t p = find_change(g, db0, db1, b, w);
-              chb = p >= 0;
-              g1b = chb ? (uint32_t)(g.E[p] & 3u) : g0b;
-            }
-          } else {
-            g0b = (e >> 2) & 3u;
-            g1b = e & 3u;
-            chb = true;
-            if (g0b != 0) {
-              keep = false;  // in N(b), seen in the merged walk
-            } else {
-              const int64_t ja = lower_id(g.nbr, oa, ea, w);
-              keep = !(ja < ea && g.nbr[ja] == w) && find_change(g, da0, da1, a, w) < 0;
-            }
-          }
-        }
-        if (!keep) continue;
-        ++ucount;
-        triad_move(g, h, lane, pk, a, b, w, f0, f1, g0a, g1a, cha, g0b, g1b, chb);
+  }
+}
+
+__device__ __forceinline__ Pair pair_of(const DeltaArgs& A, int64_t q, int64_t nE) {
+  const UpdGraph& g = A.g;
+  const uint64_t ent = A.E[q];
+  Pair p;
+  p.a = (int64_t)(ent >> (4 + g.rb));
+  p.b = (int32_t)((ent >> 4) & ((1ull << g.rb) - 1));
+  p.f0 = (uint32_t)(ent >> 2) & 3u;
+  p.f1 = (uint32_t)ent & 3u;
+  p.oa = g.off[p.a];
+  p.ea = g.off[p.a + 1];
+  p.ob = g.off[p.b];
+  p.eb = g.off[p.b + 1];
+  return p;
+}
+// The rows' changed entries: four searches, one a lane.
+__device__ __forceinline__ void pair_ranges(const DeltaArgs& A, Pair& p, int64_t nE, int lane) {
+  const int64_t x = (lane & 2 ? (int64_t)p.b : p.a) + (lane & 1);
+  const int64_t r = lane < 4 ? lower_key(A.E, 0, nE, (uint64_t)x << (A.g.rb + 4)) : 0;
+  p.da0 = (int64_t)lane64((uint64_t)r, 0);
+  p.da1 = (int64_t)lane64((uint64_t)r, 1);
+  p.db0 = (int64_t)lane64((uint64_t)r, 2);
+  p.db1 = (int64_t)lane64((uint64_t)r, 3);
+}
+__device__ __forceinline__ int64_t part_size(int64_t len) {
+  return len > UPD_PART * UPD_PARTS ? (len + UPD_PARTS - 1) / UPD_PARTS : UPD_PART;
+}
+
+__device__ void flush_classes(int32_t* h, int lane, unsigned long long* acc) {
+  __builtin_amdgcn_wave_barrier();
+  for (int c = 8; c < 16; ++c) {
+    const uint64_t x = wave_sum((uint64_t)(int64_t)h[c * 64 + lane]);
+    if (lane == 0 && x) atomicAdd(&acc[c], (unsigned long long)x);
+    h[c * 64 + lane] = 0;
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One wavefront per changed pair (the entries with row < column): the first
+// UPD_PART entries of its shorter row, and its changes. Further parts go to
+// other wavefronts (k_upd_parts) through a queue, or are taken here if it is
+// full. MORE: the queue's parts.
+template <bool MORE>
+__global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
+  __shared__ int32_t hist[UT / 64][16 * 64];
+  if (A.u[U_ERR]) return;
+  if (MORE && A.u[U_PARTS] == 0) return;
+  const int lane = threadIdx.x & 63;
+  int32_t* h = hist[threadIdx.x >> 6];
+  for (int c = 0; c < 16; ++c) h[c * 64 + lane] = 0;
+  const int64_t nw = ((int64_t)gridDim.x * UT) >> 6, nE = A.u[U_NE];
+  const int64_t items = MORE ? min((int64_t)A.u[U_PARTS], UPD_QUEUE) : nE;
+  uint64_t steps = 0;
+  for (int64_t it = ((int64_t)blockIdx.x * UT + threadIdx.x) >> 6; it < items; it += nw) {
+    const int64_t q = MORE ? (int64_t)(A.queue[it] >> 8) : it;
+    Pair p = pair_of(A, q, nE);
+    if (!MORE && p.b < p.a) continue;
+    pair_ranges(A, p, nE, lane);
+    const int64_t len = min(p.ea - p.oa, p.eb - p.ob), sz = part_size(len);
+    int64_t s0 = 0, s1 = min(len, sz);
+    if (MORE) {
+      s0 = min(len, (int64_t)(A.queue[it] & 255u) * sz);
+      s1 = min(len, s0 + sz);
+    } else {
+      pair_changes(A, p, lane, h);
+      const int parts = (int)((len + sz - 1) / sz);
+      if (parts > 1) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&A.u[U_PARTS], (uint32_t)(parts - 1));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        for (int c = 1 + lane; c < parts; c += 64)
+          if ((int64_t)at + c - 1 < UPD_QUEUE) A.queue[at + c - 1] = (uint64_t)q << 8 | (uint64_t)c;
+        // the parts that found no room
+        const int64_t room = max((int64_t)0, min((int64_t)parts - 1, UPD_QUEUE - (int64_t)at));
+        if (room < parts - 1) pair_part(A, p, (1 + room) * sz, len, lane, h);
       }
     }
-    // every other third vertex: only the pair {a, b} has arcs. Those are the
-    // n - 2 others less the vertices the pair's items met; each item takes
-    // its own count off (the first adds the n - 2).
-    uint32_t u = ucount;
-    for (int o = 32; o > 0; o >>= 1) u += __shfl_xor(u, o, 64);
-    if (lane == 0) {
-      const int64_t rest = (chunk == 0 ? g.n - 2 : 0) - (int64_t)u;
-      const uint32_t oc = class_of(g, f0), nc = class_of(g, f1);
-      if (rest != 0 && oc != nc) {
-        atomicAdd(&g.delta[oc], (unsigned long long)(-rest));
-        atomicAdd(&g.delta[nc], (unsigned long long)rest);
-      }
-    }
-    steps += (uint32_t)((c1 - c0 + da1 - da0 + db1 - db0) / 64 + 4);
+    pair_part(A, p, s0, s1, lane, h);
+    steps += (uint64_t)(len + p.da1 - p.da0 + p.db1 - p.db0) / 64 + 4;
     if (steps > (1u << 29)) {
-      __builtin_amdgcn_wave_barrier();
-      for (int c = 0; c < 16; ++c) {
-        int64_t x = h[c * 64 + lane];
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if (lane == 0 && x) atomicAdd(&g.delta[c], (unsigned long long)x);
-        h[c * 64 + lane] = 0;
-      }
+      flush_classes(h, lane, acc_of(A));
       steps = 0;
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  for (int c = 0; c < 16; ++c) {
-    int64_t x = h[c * 64 + lane];
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    if (lane == 0 && x) atomicAdd(&g.delta[c], (unsigned long long)x);
-  }
+  flush_classes(h, lane, acc_of(A));
 }
 
 // ---------------------------------------------------------- CSR after
-// Change entry e is an insertion (f0 = 0), a deletion (f1 = 0) or a new flag.
-__global__ void k_change_kinds(const uint64_t* __restrict__ E, int64_t nE, uint32_t* __restrict__ ins,
-                               uint32_t* __restrict__ del) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e <= nE; e += stride) {
-    const uint32_t f0 = e < nE ? (uint32_t)(E[e] >> 2) & 3u : 1u, f1 = e < nE ? (uint32_t)E[e] & 3u : 1u;
-    ins[e] = f0 == 0 ? 1u : 0u;
-    del[e] = f1 == 0 ? 1u : 0u;
-  }
+
+// new_off[x] = off[x] + the net of the changed entries in rows below x
+__global__ void k_new_offsets(UpdGraph g, const uint64_t* __restrict__ E, const int64_t* __restrict__ S,
+                              int64_t* __restrict__ noff, const uint32_t* __restrict__ u) {
+  if (u[U_ERR]) return;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nE = u[U_NE];
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= g.n; x += stride)
+    noff[x] = g.off[x] + S[lower_key(E, 0, nE, (uint64_t)x << (g.rb + 4))];
 }
 
-__global__ void k_row_marks(const uint64_t* __restrict__ E, int64_t nE, int rb, uint32_t* __restrict__ mark) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nE; e += stride) {
-    const uint64_t x = E[e] >> (4 + rb);
-    atomicOr(&mark[x >> 5], 1u << (x & 31));
-  }
-}
-
-// new_off[x] = off[x] + insertions - deletions in rows below x
-__global__ void k_new_offsets(int64_t n, int rb, const int64_t* __restrict__ off, const uint64_t* __restrict__ E,
-                              int64_t nE, const uint32_t* __restrict__ I, const uint32_t* __restrict__ D,
-                              int64_t* __restrict__ noff) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= n; x += stride) {
-    const int64_t e = lower_key(E, 0, nE, (uint64_t)x << (rb + 4));
-    noff[x] = off[x] + (int64_t)I[e] - (int64_t)D[e];
-  }
-}
-
-// Old entries to their new places: rows without changes shift as a whole;
-// in a changed row an entry moves by the insertions and deletions before it,
-// takes its new flag, or is dropped. The shift of an unchanged row, noff[x] -
-// off[x], changes only past a changed row, so a tile of ETILE entries whose
-// rows hold at most COPY_MAXCHG changed rows (the usual case) lists those rows
-// with their entry ranges, their ranges of change entries and the shift of
-// each run of unchanged rows between them: an entry finds its run by comparing
-// its index with the few range ends, and an entry of a changed row searches
-// only that row's change entries. Other tiles find each entry's row by a
-// search of LDS-staged row starts, and its row's change entries by a search of
-// all of them.
-constexpr int COPY_MAXCHG = 8;
-struct CopyTile {
-  TileRows T;                        // r[0], r[1]: rows of the tile's first and last entry
-  int64_t crow[COPY_MAXCHG];         // the tile's changed rows, ascending
-  int64_t cbeg[COPY_MAXCHG], cend[COPY_MAXCHG];  // their entry ranges
-  int64_t cex[COPY_MAXCHG], cexe[COPY_MAXCHG];   // their change entries E[cex, cexe)
-  int64_t sdelta[COPY_MAXCHG + 1];   // shift of the unchanged rows before changed row s
-  int32_t nchg;                      // changed rows; -1: too many (per-entry row search)
-};
-
-__global__ void __launch_bounds__(UT) k_copy_old(int64_t n, int64_t nnz, int rb, const int64_t* __restrict__ off,
-                                                 const int32_t* __restrict__ nbr, const uint8_t* __restrict__ flg,
-                                                 const uint64_t* __restrict__ E, int64_t nE,
-                                                 const uint32_t* __restrict__ I, const uint32_t* __restrict__ D,
-                                                 const uint32_t* __restrict__ mark, const int64_t* __restrict__ noff,
-                                                 int64_t nn, int32_t* __restrict__ nnbr, uint8_t* __restrict__ nfl) {
-  __shared__ CopyTile C;
-  for (int64_t t0 = (int64_t)blockIdx.x * ETILE; t0 < nnz; t0 += (int64_t)gridDim.x * ETILE) {
-    const int64_t t1 = min(t0 + (int64_t)ETILE, nnz);
+// The entries after the batch, by place: changed entry e stands at Q = P[e] +
+// S[e] (an inserted or reflagged entry; a deleted one gives its place to what
+// follows), and between two of them the old entries move by one shift. A tile
+// of places finds its changed entries by two searches and stages them in LDS;
+// a thread writes four ids and their flag byte. (By old entry, with the flags as
+// bytes and a pass to pack them: 1.0 ms per 100,000 updates on 112 M entries;
+// now 0.28.)
+constexpr int CT = 4096, CSTAGE = 1024;
+__global__ void __launch_bounds__(UT) k_upd_copy(UpdGraph g, const uint64_t* __restrict__ E,
+                                                 const uint32_t* __restrict__ P, const int64_t* __restrict__ S,
+                                                 int32_t* __restrict__ nnbr, uint8_t* __restrict__ nflg,
+                                                 const uint32_t* __restrict__ u) {
+  __shared__ int64_t range[2];
+  __shared__ int32_t sq[CSTAGE];   // place in the tile (before it: -1)
+  __shared__ int64_t ss[CSTAGE];   // shift of the entries after it
+  __shared__ int32_t sid[CSTAGE];  // id of an inserted entry, else -1
+  __shared__ uint8_t sf[CSTAGE];   // flag of the entry at its place, 0 for a deleted one
+  if (u[U_ERR]) return;
+  const int64_t nE = u[U_NE], nn = g.nnz + S[nE];
+  const uint64_t cmask = (1ull << g.rb) - 1;
+  auto Q = [&](int64_t e) { return (int64_t)P[e] + S[e]; };
+  for (int64_t t0 = (int64_t)blockIdx.x * CT; t0 < nn; t0 += (int64_t)gridDim.x * CT) {
+    const int64_t t1 = min(t0 + (int64_t)CT, nn);
     __syncthreads();
-    if (threadIdx.x < 2) C.T.r[threadIdx.x] = row_search(off, 0, n, threadIdx.x == 0 ? t0 : t1 - 1);
+    if (threadIdx.x < 2) {
+      // the last changed entry at or before the tile's first and last place
+      const int64_t j = threadIdx.x ? t1 - 1 : t0;
+      int64_t lo = 0, hi = nE;
+      while (lo < hi) {
+        const int64_t m = (lo + hi) >> 1;
+        if (Q(m) <= j) lo = m + 1; else hi = m;
+      }
+      range[threadIdx.x] = lo - 1;
+    }
     __syncthreads();
-    const int64_t r0 = C.T.r[0], r1 = C.T.r[1];
-    // the changed rows among r0..r1 in ascending order, from the row marks:
-    // one mark word (32 rows) per lane of the first wavefront
-    if (threadIdx.x < 64) {
-      const int lane = (int)threadIdx.x;
-      const int64_t w0 = r0 >> 5, w1 = r1 >> 5;
-      int32_t total = -1;
-      if (w1 - w0 < 64) {
-        const int64_t w = w0 + lane;
-        uint32_t m = 0;
-        if (w <= w1) {
-          m = mark[w];
-          if (w == w0) m &= ~0u << (r0 & 31);
-          if (w == w1 && (r1 & 31) != 31) m &= (1u << ((r1 & 31) + 1)) - 1u;
-        }
-        const uint32_t c = (uint32_t)__popc(m);
-        uint32_t pre = c;  // inclusive prefix over the lanes
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t v = __shfl_up(pre, o, 64);
-          if (lane >= o) pre += v;
-        }
-        const uint32_t all = __shfl(pre, 63, 64);
-        if (all <= (uint32_t)COPY_MAXCHG) {
-          uint32_t q = pre - c;
-          while (m) {
-            C.crow[q++] = w * 32 + __builtin_ctz(m);
-            m &= m - 1u;
+    // changed entries e0 .. e1: e0 (if any) at or before the first place
+    const int64_t e0 = max(range[0], (int64_t)0), e1 = range[1];
+    const int64_t ne = e1 - e0 + 1;
+    const bool staged = ne <= CSTAGE;
+    auto load = [&](int64_t e, int64_t& q, int64_t& sh, int32_t& id, uint32_t& f) {
+      const uint64_t x = E[e];
+      f = (uint32_t)x & 3u;
+      q = Q(e);
+      sh = S[e] + net_of((uint32_t)x & 15u);
+      id = (x >> 2 & 3u) == 0 ? (int32_t)(x >> 4 & cmask) : -1;
+    };
+    if (staged)
+      for (int64_t e = threadIdx.x; e < ne; e += UT) {
+        int64_t q, sh;
+        int32_t id;
+        uint32_t f;
+        load(e0 + e, q, sh, id, f);
+        sq[e] = q < t0 ? -1 : (int32_t)(q - t0);
+        ss[e] = sh;
+        sid[e] = id;
+        sf[e] = (uint8_t)f;
+      }
+    __syncthreads();
+    for (int64_t j = t0 + 4 * threadIdx.x; j < t1; j += 4 * UT) {
+      // the last changed entry at or before place j, k after it
+      int64_t k = 0, hi = ne;  // entries e0 .. e0 + k - 1 stand at or before j
+      while (k < hi) {
+        const int64_t m = (k + hi) >> 1;
+        if ((staged ? t0 + sq[m] : Q(e0 + m)) <= j) k = m + 1; else hi = m;
+      }
+      int32_t id[4];
+      uint32_t byte = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t jj = j + r;
+        id[r] = 0;
+        if (jj >= t1) continue;
+        while (k < ne && (staged ? t0 + sq[k] : Q(e0 + k)) <= jj) ++k;
+        int64_t q = -1, sh = 0;
+        int32_t nid = -1;
+        uint32_t f = 0;
+        if (k > 0) {
+          if (staged) {
+            q = t0 + sq[k - 1];
+            sh = ss[k - 1];
+            nid = sid[k - 1];
+            f = sf[k - 1];
+          } else {
+            load(e0 + k - 1, q, sh, nid, f);
           }
-          total = (int32_t)all;
         }
-      }
-      if (lane == 0) C.nchg = total;
-    }
-    __syncthreads();
-    const int32_t nchg = C.nchg;
-    if (nchg >= 0) {
-      const int q = (int)threadIdx.x;
-      if (q <= nchg) {
-        const int64_t xs = q == 0 ? r0 : C.crow[q - 1] + 1;  // <= r1 + 1 <= n
-        C.sdelta[q] = noff[xs] - off[xs];
-        if (q < nchg) {
-          const int64_t c = C.crow[q];
-          C.cbeg[q] = off[c];
-          C.cend[q] = off[c + 1];
-          const int64_t ex = lower_key(E, 0, nE, (uint64_t)c << (rb + 4));
-          C.cex[q] = ex;
-          C.cexe[q] = lower_key(E, ex, nE, (uint64_t)(c + 1) << (rb + 4));
+        const bool here = q == jj && f != 0;  // an inserted or a reflagged entry
+        if (here && nid >= 0) {
+          id[r] = nid;
+        } else {
+          const int64_t o = jj - sh;
+          id[r] = g.nbr[o];
+          if (!here) f = entry_flag(g.flg, o);
         }
+        byte |= f << (2 * r);
       }
-    } else {
-      const int64_t nr = r1 - r0 + 1;
-      if (nr <= TILE_ROWS)
-        for (int64_t x = threadIdx.x; x < nr; x += blockDim.x) {
-          const int64_t d = off[r0 + x] - t0;
-          C.T.rel[x] = (uint16_t)(d > 0 ? d : 0);
-        }
-    }
-    __syncthreads();
-    for (int64_t j = t0 + threadIdx.x; j < t1; j += blockDim.x) {
-      const int32_t y = nbr[j];
-      uint32_t f = entry_flag(flg, j);
-      int64_t x, pos, ex = 0, exe = nE;
-      bool changed;
-      if (nchg >= 0) {
-        int sidx = 0;  // changed rows whose entries all lie before j
-        for (int q = 0; q < nchg; ++q) sidx += C.cend[q] <= j ? 1 : 0;
-        changed = sidx < nchg && j >= C.cbeg[sidx];
-        x = 0;
-        pos = j + C.sdelta[sidx];
-        if (changed) {
-          x = C.crow[sidx];
-          pos = noff[x] + (j - C.cbeg[sidx]);
-          ex = C.cex[sidx];
-          exe = C.cexe[sidx];
-        }
-      } else {
-        x = tile_row(off, C.T, t0, j);
-        changed = (mark[x >> 5] >> (x & 31)) & 1u;
-        pos = noff[x] + (j - off[x]);
-        if (changed) ex = lower_key(E, 0, nE, (uint64_t)x << (rb + 4));
-      }
-      if (changed) {
-        const uint64_t k = (((uint64_t)x << rb) | (uint64_t)y) << 4;
-        const int64_t e = lower_key(E, ex, exe, k);
-        pos += ((int64_t)I[e] - (int64_t)I[ex]) - ((int64_t)D[e] - (int64_t)D[ex]);
-        if (e < nE && (E[e] >> 4) == (k >> 4)) {
-          f = (uint32_t)E[e] & 3u;
-          if (f == 0) continue;  // deleted
-        }
-      }
-      if (pos >= 0 && pos < nn) {  // always true; keeps a faulty position in bounds
-        nnbr[pos] = y;
-        nfl[pos] = (uint8_t)f;
-      }
+      if (j + 4 <= t1) __builtin_memcpy(nnbr + j, id, 16);
+      else
+        for (int r = 0; r < 4 && j + r < t1; ++r) nnbr[j + r] = id[r];
+      nflg[j >> 2] = (uint8_t)byte;
     }
   }
 }
 
-__global__ void k_insert_new(int rb, const int64_t* __restrict__ off, const int32_t* __restrict__ nbr,
-                             const uint64_t* __restrict__ E, int64_t nE, const uint32_t* __restrict__ I,
-                             const uint32_t* __restrict__ D, const int64_t* __restrict__ noff, int64_t nn,
-                             int32_t* __restrict__ nnbr, uint8_t* __restrict__ nfl) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const uint64_t cmask = (1ull << rb) - 1;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nE; e += stride) {
-    if (((E[e] >> 2) & 3u) != 0) continue;  // not an insertion
-    const int64_t x = (int64_t)(E[e] >> (4 + rb));
-    const int32_t y = (int32_t)((E[e] >> 4) & cmask);
-    const int64_t ex = lower_key(E, 0, nE, (uint64_t)x << (rb + 4));
-    const int64_t below = lower_id(nbr, off[x], off[x + 1], y) - off[x];
-    const int64_t pos = noff[x] + below + ((int64_t)I[e] - (int64_t)I[ex]) - ((int64_t)D[e] - (int64_t)D[ex]);
-    if (pos >= 0 && pos < nn) {
-      nnbr[pos] = y;
-      nfl[pos] = (uint8_t)(E[e] & 3u);
-    }
+// The accumulators' copies summed, then the counts: what the host reads.
+__global__ void k_upd_done(const unsigned long long* __restrict__ acc, const uint32_t* __restrict__ u,
+                           const int64_t* __restrict__ S, uint64_t* __restrict__ out) {
+  const int i = threadIdx.x;
+  if (i < UPD_ACC) {
+    uint64_t t = 0;
+    for (int k = 0; k < UPD_COPIES; ++k) t += acc[k * UPD_ACC + i];
+    out[i] = t;
   }
-}
-
-__global__ void k_pack_bytes(const uint8_t* __restrict__ f, int64_t m, uint8_t* __restrict__ out) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nb = (m + 3) / 4;
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += stride) {
-    uint32_t v = 0;
-    for (int k = 0; k < 4; ++k)
-      if (4 * b + k < m) v |= (uint32_t)(f[4 * b + k] & 3u) << (2 * k);
-    out[b] = (uint8_t)v;
+  if (i == 0) {
+    out[UPD_ACC] = u[U_ERR];
+    out[UPD_ACC + 1] = u[U_NE];
+    out[UPD_ACC + 2] = u[U_ERR] ? 0 : (uint64_t)S[u[U_NE]];
   }
 }
 
 __global__ void k_zero32(uint32_t* p, int64_t m) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) p[i] = 0;
-}
-
-__global__ void k_copy_words(const uint32_t* __restrict__ a, uint32_t* __restrict__ b, int64_t m) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) b[i] = a[i];
-}
-__global__ void k_copy_bytes(const uint8_t* __restrict__ a, uint8_t* __restrict__ b, int64_t m) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) b[i] = a[i];
-}
-__global__ void k_copy_i64(const int64_t* __restrict__ a, int64_t* __restrict__ b, int64_t m) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) b[i] = a[i];
 }
 
 }  // namespace
@@ -608,87 +670,77 @@ int census_update(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     return fail(TRIAD_EINVAL, "NULL pointer argument");
   const bool new_csr = noff != nullptr;
   if (new_csr && (!nnz_new || !nnbr || !nflg)) return fail(TRIAD_EINVAL, "NULL pointer for the new CSR");
+  DeviceInfo di;
+  if (int st = device_info(&di)) return st;
   Scratch scratch(s, 0, true);
   const int rb = std::max(1, 64 - __builtin_clzll((unsigned long long)std::max<int64_t>(n, 1)));
-  uint32_t* err = nullptr;
-  unsigned long long* delta = nullptr;
-  uint32_t* tot = nullptr;
-  ALLOC(err, 1);
-  ALLOC(delta, 16);
-  ALLOC(tot, 4);
-  k_zero32<<<1, 64, 0, s>>>(err, 1);
-  k_zero32<<<1, 64, 0, s>>>((uint32_t*)delta, 32);
-  k_zero32<<<1, 64, 0, s>>>(tot, 4);
-  int64_t np = 0, K = 0;
-  uint64_t* E = nullptr;
-  if (k > 0) {
+  const UpdGraph g{n, nnz, off, nbr, flg, rb};
+  const int64_t N = 2 * k;  // keys, and at most as many changed entries
+  constexpr int ZERO = 2 * UPD_COPIES * UPD_ACC + U_WORDS;
+  uint32_t* zero = nullptr;
+  uint64_t *out = nullptr, *E = nullptr, *queue = nullptr;
+  uint32_t* P = nullptr;
+  int64_t* S = nullptr;
+  ALLOC(zero, ZERO);
+  ALLOC(out, UPD_ACC + 3);
+  ALLOC(E, N);
+  ALLOC(P, N);
+  ALLOC(S, N + 1);
+  ALLOC(queue, std::min(UPD_QUEUE, N * UPD_PARTS));
+  unsigned long long* acc = (unsigned long long*)zero;
+  uint32_t* u = zero + 2 * UPD_COPIES * UPD_ACC;
+  k_zero32<<<2, 256, 0, s>>>(zero, ZERO);
+  if (k <= UPD_SMALL) {
+    k_upd_small<<<1, SMALL_T, 0, s>>>(g, (int)k, src, dst, ins, E, P, S, u);
+  } else {
     uint64_t *ka = nullptr, *kb = nullptr;
-    ALLOC(ka, k);
-    ALLOC(kb, k);
-    k_upd_keys<<<grid_of(k, 256, 65536), 256, 0, s>>>(n, k, rb, src, dst, ins, ka, err);
-    uint32_t eh = 0;
-    HIPCHK(hipMemcpyAsync(&eh, err, sizeof eh, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    if (eh) return fail(status_from_bits(eh), eh & ERR_RANGE ? "update endpoint outside [0, n) or kind not 0/1"
-                                                             : "update on a self-loop");
-    // by (pair, direction); operations keep their batch order within an arc
-    if (int st = radix_sort_u64(&ka, &kb, k, 1, 2 + 2 * rb, scratch, s)) return st;
-    uint32_t *head = nullptr, *hpos = nullptr;
-    ALLOC(head, k);
-    ALLOC(hpos, k);
-    k_run_heads<<<grid_of(k, 256, 65536), 256, 0, s>>>(ka, k, 2, head);
-    if (int st = scan_u32(head, k, hpos, tot, scratch, s)) return st;
-    uint32_t h = 0;
-    HIPCHK(hipMemcpyAsync(&h, tot, sizeof h, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    np = h;
-    uint64_t* pkey = nullptr;
-    uint8_t* pf = nullptr;
-    uint32_t *chg = nullptr, *cpos = nullptr;
-    ALLOC(pkey, np);
-    ALLOC(pf, np);
-    ALLOC(chg, np);
-    ALLOC(cpos, np);
-    k_pair_state<<<grid_of(k, 256, 65536), 256, 0, s>>>(ka, k, rb, head, hpos, off, nbr, flg, pkey, pf, chg);
-    if (int st = scan_u32(chg, np, cpos, tot + 1, scratch, s)) return st;
-    HIPCHK(hipMemcpyAsync(&h, tot + 1, sizeof h, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    K = h;
-    if (K > 0) {
-      uint64_t* Eb = nullptr;
-      ALLOC(E, 2 * K);
-      ALLOC(Eb, 2 * K);
-      k_changed_keys<<<grid_of(np, 256, 65536), 256, 0, s>>>(pkey, pf, chg, cpos, np, rb, E);
-      if (int st = radix_sort_u64(&E, &Eb, 2 * K, 4, 4 + 2 * rb, scratch, s)) return st;
-      DeltaArgs g{};
-      g.n = n;
-      g.off = off;
-      g.nbr = nbr;
-      g.flg = flg;
-      g.rb = rb;
-      g.E = E;
-      g.nE = 2 * K;
-      for (int c = 0; c < 64; ++c) g.lut[c >> 4] |= (uint64_t)classify_code((unsigned)c) << (4 * (c & 15));
-      g.delta = delta;
-      uint32_t *nch = nullptr, *ipre = nullptr;
-      ALLOC(nch, 2 * K);
-      ALLOC(ipre, 2 * K + 1);
-      const uint32_t maxch = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(4096, 0xFFFFFFFFll / (2 * K)));
-      k_pair_chunks<<<grid_of(2 * K, 256, 65536), 256, 0, s>>>(E, 2 * K, rb, off, maxch, nch);
-      if (int st = scan_u32(nch, 2 * K, ipre, ipre + 2 * K, scratch, s)) return st;
-      g.ipre = ipre;
-      k_upd_delta<<<grid_of(2 * K * 64, UT, 8192), UT, 0, s>>>(g);
-      HIPCHK(hipGetLastError());
-    }
+    uint32_t *chg = nullptr, *cpos = nullptr, *pos = nullptr;
+    uint8_t* st8 = nullptr;
+    int64_t* net = nullptr;
+    ALLOC(ka, N);
+    ALLOC(kb, N);
+    ALLOC(chg, N);
+    ALLOC(cpos, N);
+    ALLOC(pos, N);
+    ALLOC(st8, N);
+    ALLOC(net, N);
+    k_upd_keys<<<grid_of(k, 256, 65536), 256, 0, s>>>(g, k, src, dst, ins, ka, u);
+    // by (row, column, direction); operations keep their batch order within an arc
+    if (int st = radix_sort_u64(&ka, &kb, N, 1, 2 + 2 * rb, scratch, s)) return st;
+    k_upd_state<<<grid_of(N, 256, 65536), 256, 0, s>>>(g, ka, N, chg, st8, pos, u);
+    if (int st = scan_u32(chg, N, cpos, u + U_NE, scratch, s)) return st;
+    k_upd_emit<<<grid_of(N, 256, 65536), 256, 0, s>>>(ka, N, chg, cpos, st8, pos, E, P, net, u);
+    if (int st = scan_i64(net, N, S, scratch, s)) return st;
   }
-  // the census after the batch
-  uint64_t dh[16];
-  HIPCHK(hipMemcpyAsync(dh, delta, sizeof dh, hipMemcpyDeviceToHost, s));
+  DeltaArgs a{g, E, {}, acc, u, queue};
+  for (int c = 0; c < 64; ++c) a.lut[c >> 4] |= (uint64_t)classify_code((unsigned)c) << (4 * (c & 15));
+  if (k > 0) {
+    const unsigned waves4 = (unsigned)grid_of(N * 64, UT, di.cus * 8);
+    k_upd_rows<<<waves4, UT, 0, s>>>(a);
+    k_upd_pairs<false><<<waves4, UT, 0, s>>>(a);
+    k_upd_pairs<true><<<(unsigned)grid_of(std::min(UPD_QUEUE, N * UPD_PARTS) * 64, UT, di.cus * 8), UT, 0, s>>>(a);
+  }
+  if (new_csr) {
+    k_new_offsets<<<grid_of(n + 1, 256, 65536), 256, 0, s>>>(g, E, S, noff, u);
+    if (nnz + N > 0) k_upd_copy<<<grid_of(nnz + N, CT, di.cus * 16), UT, 0, s>>>(g, E, P, S, nnbr, nflg, u);
+  }
+  k_upd_done<<<1, 64, 0, s>>>(acc, u, S, out);
+  HIPCHK(hipGetLastError());
+  uint64_t oh[UPD_ACC + 3];
+  HIPCHK(hipMemcpyAsync(oh, out, sizeof oh, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  const uint32_t eh = (uint32_t)oh[UPD_ACC];
+  if (eh) return fail(status_from_bits(eh), eh & ERR_RANGE ? "update endpoint outside [0, n) or kind not 0/1"
+                                                           : "update on a self-loop");
+  // the census after the batch
+  uint64_t d[16];
+  for (int t = 0; t < 16; ++t) d[t] = oh[t];
+  d[2] += (uint64_t)n * (uint64_t)((int64_t)oh[SUMS_MUT] / 2);
+  open_wedges(d);
   uint64_t res[17];
   unsigned __int128 sum = 0;
   for (int t = 1; t < 16; ++t) {
-    res[t] = cin[t] + dh[t];
+    res[t] = cin[t] + d[t];
     sum += res[t];
   }
   uint64_t clo, chi;
@@ -696,47 +748,9 @@ int census_update(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
   const unsigned __int128 nul = (((unsigned __int128)chi << 64) | clo) - sum;
   res[0] = (uint64_t)nul;
   res[16] = (uint64_t)(nul >> 64);
-  // the CSR after the batch
-  int64_t nn = nnz;
-  if (new_csr) {
-    if (K == 0) {
-      k_copy_i64<<<grid_of(n + 1, 256, 65536), 256, 0, s>>>(off, noff, n + 1);
-      if (nnz > 0) {
-        k_copy_words<<<grid_of(nnz, 256, 65536), 256, 0, s>>>((const uint32_t*)nbr, (uint32_t*)nnbr, nnz);
-        k_copy_bytes<<<grid_of((nnz + 3) / 4, 256, 65536), 256, 0, s>>>(flg, nflg, (nnz + 3) / 4);
-      }
-    } else {
-      const int64_t nE = 2 * K;
-      uint32_t *ik = nullptr, *dk = nullptr, *I = nullptr, *D = nullptr, *mark = nullptr;
-      uint8_t* nf8 = nullptr;
-      ALLOC(ik, nE + 1);
-      ALLOC(dk, nE + 1);
-      ALLOC(I, nE + 1);
-      ALLOC(D, nE + 1);
-      ALLOC(mark, (n >> 5) + 1);
-      k_change_kinds<<<grid_of(nE + 1, 256, 65536), 256, 0, s>>>(E, nE, ik, dk);
-      if (int st = scan_u32(ik, nE + 1, I, tot + 2, scratch, s)) return st;
-      if (int st = scan_u32(dk, nE + 1, D, tot + 3, scratch, s)) return st;
-      uint32_t idt[2];
-      HIPCHK(hipMemcpyAsync(idt, tot + 2, sizeof idt, hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      nn = nnz + (int64_t)idt[0] - (int64_t)idt[1];
-      ALLOC(nf8, nn);
-      k_zero32<<<grid_of((n >> 5) + 1, 256, 4096), 256, 0, s>>>(mark, (n >> 5) + 1);
-      k_row_marks<<<grid_of(nE, 256, 65536), 256, 0, s>>>(E, nE, rb, mark);
-      k_new_offsets<<<grid_of(n + 1, 256, 65536), 256, 0, s>>>(n, rb, off, E, nE, I, D, noff);
-      if (nnz > 0)
-        k_copy_old<<<grid_of(nnz, ETILE, 65536), UT, 0, s>>>(n, nnz, rb, off, nbr, flg, E, nE, I, D, mark, noff,
-                                                                 nn, nnbr, nf8);
-      k_insert_new<<<grid_of(nE, 256, 65536), 256, 0, s>>>(rb, off, nbr, E, nE, I, D, noff, nn, nnbr, nf8);
-      k_pack_bytes<<<grid_of((nn + 3) / 4, 256, 65536), 256, 0, s>>>(nf8, nn, nflg);
-      HIPCHK(hipGetLastError());
-    }
-    HIPCHK(hipStreamSynchronize(s));
-    *nnz_new = nn;
-  }
+  if (new_csr) *nnz_new = nnz + (int64_t)oh[UPD_ACC + 2];
   std::memcpy(cout, res, sizeof res);
-  if (changed_pairs) *changed_pairs = K;
+  if (changed_pairs) *changed_pairs = (int64_t)oh[UPD_ACC + 1] / 2;
   return res[16] ? TRIAD_OK_003_WRAPPED : TRIAD_OK;
 }
 

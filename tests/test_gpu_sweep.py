@@ -185,3 +185,59 @@ def test_labelled_cliques(torch, sizes):
     assert c[21] == want
     assert sum(c) == comb(n, 3)
     assert all(c[s] == 0 for s in range(64) if s not in (0, 1, 4, 16, 21))
+
+
+def _updated(n, s, d, ops):
+    """Arcs after the operations (source, target, insert), in order."""
+    arcs = set(zip(s.tolist(), d.tolist()))
+    for a, b, i in ops:
+        (arcs.add if i else arcs.discard)((a, b))
+    a = np.array(sorted(arcs), np.int32).reshape(-1, 2)
+    return a[:, 0], a[:, 1]
+
+
+def _check_update(torch, n, s, d, ops):
+    g = graphs.build_csr(n, s, d)
+    s, d = g.arcs()
+    t = [torch.tensor([o[i] for o in ops], dtype=torch.uint8 if i == 2 else torch.int32, device="cuda") for i in range(3)]
+    dev = triad.to_device(g)
+    got, new, changed = triad.census_update(n, g.nnz, *dev, oracle.census_mt(g), *t)
+    want = graphs.build_csr(n, *_updated(n, s, d, ops))
+    assert got == oracle.census_mt(want)
+    for x, y in zip(new, (want.offsets, want.nbrs, want.flags)):
+        assert np.array_equal(x.cpu().numpy(), y)
+    none = triad.census_update(n, g.nnz, *dev, oracle.census_mt(g), *t, new_csr=False)
+    assert none[0] == got and none[1] is None and none[2] == changed
+
+
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 2047, 2048, 2049, 5000])
+def test_update_batch_sizes(torch, k):
+    """Around the batches that one workgroup sorts; repeated operations on few
+    vertices, so that runs of operations and shared changed rows occur."""
+    rng = np.random.default_rng(k)
+    n = 700
+    s, d = rng.integers(0, n, 6000), rng.integers(0, n, 6000)
+    keep = s != d
+    ops = []
+    while len(ops) < k:
+        a, b = (int(x) for x in rng.integers(0, n if len(ops) % 3 else 40, 2))
+        if a != b:
+            ops.append((a, b, int(rng.random() < 0.5)))
+    _check_update(torch, n, s[keep].astype(np.int32), d[keep].astype(np.int32), ops)
+
+
+def test_update_long_rows(torch):
+    """Two rows of 5,000 shared neighbours (their pair is searched in parts) that
+    change, and a row that gains and loses thousands of neighbours in a few
+    tiles of the new CSR (more changes than a tile stages)."""
+    rng = np.random.default_rng(3)
+    n = 9000
+    leaf = rng.permutation(np.arange(3, n))
+    s = np.concatenate([np.full(6000, 0), np.full(6000, 1), np.full(3000, 2), rng.integers(3, n, 4000)])
+    d = np.concatenate([leaf[:6000], leaf[1000:7000], leaf[:3000], rng.integers(3, n, 4000)])
+    keep = s != d
+    ops = [(0, 1, 1), (1, 0, 1)] + [(2, int(x), 0) for x in leaf[:2500]] + [(int(x), 2, 1) for x in leaf[3000:8000]]
+    ops += [(0, int(x), 0) for x in leaf[:40]] + [(int(x), 1, 1) for x in leaf[1000:1040]]
+    order = rng.permutation(len(ops))
+    _check_update(torch, n, s[keep].astype(np.int32), d[keep].astype(np.int32), [ops[i] for i in order])
+    _check_update(torch, n, s[keep].astype(np.int32), d[keep].astype(np.int32), ops[:2])
