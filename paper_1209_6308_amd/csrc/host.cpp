@@ -221,6 +221,20 @@ void choose3(int64_t n, uint64_t* lo, uint64_t* hi) {
   *hi = (uint64_t)(r >> 64);
 }
 
+int validate_offsets(int64_t n, const int64_t* off, const int32_t* nbr, const uint8_t* flg) {
+  if (n < 0 || n >= ((int64_t)1 << 30)) return fail(TRIAD_EINVAL, "n must be in [0, 2^30)");
+  if (!off) return fail(TRIAD_EINVAL, "csr_offsets is NULL");
+  if (off[0] != 0) return fail(TRIAD_ERANGE, "csr_offsets[0] != 0");
+  const int64_t nnz = off[n];
+  if (nnz < 0 || nnz >= ((int64_t)1 << 40)) return fail(TRIAD_ERANGE, "nnz out of range");
+  if (nnz > 0 && (!nbr || !flg)) return fail(TRIAD_EINVAL, "csr_nbrs or dir_flags is NULL");
+  for (int64_t x = 0; x < n; ++x) {
+    if (off[x + 1] < off[x]) return fail(TRIAD_ERANGE, "csr_offsets not monotone at row " + std::to_string(x));
+    if (off[x + 1] - off[x] >= ((int64_t)1 << 31)) return fail(TRIAD_EINVAL, "degree >= 2^31");
+  }
+  return TRIAD_OK;
+}
+
 int device_info(DeviceInfo* out) {
   static std::mutex mu;
   static DeviceInfo cache[64];
@@ -269,16 +283,7 @@ int triad_test_inject_device_error(int32_t count) {
 }
 
 int triad_validate_host(int64_t n, const int64_t* off, const int32_t* nbr, const uint8_t* flg, int32_t level) {
-  if (n < 0 || n >= ((int64_t)1 << 30)) return fail(TRIAD_EINVAL, "n must be in [0, 2^30)");
-  if (!off) return fail(TRIAD_EINVAL, "csr_offsets is NULL");
-  if (off[0] != 0) return fail(TRIAD_ERANGE, "csr_offsets[0] != 0");
-  const int64_t nnz = off[n];
-  if (nnz < 0 || nnz >= ((int64_t)1 << 40)) return fail(TRIAD_ERANGE, "nnz out of range");
-  if (nnz > 0 && (!nbr || !flg)) return fail(TRIAD_EINVAL, "csr_nbrs or dir_flags is NULL");
-  for (int64_t x = 0; x < n; ++x) {
-    if (off[x + 1] < off[x]) return fail(TRIAD_ERANGE, "csr_offsets not monotone at row " + std::to_string(x));
-    if (off[x + 1] - off[x] >= ((int64_t)1 << 31)) return fail(TRIAD_EINVAL, "degree >= 2^31");
-  }
+  if (int st = validate_offsets(n, off, nbr, flg)) return st;
   uint32_t bits = 0;
   for (int64_t x = 0; x < n && !(bits & ERR_RANGE); ++x) {
     for (int64_t j = off[x]; j < off[x + 1]; ++j) {

@@ -51,6 +51,9 @@ struct LabTables {
 LabTables lab_tables();
 int classify_code(unsigned code);  // 0..15, standard order
 
+// The checks of triad_validate_host that need no entry: sizes, pointers, offsets.
+int validate_offsets(int64_t n, const int64_t* off, const int32_t* nbr, const uint8_t* flg);
+
 // C(n,3) as (lo, hi) 64-bit words.
 void choose3(int64_t n, uint64_t* lo, uint64_t* hi);
 

@@ -241,3 +241,47 @@ def test_update_long_rows(torch):
     order = rng.permutation(len(ops))
     _check_update(torch, n, s[keep].astype(np.int32), d[keep].astype(np.int32), [ops[i] for i in order])
     _check_update(torch, n, s[keep].astype(np.int32), d[keep].astype(np.int32), ops[:2])
+
+
+@pytest.mark.parametrize("scale", [8, 15])
+def test_host_entry_finds_what_the_host_check_finds(torch, scale):
+    """Faulty host arrays, one and several faults at a time, at both levels of
+    validation: the host-pointer entry returns the status of triad_validate_host."""
+    g = graphs.rmat(scale, 6, seed=2, recip_p=0.2)
+    rows = np.flatnonzero(np.diff(g.offsets) >= 3)
+    rng = np.random.default_rng(scale)
+
+    def unsorted(off, nb, fl, r):
+        b = off[r]
+        nb[b], nb[b + 1] = nb[b + 1], nb[b]
+
+    def loop(off, nb, fl, r):
+        nb[off[r]:off[r + 1]] = np.sort(np.concatenate([[r], nb[off[r]:off[r + 1]][1:]]))
+
+    def wild(off, nb, fl, r):
+        nb[off[r] + 1] = g.n + 7 if r % 2 else -3
+
+    def noflag(off, nb, fl, r):
+        fl[off[r] >> 2] = 0
+
+    def onesided(off, nb, fl, r):
+        fl[off[r] >> 2] ^= 1 << (2 * (off[r] & 3)) if (fl[off[r] >> 2] >> (2 * (off[r] & 3)) & 3) != 1 else 3 << (2 * (off[r] & 3))
+
+    def offsets(off, nb, fl, r):
+        off[r] = off[r + 1] + 1
+
+    faults = [unsorted, loop, wild, noflag, onesided, offsets]
+    for i, f in enumerate(faults):
+        for h in [None] + faults[i:]:
+            off, nb, fl = g.offsets.copy(), g.nbrs.copy(), g.flags.copy()
+            f(off, nb, fl, int(rng.choice(rows)))
+            if h is not None:
+                h(off, nb, fl, int(rng.choice(rows)))
+            for level in (0, 1):
+                want = triad.triad_validate_host(g.n, off, nb, fl, level)
+                if want == triad.OK:  # level 0 does not look at symmetry; the census refuses uneven sides
+                    continue
+                with pytest.raises(triad.TriadError) as e:
+                    triad.triad_census(g.n, off, nb, fl, validate=level)
+                assert e.value.status == want, (f.__name__, h and h.__name__, level)
+    assert triad.triad_census(g.n, g.offsets, g.nbrs, g.flags, validate=1) == oracle.census_mt(g)
