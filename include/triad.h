@@ -236,8 +236,8 @@ int triad_batch_autotune(int32_t G, int64_t nv, int64_t nnz, const int64_t *d_vb
  * construction measured with HIP events on the stream. Limits: n < 2^30,
  * narcs < 2^31. Errors: TRIAD_EINVAL (sizes, NULL pointers), TRIAD_ERANGE (an
  * endpoint outside [0, n); no output is written), TRIAD_ENOMEM. Scratch comes
- * from the library's held blocks (see triad_held_memory), about 35 bytes per
- * arc. The call waits for its work on hip_stream before returning. */
+ * from the library's held blocks (see triad_held_memory), at most about 35 bytes
+ * per arc (22 where there are many arcs a vertex). The call waits for its work on hip_stream before returning. */
 int triad_csr_from_arcs(int64_t n, int64_t narcs, const int32_t *d_src, const int32_t *d_dst, void *hip_stream,
                         int64_t *d_offsets, int32_t *d_nbrs, uint8_t *d_flags, int64_t *nnz_out,
                         float *device_ms);

@@ -173,9 +173,10 @@ __device__ int64_t block_excl_scan(int64_t v, int64_t* sh, int64_t* total) {
 
 __global__ void k_scan_sums(const int64_t* __restrict__ in, int64_t m, int64_t* __restrict__ bsum) {
   __shared__ int64_t sh[SCAN_T / 64 + 1];
-  int64_t base = (int64_t)blockIdx.x * SCAN_B + (int64_t)threadIdx.x * SCAN_I, s = 0;
+  const int64_t base = (int64_t)blockIdx.x * SCAN_B + threadIdx.x;
+  int64_t s = 0;
   for (int k = 0; k < SCAN_I; ++k)
-    if (base + k < m) s += in[base + k];
+    if (base + k * SCAN_T < m) s += in[base + k * SCAN_T];
   int64_t tot;
   block_excl_scan(s, sh, &tot);
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
@@ -198,8 +199,8 @@ __global__ void k_scan_top(int64_t* __restrict__ bsum, int64_t nb) {
   }
 }
 
-__global__ void k_scan_apply(const int64_t* __restrict__ in, int64_t m, const int64_t* __restrict__ bsum,
-                             int64_t* __restrict__ out) {
+// in may be out: a thread reads its values before it writes them.
+__global__ void k_scan_apply(const int64_t* in, int64_t m, const int64_t* __restrict__ bsum, int64_t* out) {
   __shared__ int64_t sh[SCAN_T / 64 + 1];
   int64_t base = (int64_t)blockIdx.x * SCAN_B + (int64_t)threadIdx.x * SCAN_I, loc[SCAN_I], s = 0;
   for (int k = 0; k < SCAN_I; ++k) {
@@ -1217,19 +1218,25 @@ static int grid_for(int64_t work, int threads, int cap = 65536) {
   return (int)g;
 }
 
-int scan_i64(const int64_t* in, int64_t m, int64_t* out, Scratch& scratch, hipStream_t s) {
+int64_t scan_sums(int64_t m) { return (m + SCAN_B - 1) / SCAN_B + 1; }
+
+int scan_i64_with(const int64_t* in, int64_t m, int64_t* out, int64_t* sums, hipStream_t s) {
   const int64_t nb = (m + SCAN_B - 1) / SCAN_B;
-  int64_t* bsum = nullptr;
-  ALLOC(bsum, nb + 1);
   if (m > 0) {
-    k_scan_sums<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, bsum);
-    k_scan_top<<<1, SCAN_T, 0, s>>>(bsum, nb);
-    k_scan_apply<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, bsum, out);
+    k_scan_sums<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, sums);
+    k_scan_top<<<1, SCAN_T, 0, s>>>(sums, nb);
+    k_scan_apply<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, sums, out);
   } else {
     k_fill_u64<<<1, 64, 0, s>>>((uint64_t*)out, 1, 0);
   }
   HIPCHK(hipGetLastError());
   return TRIAD_OK;
+}
+
+int scan_i64(const int64_t* in, int64_t m, int64_t* out, Scratch& scratch, hipStream_t s) {
+  int64_t* sums = nullptr;
+  ALLOC(sums, scan_sums(m));
+  return scan_i64_with(in, m, out, sums, s);
 }
 
 // Kernel variants: LDS window per list x counter array layout x occupancy hint.
@@ -1789,18 +1796,6 @@ __global__ void k_batch_signature(int32_t G, int64_t nv, const int64_t* __restri
   }
 }
 
-// Three-pass exclusive scan with caller-provided block sums (capturable).
-static void scan_excl_pre(const int64_t* in, int64_t m, int64_t* out, int64_t* bsum, hipStream_t s) {
-  const int64_t nb = (m + SCAN_B - 1) / SCAN_B;
-  if (m > 0) {
-    k_scan_sums<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, bsum);
-    k_scan_top<<<1, SCAN_T, 0, s>>>(bsum, nb);
-    k_scan_apply<<<(unsigned)nb, SCAN_T, 0, s>>>(in, m, bsum, out);
-  } else {
-    k_fill_u64<<<1, 64, 0, s>>>((uint64_t*)out, 1, 0);
-  }
-}
-
 }  // namespace triad
 
 struct triad_batch_plan {
@@ -1957,7 +1952,7 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
       if (nnz > 0)
         k_entries_batch<<<grid_for(nnz, ETILE, 65536), 256, 0, s>>>(G, nnz, vbase, off, nbr, flg, rowmark, packed,
                                                                    p->err);
-      scan_excl_pre(ntask, nv, tpre, bsum, s);
+      if (int st = scan_i64_with(ntask, nv, tpre, bsum, s)) return st;
       k_check_tasks<<<1, 64, 0, s>>>(tpre, nv, nnz, p->err);
       if (ntasks > 0) {
         const EmitArgs ea{nv, off, packed, ustart, tpre, tasks, tskip, 0, -1, p->err, nullptr, nullptr};
