@@ -11,9 +11,9 @@
 // highest degree), and for a vertex y the list N+(x) of every x below y is
 // streamed against the set N+(y). The merge reads sum_x d(x)^2 list entries
 // (3.57e12 at R-MAT scale 24), this reads sum_x d+(x)^2 / 2 (4.2e10). A whole
-// call took 1,560 ms there by the merge and takes 60 ms; 37.0 and 2.9 ms at
-// R-MAT scale 20, 472 and 16.7 ms on the Chung-Lu graph of 2^22 vertices, 575
-// and 140 us at R-MAT scale 10.
+// call took 1,560 ms there by the merge and takes 44.7 ms; 36.9 and 2.35 ms at
+// R-MAT scale 20, 469 and 13.2 ms on the Chung-Lu graph of 2^22 vertices, 566
+// and 78 us at R-MAT scale 10.
 //
 // Pipeline (one stream, no host synchronisation inside):
 //   k_sw_rows    per row: offset checks, row starts, degree histogram
@@ -23,8 +23,10 @@
 //                below it, ids and flags); per-row flag counts turned into
 //                wedge and dyad sums
 //   k_sw_cross   the rows that cross tile boundaries
+//   k_sw_items   work items of k_sw_hubs and k_sw_mids
+//   k_sw_pack    large graphs: places of the N+(x) in 16-bit ranks, the short ones
 //   k_sw_sort_*  N+(x) sorted by rank where it is longer than one wavefront
-//   k_sw_items   work items of the next two
+//                (and packed)
 //   k_sw_hubs    vertices with long in-lists: a workgroup holds N+(y) as a
 //                byte table over the ranks and streams the N+(x)
 //   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
@@ -34,8 +36,8 @@
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
 // A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_small
 // as one disjoint union with ids local to each graph, its counters by graph
-// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 32.9 ms a launch; 256
-// graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.57 ms). The labelled
+// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 18.9 ms a launch; 256
+// graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.37 ms). The labelled
 // census adds k_lab_sums (54.9 -> 3.8 ms at R-MAT scale 20).
 #include <hip/hip_runtime.h>
 
@@ -65,6 +67,7 @@ constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work i
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
 constexpr int TAB_WORDS = 1024;        // its slots
 constexpr int REST_WAVES = 4;
+constexpr int64_t PACK_MIN = 6 << 20;   // entries from which N+ lists are packed for k_sw_hubs
 constexpr int64_t LIST_PAD = 4;        // list words read past a list's end
 constexpr uint32_t SORT_MIN = 64, SORT_MID = 256, SORT_MAX = 4096;
 
@@ -856,15 +859,45 @@ __global__ void __launch_bounds__(256) k_lab_cross(LabArgs a) {
 __device__ __forceinline__ uint32_t to_key(uint32_t w, int r) { return __builtin_amdgcn_alignbit(w, w, 32 - r); }
 __device__ __forceinline__ uint32_t of_key(uint32_t k, int r) { return __builtin_amdgcn_alignbit(k, k, r); }
 
+// Half a packed block from four sort keys (flags of 2 bits): 16-bit ranks, and
+// flags, those of the even entries in the low byte (the order in which k_sw_hubs
+// assembles what it reads from its table); the second half's flags go 4 bits up.
+// Ranks past the table and places past a list's end (key ~0) get the flag 0,
+// which counts for nothing.
+__device__ __forceinline__ uint2 pack_ranks(const uint32_t* k) {
+  uint32_t h[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) h[i] = min(k[i] >> 2, 0xFFFFu);
+  return make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+}
+__device__ __forceinline__ uint32_t pack_flags(const uint32_t* k) {
+  uint32_t f[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = k[i] >> 2 < (uint32_t)HUB_RANKS ? k[i] & 3u : 0u;
+  return f[0] | f[2] << 2 | f[1] << 8 | f[3] << 10;
+}
+
+// Where the lists go packed (see k_sw_pack); prow NULL: nowhere.
+struct Packed {
+  const uint64_t* prow;
+  uint4* pack;
+  const uint32_t* hubs;  // number of items of k_sw_hubs: without any, prow is not written
+};
+// Block k of a packed list that starts at unit u: its ranks' unit, its flags'
+// 16-bit word.
+__device__ __forceinline__ uint32_t rank_unit(uint32_t u, uint32_t k) { return u + (k >> 3) * 9 + 1 + (k & 7); }
+__device__ __forceinline__ uint64_t flag_word(uint32_t u, uint32_t k) {
+  return (uint64_t)(u + (k >> 3) * 9) * 8 + (k & 7);
+}
+
 // N+ lists of 65 to 256 entries, one wavefront each: a bitonic network over
 // four registers a lane.
 __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict__ rows,
                                                      const uint32_t* __restrict__ count,
                                                      const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
-                                                     const uint32_t* __restrict__ err,
-                                                      int rot, uint64_t* __restrict__ clk) {
-  stamp(clk, 1);
+                                                     const uint32_t* __restrict__ err, int rot, Packed pk) {
   if (err[0] | err[1]) return;
+  const bool pack = pk.prow && *pk.hubs;
   const int lane = threadIdx.x & 63;
   const uint32_t nw = gridDim.x * 4, cnt = *count;
   for (uint32_t r = blockIdx.x * 4 + (threadIdx.x >> 6); r < cnt; r += nw) {
@@ -902,6 +935,14 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if ((uint32_t)(lane * 4 + e) < len) p[lane * 4 + e] = of_key(k[e], rot);
+    if (pack) {
+      const uint32_t u = (uint32_t)(pk.prow[rows[r]] >> 32), b = lane >> 1;
+      const uint32_t f = pack_flags(k), f1 = __shfl_xor(f, 1, 64);
+      if (8 * b < len) {
+        reinterpret_cast<uint2*>(pk.pack)[2 * (uint64_t)rank_unit(u, b) + (lane & 1)] = pack_ranks(k);
+        if (!(lane & 1)) reinterpret_cast<uint16_t*>(pk.pack)[flag_word(u, b)] = (uint16_t)(f | f1 << 4);
+      }
+    }
   }
 }
 
@@ -909,10 +950,10 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
 __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict__ rows,
                                                       const uint32_t* __restrict__ count,
                                                       const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
-                                                      const uint32_t* __restrict__ err,
-                                                      int rot) {
+                                                      const uint32_t* __restrict__ err, int rot, Packed pk) {
   __shared__ uint32_t k[SORT_MAX];
   if (err[0] | err[1]) return;
+  const bool pack = pk.prow && *pk.hubs;
   const uint32_t cnt = *count;
   for (uint32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
     const uint64_t in = info[rows[r]];
@@ -937,6 +978,15 @@ __global__ void __launch_bounds__(256) k_sw_sort_long(const uint32_t* __restrict
         __syncthreads();
       }
     for (uint32_t i = threadIdx.x; i < len; i += 256) p[i] = of_key(k[i], rot);
+    if (pack) {
+      const uint32_t u = (uint32_t)(pk.prow[rows[r]] >> 32);
+      for (uint32_t b = threadIdx.x; 8 * b < len; b += 256) {
+        const uint2 r0 = pack_ranks(k + 8 * b), r1 = pack_ranks(k + 8 * b + 4);
+        pk.pack[rank_unit(u, b)] = make_uint4(r0.x, r0.y, r1.x, r1.y);
+        reinterpret_cast<uint16_t*>(pk.pack)[flag_word(u, b)] =
+            (uint16_t)(pack_flags(k + 8 * b) | pack_flags(k + 8 * b + 4) << 4);
+      }
+    }
   }
 }
 
@@ -1096,8 +1146,9 @@ struct XList {
 };
 
 // Lists the vertices of up to `cnt` in-list words g (one a lane) whose N+ has
-// at least two entries (y is one of them).
-template <bool LAB, bool WIDE>
+// at least two entries (y is one of them). PACK: their blocks instead (from
+// prow, in place of info).
+template <bool LAB, bool WIDE, bool PACK = false>
 __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict__ in, int cnt,
                                       const uint64_t* __restrict__ info, int lane) {
   uint64_t xi = 0;
@@ -1106,11 +1157,11 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
     g = in[lane];
     xi = info[g & IDM<LAB>];
   }
-  const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
+  const bool has = ((uint32_t)xi & LEN_MASK) >= (PACK ? 1 : 2);
   const uint64_t m = __ballot(has);
   if (has) {
     const int k = __popcll(m & below(lane));
-    L.p[k] = xi >> 24;
+    L.p[k] = PACK ? xi >> 32 : xi >> 24;
     L.m[k] = (g & ~IDM<LAB>) | ((uint32_t)xi & (LEN_MASK | UNSORTED));
   }
   return __popcll(m);
@@ -1198,7 +1249,7 @@ struct CountArgs {
   const uint32_t* tile_row;
   uint64_t* items[2];  // of k_sw_hubs, k_sw_mids: y << 32 | chunk
   uint64_t* clk;       // stage starts, or NULL
-  uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken
+  uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken, [6] units packed
   int64_t range;       // k_sw_rest: entries of one wavefront
   unsigned long long* acc;
   const uint32_t* err;
@@ -1206,6 +1257,9 @@ struct CountArgs {
   const int64_t* vbase;
   const uint32_t* grow;
   unsigned long long* gacc;
+  // N+ lists packed (k_sw_pack), or NULL
+  uint64_t* prow;
+  uint4* pack;
 };
 
 // Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
@@ -1218,6 +1272,7 @@ __device__ __forceinline__ uint32_t route(uint32_t rank, uint32_t plus, int64_t 
 
 __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
   __shared__ uint32_t cnt[2], base[2];
+  stamp(a.clk, 1);
   if (a.err[0] | a.err[1]) return;
   for (int64_t x0 = (int64_t)blockIdx.x * 4096; x0 < a.n; x0 += (int64_t)gridDim.x * 4096) {
     __syncthreads();
@@ -1255,9 +1310,170 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
   }
 }
 
+// N+ of two entries or more in blocks of eight for k_sw_hubs: 16 bytes of 16-bit
+// ranks and two bytes of flags, in groups of up to eight blocks: one unit of 16
+// bytes with the flags, then a unit of ranks a block, so that a step of k_sw_hubs
+// reads 144 bytes in a row. prow[x]: first unit << 32, the unsorted mark and the
+// blocks (0: none). Lists of 65 to SORT_MAX entries are written by the
+// kernels that sort them. One atomic takes the units of 256 * PER vertices (one
+// for 256 took 2.6 ms at 2^24 vertices: atomics on one word queue).
+template <int PER>
+__global__ void __launch_bounds__(256) k_sw_pack(CountArgs a) {
+  constexpr int V = 256 * PER;
+  __shared__ uint32_t pre[V], dst[V], ws[8], base;
+  __shared__ uint64_t row[V];
+  if (a.err[0] | a.err[1] || a.counts[2] == 0) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  for (int64_t x0 = (int64_t)blockIdx.x * V; x0 < a.n; x0 += (int64_t)gridDim.x * V) {
+    uint64_t xi[PER];
+    uint32_t nb[PER], fill[PER], all = 0, mine = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int64_t x = x0 + t * PER + i;
+      xi[i] = x < a.n ? a.info[x] : 0;
+      const uint32_t l = (uint32_t)xi[i] & LEN_MASK;
+      nb[i] = l >= 2 ? (l + 7) / 8 : 0;
+      fill[i] = l <= SORT_MIN || l > SORT_MAX ? nb[i] : 0;
+      all += nb[i] + (nb[i] + 7) / 8;
+      mine += fill[i];
+    }
+    uint32_t ea = all, em = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t va = __shfl_up(ea, o, 64), vm = __shfl_up(em, o, 64);
+      if (lane >= o) {
+        ea += va;
+        em += vm;
+      }
+    }
+    __syncthreads();
+    if (lane == 63) {
+      ws[w] = ea;
+      ws[4 + w] = em;
+    }
+    __syncthreads();
+    ea -= all;
+    em -= mine;
+    for (int q = 0; q < w; ++q) {
+      ea += ws[q];
+      em += ws[4 + q];
+    }
+    const uint32_t total = ws[0] + ws[1] + ws[2] + ws[3], todo = ws[4] + ws[5] + ws[6] + ws[7];
+    if (t == 0 && total) base = atomicAdd(&a.counts[6], total);
+    __syncthreads();
+    ea += base;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int64_t x = x0 + t * PER + i;
+      pre[t * PER + i] = em;
+      dst[t * PER + i] = ea;
+      row[t * PER + i] = xi[i];
+      if (x < a.n) a.prow[x] = nb[i] ? (uint64_t)ea << 32 | ((uint32_t)xi[i] & UNSORTED) | nb[i] : 0ull;
+      em += fill[i];
+      ea += nb[i] + (nb[i] + 7) / 8;
+    }
+    __syncthreads();
+    for (uint32_t b = t; b < todo; b += 256) {
+      uint32_t v = 0;  // the last list that starts at or before b
+#pragma unroll
+      for (int o = V / 2; o; o >>= 1)
+        if (pre[v + o] <= b) v += o;
+      const uint32_t k = b - pre[v], left = ((uint32_t)row[v] & LEN_MASK) - 8 * k;
+      const uint32_t* p = a.list + (row[v] >> 24) + 8 * k;
+      uint32_t q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      __builtin_memcpy(q, p, 16);
+      if (left > 4) __builtin_memcpy(q + 4, p + 4, 16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) q[i] = (uint32_t)i < left ? to_key(q[i], 2) : 0xFFFFFFFFu;
+      const uint2 r0 = pack_ranks(q), r1 = pack_ranks(q + 4);
+      a.pack[rank_unit(dst[v], k)] = make_uint4(r0.x, r0.y, r1.x, r1.y);
+      reinterpret_cast<uint16_t*>(a.pack)[flag_word(dst[v], k)] = (uint16_t)(pack_flags(q) | pack_flags(q + 4) << 4);
+    }
+  }
+}
+
+// Streams the cnt listed packed N+(x) against the table of y, one list per
+// eight lanes and a block of eight entries a lane, in two sets in turn as in
+// stream(). A step assembles 8 fields of f_yz, two bits each in the order of the
+// packed flags, without a shift a field: the table's bytes arrive in pairs.
+template <class T, class Table>
+__device__ __forceinline__ void stream_packed(const CountArgs& a, const XList<false>& L, int cnt, uint32_t yrank,
+                                              int lane, T& tri, const Table& tab) {
+  constexpr uint64_t G0 = 0x0101010101010101ull;
+  const int l8 = lane & 7;
+  const uint32_t lane_ranks = 16 + 16 * l8, to_flags = 16 + 14 * l8;
+  const uint64_t before = below(lane & 56);
+  struct Slot {
+    uint32_t o, g, lim;  // byte offset of the lane's next ranks; f_xy in each field; the rank that ends the list
+    int r;               // blocks of the list from there on (0 or less: none)
+    uint32_t w[4], f;
+  } sl[2];
+  auto load = [&](Slot& s) {
+    const uint32_t o = s.r > 0 ? s.o : lane_ranks;
+    __builtin_memcpy(s.w, (const char*)a.pack + o, 16);
+    s.f = *(const uint16_t*)((const char*)a.pack + (o - to_flags));
+  };
+  auto take = [&](Slot& s, int k) {
+    s.r = 0;
+    if (k < cnt) {
+      const uint32_t m = L.m[k];
+      s.o = (L.p[k] << 4) + lane_ranks;
+      s.r = (int)(m & LEN_MASK) - l8;
+      s.g = (m >> 30) * 0x00550055u;
+      // (lists of up to SORT_MIN entries, one step, are not sorted)
+      s.lim = (m & UNSORTED) || (m & LEN_MASK) <= SORT_MIN / 8 ? ~0u : yrank;
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    sl[i].o = sl[i].g = sl[i].lim = 0;
+    take(sl[i], i * 8 + lane / 8);
+    load(sl[i]);
+  }
+  int next = 16;
+  auto step = [&](Slot& s, uint32_t& X, uint32_t& Y, uint32_t& G) {
+    Y = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Y |= (uint32_t)tab[s.w[i] & 0xFFFFu] << (2 * i);
+      Y |= (uint32_t)tab[s.w[i] >> 16] << (16 + 2 * i);
+    }
+    X = s.r > 0 ? s.f : 0u;
+    G = s.g;
+    uint64_t d = __ballot(s.r <= 8) & G0;
+    d |= (__ballot((s.w[3] >> 16) >= s.lim) >> 7) & G0;
+    s.o += 144;
+    s.r -= 8;
+    if (d) {
+      const uint64_t all = (d << 8) - d;
+      if (__builtin_amdgcn_inverse_ballot_w64(all)) take(s, next + __popcll(d & before));
+      next += __popcll(d);
+    }
+    load(s);
+    // (the loads stay here, before the count: merged with those above the loop
+    // they would move to its head, half a round before their use)
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto any = [&]() { return __ballot(max(sl[0].r, sl[1].r) > 0) != 0; };
+  if (!any()) return;
+  do {
+    uint32_t X0, Y0, G0_, X1, Y1, G1;
+    step(sl[0], X0, Y0, G0_);
+    step(sl[1], X1, Y1, G1);
+    tri.X = __builtin_amdgcn_perm(X1, X0, 0x05010400);  // bytes X0[0], X1[0], X0[1], X1[1]
+    tri.Y = Y0 | Y1 << 8;
+    tri.G = G0_ | G1 << 8;
+    tri.count();
+  } while (any());
+}
+
 // Vertices with long in-lists: a workgroup takes up to CHUNK of one's in-list
-// and holds N+(y) as a byte per rank (z of N+(y) has a lower rank than y).
-template <bool LAB, bool WIDE>
+// and holds N+(y) as a byte per rank (z of N+(y) has a lower rank than y). Bound
+// by the bytes read past L2, 7.4 TB/s at R-MAT scale 24: 28.2 ms with lists of
+// 32-bit words; packed (PACK) 18.1, where ranks and flags in arrays of their own
+// took 21.9 (a line of flags for every line or two of ranks). Counting the classes
+// 32 candidates at a time instead of 16 saves a tenth of the vector instructions
+// but no time (35 ms: registers spill).
+template <bool LAB, bool WIDE, bool PACK>
 __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(CountArgs a) {
   constexpr int HUB_THREADS = hub_threads(LAB);
   __shared__ __align__(16) uint8_t tab[HUB_RANKS + 16];  // f_yz by rank of z; past the ranks: 0
@@ -1296,12 +1512,15 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
       if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
       k = __builtin_amdgcn_readfirstlane(k);
       if (k >= cnt) break;
-      const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+      const int nx = list_x<LAB, WIDE, PACK>(L, a.list + b + k, min(claim, cnt - k), PACK ? a.prow : a.info, lane);
       wave_sync();
-      stream<16, true, false, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4], uint32_t) {
+      if constexpr (PACK)
+        stream_packed(a, L, nx, yr, lane, tri, tab);
+      else
+        stream<16, true, false, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&f)[4], uint32_t) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & IDM<LAB>, (uint32_t)HUB_RANKS)];
-      });
+          for (int e = 0; e < 4; ++e) f[e] = tab[min(w[e] & IDM<LAB>, (uint32_t)HUB_RANKS)];
+        });
       wave_sync();
     }
     __syncthreads();
@@ -1760,7 +1979,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     words += (w + 1) & ~(int64_t)1;
     return at;
   };
-  const int64_t w_acc = place(2 * (labelled ? SW_LAB_WORDS : SW_WORDS) * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(6);
+  const int64_t w_acc = place(2 * (labelled ? SW_LAB_WORDS : SW_WORDS) * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(8);
   const int64_t w_hist = place(rank ? 2 * BUCKETS : 0);
   const int64_t w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
   const int64_t w_mark = place(ntiles * (OT / 32));
@@ -1810,7 +2029,17 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
   CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, clk, zero + w_cnt, 0, acc, err,
-               nullptr, nullptr, nullptr};
+               nullptr, nullptr, nullptr, nullptr, nullptr};
+  // N+ packed for the hubs: at most as many units as entries (two for two), whose
+  // byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
+  // entries (60,001 vertices, R-MAT: 322 -> 328 us); from there on it gains
+  // (6.3 M: 630 -> 619, 16 M: 1,242 -> 1,160 us, 33 M: 2.64 -> 2.35 ms). With
+  // fewer than two entries a vertex its scratch could pass the documented bound.
+  const bool pack = rank && !labelled && nnz >= 2 * n && nnz >= PACK_MIN && nnz < (int64_t)1 << 29;
+  if (pack) {
+    ALLOC(ca.prow, n);
+    ALLOC(ca.pack, nnz / 2 + 16);
+  }
   // a wavefront's range: small graphs spread over the chip, large ones in
   // ranges that spread the row search over more entries
   const int64_t waves = (int64_t)di.cus * (rank ? 32 : 16);
@@ -1827,12 +2056,23 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     if (rank) {
       k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
-      k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err, LAB ? 3 : 2, clk);
-      k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err, LAB ? 3 : 2);
       k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+      if (pack && n > 1 << 19) k_sw_pack<8><<<grid_of_work(n, 2048, INT32_MAX), 256, 0, s>>>(ca);
+      else if (pack) k_sw_pack<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ca);
+      const Packed pk{pack ? ca.prow : nullptr, ca.pack, ca.counts + 2};
+      k_sw_sort_mid<<<grid_of_work(nnz / SORT_MIN, 4, (int64_t)di.cus * 8), 256, 0, s>>>(mid, zero + w_cnt, info, list, err, LAB ? 3 : 2, pk);
+      k_sw_sort_long<<<grid_of_work(nnz / SORT_MID, 1, (int64_t)di.cus * 8), 256, 0, s>>>(lng, zero + w_cnt + 1, info, list, err, LAB ? 3 : 2, pk);
       auto count = [&](auto wide) {
         constexpr bool W = decltype(wide)::value;
-        k_sw_hubs<LAB, W><<<(unsigned)(di.cus * 2), hub_threads(LAB), 0, s>>>(ca);
+        if constexpr (!LAB && !W) {
+          if (pack) {
+            k_sw_hubs<false, false, true><<<(unsigned)(di.cus * 2), hub_threads(false), 0, s>>>(ca);
+          } else {
+            k_sw_hubs<false, false, false><<<(unsigned)(di.cus * 2), hub_threads(false), 0, s>>>(ca);
+          }
+        } else {
+          k_sw_hubs<LAB, W, false><<<(unsigned)(di.cus * 2), hub_threads(LAB), 0, s>>>(ca);
+        }
         k_sw_mids<LAB, W><<<(unsigned)(di.cus * (LAB ? 4 : 6)), MID_THREADS, 0, s>>>(ca);
         k_sw_rest<true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
       };
@@ -1863,7 +2103,7 @@ struct BatchSizes {
     };
     place(2 * SW_WORDS * SW_COPIES);  // acc first
     w_err = place(SW_ERRS);
-    w_cnt = place(6);
+    w_cnt = place(8);
     w_gacc = place(32 * (int64_t)graphs);
     w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
     w_mark = place(ntiles * (OT / 32));

@@ -105,6 +105,25 @@ def test_against_the_merge(torch, case):
     assert _census(g.n, d, validate=1) == want
 
 
+@pytest.mark.parametrize("n,k", [(20000, 2700), (600000, 2700), (900000, 1300)])
+def test_packed_lists(torch, n, k):
+    """A complete core of k vertices with arcs of all kinds (lists of every
+    length up to its size, in blocks of 8 and groups of 64 entries) among
+    sparse ones: packed by few and by many vertices at a time, and, with fewer
+    entries, not packed."""
+    rng = np.random.default_rng(n)
+    core = rng.permutation(n)[:k]
+    i, j = np.triu_indices(k, 1)
+    kind = rng.integers(0, 3, i.size)
+    s = np.concatenate([core[i[kind != 1]], core[j[kind != 0]], rng.integers(0, n, 100000)])
+    t = np.concatenate([core[j[kind != 1]], core[i[kind != 0]], rng.choice(core, 100000)])
+    g = graphs.build_csr(n, s.astype(np.int32), t.astype(np.int32))
+    d = triad.to_device(g)
+    want = _census(n, d, chunk=32768)
+    assert _census(n, d) == want
+    assert _census(n, d, validate=1) == want
+
+
 @pytest.mark.parametrize("n", [900, 40000])
 def test_one_sided_csr_is_refused(torch, n):
     """Entries above and below the diagonal that do not pair up."""
