@@ -1981,7 +1981,7 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
     Scratch arena(s, p->block, p->block_bytes);
     const SweepIn in{nv, nnz, off, nbr, flg};
     const int wpg = o.waves_per_group ? o.waves_per_group : 4;
-    const int groups = o.grid_groups > 0 ? o.grid_groups : sweep_batch_groups(wpg);
+    const int groups = o.grid_groups > 0 ? o.grid_groups : 2 * sweep_batch_groups(wpg);
     st = sweep_batch(G, nv, in, vbase, nmax, wpg, groups, batch_range(o.kernel_variant), d_out, &p->err, arena, s);
   }
   e = hipStreamEndCapture(s, &p->graph);

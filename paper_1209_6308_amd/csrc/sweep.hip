@@ -36,7 +36,7 @@
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
 // A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_small
 // as one disjoint union with ids local to each graph, its counters by graph
-// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 18.9 ms a launch; 256
+// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 17.1 ms a launch; 256
 // graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.37 ms). The labelled
 // census adds k_lab_sums (54.9 -> 3.8 ms at R-MAT scale 20).
 #include <hip/hip_runtime.h>
@@ -1699,11 +1699,13 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
 // their dependent reads overlap. (One row at a time: 17.3 ms on the 4,096-graph
 // batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10.
 // Bound by vector issue on the large batch, by the reads' latency on small ones.)
-template <int N, int R, bool BAT, bool LAB, bool WIDE>
-__global__ void __launch_bounds__(REST_WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_small(CountArgs a) {
+// WAVES: a batch plan's launch shape; tables for as many as the workgroup has
+// (with tables for four, workgroups of two took 26 ms on the large batch).
+template <int N, int R, bool BAT, bool LAB, bool WIDE, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_small(CountArgs a) {
   constexpr int TW = N >> FB<LAB>, LR = 64 / R;  // words of one table, lanes of one row
-  __shared__ uint32_t tabs[REST_WAVES][R * TW];
-  __shared__ XList<WIDE> xl[REST_WAVES];
+  __shared__ uint32_t tabs[WAVES][R * TW];
+  __shared__ XList<WIDE> xl[WAVES];
   stamp(a.clk, 1);
   stamp(a.clk, 2);
   if (a.err[0] | a.err[1]) return;
@@ -1808,11 +1810,19 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw
 
 // k_sw_small by the largest member: tables of 8 KB a wavefront in all (labelled
 // 16 KB), so that four workgroups fit a CU's LDS.
+template <bool BAT, bool LAB, bool WIDE, int WAVES>
+void launch_small_of(int64_t nmax, unsigned grid, const CountArgs& ca, hipStream_t s) {
+  if (nmax <= 4096) k_sw_small<4096, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  else if (nmax <= 8192) k_sw_small<8192, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  else k_sw_small<DIRECT_N, 2, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+}
 template <bool BAT, bool LAB, bool WIDE>
 void launch_small(int64_t nmax, unsigned grid, int waves, const CountArgs& ca, hipStream_t s) {
-  if (nmax <= 4096) k_sw_small<4096, 4, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
-  else if (nmax <= 8192) k_sw_small<8192, 4, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
-  else k_sw_small<DIRECT_N, 2, BAT, LAB, WIDE><<<grid, waves * 64, 0, s>>>(ca);
+  if constexpr (BAT) {
+    if (waves == 1) return launch_small_of<BAT, LAB, WIDE, 1>(nmax, grid, ca, s);
+    if (waves == 2) return launch_small_of<BAT, LAB, WIDE, 2>(nmax, grid, ca, s);
+  }
+  launch_small_of<BAT, LAB, WIDE, REST_WAVES>(nmax, grid, ca, s);
 }
 
 // ------------------------------------------------------------------- results
@@ -2113,7 +2123,7 @@ size_t sweep_batch_bytes(int32_t graphs, int64_t nv, int64_t nnz) {
 int sweep_batch_groups(int waves) {
   DeviceInfo di;
   if (device_info(&di) != TRIAD_OK) return 1024;
-  return di.cus * 32 / waves;
+  return di.cus * 64 / waves;
 }
 
 int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vbase, int64_t nmax, int waves,
@@ -2147,8 +2157,11 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
     k_sw_cross<false, true, false><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
     CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, nullptr, zero + z.w_cnt, range, acc,
                  err, vbase, grow, gacc};
-    // (by default 512 entries a turn, fewer where that leaves wavefronts idle)
-    if (range <= 0) range = std::max<int64_t>(64, std::min<int64_t>(512, (nnz / (di.cus * 16) + 63) & ~(int64_t)63));
+    // (by default 2,048 entries a turn, fewer where that leaves less than four
+    // turns a wavefront; 4,096 graphs, 3e8 edges: 19.5 ms with 512, 17.5 with
+    // these and twice the workgroups; 256 graphs of up to 1,024 vertices: 0.24
+    // with 2,048, 0.21 with fewer)
+    if (range <= 0) range = std::max<int64_t>(64, std::min<int64_t>(2048, (nnz / (di.cus * 64) + 63) & ~(int64_t)63));
     ca.range = range;
     const unsigned grid = grid_of_work((nnz + range - 1) / range, waves, groups);
     auto count = [&](auto wide) {
