@@ -1,32 +1,38 @@
 """Benchmark of the directed triad census on one MI355X.
 
-One step = one full census of the workload through the C ABI (validation and
-packing, task enumeration and scheduling, the merge/classify kernel, the null
-count), with the graph already resident in HBM. Prints ONE JSON line.
+One step = one full census of the workload through the C ABI (entry checks, row
+sums, orientation, the triangle listing, the null count), with the graph already
+resident in HBM. Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload rmat24]
                     [--schedule plain|heuristic|learned] [--no-cpu-baseline]
                     [--copy-calibration]   # plain copy kernel for counter scaling
 
 Metric: edge-pairs merged per second (an edge-pair is one task (u,v), u < v,
-over a symmetric edge).
+over a symmetric edge). The default call counts the one-list third vertices of
+every edge-pair from row sums and visits only those adjacent to both; the merge
+of whole lists, edge-pair by edge-pair, is what the schedules order (`schedules`,
+where `plain` is the merge in CSR order).
 
-Roofline of the census kernel: it is bound by vector-instruction issue, not by
-HBM (its DRAM traffic is about a third of the HBM peak). `roofline` therefore
-reports the vector unit: achieved = SQ_INSTS_VALU per launch (rocprofv3 counter,
-profiles/counters_k_census_<workload>.json, valid while the kernel source hash
-matches) x 64 lanes / the kernel's live duration, against the issue peak of
-256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.32e12 32-bit lane-operations/s (a
-wave64 vector instruction occupies a 16-lane SIMD for 4 cycles).
-Beside it, `roofline.hbm` gives the algorithmic-byte figures: the metric's own
-B_full = sum over tasks of 4.25*(d(u)+d(v)) + 32 (whole lists; 4-byte id and a
-quarter byte of direction flags per entry, plus the two offset pairs), the
-bytes of the merge as the kernel runs it, B_trim = 4.25 * (sum_x d+(x)^2 +
-sum_x (d(x) d-(x) - d-(x)(d-(x)-1)/2)) + 32 * m_sym (N(u) above u, d+(u) ids,
-and N(v) from u on, d(v) - i ids when u is the i-th lowest neighbour of v;
-d-(x) = d(x) - d+(x) the neighbours below x), each over the kernel time and
-the 8 TB/s peak, and the measured DRAM bytes (FETCH_SIZE + WRITE_SIZE scaled
-by a plain copy) over the same peak.
+Roofline of the listing kernels (k_sw_hubs, k_sw_mids, k_sw_rest, the census
+stage): bound by vector-instruction issue and by the list bytes read past L2.
+`roofline` reports the vector unit: achieved = SQ_INSTS_VALU per census
+(rocprofv3 counter, profiles/counters_listing_<workload>.json, valid while the
+hash of their sources matches) x 64 lanes / the stage's live duration, against
+the issue peak of 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.32e12 32-bit
+lane-operations/s (a wave64 vector instruction occupies a 16-lane SIMD for 4
+cycles). Beside it, `roofline.hbm`: the algorithmic bytes of the listing, 4 B for
+each of its sum_x d+(x) (d+(x) - 1) / 2 candidates (d+(x): neighbours of higher
+degree), and the measured bytes past L2 (FETCH_SIZE + WRITE_SIZE scaled by a
+plain copy; the 256 MB cache below L2 serves part of them), each over the stage's
+time and the 8 TB/s peak.
+
+The schedules' `hbm_frac_alg_trimmed` are the merge's own bytes, B_trim = 4.25 *
+(sum_x d+(x)^2 + sum_x (d(x) d-(x) - d-(x)(d-(x)-1)/2)) + 32 * m_sym with d+(x) /
+d-(x) the neighbours above / below x by id (N(u) above u, d+(u) ids, and N(v)
+from u on, d(v) - i ids when u is the i-th lowest neighbour of v; 4-byte id and a
+quarter byte of flags per entry, two offset pairs per task), over its kernel's
+time and the same peak.
 """
 from __future__ import annotations
 
@@ -89,7 +95,7 @@ def cpu_baseline(g, budget_entries=6.0e10, single_budget=4.0e9, seed=7):
 
 
 def list_byte_sums(d_off, d_nbr, n):
-    """(sum_x d+(x)^2, sum_x (d(x) d-(x) - d-(x)(d-(x)-1)/2)) with d-(x) /
+    """The merge's (sum_x d+(x)^2, sum_x (d(x) d-(x) - d-(x)(d-(x)-1)/2)) with d-(x) /
     d+(x) the neighbours of x below / above x: the merged list entries of all
     tasks, N(u) above u (d+(u) entries, in d+(u) tasks) and N(v) from u on (for
     the i-th lowest neighbour u of v, d(v) - i entries). Device-side
@@ -101,6 +107,20 @@ def list_byte_sums(d_off, d_nbr, n):
     del rows
     above = counts - below
     return int((above * above).sum().item()), int((counts * below - below * (below - 1) // 2).sum().item())
+
+
+def listing_candidates(d_off, d_nbr, n):
+    """sum_x d+(x) (d+(x) - 1) / 2 with d+(x) the neighbours of x of higher degree
+    (equal degrees by id): the pairs of listed neighbours, each visited once."""
+    import torch
+    deg = d_off[1:] - d_off[:-1]
+    rows = torch.repeat_interleave(torch.arange(n, device=d_off.device, dtype=torch.int32), deg)
+    plus, step = torch.zeros(n, dtype=torch.int64, device=d_off.device), 1 << 27
+    for i in range(0, d_nbr.numel(), step):
+        x, y = rows[i:i + step].long(), d_nbr[i:i + step].long()
+        up = (deg[y] > deg[x]) | ((deg[y] == deg[x]) & (y < x))
+        plus += torch.bincount(x[up], minlength=n)
+    return int((plus * (plus - 1) // 2).sum().item())
 
 
 def copy_calibration(nbytes=4 << 30, reps=3):
@@ -152,16 +172,13 @@ def main():
     models = {}
     run = make_runner(torch, triad, g, (d_off, d_nbr, d_flg), stream, models)
 
-    main = run(args.schedule, args.steps, args.warmup, spans=not args.no_schedules)
+    main = run(args.schedule, args.steps, args.warmup)
     counts = main["counts"]
     wall = main["wall_s"]
     ms_per_step = wall * 1e3 / args.steps
     value = st["m_sym"] * args.steps / wall
     kern_s = sum(main["census_ms"]) / len(main["census_ms"]) / 1e3
-    # algorithmic bytes of one census: per task (u, v) the ids of N(u) above u
-    # and of N(v) from u on, 4.25 B each (id + flag), plus 32 B of offsets
-    roof = census_roofline(args.workload, kern_s, d_off, d_nbr, g.n, st)
-    b_alg = roof["hbm"]["alg_bytes_trimmed"]
+    roof = census_roofline(args.workload, kern_s, d_off, d_nbr, g.n)
     rec = {
         "metric": "edge-pairs merged/s (R-MAT s24); census kernel roofline (vector issue; HBM figures beside it)",
         "value": round(value, 1),
@@ -183,11 +200,12 @@ def main():
     }
 
     if not args.no_schedules:
-        sched = {args.schedule: schedule_summary(main, st["m_sym"], b_alg)}
+        # the merge's bytes: per task (u, v) the ids of N(u) above u and of N(v)
+        # from u on, 4.25 B each (id + flag), plus 32 B of offsets
+        b_alg = merge_bytes(d_off, d_nbr, g.n, st)
+        sched = {}
         for other in ("plain", "heuristic", "learned"):
-            if other == args.schedule:
-                continue
-            r = run(other, args.steps, 1, spans=True)
+            r = run(other, args.steps, 1, merge=True)
             if r["counts"] != counts:
                 raise SystemExit(f"schedule {other} changed the census")
             sched[other] = schedule_summary(r, st["m_sym"], b_alg)
@@ -214,13 +232,17 @@ def main():
 
 
 def make_runner(torch, triad, g, dev, stream, models):
-    """run(schedule, steps, warmup, spans) -> timings and counts of repeated
-    census calls on the device-resident graph `dev` = (offsets, ids, flags)."""
+    """run(schedule, steps, warmup, merge) -> timings and counts of repeated
+    census calls on the device-resident graph `dev` = (offsets, ids, flags).
+    merge: plain too is the merge (a chunk size asks for it; 32,768 entries is
+    its default), with the wavefronts' spans."""
     d_off, d_nbr, d_flg = dev
     d_out = torch.empty(17, dtype=torch.int64, device="cuda")
 
-    def run(schedule, steps, warmup, spans=False):
+    def run(schedule, steps, warmup, merge=False):
         kw = {"schedule": schedule}
+        if merge and schedule == "plain":
+            kw["chunk"] = 32768
         if schedule == "learned":
             if "learned" not in models:
                 from paper_1209_6308_amd import costmodel
@@ -241,11 +263,11 @@ def make_runner(torch, triad, g, dev, stream, models):
                                                            d_out=d_out, **kw)
             census_ms.append(tm["census_ms"])
             tasks_ms.append(tm["tasks_ms"])
-            log(f"{g.name} {schedule}: step {i + 1}/{steps}: census kernel {tm['census_ms']:.1f} ms")
+            log(f"{g.name} {schedule}: step {i + 1}/{steps}: census stage {tm['census_ms']:.1f} ms")
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         out = {"wall_s": wall, "census_ms": census_ms, "tasks_ms": tasks_ms, "counts": counts, "waves": tm["waves"]}
-        if spans:
+        if merge:
             span = torch.zeros((tm["waves"], 2), dtype=torch.int64, device="cuda")
             triad.triad_census_device(g.n, g.nnz, d_off, d_nbr, d_flg, stream=stream, d_out=d_out, wave_span=span,
                                       **kw)
@@ -270,7 +292,7 @@ def schedule_summary(r, m_sym, b_alg):
 
 
 def compare_schedules(torch, graphs, triad, name, steps, stream, models):
-    """Plain / heuristic / learned census of another workload (identical counts
+    """Plain / heuristic / learned merge of another workload (identical counts
     required): the learned-schedule comparison on the Chung-Lu graph."""
     t0 = time.time()
     g = graphs.workload(name)
@@ -278,11 +300,10 @@ def compare_schedules(torch, graphs, triad, name, steps, stream, models):
     log(f"generated {name} in {time.time() - t0:.1f}s: {st}")
     dev = triad.to_device(g, "cuda")
     run = make_runner(torch, triad, g, dev, stream, models)
-    s_above2, s_d_below = list_byte_sums(dev[0], dev[1], g.n)
-    b_alg = 4.25 * (s_above2 + s_d_below) + 32.0 * st["m_sym"]
+    b_alg = merge_bytes(dev[0], dev[1], g.n, st)
     out, counts = {"workload": WORKLOAD_TEXT[name], "m_sym": st["m_sym"], "steps": steps}, None
     for sched in ("plain", "heuristic", "learned"):
-        r = run(sched, steps, 1, spans=True)
+        r = run(sched, steps, 1, merge=True)
         if counts is not None and r["counts"] != counts:
             raise SystemExit(f"schedule {sched} changed the {name} census")
         counts = r["counts"]
@@ -428,20 +449,21 @@ def significance_bench(torch, graphs, triad, scale=12, K=1024):
             "profile": [round(x, 4) for x in sp]}
 
 
-def census_roofline(workload, kern_s, d_off, d_nbr, n, st):
-    """Roofline record of the census kernel (see the module docstring)."""
+def merge_bytes(d_off, d_nbr, n, st):
     s_above2, s_d_below = list_byte_sums(d_off, d_nbr, n)
-    b_trim = 4.25 * (s_above2 + s_d_below) + 32.0 * st["m_sym"]
-    b_full = 4.25 * st["sum_d2"] + 32.0 * st["m_sym"]
-    hbm = {"peak_gbs": HBM_PEAK_GBS,
-           "alg_bytes_full": b_full, "frac_alg_full": round(b_full / kern_s / 1e9 / HBM_PEAK_GBS, 4),
-           "alg_bytes_trimmed": b_trim, "frac_alg_trimmed": round(b_trim / kern_s / 1e9 / HBM_PEAK_GBS, 4),
-           "sum_dplus2": s_above2, "sum_d_dminus": s_d_below, "dram_bytes": None, "frac_dram": None}
+    return 4.25 * (s_above2 + s_d_below) + 32.0 * st["m_sym"]
+
+
+def census_roofline(workload, kern_s, d_off, d_nbr, n):
+    """Roofline record of the listing kernels (see the module docstring)."""
+    cand = listing_candidates(d_off, d_nbr, n)
+    hbm = {"peak_gbs": HBM_PEAK_GBS, "candidates": cand, "alg_bytes": 4.0 * cand,
+           "frac_alg": round(4.0 * cand / kern_s / 1e9 / HBM_PEAK_GBS, 4), "past_l2_bytes": None, "frac_past_l2": None}
     roof = {"bound": "alu", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "Tops/s", "frac": None,
-            "traffic": None, "kernel": "k_census", "kernel_ms": round(kern_s * 1e3, 2),
+            "traffic": None, "kernel": "k_sw_hubs + k_sw_mids + k_sw_rest", "kernel_ms": round(kern_s * 1e3, 2),
             "peak_basis": "vector issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, 32-bit lane-ops",
             "counters": None, "hbm": hbm}
-    cfile = os.path.join(ROOT, "profiles", f"counters_k_census_{workload}.json")
+    cfile = os.path.join(ROOT, "profiles", f"counters_listing_{workload}.json")
     if os.path.exists(cfile):
         with open(cfile) as f:
             c = json.load(f)
@@ -451,12 +473,12 @@ def census_roofline(workload, kern_s, d_off, d_nbr, n, st):
             ach = valu * 64 / kern_s / 1e12
             roof["achieved"] = round(ach, 3)
             roof["frac"] = round(ach / VALU_PEAK_TOPS, 4)
-            roof["valu_insts_per_launch"] = valu
-            roof["salu_insts_per_launch"] = float(c["SQ_INSTS_SALU"])
-            roof["lds_insts_per_launch"] = float(c["SQ_INSTS_LDS"])
-            roof["traffic"] = c["hbm_bytes_per_launch"]
-            hbm["dram_bytes"] = c["hbm_bytes_per_launch"]
-            hbm["frac_dram"] = round(c["hbm_bytes_per_launch"] / kern_s / 1e9 / HBM_PEAK_GBS, 4)
+            roof["valu_insts_per_census"] = valu
+            roof["salu_insts_per_census"] = float(c["SQ_INSTS_SALU"])
+            roof["lds_insts_per_census"] = float(c["SQ_INSTS_LDS"])
+            roof["traffic"] = c["past_l2_bytes"]
+            hbm["past_l2_bytes"] = c["past_l2_bytes"]
+            hbm["frac_past_l2"] = round(c["past_l2_bytes"] / kern_s / 1e9 / HBM_PEAK_GBS, 4)
         else:
             roof["note"] = "kernel source changed since the counters were taken"
     return roof
@@ -515,10 +537,10 @@ def batched_bench(torch, reps=3):
 
 
 def kernel_source_hash():
-    """Hash of the sources the census kernel is compiled from."""
+    """Hash of the sources the listing kernels are compiled from."""
     import hashlib
     h = hashlib.sha256()
-    for fn in ("census.hip", "triad_internal.h"):
+    for fn in ("sweep.hip", "sweep.h", "sums.h", "lds_sort.h", "triad_internal.h"):
         with open(os.path.join(ROOT, "paper_1209_6308_amd", "csrc", fn), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
