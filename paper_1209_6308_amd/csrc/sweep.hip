@@ -11,9 +11,9 @@
 // highest degree), and for a vertex y the list N+(x) of every x below y is
 // streamed against the set N+(y). The merge reads sum_x d(x)^2 list entries
 // (3.57e12 at R-MAT scale 24), this reads sum_x d+(x)^2 / 2 (4.2e10). A whole
-// call took 1,560 ms there by the merge and takes 44.7 ms; 36.9 and 2.35 ms at
-// R-MAT scale 20, 469 and 13.2 ms on the Chung-Lu graph of 2^22 vertices, 566
-// and 78 us at R-MAT scale 10.
+// call took 1,560 ms there by the merge and takes 43.5 ms; 37.0 and 2.31 ms at
+// R-MAT scale 20, 469 and 13.1 ms on the Chung-Lu graph of 2^22 vertices, 566
+// and 79 us at R-MAT scale 10.
 //
 // Pipeline (one stream, no host synchronisation inside):
 //   k_sw_rows    per row: offset checks, row starts, degree histogram
@@ -36,9 +36,9 @@
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
 // A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_small
 // as one disjoint union with ids local to each graph, its counters by graph
-// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 17.1 ms a launch; 256
+// (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 16.7 ms a launch; 256
 // graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.37 ms). The labelled
-// census adds k_lab_sums (54.9 -> 3.8 ms at R-MAT scale 20).
+// census adds k_lab_sums (54.7 -> 3.6 ms at R-MAT scale 20).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1013,16 +1013,16 @@ struct Tri {
     c[6] += __popc(g3 & x3 & y3);
   }
   // Four candidates of one x: x holds f_xz in the top two bits, y f_yz in the
-  // top (TOP) or the low ones; all but the first left of them (left may be
-  // negative) are dropped. g8: f_xy in each field of a byte.
+  // top (TOP) or the low ones; as many of the last as r, taken to 0 .. 8, has
+  // pairs of bits are dropped. g8: f_xy in each field of a byte.
   template <bool TOP>
-  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int left, uint32_t g8) {
+  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int r, uint32_t g8) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       X = __builtin_amdgcn_alignbit(X, x[e], 30);
       Y = TOP ? __builtin_amdgcn_alignbit(Y, y[e], 30) : (Y << 2 | y[e]);
     }
-    X &= ~0u << (8 - 2 * max(0, min(left, 4)));
+    X &= ~((1u << min(max(r, 0), 8)) - 1u);
     G = G << 8 | g8;
   }
   __device__ __forceinline__ void flush(unsigned long long* acc, int lane) {
@@ -1074,7 +1074,7 @@ struct TriLab {
   }
   // g8: the flag in each field of the low byte, y < x in those of the next
   template <bool TOP>
-  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int left, uint32_t g8) {
+  __device__ __forceinline__ void add4(const uint32_t (&x)[4], const uint32_t (&y)[4], int r, uint32_t g8) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       X = __builtin_amdgcn_alignbit(X, x[e], 30);
@@ -1082,7 +1082,7 @@ struct TriLab {
       Y = TOP ? __builtin_amdgcn_alignbit(Y, y[e], 30) : (Y << 2 | y[e] >> 1);
       LY = TOP ? __builtin_amdgcn_alignbit(LY, y[e] << 2, 30) : (LY << 2 | (y[e] << 1 & 2u));
     }
-    X &= ~0u << (8 - 2 * max(0, min(left, 4)));
+    X &= ~((1u << min(max(r, 0), 8)) - 1u);
     G = G << 8 | (g8 & 0xFFu);
     LG = LG << 8 | g8 >> 8;
   }
@@ -1129,9 +1129,9 @@ __device__ __forceinline__ void set_hash(uint32_t* tab, uint32_t w) {
   while (atomicCAS(&tab[h], SLOT_FREE, w) != SLOT_FREE) h = (h + 1) & (TAB_WORDS - 1);
 }
 
-// The in-list vertices x of one batch: first entry of N+(x); its length, the
-// unsorted mark, and f_xy on top. Offsets take 32 bits where the byte offsets
-// of the whole list do (a load then adds them to a scalar base).
+// The in-list vertices x of one batch: byte offset of N+(x); its length, the
+// unsorted mark, and f_xy on top. Offsets take 32 bits where those of the whole
+// list do (a load then adds them to a scalar base).
 template <bool WIDE>
 struct XList {
   typename std::conditional<WIDE, uint64_t, uint32_t>::type p[64];
@@ -1154,7 +1154,7 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
   const uint64_t m = __ballot(has);
   if (has) {
     const int k = __popcll(m & below(lane));
-    L.p[k] = PACK ? xi >> 32 : xi >> 24;
+    L.p[k] = PACK ? xi >> 32 : xi >> 24 << 2;
     L.m[k] = (g & ~IDM<LAB>) | ((uint32_t)xi & (LEN_MASK | UNSORTED));
   }
   return __popcll(m);
@@ -1173,25 +1173,22 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
   const int l4 = (lane & (GL - 1)) * 4;
   const uint64_t before = below(lane & (64 - GL));
   struct Slot {
-    typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // the lane's next entries
-    int left;      // entries of the list from there on (0 or less: none)
+    typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // byte offset of the lane's next entries
+    int r;         // 8 - 2 * entries of the list from there on (8 or more: none)
     uint32_t g8;
     uint32_t lim;  // SORTED: the rank that ends the list; MULTI: the list's table
     uint32_t w[4];
   } sl[2];
   auto load = [&](Slot& s) {
-    const auto o = s.left > 0 ? s.o : 0;
-    if constexpr (WIDE)
-      __builtin_memcpy(s.w, list + o, 16);
-    else
-      __builtin_memcpy(s.w, (const char*)list + (o << 2), 16);
+    const auto o = s.r < 8 ? s.o : 0;
+    __builtin_memcpy(s.w, (const char*)list + o, 16);
   };
   auto take = [&](Slot& s, int k) {
-    s.left = 0;
+    s.r = 8;
     if (k < cnt) {
       const uint32_t m = L.m[k];
-      s.o = L.p[k] + l4;
-      s.left = (int)(m & LEN_MASK) - l4;
+      s.o = L.p[k] + 4 * l4;
+      s.r = 8 + 2 * (l4 - (int)(m & LEN_MASK));
       s.g8 = (m >> 30) * 0x55u | (T::LAB ? (m >> 29 & 1u) * 0xAA00u : 0u);
       // (lists of up to SORT_MIN entries are not sorted)
       if (MULTI) s.lim = m >> 24 & 15u;
@@ -1209,13 +1206,13 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
   auto step = [&](Slot& s) {
     uint32_t y[4];
     probe(s.w, y, s.lim);
-    tri.template add4<TOP>(s.w, y, s.left, s.g8);
+    tri.template add4<TOP>(s.w, y, s.r, s.g8);
     // lists that end here: their first lane has at most one step left, or the
     // last entry read has reached y
-    uint64_t d = __ballot(s.left <= STEP) & G0;
+    uint64_t d = __ballot(s.r >= 8 - 2 * STEP) & G0;
     if (SORTED) d |= (__ballot((s.w[3] & IDM<T::LAB>) >= s.lim) >> (GL - 1)) & G0;
-    s.o += STEP;
-    s.left -= STEP;
+    s.o += 4 * STEP;
+    s.r += 2 * STEP;
     if (d) {
       const uint64_t all = (d << GL) - d;
       if (__builtin_amdgcn_inverse_ballot_w64(all)) take(s, next + __popcll(d & before));
@@ -1223,14 +1220,18 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
     }
     load(s);
   };
-  for (;;) {
-    if (!__ballot(sl[0].left > 0 || sl[1].left > 0)) break;
+  auto any = [&]() { return __ballot(min(sl[0].r, sl[1].r) < 8) != 0; };
+  if (!any()) return;
+  do {
     step(sl[0]);
     step(sl[1]);
     step(sl[0]);
     step(sl[1]);
+    // (the last loads stay before the count: merged with those above the loop
+    // they would move to its head, right before their use)
+    __builtin_amdgcn_sched_barrier(0);
     tri.count();
-  }
+  } while (any());
 }
 
 struct CountArgs {
@@ -1697,7 +1698,8 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
 // table of N+(y) (a field per id), then the R in-lists as one list whose x carry
 // their row's table: short rows fill the steps of one stream together, and
 // their dependent reads overlap. (One row at a time: 17.3 ms on the 4,096-graph
-// batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10.
+// batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10,
+// and 10.3 with longer turns and the loads of stream() ahead of its count.
 // Bound by vector issue on the large batch, by the reads' latency on small ones.)
 // WAVES: a batch plan's launch shape; tables for as many as the workgroup has
 // (with tables for four, workgroups of two took 26 ms on the large batch).
@@ -1786,7 +1788,7 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
           const uint64_t m = __ballot(has);
           if (has) {
             const int i = __popcll(m & below(lane));
-            L.p[i] = xi >> 24;
+            L.p[i] = xi >> 24 << 2;
             L.m[i] = (g & ~IDM<LAB>) | q << 24 | ((uint32_t)xi & LEN_MASK);
           }
           wave_sync();
