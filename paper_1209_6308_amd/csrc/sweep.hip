@@ -118,6 +118,10 @@ __device__ __forceinline__ void stamp(uint64_t* clk, int i) {
   if (clk && blockIdx.x == 0 && threadIdx.x == 0) clk[i] = __builtin_amdgcn_s_memrealtime();
 }
 
+// No kernel past k_sw_pack runs on a graph with an error; the symmetry check's
+// and k_sw_pack's are in the third word.
+__device__ __forceinline__ bool refused(const uint32_t* err) { return (err[0] | err[1] | err[2]) != 0; }
+
 __global__ void k_sw_zero(uint32_t* __restrict__ p, int64_t m, uint64_t* __restrict__ clk) {
   stamp(clk, 0);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -897,7 +901,7 @@ __global__ void __launch_bounds__(256) k_sw_sort_mid(const uint32_t* __restrict_
                                                      const uint32_t* __restrict__ count,
                                                      const uint64_t* __restrict__ info, uint32_t* __restrict__ list,
                                                      const uint32_t* __restrict__ err, int rot, Packed pk) {
-  if (err[0] | err[1]) return;
+  if (refused(err)) return;
   const bool pack = pk.prow && *pk.hubs;
   const int lane = threadIdx.x & 63;
   const uint32_t nw = gridDim.x * 4, cnt = *count;
@@ -959,7 +963,7 @@ __global__ void __launch_bounds__(256, 5) k_sw_sort_long(const uint32_t* __restr
   __shared__ uint32_t s[SORT_MAX];
   __shared__ alignas(16) uint32_t cnt[4][256];
   __shared__ uint32_t sh[4];
-  if (err[0] | err[1]) return;
+  if (refused(err)) return;
   const bool pack = pk.prow && *pk.hubs;
   const uint32_t rows_listed = *count;
   for (uint32_t r = blockIdx.x; r < rows_listed; r += gridDim.x) {
@@ -1246,14 +1250,15 @@ struct CountArgs {
   uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken, [6] units packed
   int64_t range;       // k_sw_rest: entries of one wavefront
   unsigned long long* acc;
-  const uint32_t* err;
+  uint32_t* err;
   // a batch (see OrientArgs)
   const int64_t* vbase;
   const uint32_t* grow;
   unsigned long long* gacc;
-  // N+ lists packed (k_sw_pack), or NULL
+  // N+ lists packed (k_sw_pack) in so many units, or NULL
   uint64_t* prow;
   uint4* pack;
+  uint32_t units;
 };
 
 // Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
@@ -1309,7 +1314,10 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
 // bytes with the flags, then a unit of ranks a block, so that a step of k_sw_hubs
 // reads 144 bytes in a row. prow[x]: first unit << 32, the unsorted mark and the
 // blocks (0: none). Lists of 65 to SORT_MAX entries are written by the
-// kernels that sort them. One atomic takes the units of 256 * PER vertices (one
+// kernels that sort them. Half the entries are in N+ only if the graph is
+// symmetric, which nothing has shown yet (the symmetry check is an option and the
+// entries above the diagonal are compared at the end): a workgroup whose units do
+// not fit refuses the graph and leaves its lists out. One atomic takes the units of 256 * PER vertices (one
 // for 256 took 2.6 ms at 2^24 vertices: atomics on one word queue).
 template <int PER>
 __global__ void __launch_bounds__(256) k_sw_pack(CountArgs a) {
@@ -1354,10 +1362,13 @@ __global__ void __launch_bounds__(256) k_sw_pack(CountArgs a) {
     const uint32_t total = ws[0] + ws[1] + ws[2] + ws[3], todo = ws[4] + ws[5] + ws[6] + ws[7];
     if (t == 0 && total) base = atomicAdd(&a.counts[6], total);
     __syncthreads();
+    const bool fits = total == 0 || (uint64_t)base + total <= a.units;
+    if (!fits && t == 0) atomicOr(&a.err[2], ERR_ASYM);
     ea += base;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int64_t x = x0 + t * PER + i;
+      if (!fits) nb[i] = 0;
       pre[t * PER + i] = em;
       dst[t * PER + i] = ea;
       row[t * PER + i] = xi[i];
@@ -1366,7 +1377,7 @@ __global__ void __launch_bounds__(256) k_sw_pack(CountArgs a) {
       ea += nb[i] + (nb[i] + 7) / 8;
     }
     __syncthreads();
-    for (uint32_t b = t; b < todo; b += 256) {
+    for (uint32_t b = t; fits && b < todo; b += 256) {
       uint32_t v = 0;  // the last list that starts at or before b
 #pragma unroll
       for (int o = V / 2; o; o >>= 1)
@@ -1474,7 +1485,7 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
   __shared__ XList<WIDE> xl[HUB_THREADS / 64];
   __shared__ uint32_t item, next;
   stamp(a.clk, 2);
-  if (a.err[0] | a.err[1]) return;
+  if (refused(a.err)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   for (int i = tid; i < (int)sizeof(tab) / 4; i += HUB_THREADS) ((uint32_t*)tab)[i] = 0;
   const uint32_t nitems = a.counts[2];
@@ -1531,7 +1542,7 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
   __shared__ uint32_t tab[W], high[TAB_WORDS];
   __shared__ XList<WIDE> xl[MID_THREADS / 64];
   __shared__ uint32_t item, next;
-  if (a.err[0] | a.err[1]) return;
+  if (refused(a.err)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   for (int i = tid; i < W; i += MID_THREADS) tab[i] = 0;
   for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
@@ -1625,7 +1636,7 @@ template <bool RANK, bool BAT, bool LAB, bool WIDE>
 __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
   __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
   __shared__ XList<WIDE> xl[REST_WAVES];
-  if (a.err[0] | a.err[1]) return;
+  if (refused(a.err)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   XList<WIDE>& L = xl[w];
@@ -1710,7 +1721,7 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
   __shared__ XList<WIDE> xl[WAVES];
   stamp(a.clk, 1);
   stamp(a.clk, 2);
-  if (a.err[0] | a.err[1]) return;
+  if (refused(a.err)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   uint32_t* mine = tab + lane / LR * TW;
@@ -2034,16 +2045,17 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
   CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, clk, zero + w_cnt, 0, acc, err,
-               nullptr, nullptr, nullptr, nullptr, nullptr};
-  // N+ packed for the hubs: at most as many units as entries (two for two), whose
-  // byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
+               nullptr, nullptr, nullptr, nullptr, nullptr, 0};
+  // N+ packed for the hubs: at most as many units as entries (two for two; half
+  // of all of them in a symmetric graph), whose byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
   // entries (60,001 vertices, R-MAT: 322 -> 328 us); from there on it gains
   // (6.3 M: 630 -> 619, 16 M: 1,242 -> 1,160 us, 33 M: 2.64 -> 2.35 ms). With
   // fewer than two entries a vertex its scratch could pass the documented bound.
   const bool pack = rank && !labelled && nnz >= 2 * n && nnz >= PACK_MIN && nnz < (int64_t)1 << 29;
   if (pack) {
     ALLOC(ca.prow, n);
-    ALLOC(ca.pack, nnz / 2 + 16);
+    ca.units = (uint32_t)(nnz / 2 + 16);
+    ALLOC(ca.pack, ca.units);
   }
   // a wavefront's range: small graphs spread over the chip, large ones in
   // ranges that spread the row search over more entries
