@@ -290,14 +290,14 @@ template <bool RANK, bool BAT, bool LAB>
 __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
   __shared__ uint32_t srow[OT], skey[OT];  // per segment: its row (BAT: within its graph), its key; later N+ entries
   __shared__ uint16_t spos[OT + 1];        // its first entry
-  __shared__ uint16_t sgr[BAT ? OT : 1];   // BAT: its graph, from the tile's first
+  __shared__ uint32_t sgr[BAT ? OT : 1];   // BAT: its graph, from the tile's first (any number without entries may lie between)
   __shared__ uint64_t heads[OWORDS], fwd[OWORDS + 1], b0[OWORDS], b1[OWORDS];
   __shared__ uint32_t hpre[OWORDS + 1];  // segments, N+ entries before each 64-entry word
   __shared__ uint32_t pre[OWORDS + 1];
   __shared__ int64_t cF[2], cB[2];       // crossing rows (first, last segment): where their entries go
   __shared__ int32_t edge[OWORDS + 1];   // the entry before each 64-entry word
   __shared__ int64_t ends[4];            // the first and the last segment's row: its entry range
-  __shared__ uint32_t longs[2][LONG_KEEP], nlong[2], lbase[2];  // rows with long N+, over several tiles
+  __shared__ uint32_t longs[2][RANK ? LONG_KEEP : 1], nlong[2], lbase[2];  // rows with long N+, over several tiles
   __shared__ unsigned long long gsum[BAT ? TILE_GRAPHS : 1][9];  // sums of the block, BAT: of the tile's first graphs
   if (a.err[0]) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -376,7 +376,7 @@ __global__ void __launch_bounds__(OTHREADS, 5) k_sw_orient(OrientArgs a) {
       skey[s] = a.key[x];
       if constexpr (BAT) {
         const uint32_t g = a.grow[x];
-        sgr[s] = (uint16_t)(g - g0);
+        sgr[s] = g - g0;
         srow[s] = (uint32_t)(x - a.vbase[g]);
       } else {
         srow[s] = x;

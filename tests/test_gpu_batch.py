@@ -199,3 +199,28 @@ def test_full_ensemble_golden(torch):
     for short_tasks in (0, -1):
         got = triad.triad_census_batch(B.G, int(B.vbase[-1]), B.nnz, *d, short_tasks=short_tasks)
         assert [[str(x) for x in row] for row in got] == rec["census"], short_tasks
+
+
+@pytest.mark.parametrize("between", [65534, 65535, 65536, 70000, 140000])
+def test_members_without_edges_between_members_with(torch, between):
+    """Members with edges that share a tile of entries although tens of thousands
+    of members of one to three vertices and no edge lie between them."""
+    ends = [graphs.rmat(7, 3, seed=1), graphs.rmat(8, 2, seed=2), graphs.rmat(6, 4, seed=3)]
+    gap = 1 + np.arange(between) % 3
+    sizes = np.concatenate([[ends[0].n], gap, [ends[1].n], gap, [ends[2].n]]).astype(np.int64)
+    vbase = np.concatenate([[0], np.cumsum(sizes)])
+    deg = np.zeros(vbase[-1], np.int64)
+    at = [0, between + 1, 2 * between + 2]
+    for i, g in zip(at, ends):
+        deg[vbase[i]:vbase[i + 1]] = np.diff(g.offsets)
+    off = np.concatenate([[0], np.cumsum(deg)])
+    nbr = np.concatenate([g.nbrs for g in ends])
+    f = np.concatenate([g.flag_array() for g in ends])
+    f = np.pad(f, (0, -f.size % 4)).reshape(-1, 4)
+    flg = (f[:, 0] | f[:, 1] << 2 | f[:, 2] << 4 | f[:, 3] << 6).astype(np.uint8)
+    d = [torch.from_numpy(a).cuda() for a in (vbase, off, nbr, flg)]
+    got = triad.triad_census_batch(sizes.size, int(vbase[-1]), nbr.size, *d)
+    want = [[int(n == 3)] + [0] * 15 for n in sizes]
+    for i, g in zip(at, ends):
+        want[i] = oracle.census(g)
+    assert got == want
