@@ -1810,6 +1810,7 @@ struct triad_batch_plan {
   hipStream_t last = nullptr;
   int launched = 0;
   bool drained = true;  // nothing launched since the last wait
+  bool several = false;  // launches on several streams that no wait has covered
   size_t bytes = 0;  // device memory the plan holds (counted against the memory cap)
   void* block = nullptr;  // its one scratch block, from the held blocks of `device`
   size_t block_bytes = 0;
@@ -2119,6 +2120,7 @@ int triad_batch_plan_launch(triad_batch_plan* plan, void* hip_stream) {
   if (!plan || !plan->exec) return fail(TRIAD_EINVAL, "invalid plan");
   hipStream_t s = (hipStream_t)hip_stream;
   HIPCHK(hipGraphLaunch(plan->exec, s));
+  if (!plan->drained && plan->last != s) plan->several = true;
   plan->last = s;
   plan->launched = 1;
   plan->drained = false;
@@ -2131,7 +2133,7 @@ int triad_batch_plan_status(triad_batch_plan* plan) {
   uint32_t e = 0;
   HIPCHK(hipMemcpyAsync(&e, plan->err, sizeof(e), hipMemcpyDeviceToHost, plan->last));
   HIPCHK(hipStreamSynchronize(plan->last));
-  plan->drained = true;
+  plan->drained = !plan->several;  // (only the last launch's stream was waited for)
   if (e) return fail(status_from_bits(e), "batch input validation failed on the device");
   return TRIAD_OK;
 }

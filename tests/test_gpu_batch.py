@@ -224,3 +224,29 @@ def test_members_without_edges_between_members_with(torch, between):
     for i, g in zip(at, ends):
         want[i] = oracle.census(g)
     assert got == want
+
+
+def test_destroyed_plan_waits_for_every_stream(torch):
+    """A plan launched on two streams, of which only the last one was waited for:
+    its scratch goes back only when the other launch has ended too."""
+    B = graphs.null_ensemble(G=40, seed=3, nmin=64, nmax=500, dmin=4, dmax=16)
+    want = [oracle.census(B.graph(g)) for g in range(B.G)]
+    d = triad.batch_to_device(B)
+    plan = triad.BatchPlan(B.G, int(B.vbase[-1]), B.nnz, *d)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(100_000_000)
+    plan.launch(a)
+    plan.launch(b)
+    assert not a.query()
+    plan.status()
+    plan.close()
+    assert a.query()
+    assert [[int(x) for x in row] for row in plan.d_out.cpu().tolist()] == want
+    # one stream after another, each waited for
+    plan = triad.BatchPlan(B.G, int(B.vbase[-1]), B.nnz, *d)
+    for s in (a, b, a):
+        plan.launch(s)
+        assert plan.result() == want
+    plan.close()
