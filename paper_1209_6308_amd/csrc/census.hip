@@ -1953,7 +1953,7 @@ static int plan_build(int32_t G, int64_t nv, int64_t nnz, const int64_t* vbase, 
       if (nnz > 0)
         k_entries_batch<<<grid_for(nnz, ETILE, 65536), 256, 0, s>>>(G, nnz, vbase, off, nbr, flg, rowmark, packed,
                                                                    p->err);
-      if (int st = scan_i64_with(ntask, nv, tpre, bsum, s)) return st;
+      st = scan_i64_with(ntask, nv, tpre, bsum, s);  // (a failure: the capture is ended and the plan freed below)
       k_check_tasks<<<1, 64, 0, s>>>(tpre, nv, nnz, p->err);
       if (ntasks > 0) {
         const EmitArgs ea{nv, off, packed, ustart, tpre, tasks, tskip, 0, -1, p->err, nullptr, nullptr};
