@@ -19,10 +19,11 @@ def torch():
 
 
 def _one_sided(n, hubs, back):
-    """Every other row lists the same two hubs, whose rows list `back` of them each:
-    the lists towards higher degrees hold nearly all entries, in pairs."""
+    """Every other row lists the same two hubs, whose rows list each other and `back`
+    of the others: the lists towards higher degrees hold nearly all entries, in
+    pairs, and one hub has a long in-list and a higher neighbour."""
     rows = np.full(n, 2, np.int64)
-    rows[list(hubs)] = back
+    rows[list(hubs)] = back + 1
     off = np.zeros(n + 1, np.int64)
     np.cumsum(rows, out=off[1:])
     nbr = np.empty(off[-1], np.int32)
@@ -32,8 +33,8 @@ def _one_sided(n, hubs, back):
     nbr[at], nbr[at + 1] = hubs
     leaf = np.flatnonzero(others)
     leaf = np.concatenate([leaf[:back // 2], leaf[-(back // 2):]])
-    for h in hubs:
-        nbr[off[h]:off[h + 1]] = leaf
+    for h, other in (hubs, hubs[::-1]):
+        nbr[off[h]:off[h + 1]] = np.sort(np.append(leaf, other))
     return off, nbr, np.full((nbr.size + 3) // 4, 0x55, np.uint8)
 
 
