@@ -30,6 +30,7 @@
 //   k_sw_hubs    vertices with long in-lists: a workgroup holds N+(y) as a
 //                byte table over the ranks and streams the N+(x)
 //   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
+//   k_sw_dense   long N+ past the ranks of that table: one of 524,288 ranks
 //   k_sw_rest    all others: one wavefront and a hash table in LDS
 //   k_sw_small   graphs of up to 16,384 vertices instead of the last three: lists
 //                in ids, several rows a wavefront, a table field per id
@@ -67,6 +68,7 @@ constexpr int64_t MID_MIN_IN = 32;     // in-lists from here on: k_sw_mids
 constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
 constexpr int TAB_WORDS = 1024;        // its slots
+constexpr int DENSE_THREADS = 1024, DENSE_WORDS = 32768;  // one workgroup a CU: a table of 128 KB
 constexpr int REST_WAVES = 4;
 constexpr int64_t PACK_MIN = 6 << 20;   // entries from which N+ lists are packed for k_sw_hubs
 constexpr int64_t LIST_PAD = 4;        // list words read past a list's end
@@ -1245,9 +1247,9 @@ struct CountArgs {
   const uint64_t* info;
   const uint32_t* rank;
   const uint32_t* tile_row;
-  uint64_t* items[2];  // of k_sw_hubs, k_sw_mids: y << 32 | chunk
+  uint64_t* items[3];  // of k_sw_hubs, k_sw_mids, k_sw_dense: y << 32 | chunk
   uint64_t* clk;       // stage starts, or NULL
-  uint32_t* counts;    // [2], [3] items listed, [4], [5] items taken, [6] units packed
+  uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed
   int64_t range;       // k_sw_rest: entries of one wavefront
   unsigned long long* acc;
   uint32_t* err;
@@ -1261,21 +1263,32 @@ struct CountArgs {
   uint32_t units;
 };
 
+// Ranks of k_sw_dense's table.
+template <bool LAB>
+constexpr uint32_t DENSE_RANKS = (uint32_t)DENSE_WORDS << FB<LAB>;
+
 // Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
-// k_sw_rest, 3 none.
+// k_sw_dense, 3 k_sw_rest, 4 none. k_sw_mids reads the lists again for every
+// TAB_MAX entries of N+(y) past its bits, k_sw_dense for every window of its
+// table: the one with fewer passes (at most, by the number of such ranks).
+template <bool LAB>
 __device__ __forceinline__ uint32_t route(uint32_t rank, uint32_t plus, int64_t minus) {
-  if (plus == 0 || minus == 0) return 3;
+  if (plus == 0 || minus == 0) return 4;
   if (rank < HUB_RANKS && minus >= HUB_MIN_IN) return 0;
-  return minus >= MID_MIN_IN || plus > TAB_MAX ? 1 : 2;
+  if (plus <= TAB_MAX) return minus >= MID_MIN_IN ? 1 : 3;
+  if (rank <= HUB_RANKS) return 1;
+  const uint32_t high = min(plus, rank - (uint32_t)HUB_RANKS);
+  return (high + TAB_MAX - 1) / TAB_MAX > (rank - 1) / DENSE_RANKS<LAB> + 1 ? 2 : 1;
 }
 
+template <bool LAB>
 __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
-  __shared__ uint32_t cnt[2], base[2];
+  __shared__ uint32_t cnt[3], base[3];
   stamp(a.clk, 1);
   if (a.err[0] | a.err[1]) return;
   for (int64_t x0 = (int64_t)blockIdx.x * 4096; x0 < a.n; x0 += (int64_t)gridDim.x * 4096) {
     __syncthreads();
-    if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+    if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
     __syncthreads();
     uint32_t at[16], num[16], kind = 0;
 #pragma unroll
@@ -1286,23 +1299,20 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
         const uint64_t in = a.info[x];
         const uint32_t plus = (uint32_t)in & LEN_MASK;
         const int64_t minus = a.off[x + 1] - (int64_t)(in >> 24) - plus;
-        if (plus && minus >= MID_MIN_IN) {
-          const uint32_t r = route(a.rank[x], plus, minus);
+        if (plus && minus && (minus >= MID_MIN_IN || plus > TAB_MAX)) {
+          const uint32_t r = route<LAB>(a.rank[x], plus, minus);
           kind |= r << (2 * i);
           num[i] = (uint32_t)((minus + CHUNK - 1) / CHUNK);
-        } else if (plus > TAB_MAX && minus) {
-          kind |= 1u << (2 * i);
-          num[i] = 1;
+          at[i] = atomicAdd(&cnt[r], num[i]);
         }
-        if (num[i]) at[i] = atomicAdd(&cnt[(kind >> (2 * i)) & 1u], num[i]);
       }
     }
     __syncthreads();
-    if (threadIdx.x < 2 && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&a.counts[2 + threadIdx.x], cnt[threadIdx.x]);
+    if (threadIdx.x < 3 && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&a.counts[2 + threadIdx.x], cnt[threadIdx.x]);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const uint32_t r = (kind >> (2 * i)) & 1u;
+      const uint32_t r = (kind >> (2 * i)) & 3u;
       for (uint32_t c = 0; c < num[i]; ++c)
         a.items[r][base[r] + at[i] + c] = (uint64_t)(x0 + i * 256 + threadIdx.x) << 32 | c;
     }
@@ -1360,7 +1370,7 @@ __global__ void __launch_bounds__(256) k_sw_pack(CountArgs a) {
       em += ws[4 + q];
     }
     const uint32_t total = ws[0] + ws[1] + ws[2] + ws[3], todo = ws[4] + ws[5] + ws[6] + ws[7];
-    if (t == 0 && total) base = atomicAdd(&a.counts[6], total);
+    if (t == 0 && total) base = atomicAdd(&a.counts[8], total);
     __syncthreads();
     const bool fits = total == 0 || (uint64_t)base + total <= a.units;
     if (!fits && t == 0) atomicOr(&a.err[2], ERR_ASYM);
@@ -1493,7 +1503,7 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   for (;;) {
     if (tid == 0) {
-      item = atomicAdd(&a.counts[4], 1u);
+      item = atomicAdd(&a.counts[5], 1u);
       next = 0;
     }
     __syncthreads();
@@ -1535,7 +1545,8 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
 }
 
 // Vertices with in-lists of middling length, of any rank: a smaller workgroup,
-// N+(y) as two bits per rank up to HUB_RANKS and a hash table beyond.
+// N+(y) as two bits per rank up to HUB_RANKS and a hash table beyond, which takes
+// TAB_MAX entries of the list at a time whatever their ranks.
 template <bool LAB, bool WIDE>
 __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs a) {
   constexpr int W = (HUB_RANKS >> FB<LAB>) + 1;
@@ -1550,7 +1561,7 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
   XList<WIDE>& L = xl[tid >> 6];
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   for (;;) {
-    if (tid == 0) item = atomicAdd(&a.counts[5], 1u);
+    if (tid == 0) item = atomicAdd(&a.counts[6], 1u);
     __syncthreads();
     const uint32_t it = item;
     if (it >= nitems) break;
@@ -1562,15 +1573,22 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
     const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
     const int claim = cnt >= 256 ? 64 : cnt >= 128 ? 32 : 16;
     const bool far = yr > HUB_RANKS;  // N+(y) may reach past the bits
-    // TAB_MAX entries of N+(y) at a time fit the hash table whatever their ranks
-    for (uint32_t f = 0; f < plus; f += TAB_MAX) {
+    for (uint32_t f = 0; f < plus && (f == 0 || far); f += TAB_MAX) {
       const uint32_t fe = min(f + TAB_MAX, plus);
-      for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
+      // the first pass has all the bits
+      bool any = f == 0;
+      for (uint32_t i = f + tid; i < (f ? fe : plus); i += MID_THREADS) {
         const uint32_t z = a.list[s + i];
-        if ((z & IDM<LAB>) < HUB_RANKS) set_bits<LAB>(tab, z); else set_hash(high, z);
+        if ((z & IDM<LAB>) < HUB_RANKS) {
+          if (f == 0) set_bits<LAB>(tab, z);
+        } else if (i < fe) {
+          set_hash(high, z);
+          any = true;
+        }
       }
       if (tid == 0) next = 0;
-      __syncthreads();
+      if (f == 0) __syncthreads();
+      else if (!__syncthreads_or(any)) continue;
       for (;;) {
         int k = 0;
         if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
@@ -1594,13 +1612,78 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
         wave_sync();
       }
       __syncthreads();
-      for (uint32_t i = f + tid; i < fe; i += MID_THREADS) {
-        const uint32_t z = a.list[s + i] & IDM<LAB>;
-        if (z < HUB_RANKS) tab[z >> FB<LAB>] = 0;
-      }
+      if (f == 0)
+        for (uint32_t i = tid; i < plus; i += MID_THREADS) {
+          const uint32_t z = a.list[s + i] & IDM<LAB>;
+          if (z < HUB_RANKS) tab[z >> FB<LAB>] = 0;
+        }
       if (far)
         for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
       if (fe < plus) __syncthreads();
+    }
+  }
+  tri.flush(copy_of<LAB>(a.acc), lane);
+}
+
+// Vertices with N+ longer than k_sw_mids takes in few passes, past its bits: a
+// workgroup a CU and bits for a window of DENSE_RANKS ranks at a time. (Dense
+// graphs of more than 65,536 vertices: with hash tables of 512 entries only,
+// every list was read plus / 512 times.)
+template <bool LAB, bool WIDE>
+__global__ void __launch_bounds__(DENSE_THREADS, 4) k_sw_dense(CountArgs a) {
+  constexpr int W = DENSE_WORDS + 1;
+  __shared__ uint32_t tab[W];  // past the window: 0
+  __shared__ XList<WIDE> xl[DENSE_THREADS / 64];
+  __shared__ uint32_t item, next;
+  if (refused(a.err)) return;
+  const uint32_t nitems = a.counts[4];
+  if (blockIdx.x >= nitems) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < W; i += DENSE_THREADS) tab[i] = 0;
+  XList<WIDE>& L = xl[tid >> 6];
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
+  for (;;) {
+    if (tid == 0) item = atomicAdd(&a.counts[7], 1u);
+    __syncthreads();
+    const uint32_t it = item;
+    if (it >= nitems) break;
+    const uint64_t q = a.items[2][it];
+    const uint32_t y = (uint32_t)(q >> 32);
+    const uint64_t in = a.info[y];
+    const uint32_t plus = (uint32_t)in & LEN_MASK, yr = a.rank[y];
+    const int64_t s = (int64_t)(in >> 24), b = s + plus + (int64_t)(uint32_t)q * CHUNK;
+    const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
+    const int claim = cnt >= 1024 ? 64 : cnt >= 512 ? 32 : 16;
+    for (uint32_t from = 0; from < yr; from += DENSE_RANKS<LAB>) {
+      bool any = false;
+      for (uint32_t i = tid; i < plus; i += DENSE_THREADS) {
+        const uint32_t z = a.list[s + i];
+        if ((z & IDM<LAB>) - from < DENSE_RANKS<LAB>) {
+          set_bits<LAB>(tab, z - from);
+          any = true;
+        }
+      }
+      if (tid == 0) next = 0;
+      if (!__syncthreads_or(any)) continue;
+      for (;;) {
+        int k = 0;
+        if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
+        k = __builtin_amdgcn_readfirstlane(k);
+        if (k >= cnt) break;
+        const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+        wave_sync();
+        stream<16, true, true, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4], uint32_t) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) g[e] = probe_bits<W, LAB>(tab, (w[e] & IDM<LAB>) - from);
+        });
+        wave_sync();
+      }
+      __syncthreads();
+      for (uint32_t i = tid; i < plus; i += DENSE_THREADS) {
+        const uint32_t z = (a.list[s + i] & IDM<LAB>) - from;
+        if (z < DENSE_RANKS<LAB>) tab[z >> FB<LAB>] = 0;
+      }
+      __syncthreads();
     }
   }
   tri.flush(copy_of<LAB>(a.acc), lane);
@@ -1660,7 +1743,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
         if (plus == 0) hi = lo;
         if (RANK && hi > lo) {
           yr = a.rank[r + lane];
-          if (route(yr, plus, e - bs) != 2) hi = lo;
+          if (route<LAB>(yr, plus, e - bs) != 3) hi = lo;
         }
         if (BAT && hi > lo) yr = a.grow[r + lane];
       }
@@ -1995,7 +2078,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     words += (w + 1) & ~(int64_t)1;
     return at;
   };
-  const int64_t w_acc = place(2 * (labelled ? SW_LAB_WORDS : SW_WORDS) * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(8);
+  const int64_t w_acc = place(2 * (labelled ? SW_LAB_WORDS : SW_WORDS) * SW_COPIES), w_err = place(SW_ERRS), w_cnt = place(10);
   const int64_t w_hist = place(rank ? 2 * BUCKETS : 0);
   const int64_t w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
   const int64_t w_mark = place(ntiles * (OT / 32));
@@ -2008,7 +2091,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   k_sw_zero<<<grid_of_work(words, 1024, 2048), 256, 0, s>>>(zero, words, clk);
   if (n == 0) return TRIAD_OK;
   uint32_t *key = nullptr, *list = nullptr, *tile_row = nullptr, *mid = nullptr, *lng = nullptr;
-  uint64_t *info = nullptr, *hub_items = nullptr, *mid_items = nullptr;
+  uint64_t *info = nullptr, *hub_items = nullptr, *mid_items = nullptr, *dense_items = nullptr;
   SegCounts* segs = nullptr;
   if (labelled) ALLOC(segs, 2 * ntiles);
   ALLOC(key, n);
@@ -2022,6 +2105,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     // only in-lists of MID_MIN_IN entries or N+ of more than TAB_MAX make any
     ALLOC(hub_items, std::min(n, HUB_RANKS) + nnz / CHUNK + 1);
     ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
+    ALLOC(dense_items, nnz / TAB_MAX + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
                    tile_row, err, 0, nullptr, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
@@ -2044,7 +2128,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
                       (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err, nullptr, nullptr, nullptr};
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
-  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items}, clk, zero + w_cnt, 0, acc, err,
+  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items, dense_items}, clk, zero + w_cnt, 0, acc, err,
                nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   // N+ packed for the hubs: at most as many units as entries (two for two; half
   // of all of them in a symmetric graph), whose byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
@@ -2074,7 +2158,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     if (rank) {
       k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
-      k_sw_items<<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+      k_sw_items<LAB><<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
       if (pack && n > 1 << 19) k_sw_pack<8><<<grid_of_work(n, 2048, INT32_MAX), 256, 0, s>>>(ca);
       else if (pack) k_sw_pack<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ca);
       const Packed pk{pack ? ca.prow : nullptr, ca.pack, ca.counts + 2};
@@ -2092,6 +2176,8 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
           k_sw_hubs<LAB, W, false><<<(unsigned)(di.cus * 2), hub_threads(LAB), 0, s>>>(ca);
         }
         k_sw_mids<LAB, W><<<(unsigned)(di.cus * (LAB ? 4 : 6)), MID_THREADS, 0, s>>>(ca);
+        // (an N+ of more than TAB_MAX entries takes as many rows of about its degree)
+        if (n > HUB_RANKS && nnz >= (int64_t)TAB_MAX * TAB_MAX / 2) k_sw_dense<LAB, W><<<(unsigned)di.cus, DENSE_THREADS, 0, s>>>(ca);
         k_sw_rest<true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
       };
       if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
@@ -2169,7 +2255,7 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
                         (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
     k_sw_orient<false, true, false><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
     k_sw_cross<false, true, false><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
-    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr}, nullptr, zero + z.w_cnt, range, acc,
+    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr, nullptr}, nullptr, zero + z.w_cnt, range, acc,
                  err, vbase, grow, gacc};
     // (by default 2,048 entries a turn, fewer where that leaves less than four
     // turns a wavefront; 4,096 graphs, 3e8 edges: 19.5 ms with 512, 17.5 with
