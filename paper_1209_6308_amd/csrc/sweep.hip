@@ -68,7 +68,9 @@ constexpr int64_t MID_MIN_IN = 32;     // in-lists from here on: k_sw_mids
 constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
 constexpr int TAB_WORDS = 1024;        // its slots
-constexpr int DENSE_THREADS = 1024, DENSE_WORDS = 32768;  // one workgroup a CU: a table of 128 KB
+// threads and table of k_sw_dense's workgroups: one a CU, or four (batches of smaller members)
+constexpr int DENSE_THREADS = 1024, DENSE_WORDS = 32768, DENSE_LOW = 8192;
+constexpr int64_t DENSE_MIN_IN = 256;  // in-lists of a batch from here on, where it saves no pass
 constexpr int REST_WAVES = 4;
 constexpr int64_t PACK_MIN = 6 << 20;   // entries from which N+ lists are packed for k_sw_hubs
 constexpr int64_t LIST_PAD = 4;        // list words read past a list's end
@@ -1251,6 +1253,7 @@ struct CountArgs {
   uint64_t* clk;       // stage starts, or NULL
   uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed
   int64_t range;       // k_sw_rest: entries of one wavefront
+  uint32_t window;     // a batch: ids of k_sw_dense's table
   unsigned long long* acc;
   uint32_t* err;
   // a batch (see OrientArgs)
@@ -1264,8 +1267,8 @@ struct CountArgs {
 };
 
 // Ranks of k_sw_dense's table.
-template <bool LAB>
-constexpr uint32_t DENSE_RANKS = (uint32_t)DENSE_WORDS << FB<LAB>;
+template <bool LAB, int WORDS = DENSE_WORDS>
+constexpr uint32_t DENSE_RANKS = (uint32_t)WORDS << FB<LAB>;
 
 // Which kernel counts the triangles of y: 0 k_sw_hubs, 1 k_sw_mids, 2
 // k_sw_dense, 3 k_sw_rest, 4 none. k_sw_mids reads the lists again for every
@@ -1281,7 +1284,17 @@ __device__ __forceinline__ uint32_t route(uint32_t rank, uint32_t plus, int64_t 
   return (high + TAB_MAX - 1) / TAB_MAX > (rank - 1) / DENSE_RANKS<LAB> + 1 ? 2 : 1;
 }
 
-template <bool LAB>
+// A batch (members above DIRECT_N): does k_sw_dense take y, of a graph of n
+// vertices, rather than k_sw_rest? Where it needs fewer passes, or no more and
+// the in-list feeds a workgroup. ms before / now: 8 members of 20,011 vertices of
+// degree 1,000 202 / 39, 16 of 50,021 of degree 600 191 / 136, of degree 300 (few
+// in-lists so long) 38 / 38; with workgroups of 1,024 alone 110, 200, 53.
+__device__ __forceinline__ bool dense_member(uint32_t window, uint32_t plus, int64_t minus, uint32_t n) {
+  const uint32_t there = (plus + TAB_MAX - 1) / TAB_MAX, here = (n - 1) / window + 1;
+  return there > here || (there == here && minus >= DENSE_MIN_IN);
+}
+
+template <bool BAT, bool LAB>
 __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
   __shared__ uint32_t cnt[3], base[3];
   stamp(a.clk, 1);
@@ -1299,8 +1312,13 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
         const uint64_t in = a.info[x];
         const uint32_t plus = (uint32_t)in & LEN_MASK;
         const int64_t minus = a.off[x + 1] - (int64_t)(in >> 24) - plus;
-        if (plus && minus && (minus >= MID_MIN_IN || plus > TAB_MAX)) {
-          const uint32_t r = route<LAB>(a.rank[x], plus, minus);
+        bool listed = plus && minus && (minus >= (BAT ? DENSE_MIN_IN : MID_MIN_IN) || plus > TAB_MAX);
+        if (BAT && listed) {
+          const uint32_t g = a.grow[x];
+          listed = dense_member(a.window, plus, minus, (uint32_t)(a.vbase[g + 1] - a.vbase[g]));
+        }
+        if (listed) {
+          const uint32_t r = BAT ? 2 : route<LAB>(a.rank[x], plus, minus);
           kind |= r << (2 * i);
           num[i] = (uint32_t)((minus + CHUNK - 1) / CHUNK);
           at[i] = atomicAdd(&cnt[r], num[i]);
@@ -1625,21 +1643,24 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
   tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
-// Vertices with N+ longer than k_sw_mids takes in few passes, past its bits: a
-// workgroup a CU and bits for a window of DENSE_RANKS ranks at a time. (Dense
+// Vertices with N+ longer than k_sw_mids takes in few passes, past its bits: bits
+// for a window of ranks at a time, 128 KB of them and one workgroup a CU. (Dense
 // graphs of more than 65,536 vertices: with hash tables of 512 entries only,
-// every list was read plus / 512 times.)
-template <bool LAB, bool WIDE>
-__global__ void __launch_bounds__(DENSE_THREADS, 4) k_sw_dense(CountArgs a) {
-  constexpr int W = DENSE_WORDS + 1;
+// every list was read plus / 512 times, 2,041 ms where this takes 313 on 300,007
+// vertices of degree 3,000.) BAT: the same for members of a batch, by ids, in a
+// quarter of the size where the largest member fits (see dense_member).
+template <bool BAT, bool LAB, bool WIDE, int WORDS>
+__global__ void __launch_bounds__(DENSE_THREADS / (DENSE_WORDS / WORDS), 4) k_sw_dense(CountArgs a) {
+  constexpr int THREADS = DENSE_THREADS / (DENSE_WORDS / WORDS), W = WORDS + 1;
+  constexpr uint32_t RANKS = DENSE_RANKS<LAB, WORDS>;
   __shared__ uint32_t tab[W];  // past the window: 0
-  __shared__ XList<WIDE> xl[DENSE_THREADS / 64];
+  __shared__ XList<WIDE> xl[THREADS / 64];
   __shared__ uint32_t item, next;
   if (refused(a.err)) return;
   const uint32_t nitems = a.counts[4];
   if (blockIdx.x >= nitems) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  for (int i = tid; i < W; i += DENSE_THREADS) tab[i] = 0;
+  for (int i = tid; i < W; i += THREADS) tab[i] = 0;
   XList<WIDE>& L = xl[tid >> 6];
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   for (;;) {
@@ -1650,15 +1671,18 @@ __global__ void __launch_bounds__(DENSE_THREADS, 4) k_sw_dense(CountArgs a) {
     const uint64_t q = a.items[2][it];
     const uint32_t y = (uint32_t)(q >> 32);
     const uint64_t in = a.info[y];
-    const uint32_t plus = (uint32_t)in & LEN_MASK, yr = a.rank[y];
+    const uint32_t plus = (uint32_t)in & LEN_MASK;
+    const uint32_t graph = BAT ? a.grow[y] : 0u;
+    const int64_t base = BAT ? a.vbase[graph] : 0;
+    const uint32_t yr = BAT ? (uint32_t)(a.vbase[graph + 1] - base) : a.rank[y];  // above every z
     const int64_t s = (int64_t)(in >> 24), b = s + plus + (int64_t)(uint32_t)q * CHUNK;
     const int cnt = (int)min(CHUNK, a.off[y + 1] - b);
     const int claim = cnt >= 1024 ? 64 : cnt >= 512 ? 32 : 16;
-    for (uint32_t from = 0; from < yr; from += DENSE_RANKS<LAB>) {
+    for (uint32_t from = 0; from < yr; from += RANKS) {
       bool any = false;
-      for (uint32_t i = tid; i < plus; i += DENSE_THREADS) {
+      for (uint32_t i = tid; i < plus; i += THREADS) {
         const uint32_t z = a.list[s + i];
-        if ((z & IDM<LAB>) - from < DENSE_RANKS<LAB>) {
+        if ((z & IDM<LAB>) - from < RANKS) {
           set_bits<LAB>(tab, z - from);
           any = true;
         }
@@ -1670,23 +1694,24 @@ __global__ void __launch_bounds__(DENSE_THREADS, 4) k_sw_dense(CountArgs a) {
         if (lane == 0) k = (int)atomicAdd(&next, (uint32_t)claim);
         k = __builtin_amdgcn_readfirstlane(k);
         if (k >= cnt) break;
-        const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info, lane);
+        const int nx = list_x<LAB, WIDE>(L, a.list + b + k, min(claim, cnt - k), a.info + base, lane);
         wave_sync();
-        stream<16, true, true, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4], uint32_t) {
+        stream<16, !BAT, true, WIDE, false>(a.list, L, nx, yr, lane, tri, [&](const uint32_t (&w)[4], uint32_t (&g)[4], uint32_t) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) g[e] = probe_bits<W, LAB>(tab, (w[e] & IDM<LAB>) - from);
         });
         wave_sync();
       }
       __syncthreads();
-      for (uint32_t i = tid; i < plus; i += DENSE_THREADS) {
+      for (uint32_t i = tid; i < plus; i += THREADS) {
         const uint32_t z = (a.list[s + i] & IDM<LAB>) - from;
-        if (z < DENSE_RANKS<LAB>) tab[z >> FB<LAB>] = 0;
+        if (z < RANKS) tab[z >> FB<LAB>] = 0;
       }
       __syncthreads();
     }
+    if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
   }
-  tri.flush(copy_of<LAB>(a.acc), lane);
+  if (!BAT) tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
 // The row that holds entry j, by a 64-way search between tile starts.
@@ -1745,7 +1770,12 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
           yr = a.rank[r + lane];
           if (route<LAB>(yr, plus, e - bs) != 3) hi = lo;
         }
-        if (BAT && hi > lo) yr = a.grow[r + lane];
+        if (BAT && hi > lo) {
+          yr = a.grow[r + lane];
+          if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
+              dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[yr + 1] - a.vbase[yr])))
+            hi = lo;
+        }
       }
       uint64_t todo = __ballot(hi > lo);
       while (todo) {
@@ -2128,7 +2158,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
                       (Cross*)(zero + w_cross), mid, lng, zero + w_cnt, acc, err, nullptr, nullptr, nullptr};
   const unsigned ogrid = grid_of_work(ntiles, 1, (int64_t)di.cus * 8);
   const unsigned cgrid = grid_of_work(ntiles, 256, 256);
-  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items, dense_items}, clk, zero + w_cnt, 0, acc, err,
+  CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items, dense_items}, clk, zero + w_cnt, 0, 0, acc, err,
                nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   // N+ packed for the hubs: at most as many units as entries (two for two; half
   // of all of them in a symmetric graph), whose byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
@@ -2158,7 +2188,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     if (rank) {
       k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
-      k_sw_items<LAB><<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+      k_sw_items<false, LAB><<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
       if (pack && n > 1 << 19) k_sw_pack<8><<<grid_of_work(n, 2048, INT32_MAX), 256, 0, s>>>(ca);
       else if (pack) k_sw_pack<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ca);
       const Packed pk{pack ? ca.prow : nullptr, ca.pack, ca.counts + 2};
@@ -2177,7 +2207,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
         }
         k_sw_mids<LAB, W><<<(unsigned)(di.cus * (LAB ? 4 : 6)), MID_THREADS, 0, s>>>(ca);
         // (an N+ of more than TAB_MAX entries takes as many rows of about its degree)
-        if (n > HUB_RANKS && nnz >= (int64_t)TAB_MAX * TAB_MAX / 2) k_sw_dense<LAB, W><<<(unsigned)di.cus, DENSE_THREADS, 0, s>>>(ca);
+        if (n > HUB_RANKS && nnz >= (int64_t)TAB_MAX * TAB_MAX / 2) k_sw_dense<false, LAB, W, DENSE_WORDS><<<(unsigned)di.cus, DENSE_THREADS, 0, s>>>(ca);
         k_sw_rest<true, false, LAB, W><<<wgrid, REST_WAVES * 64, 0, s>>>(ca);
       };
       if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
@@ -2196,9 +2226,10 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
 // A batch: the pieces of its scratch block in order (sizes in bytes, rounded
 // up as Scratch hands them out).
 struct BatchSizes {
-  int64_t ntiles, zero_words, w_err, w_cnt, w_gacc, w_cross, w_mark;
+  int64_t ntiles, dense_items, zero_words, w_err, w_cnt, w_gacc, w_cross, w_mark;
   BatchSizes(int32_t graphs, int64_t nnz) {
     ntiles = (nnz + OT - 1) / OT;
+    dense_items = nnz / DENSE_MIN_IN + nnz / TAB_MAX + nnz / CHUNK + 1;
     zero_words = 0;
     auto place = [&](int64_t w) {
       const int64_t at = zero_words;
@@ -2207,7 +2238,7 @@ struct BatchSizes {
     };
     place(2 * SW_WORDS * SW_COPIES);  // acc first
     w_err = place(SW_ERRS);
-    w_cnt = place(8);
+    w_cnt = place(10);
     w_gacc = place(32 * (int64_t)graphs);
     w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
     w_mark = place(ntiles * (OT / 32));
@@ -2217,7 +2248,8 @@ struct BatchSizes {
 size_t sweep_batch_bytes(int32_t graphs, int64_t nv, int64_t nnz) {
   const BatchSizes z(graphs, nnz);
   auto r = [](int64_t b) { return (size_t)((std::max<int64_t>(b, 1) + 255) & ~(int64_t)255); };
-  return r(4 * z.zero_words) + 2 * r(4 * nv) + r(8 * nv) + r(4 * (nnz + LIST_PAD)) + r(4 * z.ntiles);
+  return r(4 * z.zero_words) + 2 * r(4 * nv) + r(8 * nv) + r(4 * (nnz + LIST_PAD)) + r(4 * z.ntiles) +
+         r(8 * z.dense_items);
 }
 
 int sweep_batch_groups(int waves) {
@@ -2231,13 +2263,14 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   const int64_t nnz = in.nnz;
   const BatchSizes z(graphs, nnz);
   uint32_t *zero = nullptr, *key = nullptr, *grow = nullptr, *list = nullptr, *tile_row = nullptr;
-  uint64_t* info = nullptr;
+  uint64_t *info = nullptr, *dense_items = nullptr;
   ALLOC(zero, z.zero_words);
   ALLOC(key, nv);
   ALLOC(grow, nv);
   ALLOC(info, nv);
   ALLOC(list, nnz + LIST_PAD);
   ALLOC(tile_row, z.ntiles);
+  ALLOC(dense_items, z.dense_items);
   unsigned long long* acc = (unsigned long long*)zero;
   unsigned long long* gacc = (unsigned long long*)(zero + z.w_gacc);
   uint32_t* err = zero + z.w_err;
@@ -2255,7 +2288,7 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
                         (Cross*)(zero + z.w_cross), nullptr, nullptr, zero + z.w_cnt, acc, err, vbase, grow, gacc};
     k_sw_orient<false, true, false><<<grid_of_work(z.ntiles, 1, (int64_t)di.cus * 8), OTHREADS, 0, s>>>(oa);
     k_sw_cross<false, true, false><<<grid_of_work(z.ntiles, 256, 256), 256, 0, s>>>(oa);
-    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr, nullptr}, nullptr, zero + z.w_cnt, range, acc,
+    CountArgs ca{nv, nnz, z.ntiles, in.off, list, info, key, tile_row, {nullptr, nullptr, dense_items}, nullptr, zero + z.w_cnt, range, 0, acc,
                  err, vbase, grow, gacc};
     // (by default 2,048 entries a turn, fewer where that leaves less than four
     // turns a wavefront; 4,096 graphs, 3e8 edges: 19.5 ms with 512, 17.5 with
@@ -2263,11 +2296,19 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
     // with 2,048, 0.21 with fewer)
     if (range <= 0) range = std::max<int64_t>(64, std::min<int64_t>(2048, (nnz / (di.cus * 64) + 63) & ~(int64_t)63));
     ca.range = range;
+    const bool low = nmax <= DENSE_RANKS<false, DENSE_LOW>;
+    ca.window = low ? DENSE_RANKS<false, DENSE_LOW> : DENSE_RANKS<false>;
     const unsigned grid = grid_of_work((nnz + range - 1) / range, waves, groups);
     auto count = [&](auto wide) {
       constexpr bool W = decltype(wide)::value;
-      if (nmax <= DIRECT_N) launch_small<true, false, W>(nmax, grid, waves, ca, s);
-      else k_sw_rest<false, true, false, W><<<grid, waves * 64, 0, s>>>(ca);
+      if (nmax <= DIRECT_N) {
+        launch_small<true, false, W>(nmax, grid, waves, ca, s);
+      } else {
+        k_sw_items<true, false><<<grid_of_work(nv, 4096, 4096), 256, 0, s>>>(ca);
+        if (low) k_sw_dense<true, false, W, DENSE_LOW><<<(unsigned)di.cus * 4, DENSE_THREADS / 4, 0, s>>>(ca);
+        else k_sw_dense<true, false, W, DENSE_WORDS><<<(unsigned)di.cus, DENSE_THREADS, 0, s>>>(ca);
+        k_sw_rest<false, true, false, W><<<grid, waves * 64, 0, s>>>(ca);
+      }
     };
     if (nnz + LIST_PAD < ((int64_t)1 << 30)) count(std::false_type{}); else count(std::true_type{});
   }
