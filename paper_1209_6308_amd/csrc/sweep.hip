@@ -1121,20 +1121,20 @@ __device__ __forceinline__ void set_bits(uint32_t* tab, uint32_t w) {
 }
 
 // Hash table of list words, open addressing on the low bits of the id; at most
-// TAB_MAX of its TAB_WORDS slots are taken, so every search ends.
+// half of its mask + 1 slots are taken, so every search ends.
 template <bool LAB>
-__device__ __forceinline__ uint32_t probe_hash(const uint32_t* tab, uint32_t w) {
+__device__ __forceinline__ uint32_t probe_hash(const uint32_t* tab, uint32_t w, uint32_t mask = TAB_WORDS - 1) {
   const uint32_t key = w & IDM<LAB>;
-  uint32_t h = key & (TAB_WORDS - 1), v = tab[h];
+  uint32_t h = key & mask, v = tab[h];
   while (v != SLOT_FREE && (v & IDM<LAB>) != key) {
-    h = (h + 1) & (TAB_WORDS - 1);
+    h = (h + 1) & mask;
     v = tab[h];
   }
   return (v & IDM<LAB>) == key ? v : 0u;
 }
-__device__ __forceinline__ void set_hash(uint32_t* tab, uint32_t w) {
-  uint32_t h = w & (TAB_WORDS - 1);
-  while (atomicCAS(&tab[h], SLOT_FREE, w) != SLOT_FREE) h = (h + 1) & (TAB_WORDS - 1);
+__device__ __forceinline__ void set_hash(uint32_t* tab, uint32_t w, uint32_t mask = TAB_WORDS - 1) {
+  uint32_t h = w & mask;
+  while (atomicCAS(&tab[h], SLOT_FREE, w) != SLOT_FREE) h = (h + 1) & mask;
 }
 
 // The in-list vertices x of one batch: byte offset of N+(x); its length, the
@@ -1173,9 +1173,12 @@ __device__ __forceinline__ int list_x(XList<WIDE>& L, const uint32_t* __restrict
 // are in flight while the other is counted (loads are never skipped, an idle
 // lane rereads the list's first words: the wait for a set is then for its own
 // loads only). A list in rank order ends with the step that reaches y's rank.
+// MULTI: of several y, each list with the number of its y's table, and yranks
+// their ranks if SORTED.
 template <int GL, bool SORTED, bool TOP, bool WIDE, bool MULTI, class T, class Probe>
 __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const XList<WIDE>& L, int cnt,
-                                       uint32_t yrank, int lane, T& tri, Probe probe) {
+                                       uint32_t yrank, int lane, T& tri, Probe probe,
+                                       const uint32_t* yranks = nullptr) {
   constexpr uint64_t G0 = GL == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;  // first lane of each group
   constexpr int STEP = 4 * GL, SETS = 64 / GL;
   const int l4 = (lane & (GL - 1)) * 4;
@@ -1184,7 +1187,8 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
     typename std::conditional<WIDE, uint64_t, uint32_t>::type o;  // byte offset of the lane's next entries
     int r;         // 8 - 2 * entries of the list from there on (8 or more: none)
     uint32_t g8;
-    uint32_t lim;  // SORTED: the rank that ends the list; MULTI: the list's table
+    uint32_t lim;  // SORTED: the rank that ends the list
+    uint32_t tab;  // MULTI: the list's table
     uint32_t w[4];
   } sl[2];
   auto load = [&](Slot& s) {
@@ -1199,21 +1203,22 @@ __device__ __forceinline__ void stream(const uint32_t* __restrict__ list, const 
       s.r = 8 + 2 * (l4 - (int)(m & LEN_MASK));
       s.g8 = (m >> 30) * 0x55u | (T::LAB ? (m >> 29 & 1u) * 0xAA00u : 0u);
       // (lists of up to SORT_MIN entries are not sorted)
-      if (MULTI) s.lim = m >> 24 & 15u;
-      else s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : yrank;
+      if (MULTI) s.tab = m >> 24 & 15u;
+      if (SORTED)
+        s.lim = (m & UNSORTED) || (STEP < (int)SORT_MIN && (m & LEN_MASK) <= SORT_MIN) ? ~0u : MULTI ? yranks[s.tab] : yrank;
     }
   };
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     sl[i].o = 0;
-    sl[i].g8 = sl[i].lim = 0;
+    sl[i].g8 = sl[i].lim = sl[i].tab = 0;
     take(sl[i], i * SETS + lane / GL);
     load(sl[i]);
   }
   int next = 2 * SETS;
   auto step = [&](Slot& s) {
     uint32_t y[4];
-    probe(s.w, y, s.lim);
+    probe(s.w, y, s.tab);
     tri.template add4<TOP>(s.w, y, s.r, s.g8);
     // lists that end here: their first lane has at most one step left, or the
     // last entry read has reached y
@@ -1736,81 +1741,149 @@ __device__ __forceinline__ uint32_t xcd_block() {
   return x * q + min(x, r) + blockIdx.x / 8;
 }
 
+// inclusive maximum over the lanes of a wavefront
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));  // row_bcast:15, 31
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
 // The other vertices of a ranked graph (RANK), and all vertices of a batch with
-// members above DIRECT_N: a wavefront takes a range of entries and the rows
-// whose in-lists lie in it, one row at a time, with a hash table of N+(y) filled
-// TAB_MAX entries at a time. BAT: a batch, counted by graph.
+// members above DIRECT_N that k_sw_dense does not take: a wavefront takes a range
+// of entries and the rows whose in-lists lie in it, up to 16 of at most 32
+// entries of N+(y) at once (4 of at most 128), each with its share of the hash
+// table, their in-lists of up to 64 entries in all as one list whose x carry
+// their row's table. Longer ones go alone, the table filled TAB_MAX entries at a
+// time. One row at a time spent its time on the dependent reads of two or three
+// entries: slower than the merge on graphs of low degree. BAT: a batch, counted
+// by graph.
 template <bool RANK, bool BAT, bool LAB, bool WIDE>
 __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
-  __shared__ uint32_t tabs[REST_WAVES][TAB_WORDS];
+  __shared__ alignas(16) uint32_t tabs[REST_WAVES][TAB_WORDS];
+  __shared__ uint32_t marks[REST_WAVES][64], rows[REST_WAVES][16], ranks[RANK ? REST_WAVES : 1][16];
   __shared__ XList<WIDE> xl[REST_WAVES];
   if (refused(a.err)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t* tab = tabs[w];
+  uint32_t *tab = tabs[w], *mark = marks[w], *row = rows[w], *yranks = ranks[RANK ? w : 0];
   XList<WIDE>& L = xl[w];
-  for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < TAB_WORDS / 256; ++i)
+      reinterpret_cast<uint4*>(tab)[i * 64 + lane] = make_uint4(SLOT_FREE, SLOT_FREE, SLOT_FREE, SLOT_FREE);
+  };
+  clear();
+  using Pos = typename std::conditional<WIDE, uint64_t, uint32_t>::type;  // in the list
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   uint32_t graph = 0;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
   for (int64_t j0 = ((int64_t)xcd_block() * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
     const int64_t j1 = min(j0 + a.range, a.nnz);
     for (int64_t r = row_of(a, j0, lane);; r += 64) {
-      int64_t lo = 0, hi = 0, e = a.nnz;
-      uint64_t in = 0;
-      uint32_t yr = 0;
+      // 64 rows, one a lane: N+ and the part of the in-list in the range
+      Pos start = 0, lo = 0;
+      uint32_t plus = 0, num = 0, yr = 0;
+      int64_t e = a.nnz;
       if (r + lane < a.n) {
-        in = a.info[r + lane];
+        const uint64_t in = a.info[r + lane];
         e = a.off[r + lane + 1];
-        const uint32_t plus = (uint32_t)in & LEN_MASK;
-        const int64_t bs = (int64_t)(in >> 24) + plus;
-        lo = max(bs, j0);
-        hi = min(e, j1);
-        if (plus == 0) hi = lo;
-        if (RANK && hi > lo) {
-          yr = a.rank[r + lane];
-          if (route<LAB>(yr, plus, e - bs) != 3) hi = lo;
-        }
-        if (BAT && hi > lo) {
-          yr = a.grow[r + lane];
-          if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
-              dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[yr + 1] - a.vbase[yr])))
-            hi = lo;
+        plus = (uint32_t)in & LEN_MASK;
+        start = (Pos)(in >> 24);
+        const int64_t bs = (int64_t)(in >> 24) + plus, b = max(bs, j0);
+        const int64_t hi = min(e, j1);
+        if (plus && hi > b) {
+          lo = (Pos)b;
+          num = (uint32_t)(hi - b);
+          if (RANK) {
+            yr = a.rank[r + lane];
+            if (route<LAB>(yr, plus, e - bs) != 3) num = 0;
+          }
+          if (BAT) {
+            yr = a.grow[r + lane];
+            if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
+                dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[yr + 1] - a.vbase[yr])))
+              num = 0;
+          }
         }
       }
-      uint64_t todo = __ballot(hi > lo);
+      const bool done = rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n;
+      uint64_t todo = __ballot(num > 0);
       while (todo) {
         const int s = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const uint64_t yi = rl64(in, s);
-        const int64_t f0 = (int64_t)(yi >> 24), l0 = (int64_t)rl64((uint64_t)lo, s), l1 = (int64_t)rl64((uint64_t)hi, s);
-        const uint32_t plus = (uint32_t)yi & LEN_MASK, rk = rl(yr, s);
         const uint64_t* info = a.info;
         if (BAT) {
-          if (rk != graph) {
+          const uint32_t g = rl(yr, s);
+          if (g != graph) {
             tri.flush(a.gacc + (uint64_t)graph * 16, lane);
-            graph = rk;
+            graph = g;
           }
           info += a.vbase[graph];
         }
-        for (uint32_t f = 0; f < plus; f += TAB_MAX) {
-          const uint32_t fe = min(f + TAB_MAX, plus);
-          for (uint32_t i = f + lane; i < fe; i += 64) set_hash(tab, a.list[f0 + i]);
+        // the next rows that take a table of this size: 2^bits slots, 2^lanes lanes
+        const uint32_t first = rl(plus, s);
+        int bits = first <= 16 ? 6 : min(34 - (int)__builtin_clz(first - 1), 10);  // at most a quarter of them taken
+        uint64_t sel = todo & __ballot(plus <= 1u << (bits - 2) && (!BAT || yr == graph));
+        if (bits == 10) sel = 1ull << s;
+        const uint32_t v = sel >> lane & 1 ? num : 0u, upto = wave_scan(v);
+        const uint32_t q = (uint32_t)__popcll(sel & below(lane));
+        sel = __ballot(v && (q == 0 || (upto <= 64 && q < 1u << (10 - bits))));
+        todo &= ~sel;
+        const bool alone = (sel & (sel - 1)) == 0;  // (also a row whose in-list fills more than a step)
+        if (alone) bits = 10;
+        const int lanes = bits - 4;
+        const bool mine = sel >> lane & 1;
+        mark[lane] = 0;
+        wave_sync();
+        if (mine) {
+          mark[upto - v] = (uint32_t)lane + 1;
+          row[q] = (uint32_t)lane;
+          if (RANK) yranks[q] = yr;
+        }
+        wave_sync();
+        // entry p of the in-lists is of row `own`; lanes 2^lanes k .. fill the table of row k
+        const int own = (int)wave_max(mark[lane]) - 1, k0 = lane >> lanes, n0 = __popcll(sel);
+        const uint32_t total = rl(upto, 63 - __builtin_clzll(sel)), tag = __shfl(q, own, 64) << 24;
+        const Pos from = __shfl(lo - (Pos)(upto - v), own, 64);
+        const int of = k0 < n0 ? (int)row[k0] : -1;
+        const Pos mylist = __shfl(start, max(of, 0), 64);
+        const uint32_t len = __shfl(plus, max(of, 0), 64), mylen = of < 0 ? 0u : len, mask = (1u << bits) - 1;
+        uint32_t* mytab = tab + (k0 << bits);
+        const uint32_t longest = alone ? first : 1u;  // (the others take one filling)
+        for (uint32_t f = 0; f < longest; f += TAB_MAX) {
+          for (uint32_t i = f + (lane & ((1 << lanes) - 1)); i < min(f + TAB_MAX, mylen); i += 1u << lanes)
+            set_hash(mytab, a.list[mylist + i], mask);
           wave_sync();
-          for (int64_t k = l0; k < l1; k += 64) {
-            const int nx = list_x<LAB, WIDE>(L, a.list + k, (int)min((int64_t)64, l1 - k), info, lane);
+          for (uint32_t k = 0; k < total; k += 64) {
+            uint32_t g = 0;
+            uint64_t xi = 0;
+            if (k + lane < total) {
+              g = a.list[from + (k + lane)];
+              xi = info[g & IDM<LAB>];
+            }
+            const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
+            const uint64_t m = __ballot(has);
+            if (has) {
+              const int i = __popcll(m & below(lane));
+              L.p[i] = xi >> 24 << 2;
+              L.m[i] = (g & ~IDM<LAB>) | tag | ((uint32_t)xi & (LEN_MASK | UNSORTED));
+            }
             wave_sync();
-            stream<8, RANK, true, WIDE, false>(a.list, L, nx, rk, lane, tri,
-                                               [&](const uint32_t (&q)[4], uint32_t (&g)[4], uint32_t) {
+            stream<8, RANK, true, WIDE, true>(a.list, L, __popcll(m), 0, lane, tri,
+                                              [&](const uint32_t (&z)[4], uint32_t (&y)[4], uint32_t t) {
+              const uint32_t* mt = tab + (t << bits);
 #pragma unroll
-              for (int i = 0; i < 4; ++i) g[i] = probe_hash<LAB>(tab, q[i]);
-            });
+              for (int i = 0; i < 4; ++i) y[i] = probe_hash<LAB>(mt, z[i], mask);
+            }, yranks);
             wave_sync();
           }
-          for (int i = lane; i < TAB_WORDS; i += 64) tab[i] = SLOT_FREE;
+          clear();
           wave_sync();
         }
       }
-      if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
+      if (done) break;
     }
   }
   if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);

@@ -304,3 +304,68 @@ def test_host_entry_finds_what_the_host_check_finds(torch, scale):
                     triad.triad_census(g.n, off, nb, fl, validate=level)
                 assert e.value.status == want, (f.__name__, h and h.__name__, level)
     assert triad.triad_census(g.n, g.offsets, g.nbrs, g.flags, validate=1) == oracle.census_mt(g)
+
+
+@pytest.mark.parametrize("sizes", [
+    [2] * 9000, [3] * 7000, [2, 3, 4, 5] * 4000,  # many rows of an in-list of one or two
+    [16, 17, 18, 19] * 300,                       # N+ around 16 entries: 16 or 8 rows at once
+    [31, 32, 33, 34, 35] * 150,                   # around 32, in-lists up to the workgroups'
+    [64, 65, 66, 128, 129, 130] * 60,             # around 64 and 128: four, two rows, one
+    [1, 2, 40, 3, 100, 2, 300, 17] * 60,          # all mixed
+], ids=lambda s: "%dx%d" % (len(s), s[0]))
+def test_rows_taken_together(torch, sizes):
+    """Vertices with short in-lists, as many of which share a wavefront as their
+    lists towards higher degrees allow."""
+    n, d = _cliques(torch, sizes, False)
+    want = [0] * 16
+    want[8], want[1] = sum(comb(k, 3) for k in sizes), sum(comb(k, 2) * (n - k) for k in sizes)
+    want[0] = comb(n, 3) - sum(want)
+    assert n > 16384
+    assert _census(n, d) == want
+    lab = _lab(n, d)
+    assert lab[21] == want[8] and sum(lab) == comb(n, 3)
+    assert all(lab[s] == 0 for s in range(64) if s not in (0, 1, 4, 16, 21))
+
+
+@pytest.mark.parametrize("shape", ["path", "grid", "tree"])
+def test_low_degrees_against_the_merge(torch, shape):
+    rng = np.random.default_rng(5)
+    n = 60000
+    i = np.arange(n)
+    if shape == "path":
+        s, t = i[:-1], i[1:]
+    elif shape == "grid":
+        s, t = np.concatenate([i[i % 300 > 0], i[300:]]), np.concatenate([i[i % 300 > 0] - 1, i[300:] - 300])
+    else:
+        s, t = i[1:], (rng.random(n - 1) * i[1:]).astype(np.int64)
+    extra = rng.integers(0, n, 20000)  # some triangles
+    s, t = np.concatenate([s, extra]), np.concatenate([t, np.minimum(extra + 2, n - 1)])
+    p = rng.permutation(n)
+    flip = rng.random(s.size) < 0.5
+    g = graphs.build_csr(n, p[np.where(flip, t, s)].astype(np.int32), p[np.where(flip, s, t)].astype(np.int32),
+                         recip_p=0.2, recip_seed=1)
+    d = triad.to_device(g)
+    assert _census(n, d) == _census(n, d, chunk=32768) == oracle.census_mt(g)
+    assert _lab(n, d) == _lab(n, d, chunk=32768)
+
+
+def test_batch_rows_taken_together(torch):
+    """Members above and below the id-indexed tables one after another, so that the
+    64 rows a wavefront looks at belong to several: rows of all list lengths."""
+    rng = np.random.default_rng(12)
+    members = []
+    for n in (17000, 5, 30, 9, 20000, 1, 300, 16500, 40, 2):
+        k = min(n, 150)
+        core = rng.permutation(n)[:k]
+        s = np.concatenate([rng.choice(core, 2 * k), rng.integers(0, n, 3 * n)])
+        t = np.concatenate([rng.choice(core, 2 * k), rng.integers(0, n, n), rng.choice(core, 2 * n)])
+        members.append(graphs.build_csr(n, s.astype(np.int32), t.astype(np.int32), recip_p=0.2, recip_seed=2))
+    B = graphs.concat_csrs(members * 2)
+    d = triad.batch_to_device(B)
+    want = [oracle.census_mt(g) for g in members] * 2
+    assert triad.triad_census_batch(B.G, int(B.vbase[-1]), B.nnz, *d) == want
+    plan = triad.BatchPlan(B.G, int(B.vbase[-1]), B.nnz, *d, waves_per_group=1, grid_groups=5, kernel_variant=1)
+    for _ in range(2):
+        plan.launch()
+        assert plan.result() == want
+    plan.close()
