@@ -1762,21 +1762,27 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
 // entries: slower than the merge on graphs of low degree. BAT: a batch, counted
 // by graph.
 template <bool RANK, bool BAT, bool LAB, bool WIDE>
-__global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
+__global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountArgs a) {
   __shared__ alignas(16) uint32_t tabs[REST_WAVES][TAB_WORDS];
   __shared__ uint32_t marks[REST_WAVES][64], rows[REST_WAVES][16], ranks[RANK ? REST_WAVES : 1][16];
   __shared__ XList<WIDE> xl[REST_WAVES];
+  using Pos = typename std::conditional<WIDE, uint64_t, uint32_t>::type;  // in the list
+  struct Row {
+    Pos start, lo;  // of N+, of the part of the in-list
+    uint32_t plus, num, key;  // their lengths; the rank or the graph
+  };
+  __shared__ Row kept[REST_WAVES][64];  // (in registers, they spill in every step over the rows)
   if (refused(a.err)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t *tab = tabs[w], *mark = marks[w], *row = rows[w], *yranks = ranks[RANK ? w : 0];
   XList<WIDE>& L = xl[w];
+  Row* keep = kept[w];
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < TAB_WORDS / 256; ++i)
       reinterpret_cast<uint4*>(tab)[i * 64 + lane] = make_uint4(SLOT_FREE, SLOT_FREE, SLOT_FREE, SLOT_FREE);
   };
   clear();
-  using Pos = typename std::conditional<WIDE, uint64_t, uint32_t>::type;  // in the list
   typename std::conditional<LAB, TriLab, Tri>::type tri;
   uint32_t graph = 0;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
@@ -1784,29 +1790,28 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
     const int64_t j1 = min(j0 + a.range, a.nnz);
     for (int64_t r = row_of(a, j0, lane);; r += 64) {
       // 64 rows, one a lane: N+ and the part of the in-list in the range
-      Pos start = 0, lo = 0;
-      uint32_t plus = 0, num = 0, yr = 0;
+      uint32_t num = 0;
       int64_t e = a.nnz;
       if (r + lane < a.n) {
         const uint64_t in = a.info[r + lane];
         e = a.off[r + lane + 1];
-        plus = (uint32_t)in & LEN_MASK;
-        start = (Pos)(in >> 24);
+        const uint32_t plus = (uint32_t)in & LEN_MASK;
         const int64_t bs = (int64_t)(in >> 24) + plus, b = max(bs, j0);
         const int64_t hi = min(e, j1);
         if (plus && hi > b) {
-          lo = (Pos)b;
           num = (uint32_t)(hi - b);
+          uint32_t key = 0;
           if (RANK) {
-            yr = a.rank[r + lane];
-            if (route<LAB>(yr, plus, e - bs) != 3) num = 0;
+            key = a.rank[r + lane];
+            if (route<LAB>(key, plus, e - bs) != 3) num = 0;
           }
           if (BAT) {
-            yr = a.grow[r + lane];
+            key = a.grow[r + lane];
             if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
-                dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[yr + 1] - a.vbase[yr])))
+                dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[key + 1] - a.vbase[key])))
               num = 0;
           }
+          keep[lane] = Row{(Pos)(in >> 24), (Pos)b, plus, num, key};
         }
       }
       const bool done = rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n;
@@ -1814,8 +1819,9 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
       while (todo) {
         const int s = __builtin_ctzll(todo);
         const uint64_t* info = a.info;
+        const Row me = keep[lane];  // (rows not listed: of an earlier step, out of `todo`)
         if (BAT) {
-          const uint32_t g = rl(yr, s);
+          const uint32_t g = rl(me.key, s);
           if (g != graph) {
             tri.flush(a.gacc + (uint64_t)graph * 16, lane);
             graph = g;
@@ -1823,16 +1829,17 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
           info += a.vbase[graph];
         }
         // the next rows that take a table of this size: 2^bits slots, 2^lanes lanes
-        const uint32_t first = rl(plus, s);
+        const uint32_t first = rl(me.plus, s);
         int bits = first <= 16 ? 6 : min(34 - (int)__builtin_clz(first - 1), 10);  // at most a quarter of them taken
-        uint64_t sel = todo & __ballot(plus <= 1u << (bits - 2) && (!BAT || yr == graph));
+        uint64_t sel = todo & __ballot(me.plus <= 1u << (bits - 2) && (!BAT || me.key == graph));
         if (bits == 10) sel = 1ull << s;
-        const uint32_t v = sel >> lane & 1 ? num : 0u, upto = wave_scan(v);
+        const uint32_t v = sel >> lane & 1 ? me.num : 0u, upto = wave_scan(v);
         const uint32_t q = (uint32_t)__popcll(sel & below(lane));
         sel = __ballot(v && (q == 0 || (upto <= 64 && q < 1u << (10 - bits))));
         todo &= ~sel;
-        const bool alone = (sel & (sel - 1)) == 0;  // (also a row whose in-list fills more than a step)
-        if (alone) bits = 10;
+        const int n0 = (int)__popcll(sel);
+        const bool alone = n0 == 1;  // (also a row whose in-list fills more than a step)
+        bits = alone ? 10 : 10 - (32 - (int)__builtin_clz(n0 - 1));  // as large as so few rows leave it
         const int lanes = bits - 4;
         const bool mine = sel >> lane & 1;
         mark[lane] = 0;
@@ -1840,16 +1847,16 @@ __global__ void __launch_bounds__(REST_WAVES * 64, 4) k_sw_rest(CountArgs a) {
         if (mine) {
           mark[upto - v] = (uint32_t)lane + 1;
           row[q] = (uint32_t)lane;
-          if (RANK) yranks[q] = yr;
+          if (RANK) yranks[q] = me.key;
         }
         wave_sync();
         // entry p of the in-lists is of row `own`; lanes 2^lanes k .. fill the table of row k
-        const int own = (int)wave_max(mark[lane]) - 1, k0 = lane >> lanes, n0 = __popcll(sel);
+        const int own = (int)wave_max(mark[lane]) - 1, k0 = lane >> lanes;
         const uint32_t total = rl(upto, 63 - __builtin_clzll(sel)), tag = __shfl(q, own, 64) << 24;
-        const Pos from = __shfl(lo - (Pos)(upto - v), own, 64);
+        const Pos from = keep[own].lo - (Pos)__shfl(upto - v, own, 64);
         const int of = k0 < n0 ? (int)row[k0] : -1;
-        const Pos mylist = __shfl(start, max(of, 0), 64);
-        const uint32_t len = __shfl(plus, max(of, 0), 64), mylen = of < 0 ? 0u : len, mask = (1u << bits) - 1;
+        const Pos mylist = keep[max(of, 0)].start;
+        const uint32_t mylen = of < 0 ? 0u : keep[of].plus, mask = (1u << bits) - 1;
         uint32_t* mytab = tab + (k0 << bits);
         const uint32_t longest = alone ? first : 1u;  // (the others take one filling)
         for (uint32_t f = 0; f < longest; f += TAB_MAX) {
