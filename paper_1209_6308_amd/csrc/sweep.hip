@@ -148,6 +148,8 @@ struct RowArgs {
   int32_t graphs;
   const int64_t* vbase;
   uint32_t* grow;
+  int64_t small;  // the largest member that k_sw_small's tables take (0: it is not launched)
+  uint32_t* big;  // set where a member is larger
   // labelled: the entries below the row's own id, for rows that cross tiles
   const int32_t* nbr;
   struct Cross* cross;
@@ -187,6 +189,7 @@ __global__ void __launch_bounds__(PER > 1 ? ROWS_THREADS : 256) k_sw_rows(RowArg
         if (a.vbase[mid] <= u) lo = mid; else hi = mid;
       }
       a.grow[u] = (uint32_t)lo;
+      if (a.small && a.vbase[lo + 1] - a.vbase[lo] > a.small) *a.big = 1;
     }
     if (a.deg) a.deg[u] = d;
     if (PER > 1) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
@@ -1256,9 +1259,9 @@ struct CountArgs {
   const uint32_t* tile_row;
   uint64_t* items[3];  // of k_sw_hubs, k_sw_mids, k_sw_dense: y << 32 | chunk
   uint64_t* clk;       // stage starts, or NULL
-  uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed
+  uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed, [9] see RowArgs::big
   int64_t range;       // k_sw_rest: entries of one wavefront
-  uint32_t window;     // a batch: ids of k_sw_dense's table
+  uint32_t window;     // a batch: ids of k_sw_dense's table (0: it is not launched)
   unsigned long long* acc;
   uint32_t* err;
   // a batch (see OrientArgs)
@@ -1772,7 +1775,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
     uint32_t plus, num, key;  // their lengths; the rank or the graph
   };
   __shared__ Row kept[REST_WAVES][64];  // (in registers, they spill in every step over the rows)
-  if (refused(a.err)) return;
+  if (refused(a.err) || (BAT && a.window == 0 && a.counts[9] == 0)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t *tab = tabs[w], *mark = marks[w], *row = rows[w], *yranks = ranks[RANK ? w : 0];
   XList<WIDE>& L = xl[w];
@@ -1807,7 +1810,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
           }
           if (BAT) {
             key = a.grow[r + lane];
-            if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
+            if (a.window && (plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
                 dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[key + 1] - a.vbase[key])))
               num = 0;
           }
@@ -1914,7 +1917,7 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
   __shared__ XList<WIDE> xl[WAVES];
   stamp(a.clk, 1);
   stamp(a.clk, 2);
-  if (refused(a.err)) return;
+  if (refused(a.err) || (BAT && a.counts[9])) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t* tab = tabs[w];
   uint32_t* mine = tab + lane / LR * TW;
@@ -2015,11 +2018,13 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
 }
 
 // k_sw_small by the largest member: tables of 8 KB a wavefront in all (labelled
-// 16 KB), so that four workgroups fit a CU's LDS.
+// 16 KB), so that four workgroups fit a CU's LDS. The members that fit: 0 if k_sw_rest
+// takes the batch.
+int64_t small_table(int64_t nmax) { return nmax <= 4096 ? 4096 : nmax <= 8192 ? 8192 : nmax <= DIRECT_N ? DIRECT_N : 0; }
 template <bool BAT, bool LAB, bool WIDE, int WAVES>
 void launch_small_of(int64_t nmax, unsigned grid, const CountArgs& ca, hipStream_t s) {
-  if (nmax <= 4096) k_sw_small<4096, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
-  else if (nmax <= 8192) k_sw_small<8192, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  if (small_table(nmax) == 4096) k_sw_small<4096, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  else if (small_table(nmax) == 8192) k_sw_small<8192, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
   else k_sw_small<DIRECT_N, 2, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
 }
 template <bool BAT, bool LAB, bool WIDE>
@@ -2218,7 +2223,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     ALLOC(dense_items, nnz / TAB_MAX + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
-                   tile_row, err, 0, nullptr, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
+                   tile_row, err, 0, nullptr, nullptr, 0, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
   // (16 rows a thread: fewer atomics on the bucket counters; 4 while that
   // leaves fewer workgroups than four a CU)
   const bool many = n > (int64_t)di.cus * 4 * ROWS_THREADS * 16;
@@ -2358,7 +2363,7 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words, nullptr);
   if (nv > 0) {
     const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow,
-                     nullptr, nullptr};
+                     small_table(nmax), zero + z.w_cnt + 9, nullptr, nullptr};
     k_sw_rows<1><<<grid_of_work(nv, 256, INT32_MAX), 256, 0, s>>>(ra);
   }
   if (nv > 0 && nnz > 0) {
@@ -2383,6 +2388,11 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
       constexpr bool W = decltype(wide)::value;
       if (nmax <= DIRECT_N) {
         launch_small<true, false, W>(nmax, grid, waves, ca, s);
+        // A plan's launches read the graph bases as they are then: if they were
+        // rewritten with a member past these tables, k_sw_small leaves the batch to
+        // this one (else 3 us).
+        ca.window = 0;
+        k_sw_rest<false, true, false, W><<<grid, waves * 64, 0, s>>>(ca);
       } else {
         k_sw_items<true, false><<<grid_of_work(nv, 4096, 4096), 256, 0, s>>>(ca);
         if (low) k_sw_dense<true, false, W, DENSE_LOW><<<(unsigned)di.cus * 4, DENSE_THREADS / 4, 0, s>>>(ca);

@@ -250,3 +250,41 @@ def test_destroyed_plan_waits_for_every_stream(torch):
         plan.launch(s)
         assert plan.result() == want
     plan.close()
+
+
+def _pairs(n, k, rng):
+    """A graph of n vertices and exactly k connected pairs."""
+    key = np.zeros(0, np.int64)
+    while key.size < k:
+        a, b = rng.integers(0, n, (2, 2 * k))
+        key = np.unique(np.concatenate([key, (np.minimum(a, b) * n + np.maximum(a, b))[a != b]]))
+    key = rng.permutation(key)[:k]
+    a, b = key // n, key % n
+    flip = rng.random(k) < 0.5
+    return graphs.build_csr(n, np.where(flip, b, a).astype(np.int32), np.where(flip, a, b).astype(np.int32),
+                            recip_p=0.2, recip_seed=1)
+
+
+@pytest.mark.parametrize("before,after", [(2000, 4097), (2000, 20000), (8192, 8193), (5000, 20000), (16384, 16385)])
+def test_plan_inputs_rewritten_with_larger_members(torch, before, after):
+    """A kept plan whose arrays are refilled in place with another batch of the same
+    totals, a member of which outgrows the tables chosen at creation, and back."""
+    rng = np.random.default_rng(after)
+    rows = 24000
+    batches = []
+    for big in (before, after):
+        sizes = [big] + [(rows - big) // 11] * 10
+        sizes.append(rows - sum(sizes))
+        ks = [20000] + [1000] * 11
+        batches.append(concat([_pairs(n, k, rng) for n, k in zip(sizes, ks)]))
+    a, b = batches
+    assert a.nnz == b.nnz and int(a.vbase[-1]) == int(b.vbase[-1]) == rows
+    want = [[oracle.census(B.graph(g)) for g in range(B.G)] for B in batches]
+    d = triad.batch_to_device(a)
+    plan = triad.BatchPlan(a.G, rows, a.nnz, *d)
+    for k in (0, 1, 0, 1):
+        for t, x in zip(d, (batches[k].vbase, batches[k].offsets, batches[k].nbrs, batches[k].flags)):
+            t.copy_(torch.from_numpy(x))
+        plan.launch()
+        assert plan.result() == want[k]
+    plan.close()
