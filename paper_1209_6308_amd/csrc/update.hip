@@ -47,7 +47,7 @@ constexpr int UPD_SMALL = 2048;      // operations that one workgroup sorts in L
 constexpr int SMALL_T = 1024;
 constexpr int64_t UPD_PART = 1024;   // entries of the shorter row that one wavefront searches
 constexpr int64_t UPD_PARTS = 64;    // parts of one pair at most
-constexpr int64_t UPD_QUEUE = 1 << 18;  // parts put off to k_upd_parts
+constexpr int64_t UPD_QUEUE = 1 << 18;  // parts put off at most
 
 __device__ __forceinline__ uint32_t mirror2(uint32_t f) { return ((f & 1u) << 1) | (f >> 1); }
 __device__ __forceinline__ uint32_t entry_flag(const uint8_t* flg, int64_t j) {
@@ -275,6 +275,7 @@ struct DeltaArgs {
   unsigned long long* acc;  // UPD_COPIES x UPD_ACC words, two's complement
   uint32_t* u;
   uint64_t* queue;    // parts put off: entry << 8 | part
+  uint32_t room;      // their number at most
 };
 constexpr int UPD_COPIES = 32, UPD_ACC = 32;
 __device__ __forceinline__ unsigned long long* acc_of(const DeltaArgs& a) {
@@ -474,8 +475,8 @@ __device__ void flush_classes(int32_t* h, int lane, unsigned long long* acc) {
 
 // One wavefront per changed pair (the entries with row < column): the first
 // UPD_PART entries of its shorter row, and its changes. Further parts go to
-// other wavefronts (k_upd_parts) through a queue, or are taken here if it is
-// full. MORE: the queue's parts.
+// other wavefronts (MORE, a second launch) through a queue, or are taken here if
+// it is full.
 template <bool MORE>
 __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
   __shared__ int32_t hist[UT / 64][16 * 64];
@@ -485,7 +486,7 @@ __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
   int32_t* h = hist[threadIdx.x >> 6];
   for (int c = 0; c < 16; ++c) h[c * 64 + lane] = 0;
   const int64_t nw = ((int64_t)gridDim.x * UT) >> 6, nE = A.u[U_NE];
-  const int64_t items = MORE ? min((int64_t)A.u[U_PARTS], UPD_QUEUE) : nE;
+  const int64_t items = MORE ? (int64_t)min(A.u[U_PARTS], A.room) : nE;
   uint64_t steps = 0;
   for (int64_t it = ((int64_t)blockIdx.x * UT + threadIdx.x) >> 6; it < items; it += nw) {
     const int64_t q = MORE ? (int64_t)(A.queue[it] >> 8) : it;
@@ -501,13 +502,15 @@ __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
       pair_changes(A, p, lane, h);
       const int parts = (int)((len + sz - 1) / sz);
       if (parts > 1) {
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&A.u[U_PARTS], (uint32_t)(parts - 1));
+        // no ticket is drawn from a full queue: the pairs of one call could wrap it
+        uint32_t at = A.room;
+        if (lane == 0 && __hip_atomic_load(&A.u[U_PARTS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < A.room)
+          at = atomicAdd(&A.u[U_PARTS], (uint32_t)(parts - 1));
         at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
         for (int c = 1 + lane; c < parts; c += 64)
-          if ((int64_t)at + c - 1 < UPD_QUEUE) A.queue[at + c - 1] = (uint64_t)q << 8 | (uint64_t)c;
+          if ((int64_t)at + c - 1 < A.room) A.queue[at + c - 1] = (uint64_t)q << 8 | (uint64_t)c;
         // the parts that found no room
-        const int64_t room = max((int64_t)0, min((int64_t)parts - 1, UPD_QUEUE - (int64_t)at));
+        const int64_t room = max((int64_t)0, min((int64_t)parts - 1, (int64_t)A.room - (int64_t)at));
         if (room < parts - 1) pair_part(A, p, (1 + room) * sz, len, lane, h);
       }
     }
@@ -686,7 +689,8 @@ int census_update(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
   ALLOC(E, N);
   ALLOC(P, N);
   ALLOC(S, N + 1);
-  ALLOC(queue, std::min(UPD_QUEUE, N * UPD_PARTS));
+  const int64_t room = std::min(UPD_QUEUE, N * UPD_PARTS);
+  ALLOC(queue, room);
   unsigned long long* acc = (unsigned long long*)zero;
   uint32_t* u = zero + 2 * UPD_COPIES * UPD_ACC;
   k_zero32<<<2, 256, 0, s>>>(zero, ZERO);
@@ -712,13 +716,13 @@ int census_update(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
     k_upd_emit<<<grid_of(N, 256, 65536), 256, 0, s>>>(ka, N, chg, cpos, st8, pos, E, P, net, u);
     if (int st = scan_i64(net, N, S, scratch, s)) return st;
   }
-  DeltaArgs a{g, E, {}, acc, u, queue};
+  DeltaArgs a{g, E, {}, acc, u, queue, (uint32_t)room};
   for (int c = 0; c < 64; ++c) a.lut[c >> 4] |= (uint64_t)classify_code((unsigned)c) << (4 * (c & 15));
   if (k > 0) {
     const unsigned waves4 = (unsigned)grid_of(N * 64, UT, di.cus * 8);
     k_upd_rows<<<waves4, UT, 0, s>>>(a);
     k_upd_pairs<false><<<waves4, UT, 0, s>>>(a);
-    k_upd_pairs<true><<<(unsigned)grid_of(std::min(UPD_QUEUE, N * UPD_PARTS) * 64, UT, di.cus * 8), UT, 0, s>>>(a);
+    k_upd_pairs<true><<<(unsigned)grid_of(room * 64, UT, di.cus * 8), UT, 0, s>>>(a);
   }
   if (new_csr) {
     k_new_offsets<<<grid_of(n + 1, 256, 65536), 256, 0, s>>>(g, E, S, noff, u);

@@ -219,3 +219,26 @@ def test_sliding_window_series(torch):
         assert np.array_equal(dev[0].cpu().numpy(), want.offsets)
         steps += 1
     assert steps == 17
+
+
+def test_more_parts_than_the_queue_holds(torch):
+    """All pairs of 100 hubs connected at once, then half of them cut again: 4,950
+    changed pairs of rows of 70,000 entries, cut into 64 parts each, of which the
+    queue for other wavefronts holds 262,144. Against the census of the new graph."""
+    hubs, n = 100, 100_100
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    leaf = torch.cat([torch.randperm(n - hubs, device="cuda", generator=g)[:70_000] + hubs for _ in range(hubs)])
+    hub = torch.arange(hubs, device="cuda").repeat_interleave(70_000)
+    flip = torch.rand(hub.numel(), device="cuda", generator=g) < 0.4
+    dev = triad.csr_from_arcs(n, torch.where(flip, hub, leaf).int(), torch.where(flip, leaf, hub).int())
+    i, j = torch.triu_indices(hubs, hubs, 1, device="cuda").int()
+    up = torch.rand(i.numel(), device="cuda", generator=g) < 0.5
+    a, b = torch.where(up, i, j), torch.where(up, j, i)
+    census = triad.triad_census_device(n, dev[1].numel(), *dev)[0]
+    for k, ins in ((a.numel(), 1), (a.numel() // 2, 0)):
+        kind = torch.full((k,), ins, dtype=torch.uint8, device="cuda")
+        got, dev, changed = triad.census_update(n, dev[1].numel(), *dev, census, a[:k].contiguous(), b[:k].contiguous(), kind)
+        assert changed == k
+        census = triad.triad_census_device(n, dev[1].numel(), *dev)[0]
+        assert got == census
