@@ -2217,8 +2217,9 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     ALLOC(mid, nnz / SORT_MIN + 1);
     ALLOC(lng, nnz / SORT_MID + 1);
     // an in-list of `minus` entries makes at most minus / CHUNK + 1 items, and
-    // only in-lists of MID_MIN_IN entries or N+ of more than TAB_MAX make any
-    ALLOC(hub_items, std::min(n, HUB_RANKS) + nnz / CHUNK + 1);
+    // only in-lists of MID_MIN_IN entries (hubs: HUB_MIN_IN) or N+ of more than
+    // TAB_MAX make any
+    ALLOC(hub_items, std::min(std::min(n, HUB_RANKS), nnz / HUB_MIN_IN) + nnz / CHUNK + 1);
     ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
     ALLOC(dense_items, nnz / TAB_MAX + nnz / CHUNK + 1);
   }

@@ -257,3 +257,17 @@ def test_held_memory_is_reused_and_released(torch):
     st, dw, hw = _raw(torch, fn, g, d, 17)
     assert st == 0 and _counts(hw) == want
     triad.release_memory()
+
+
+def test_census_scratch_of_ranked_graphs_with_few_entries(torch):
+    """At a cap of 20 bytes a vertex and 22 an entry, as the no-allocation entry
+    documents (28 and 22): enough from 16,385 vertices on."""
+    for n, arcs in ((16385, 0), (16385, 50), (30000, 3000), (65536, 0), (65536, 20), (100003, 70000)):
+        rng = np.random.default_rng(arcs)
+        s, d = rng.integers(0, n, (2, arcs))
+        g = graphs.build_csr(n, s.astype(np.int32), d.astype(np.int32))
+        dev = triad.to_device(g)
+        triad.set_memory_cap(20 * n + 22 * g.nnz)
+        got = triad.triad_census_device(n, g.nnz, *dev)[0]
+        triad.set_memory_cap(0)
+        assert got == oracle.census_mt(g)
