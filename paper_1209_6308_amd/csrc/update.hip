@@ -686,35 +686,36 @@ int census_update(int64_t n, int64_t nnz, const int64_t* off, const int32_t* nbr
   int64_t* S = nullptr;
   ALLOC(zero, ZERO);
   ALLOC(out, UPD_ACC + 3);
-  ALLOC(E, N);
   ALLOC(P, N);
   ALLOC(S, N + 1);
-  const int64_t room = std::min(UPD_QUEUE, N * UPD_PARTS);
+  // a pair has further parts for every UPD_PART entries of its shorter row, and at
+  // most nnz / UPD_PART rows are that long
+  const int64_t longs = nnz / UPD_PART, room = std::min(std::min(UPD_QUEUE, N * UPD_PARTS), longs * longs);
   ALLOC(queue, room);
   unsigned long long* acc = (unsigned long long*)zero;
   uint32_t* u = zero + 2 * UPD_COPIES * UPD_ACC;
   k_zero32<<<2, 256, 0, s>>>(zero, ZERO);
   if (k <= UPD_SMALL) {
+    ALLOC(E, N);
     k_upd_small<<<1, SMALL_T, 0, s>>>(g, (int)k, src, dst, ins, E, P, S, u);
   } else {
     uint64_t *ka = nullptr, *kb = nullptr;
     uint32_t *chg = nullptr, *cpos = nullptr, *pos = nullptr;
     uint8_t* st8 = nullptr;
-    int64_t* net = nullptr;
     ALLOC(ka, N);
     ALLOC(kb, N);
     ALLOC(chg, N);
     ALLOC(cpos, N);
     ALLOC(pos, N);
     ALLOC(st8, N);
-    ALLOC(net, N);
     k_upd_keys<<<grid_of(k, 256, 65536), 256, 0, s>>>(g, k, src, dst, ins, ka, u);
     // by (row, column, direction); operations keep their batch order within an arc
     if (int st = radix_sort_u64(&ka, &kb, N, 1, 2 + 2 * rb, scratch, s)) return st;
     k_upd_state<<<grid_of(N, 256, 65536), 256, 0, s>>>(g, ka, N, chg, st8, pos, u);
     if (int st = scan_u32(chg, N, cpos, u + U_NE, scratch, s)) return st;
-    k_upd_emit<<<grid_of(N, 256, 65536), 256, 0, s>>>(ka, N, chg, cpos, st8, pos, E, P, net, u);
-    if (int st = scan_i64(net, N, S, scratch, s)) return st;
+    E = kb;  // (the sort is done with it)
+    k_upd_emit<<<grid_of(N, 256, 65536), 256, 0, s>>>(ka, N, chg, cpos, st8, pos, E, P, S, u);
+    if (int st = scan_i64(S, N, S, scratch, s)) return st;
   }
   DeltaArgs a{g, E, {}, acc, u, queue, (uint32_t)room};
   for (int c = 0; c < 64; ++c) a.lut[c >> 4] |= (uint64_t)classify_code((unsigned)c) << (4 * (c & 15));

@@ -259,6 +259,32 @@ def test_held_memory_is_reused_and_released(torch):
     triad.release_memory()
 
 
+@pytest.mark.parametrize("updates", [601, 50000])
+def test_update_scratch_stays_in_its_bytes_per_update(torch, updates):
+    """A batch of arcs that all change something, at a cap of 89 bytes an update (with
+    the new CSR 32 more and a byte an entry): enough."""
+    n = 3001 if updates < 2048 else 400_000
+    rng = np.random.default_rng(updates)
+    s, d = rng.integers(0, n, (2, 12000))
+    g = graphs.build_csr(n, s[s != d].astype(np.int32), d[s != d].astype(np.int32))
+    key = rng.permutation(np.unique(rng.integers(0, n * n, 3 * updates)))
+    a, b = key // n, key % n
+    old = set(zip(*(x.tolist() for x in g.arcs())))
+    new = [(x, y) for x, y in zip(a.tolist(), b.tolist()) if x < y and (x, y) not in old and (y, x) not in old][:updates]
+    assert len(new) == updates
+    us, ud = (torch.tensor(c, dtype=torch.int32, device="cuda") for c in zip(*new))
+    ins = torch.ones(len(new), dtype=torch.uint8, device="cuda")
+    dev = triad.to_device(g)
+    census = oracle.census_mt(g)
+    triad.set_memory_cap(89 * len(new))
+    got, _, changed = triad.census_update(n, g.nnz, *dev, census, us, ud, ins, new_csr=False)
+    assert changed == len(new)
+    triad.set_memory_cap(121 * len(new) + g.nnz)
+    again, after, _ = triad.census_update(n, g.nnz, *dev, census, us, ud, ins)
+    triad.set_memory_cap(0)
+    assert again == got == triad.triad_census_device(n, after[1].numel(), *after)[0]
+
+
 def test_census_scratch_of_ranked_graphs_with_few_entries(torch):
     """At a cap of 20 bytes a vertex and 22 an entry, as the no-allocation entry
     documents (28 and 22): enough from 16,385 vertices on."""
