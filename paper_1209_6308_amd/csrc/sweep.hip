@@ -1036,6 +1036,10 @@ struct Tri {
     X &= ~((1u << min(max(r, 0), 8)) - 1u);
     G = G << 8 | g8;
   }
+  // May a counter pass 32 bits with the next item? (A wavefront adds at most 2^30
+  // a lane per item; on a whole chip a lane does not get that far, but the launch
+  // shape of a batch is the caller's.)
+  __device__ __forceinline__ bool full() const { return __ballot(c[0] >> 30) != 0; }
   __device__ __forceinline__ void flush(unsigned long long* acc, int lane) {
     uint64_t s[7];
     for (int k = 0; k < 7; ++k) {
@@ -1096,6 +1100,12 @@ struct TriLab {
     X &= ~((1u << min(max(r, 0), 8)) - 1u);
     G = G << 8 | (g8 & 0xFFu);
     LG = LG << 8 | g8 >> 8;
+  }
+  __device__ __forceinline__ bool full() const {
+    uint32_t o = 0;
+#pragma unroll
+    for (int k = 0; k < 27; ++k) o |= c[k];
+    return __ballot(o >> 30) != 0;
   }
   __device__ __forceinline__ void flush(unsigned long long* acc, int lane) {
 #pragma unroll
@@ -1566,6 +1576,7 @@ __global__ void __launch_bounds__(hub_threads(LAB), LAB ? 4 : 6) k_sw_hubs(Count
     }
     __syncthreads();
     for (uint32_t i = tid; i < plus; i += HUB_THREADS) tab[a.list[s + i] & IDM<LAB>] = 0;
+    if (tri.full()) tri.flush(copy_of<LAB>(a.acc), lane);
   }
   tri.flush(copy_of<LAB>(a.acc), lane);
 }
@@ -1647,6 +1658,7 @@ __global__ void __launch_bounds__(MID_THREADS, LAB ? 4 : 5) k_sw_mids(CountArgs 
         for (int i = tid; i < TAB_WORDS; i += MID_THREADS) high[i] = SLOT_FREE;
       if (fe < plus) __syncthreads();
     }
+    if (tri.full()) tri.flush(copy_of<LAB>(a.acc), lane);
   }
   tri.flush(copy_of<LAB>(a.acc), lane);
 }
@@ -1718,6 +1730,7 @@ __global__ void __launch_bounds__(DENSE_THREADS / (DENSE_WORDS / WORDS), 4) k_sw
       __syncthreads();
     }
     if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
+    else if (tri.full()) tri.flush(copy_of<LAB>(a.acc), lane);
   }
   if (!BAT) tri.flush(copy_of<LAB>(a.acc), lane);
 }
@@ -1892,6 +1905,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
           clear();
           wave_sync();
         }
+        if (BAT && tri.full()) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
       }
       if (done) break;
     }
@@ -2009,6 +2023,7 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
         }
         for (uint32_t i = lane % LR; i < plus; i += LR) mine[(mylist[i] & IDM<LAB>) >> FB<LAB>] = 0;
         wave_sync();
+        if (BAT && tri.full()) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
       }
       if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
     }
