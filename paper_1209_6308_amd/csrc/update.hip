@@ -81,7 +81,11 @@ struct UpdGraph {
 };
 
 // Words the kernels share (zeroed first).
+// U_PARTS is one of 64 bits: every long pair draws a ticket, full queue or not.
 enum { U_ERR = 0, U_NE = 1, U_PARTS = 2, U_WORDS = 4 };
+__device__ __forceinline__ unsigned long long* parts_of(uint32_t* u) {
+  return reinterpret_cast<unsigned long long*>(u + U_PARTS);
+}
 
 // Operation i as two keys (row << rb | column) << 2 | direction << 1 | insert,
 // direction 0 for the arc row -> column.
@@ -481,12 +485,13 @@ template <bool MORE>
 __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
   __shared__ int32_t hist[UT / 64][16 * 64];
   if (A.u[U_ERR]) return;
-  if (MORE && A.u[U_PARTS] == 0) return;
+  const uint64_t listed = MORE ? *parts_of(A.u) : 0;
+  if (MORE && listed == 0) return;
   const int lane = threadIdx.x & 63;
   int32_t* h = hist[threadIdx.x >> 6];
   for (int c = 0; c < 16; ++c) h[c * 64 + lane] = 0;
   const int64_t nw = ((int64_t)gridDim.x * UT) >> 6, nE = A.u[U_NE];
-  const int64_t items = MORE ? (int64_t)min(A.u[U_PARTS], A.room) : nE;
+  const int64_t items = MORE ? (int64_t)min(listed, (uint64_t)A.room) : nE;
   uint64_t steps = 0;
   for (int64_t it = ((int64_t)blockIdx.x * UT + threadIdx.x) >> 6; it < items; it += nw) {
     const int64_t q = MORE ? (int64_t)(A.queue[it] >> 8) : it;
@@ -502,10 +507,8 @@ __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
       pair_changes(A, p, lane, h);
       const int parts = (int)((len + sz - 1) / sz);
       if (parts > 1) {
-        // no ticket is drawn from a full queue: the pairs of one call could wrap it
-        uint32_t at = A.room;
-        if (lane == 0 && __hip_atomic_load(&A.u[U_PARTS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < A.room)
-          at = atomicAdd(&A.u[U_PARTS], (uint32_t)(parts - 1));
+        uint32_t at = 0;
+        if (lane == 0) at = (uint32_t)min((uint64_t)atomicAdd(parts_of(A.u), (unsigned long long)(parts - 1)), (uint64_t)A.room);
         at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
         for (int c = 1 + lane; c < parts; c += 64)
           if ((int64_t)at + c - 1 < A.room) A.queue[at + c - 1] = (uint64_t)q << 8 | (uint64_t)c;
