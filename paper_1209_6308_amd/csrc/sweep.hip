@@ -64,7 +64,11 @@ constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover
 constexpr int hub_threads(bool lab) { return lab ? 512 : 768; }
 constexpr int64_t HUB_MIN_IN = 256;    // in-lists from here on: k_sw_hubs (ranks in its table)
 constexpr int MID_THREADS = 256;
-constexpr int64_t MID_MIN_IN = 32;     // in-lists from here on: k_sw_mids
+// In-lists from here on: k_sw_mids. Chung-Lu 2^22, R-MAT scale 20, R-MAT of 30,000
+// vertices, ms: 32 10.86, 2.12, 0.257; 48 10.07, 2.06, 0.262; 64 9.73, 2.11, 0.266; 128
+// 9.53, 2.13, 0.286. Labelled, scale 20: 24 3.25, 32 3.24, 48 3.31, 64 3.37.
+template <bool LAB>
+constexpr int64_t MID_MIN_IN = LAB ? 32 : 48;
 constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
 constexpr int TAB_WORDS = 1024;        // its slots
@@ -1296,7 +1300,7 @@ template <bool LAB>
 __device__ __forceinline__ uint32_t route(uint32_t rank, uint32_t plus, int64_t minus) {
   if (plus == 0 || minus == 0) return 4;
   if (rank < HUB_RANKS && minus >= HUB_MIN_IN) return 0;
-  if (plus <= TAB_MAX) return minus >= MID_MIN_IN ? 1 : 3;
+  if (plus <= TAB_MAX) return minus >= MID_MIN_IN<LAB> ? 1 : 3;
   if (rank <= HUB_RANKS) return 1;
   const uint32_t high = min(plus, rank - (uint32_t)HUB_RANKS);
   return (high + TAB_MAX - 1) / TAB_MAX > (rank - 1) / DENSE_RANKS<LAB> + 1 ? 2 : 1;
@@ -1330,7 +1334,7 @@ __global__ void __launch_bounds__(256) k_sw_items(CountArgs a) {
         const uint64_t in = a.info[x];
         const uint32_t plus = (uint32_t)in & LEN_MASK;
         const int64_t minus = a.off[x + 1] - (int64_t)(in >> 24) - plus;
-        bool listed = plus && minus && (minus >= (BAT ? DENSE_MIN_IN : MID_MIN_IN) || plus > TAB_MAX);
+        bool listed = plus && minus && (minus >= (BAT ? DENSE_MIN_IN : MID_MIN_IN<LAB>) || plus > TAB_MAX);
         if (BAT && listed) {
           const uint32_t g = a.grow[x];
           listed = dense_member(a.window, plus, minus, (uint32_t)(a.vbase[g + 1] - a.vbase[g]));
@@ -2235,7 +2239,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     // only in-lists of MID_MIN_IN entries (hubs: HUB_MIN_IN) or N+ of more than
     // TAB_MAX make any
     ALLOC(hub_items, std::min(std::min(n, HUB_RANKS), nnz / HUB_MIN_IN) + nnz / CHUNK + 1);
-    ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN + nnz / TAB_MAX) + nnz / CHUNK + 1);
+    ALLOC(mid_items, std::min(n, nnz / MID_MIN_IN<true> + nnz / TAB_MAX) + nnz / CHUNK + 1);
     ALLOC(dense_items, nnz / TAB_MAX + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
