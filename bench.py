@@ -14,7 +14,7 @@ every edge-pair from row sums and visits only those adjacent to both; the merge
 of whole lists, edge-pair by edge-pair, is what the schedules order (`schedules`,
 where `plain` is the merge in CSR order).
 
-Roofline of the listing kernels (k_sw_hubs, k_sw_mids, k_sw_rest, the census
+Roofline of the listing kernels (k_sw_hubs, k_sw_mids, k_sw_dense, k_sw_rest, the census
 stage): bound by vector-instruction issue and by the list bytes read past L2.
 `roofline` reports the vector unit: achieved = SQ_INSTS_VALU per census
 (rocprofv3 counter, profiles/counters_listing_<workload>.json, valid while the
@@ -460,7 +460,7 @@ def census_roofline(workload, kern_s, d_off, d_nbr, n):
     hbm = {"peak_gbs": HBM_PEAK_GBS, "candidates": cand, "alg_bytes": 4.0 * cand,
            "frac_alg": round(4.0 * cand / kern_s / 1e9 / HBM_PEAK_GBS, 4), "past_l2_bytes": None, "frac_past_l2": None}
     roof = {"bound": "alu", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "Tops/s", "frac": None,
-            "traffic": None, "kernel": "k_sw_hubs + k_sw_mids + k_sw_rest", "kernel_ms": round(kern_s * 1e3, 2),
+            "traffic": None, "kernel": "k_sw_hubs + k_sw_mids + k_sw_dense + k_sw_rest", "kernel_ms": round(kern_s * 1e3, 2),
             "peak_basis": "vector issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, 32-bit lane-ops",
             "counters": None, "hbm": hbm}
     cfile = os.path.join(ROOT, "profiles", f"counters_listing_{workload}.json")

@@ -102,7 +102,9 @@ typedef struct triad_timing {
 typedef struct triad_opts {
   int32_t schedule;        /* enum triad_schedule */
   int32_t validate;        /* 0 = O(nnz) checks of ranges, flags, order and self-loops
-                              (default), 1 = also symmetry and flag mirroring */
+                              (default; a graph that turns out one-sided on the way
+                              is refused with TRIAD_EASYM as well), 1 = also symmetry
+                              and flag mirroring */
   int64_t hub_threshold;   /* tasks with d(u)+d(v) above this are split into chunks
                               merged by different wavefronts; 0 = default, < 0 = never */
   int64_t chunk;           /* merge entries per chunk of a split task; 0 = default */
@@ -197,7 +199,10 @@ int triad_validate_host(int64_t n, const int64_t *csr_offsets, const int32_t *cs
  * neighbour ids are graph-local (0 .. vbase[g+1]-vbase[g]-1). Each graph must
  * satisfy the single-graph contract and have fewer than 4,801,281 vertices.
  * A plan owns the scratch memory and a captured hipGraph of the whole batched
- * census (one persistent launch); launching it replays the graph on a stream.
+ * census (kernels only); launching it replays the graph on a stream, on the
+ * arrays' contents of that moment (the graph bases still within the bounds that
+ * creation checked). Launches share the scratch: one after another, or on
+ * streams that are ordered.
  * d_out receives G x 16 uint64 (graph-major). */
 typedef struct triad_batch_plan triad_batch_plan;
 
@@ -216,7 +221,7 @@ int triad_census_batch(int32_t G, int64_t nv, int64_t nnz, const int64_t *d_vbas
 
 /* Autotuner for the batched census: times the candidate launch shapes on the
  * given batch with HIP events and returns the fastest in *best (its
- * waves_per_group, grid_groups, hub_threshold and chunk fields are set).
+ * kernel_variant, waves_per_group and grid_groups fields are set).
  * If cache_path is not NULL the result is read from / appended to that JSON
  * lines file, keyed by the device name and a signature of the batch. */
 int triad_batch_autotune(int32_t G, int64_t nv, int64_t nnz, const int64_t *d_vbase, const int64_t *d_offsets,
@@ -336,16 +341,16 @@ int triad_version(void);
 int triad_set_memory_cap(int64_t bytes);
 
 /* Held device memory. A batch plan's scratch is one such block, given back when
- * the plan is destroyed (after its last launch has finished). The census entry
- * points that allocate
- * (triad_census_device, triad_labelled_census_device), triad_csr_from_arcs
+ * the plan is destroyed (after its launches have finished). The census entry
+ * points that allocate (triad_census, triad_census_ex with their copies of the
+ * input, triad_census_device, triad_labelled_census_device), triad_csr_from_arcs
  * and triad_census_update wait for their stream before they return. When the
  * stream belongs to the current device, their scratch blocks are then kept by
  * the library, per device, and reused by later calls that need a block of at
  * least the same size and at most twice it (sizes rounded up to 256 B, and to
  * whole MiB from 1 MiB on), instead of being freed and allocated again (at
- * R-MAT scale 24 a census takes about 15 GB of scratch, whose release alone
- * costs milliseconds); a stream of another device gets stream-ordered
+ * R-MAT scale 24 a census takes about 6.8 GB of scratch, by the merge 15 GB,
+ * whose release alone costs milliseconds); a stream of another device gets stream-ordered
  * allocations on that device, freed on return. At most
  * 64 GiB of free blocks are kept per device; an allocation that finds the
  * device out of memory frees that device's held blocks and tries again.

@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(ST) k_bp_split1(Bp a, int64_t per, const uint3
       if (x[k] != y[k]) {
         const uint32_t r0 = atomicAdd(&cnt[digit1(a, mix(a, x[k]))], 1u);
         const uint32_t r1 = atomicAdd(&cnt[digit1(a, mix(a, y[k]))], 1u);
-        rank[k] = r0 | r1 << 16;  // below 8,192
+        rank[k] = r0 | r1 << 16;  // below 16,384 (both ends of an arc may share a digit)
       }
     }
     __syncthreads();

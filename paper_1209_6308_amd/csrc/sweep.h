@@ -9,7 +9,7 @@
 
 namespace triad {
 
-// Device counters of one sweep (64-bit words, zeroed by sweep_begin):
+// Device counters of one sweep (64-bit words, zeroed by its first kernel):
 // acc[0..15] the 16 classes as signed sums (triangle classes exact, the open
 // and dyadic classes before the triangles' share is taken out; see sums.h), then
 constexpr int SW_ABOVE = 17;  // entries above their row's own id
@@ -17,7 +17,8 @@ constexpr int SW_WORDS = 32;
 constexpr int SW_COPIES = 64;
 // labelled: the 64 states, then the entries above
 constexpr int SW_LAB_ABOVE = 64, SW_LAB_WORDS = 80;
-// err[0]: raised by the row checks, err[1]: by the entry checks, err[2]: later
+// err[0]: raised by the row checks, err[1]: by the entry checks, err[2]: by the
+// symmetry check and k_sw_pack
 constexpr int SW_ERRS = 4;
 
 constexpr int SW_CLK = 66, SW_STATUS = SW_CLK + 5;

@@ -11,9 +11,10 @@
 // highest degree), and for a vertex y the list N+(x) of every x below y is
 // streamed against the set N+(y). The merge reads sum_x d(x)^2 list entries
 // (3.57e12 at R-MAT scale 24), this reads sum_x d+(x)^2 / 2 (4.2e10). A whole
-// call took 1,560 ms there by the merge and takes 43.5 ms; 37.0 and 2.31 ms at
-// R-MAT scale 20, 469 and 13.1 ms on the Chung-Lu graph of 2^22 vertices, 566
-// and 79 us at R-MAT scale 10.
+// call took 1,560 ms there by the merge and takes 42.2 ms; 37.0 and 2.07 ms at
+// R-MAT scale 20, 469 and 10.1 ms on the Chung-Lu graph of 2^22 vertices, 566
+// and 79 us at R-MAT scale 10, 24.1 and 7.4 ms on a grid of 2^25, 1,470 and 313 ms
+// on 300,007 vertices of degree 3,000.
 //
 // Pipeline (one stream, no host synchronisation inside):
 //   k_sw_rows    per row: offset checks, row starts, degree histogram
@@ -31,15 +32,16 @@
 //                byte table over the ranks and streams the N+(x)
 //   k_sw_mids    in-lists of middling length: a smaller workgroup, 2-bit table
 //   k_sw_dense   long N+ past the ranks of that table: one of 524,288 ranks
-//   k_sw_rest    all others: one wavefront and a hash table in LDS
+//   k_sw_rest    all others: up to 16 a wavefront, hash tables in LDS
 //   k_sw_small   graphs of up to 16,384 vertices instead of the last three: lists
 //                in ids, several rows a wavefront, a table field per id
 //   k_sw_finish  classes from sums, 003 = C(n,3) less the rest
 // A batch of graphs goes through k_sw_rows, k_sw_orient, k_sw_cross, k_sw_small
-// as one disjoint union with ids local to each graph, its counters by graph
+// (k_sw_items, k_sw_dense and k_sw_rest where a member is larger) as one disjoint
+// union with ids local to each graph, its counters by graph
 // (4,096 graphs of 64 to 8,192 vertices, 3e8 edges: 121 -> 16.7 ms a launch; 256
 // graphs of up to 1,024, plan, launch and z-scores: 4.3 -> 0.37 ms). The labelled
-// census adds k_lab_sums (54.7 -> 3.6 ms at R-MAT scale 20).
+// census adds k_lab_sums (54.7 -> 3.25 ms at R-MAT scale 20).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,18 +60,27 @@ constexpr int LONG_KEEP = 256;  // rows with long N+ kept in LDS before they are
 constexpr int TILE_GRAPHS = 8;  // graphs of a batch whose sums a tile keeps in LDS
 constexpr int ROWS_THREADS = 1024;  // of the ranking kernels, 4 or 16 rows a thread
 constexpr int BUCKETS = 1024;          // degree buckets of the ranking
-constexpr int64_t DIRECT_N = 16384;    // graphs up to here index their tables by vertex id
-constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover
+// Graphs up to here index their tables by vertex id, without ranks and sorts: R-MAT
+// of 16,000 vertices 0.107 ms, ranked 0.223; of 9,001 0.095 and 0.205. The tables
+// of two rows a wavefront then fill the LDS of four workgroups a CU. (Tables of
+// 32,768 ids, two workgroups a CU, would take 30,000 vertices in 0.162 instead of 0.258
+// ms, and, used for all, 16,000 in 0.119.)
+constexpr int64_t DIRECT_N = 16384;
+constexpr int64_t HUB_RANKS = 65536;   // ranks the workgroup tables cover (k_sw_pack: 16 bits)
 // two workgroups a CU: six wavefronts a SIMD, four with the labels' counters
 constexpr int hub_threads(bool lab) { return lab ? 512 : 768; }
-constexpr int64_t HUB_MIN_IN = 256;    // in-lists from here on: k_sw_hubs (ranks in its table)
+// In-lists from here on: k_sw_hubs (ranks in its table). R-MAT scale 24, scale 20,
+// labelled scale 20, ms: 128 42.3, 2.13, 3.42; 256 42.2, 2.12, 3.24; 512 42.3, 2.11, 3.24.
+constexpr int64_t HUB_MIN_IN = 256;
 constexpr int MID_THREADS = 256;
 // In-lists from here on: k_sw_mids. Chung-Lu 2^22, R-MAT scale 20, R-MAT of 30,000
 // vertices, ms: 32 10.86, 2.12, 0.257; 48 10.07, 2.06, 0.262; 64 9.73, 2.11, 0.266; 128
 // 9.53, 2.13, 0.286. Labelled, scale 20: 24 3.25, 32 3.24, 48 3.31, 64 3.37.
 template <bool LAB>
 constexpr int64_t MID_MIN_IN = LAB ? 32 : 48;
-constexpr int64_t CHUNK = 2048;        // in-list entries of one of their work items
+// In-list entries of one of their work items. R-MAT scale 24, scale 20, ms: 1,024 43.6,
+// 2.14; 2,048 42.2, 2.12; 4,096 42.2, 2.13.
+constexpr int64_t CHUNK = 2048;
 constexpr uint32_t TAB_MAX = 512;      // entries of one hash table
 constexpr int TAB_WORDS = 1024;        // its slots
 // threads and table of k_sw_dense's workgroups: one a CU, or four (batches of smaller members)
@@ -293,7 +304,7 @@ __device__ __forceinline__ uint64_t below(int k) { return (1ull << k) - 1; }  //
 // dependent reads of a tile are its entries, then the keys of their ends
 // (tiles of 4,096 entries with a search and three row reads per segment in
 // turn, at 2 wavefronts per SIMD: 11.4 ms at R-MAT scale 24 and 13.7 ms on the
-// 4,096-graph batch, now 9.6 and 5.9; bound by the random reads of the keys).
+// 4,096-graph batch, now 6.2 and 5.4; bound by the random reads of the keys).
 // Five wavefronts per SIMD hide more of them than three without spills.
 // RANK: lists hold ranks, else ids. BAT: a batch (ids). LAB: labelled words,
 // the sums are k_lab_sums'.
@@ -1774,13 +1785,14 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
 
 // The other vertices of a ranked graph (RANK), and all vertices of a batch with
 // members above DIRECT_N that k_sw_dense does not take: a wavefront takes a range
-// of entries and the rows whose in-lists lie in it, up to 16 of at most 32
-// entries of N+(y) at once (4 of at most 128), each with its share of the hash
-// table, their in-lists of up to 64 entries in all as one list whose x carry
-// their row's table. Longer ones go alone, the table filled TAB_MAX entries at a
-// time. One row at a time spent its time on the dependent reads of two or three
-// entries: slower than the merge on graphs of low degree. BAT: a batch, counted
-// by graph.
+// of entries and the rows whose in-lists lie in it, up to 16 at once, each with
+// its share of the hash table (at most a quarter full), their in-lists of up to 64
+// entries in all as one list whose x carry their row's table. Longer ones go alone,
+// the table filled TAB_MAX entries at a time (at most half full). Bound by the
+// dependent reads of short lists: one row at a time took 33 of 37.4 ms on a grid of
+// 2^25 vertices (24.1 in all by the merge), now 3.1 of 7.4; 3.8 and 3.0 ms at R-MAT
+// scale 24. Four wavefronts a SIMD (three: Chung-Lu 2^22 10.85 -> 11.09 ms); with
+// labels three, where four spill 30 registers. BAT: a batch, counted by graph.
 template <bool RANK, bool BAT, bool LAB, bool WIDE>
 __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountArgs a) {
   __shared__ alignas(16) uint32_t tabs[REST_WAVES][TAB_WORDS];
@@ -2245,7 +2257,8 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
                    tile_row, err, 0, nullptr, nullptr, 0, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
   // (16 rows a thread: fewer atomics on the bucket counters; 4 while that
-  // leaves fewer workgroups than four a CU)
+  // leaves fewer workgroups than four a CU. 2^26 vertices in 2^25 pairs: 6.02 ms
+  // with 16, 6.60 with 4; 2^24, R-MAT: 42.3 and 42.2)
   const bool many = n > (int64_t)di.cus * 4 * ROWS_THREADS * 16;
   const unsigned rgrid = grid_of_work(n, ROWS_THREADS * (many ? 16 : 4), INT32_MAX);
   if (!rank) k_sw_rows<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ra);
@@ -2294,6 +2307,8 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
       k_sw_orient<true, false, LAB><<<ogrid, OTHREADS, 0, s>>>(oa);
       k_sw_cross<true, false, LAB><<<cgrid, 256, 0, s>>>(oa);
       k_sw_items<false, LAB><<<grid_of_work(n, 4096, 4096), 256, 0, s>>>(ca);
+      // (2^24 vertices 42.2 ms with 8 a thread, 42.6 with one; 600,011 1.11 and 1.12;
+      // 300,007 0.876 and 0.848)
       if (pack && n > 1 << 19) k_sw_pack<8><<<grid_of_work(n, 2048, INT32_MAX), 256, 0, s>>>(ca);
       else if (pack) k_sw_pack<1><<<grid_of_work(n, 256, INT32_MAX), 256, 0, s>>>(ca);
       const Packed pk{pack ? ca.prow : nullptr, ca.pack, ca.counts + 2};

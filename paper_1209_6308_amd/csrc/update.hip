@@ -49,7 +49,6 @@ constexpr int64_t UPD_PART = 1024;   // entries of the shorter row that one wave
 constexpr int64_t UPD_PARTS = 64;    // parts of one pair at most
 constexpr int64_t UPD_QUEUE = 1 << 18;  // parts put off at most
 
-__device__ __forceinline__ uint32_t mirror2(uint32_t f) { return ((f & 1u) << 1) | (f >> 1); }
 __device__ __forceinline__ uint32_t entry_flag(const uint8_t* flg, int64_t j) {
   return (flg[j >> 2] >> (2 * (j & 3))) & 3u;
 }
@@ -440,7 +439,7 @@ __device__ void pair_changes(const DeltaArgs& A, const Pair& p, int lane, int32_
   }
 }
 
-__device__ __forceinline__ Pair pair_of(const DeltaArgs& A, int64_t q, int64_t nE) {
+__device__ __forceinline__ Pair pair_of(const DeltaArgs& A, int64_t q) {
   const UpdGraph& g = A.g;
   const uint64_t ent = A.E[q];
   Pair p;
@@ -495,7 +494,7 @@ __global__ void __launch_bounds__(UT) k_upd_pairs(DeltaArgs A) {
   uint64_t steps = 0;
   for (int64_t it = ((int64_t)blockIdx.x * UT + threadIdx.x) >> 6; it < items; it += nw) {
     const int64_t q = MORE ? (int64_t)(A.queue[it] >> 8) : it;
-    Pair p = pair_of(A, q, nE);
+    Pair p = pair_of(A, q);
     if (!MORE && p.b < p.a) continue;
     pair_ranges(A, p, nE, lane);
     const int64_t len = min(p.ea - p.oa, p.eb - p.ob), sz = part_size(len);
