@@ -163,8 +163,6 @@ struct RowArgs {
   int32_t graphs;
   const int64_t* vbase;
   uint32_t* grow;
-  int64_t small;  // the largest member that k_sw_small's tables take (0: it is not launched)
-  uint32_t* big;  // set where a member is larger
   // labelled: the entries below the row's own id, for rows that cross tiles
   const int32_t* nbr;
   struct Cross* cross;
@@ -204,7 +202,6 @@ __global__ void __launch_bounds__(PER > 1 ? ROWS_THREADS : 256) k_sw_rows(RowArg
         if (a.vbase[mid] <= u) lo = mid; else hi = mid;
       }
       a.grow[u] = (uint32_t)lo;
-      if (a.small && a.vbase[lo + 1] - a.vbase[lo] > a.small) *a.big = 1;
     }
     if (a.deg) a.deg[u] = d;
     if (PER > 1) atomicAdd(&h[BUCKETS - 1 - degree_bucket(d)], 1u);
@@ -1284,9 +1281,9 @@ struct CountArgs {
   const uint32_t* tile_row;
   uint64_t* items[3];  // of k_sw_hubs, k_sw_mids, k_sw_dense: y << 32 | chunk
   uint64_t* clk;       // stage starts, or NULL
-  uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed, [9] see RowArgs::big
+  uint32_t* counts;    // [2 .. 4] items listed, [5 .. 7] items taken, [8] units packed
   int64_t range;       // k_sw_rest: entries of one wavefront
-  uint32_t window;     // a batch: ids of k_sw_dense's table (0: it is not launched)
+  uint32_t window;     // a batch: ids of k_sw_dense's table
   unsigned long long* acc;
   uint32_t* err;
   // a batch (see OrientArgs)
@@ -1804,7 +1801,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
     uint32_t plus, num, key;  // their lengths; the rank or the graph
   };
   __shared__ Row kept[REST_WAVES][64];  // (in registers, they spill in every step over the rows)
-  if (refused(a.err) || (BAT && a.window == 0 && a.counts[9] == 0)) return;
+  if (refused(a.err)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t *tab = tabs[w], *mark = marks[w], *row = rows[w], *yranks = ranks[RANK ? w : 0];
   XList<WIDE>& L = xl[w];
@@ -1839,7 +1836,7 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
           }
           if (BAT) {
             key = a.grow[r + lane];
-            if (a.window && (plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
+            if ((plus > TAB_MAX || e - bs >= DENSE_MIN_IN) &&
                 dense_member(a.window, plus, e - bs, (uint32_t)(a.vbase[key + 1] - a.vbase[key])))
               num = 0;
           }
@@ -1930,31 +1927,14 @@ __global__ void __launch_bounds__(REST_WAVES * 64, LAB ? 3 : 4) k_sw_rest(CountA
   else tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
-// Graphs and batch members of up to N vertices, lists in ids: a wavefront takes
-// a range of entries and R rows at a time, 64 / R lanes each filling that row's
-// table of N+(y) (a field per id), then the R in-lists as one list whose x carry
-// their row's table: short rows fill the steps of one stream together, and
-// their dependent reads overlap. (One row at a time: 17.3 ms on the 4,096-graph
-// batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10,
-// and 10.3 with longer turns and the loads of stream() ahead of its count.
-// Bound by vector issue on the large batch, by the reads' latency on small ones.)
-// WAVES: a batch plan's launch shape; tables for as many as the workgroup has
-// (with tables for four, workgroups of two took 26 ms on the large batch).
-template <int N, int R, bool BAT, bool LAB, bool WIDE, int WAVES>
-__global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_small(CountArgs a) {
+// One walk of k_sw_small over a wavefront's ranges. LARGE: the members of a batch
+// past the tables, their ids N at a time; else the others (true if it met such).
+template <int N, int R, bool BAT, bool LAB, bool WIDE, bool LARGE, class T>
+__device__ __forceinline__ bool small_walk(const CountArgs& a, uint32_t* tab, XList<WIDE>& L, T& tri, uint32_t& graph,
+                                           int lane, int w) {
   constexpr int TW = N >> FB<LAB>, LR = 64 / R;  // words of one table, lanes of one row
-  __shared__ uint32_t tabs[WAVES][R * TW];
-  __shared__ XList<WIDE> xl[WAVES];
-  stamp(a.clk, 1);
-  stamp(a.clk, 2);
-  if (refused(a.err) || (BAT && a.counts[9])) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t* tab = tabs[w];
   uint32_t* mine = tab + lane / LR * TW;
-  XList<WIDE>& L = xl[w];
-  for (int i = lane; i < R * TW; i += 64) tab[i] = 0;
-  typename std::conditional<LAB, TriLab, Tri>::type tri;
-  uint32_t graph = 0;
+  bool large = false;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
   for (int64_t j0 = ((int64_t)xcd_block() * (blockDim.x >> 6) + w) * a.range; j0 < a.nnz; j0 += nw * a.range) {
     const int64_t j1 = min(j0 + a.range, a.nnz);
@@ -1977,13 +1957,21 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
       uint64_t todo = __ballot(num > 0);
       while (todo) {
         const uint64_t* info = a.info;
+        uint32_t ids = 0;
         if (BAT) {
           const uint32_t g = rl(gr, __builtin_ctzll(todo));
           if (g != graph) {
             tri.flush(a.gacc + (uint64_t)graph * 16, lane);
             graph = g;
           }
-          info += a.vbase[graph];
+          const int64_t base = a.vbase[graph], ng = a.vbase[graph + 1] - base;
+          if ((ng > N) != LARGE) {
+            large = true;
+            todo &= ~__ballot(gr == graph);
+            continue;
+          }
+          ids = (uint32_t)ng;
+          info += base;
         }
         // the next R rows (of one graph): lanes LR q .. take the q-th
         int src = -1;
@@ -2005,57 +1993,102 @@ __global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_smal
         const uint64_t yi = __shfl(in, max(src, 0), 64);
         const uint32_t plus = src < 0 ? 0u : (uint32_t)yi & LEN_MASK;
         const uint32_t* mylist = a.list + (yi >> 24);
-        for (uint32_t i = lane % LR; i < plus; i += LR) set_bits<LAB>(mine, mylist[i]);
-        wave_sync();
-        for (uint32_t k = 0; k < total; k += 64) {
-          const uint32_t p = k + lane;
-          uint32_t q = 0, g = 0;
-          uint64_t xi = 0, from = at[0];
+        uint32_t first = 0;  // of the ids in the table
+        do {
+          for (uint32_t i = lane % LR; i < plus; i += LR)
+            if (!LARGE || (mylist[i] & IDM<LAB>) - first < (uint32_t)N) set_bits<LAB>(mine, mylist[i] - first);
+          wave_sync();
+          for (uint32_t k = 0; k < total; k += 64) {
+            const uint32_t p = k + lane;
+            uint32_t q = 0, g = 0;
+            uint64_t xi = 0, from = at[0];
 #pragma unroll
-          for (int i = 1; i < R; ++i)
-            if (p >= end[i - 1]) {
-              q = i;
-              from = at[i];
+            for (int i = 1; i < R; ++i)
+              if (p >= end[i - 1]) {
+                q = i;
+                from = at[i];
+              }
+            if (p < total) {
+              g = a.list[from + p];
+              xi = info[g & IDM<LAB>];
             }
-          if (p < total) {
-            g = a.list[from + p];
-            xi = info[g & IDM<LAB>];
-          }
-          const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
-          const uint64_t m = __ballot(has);
-          if (has) {
-            const int i = __popcll(m & below(lane));
-            L.p[i] = xi >> 24 << 2;
-            L.m[i] = (g & ~IDM<LAB>) | q << 24 | ((uint32_t)xi & LEN_MASK);
-          }
-          wave_sync();
-          stream<8, false, true, WIDE, true>(a.list, L, __popcll(m), 0, lane, tri,
-                                             [&](const uint32_t (&q)[4], uint32_t (&f)[4], uint32_t t) {
-            const uint32_t* mt = tab + t * TW;
+            const bool has = ((uint32_t)xi & LEN_MASK) >= 2;
+            const uint64_t m = __ballot(has);
+            if (has) {
+              const int i = __popcll(m & below(lane));
+              L.p[i] = xi >> 24 << 2;
+              L.m[i] = (g & ~IDM<LAB>) | q << 24 | ((uint32_t)xi & LEN_MASK);
+            }
+            wave_sync();
+            stream<8, false, true, WIDE, true>(a.list, L, __popcll(m), 0, lane, tri,
+                                               [&](const uint32_t (&q)[4], uint32_t (&f)[4], uint32_t t) {
+              const uint32_t* mt = tab + t * TW;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) f[i] = probe_bits<TW, LAB>(mt, q[i]);
-          });
+              for (int i = 0; i < 4; ++i) {
+                if constexpr (LARGE) {
+                  const uint32_t z = (q[i] & IDM<LAB>) - first;
+                  f[i] = z < (uint32_t)N ? probe_bits<TW, LAB>(mt, z) : 0u;
+                } else {
+                  f[i] = probe_bits<TW, LAB>(mt, q[i]);
+                }
+              }
+            });
+            wave_sync();
+          }
+          for (uint32_t i = lane % LR; i < plus; i += LR) {
+            const uint32_t z = (mylist[i] & IDM<LAB>) - first;
+            if (!LARGE || z < (uint32_t)N) mine[z >> FB<LAB>] = 0;
+          }
           wave_sync();
-        }
-        for (uint32_t i = lane % LR; i < plus; i += LR) mine[(mylist[i] & IDM<LAB>) >> FB<LAB>] = 0;
-        wave_sync();
+        } while (LARGE && (first += N) < ids);
         if (BAT && tri.full()) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
       }
       if (rl64((uint64_t)e, 63) >= (uint64_t)j1 || r + 64 >= a.n) break;
     }
+  }
+  return large;
+}
+
+// Graphs and batch members of up to N vertices, lists in ids: a wavefront takes
+// a range of entries and R rows at a time, 64 / R lanes each filling that row's
+// table of N+(y) (a field per id), then the R in-lists as one list whose x carry
+// their row's table: short rows fill the steps of one stream together, and
+// their dependent reads overlap. (One row at a time: 17.3 ms on the 4,096-graph
+// batch, 0.19 ms on 256 graphs of up to 1,024 vertices; R rows: 12.3 and 0.10,
+// and 10.3 with longer turns and the loads of stream() ahead of its count.
+// Bound by vector issue on the large batch, by the reads' latency on small ones.)
+// WAVES: a batch plan's launch shape; tables for as many as the workgroup has
+// (with tables for four, workgroups of two took 26 ms on the large batch).
+template <int N, int R, bool BAT, bool LAB, bool WIDE, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, LAB && N > 4096 ? 2 : 4) k_sw_small(CountArgs a) {
+  constexpr int TW = N >> FB<LAB>;
+  __shared__ uint32_t tabs[WAVES][R * TW];
+  __shared__ XList<WIDE> xl[WAVES];
+  stamp(a.clk, 1);
+  stamp(a.clk, 2);
+  if (refused(a.err)) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t* tab = tabs[w];
+  XList<WIDE>& L = xl[w];
+  for (int i = lane; i < R * TW; i += 64) tab[i] = 0;
+  typename std::conditional<LAB, TriLab, Tri>::type tri;
+  uint32_t graph = 0;
+  const bool large = small_walk<N, R, BAT, LAB, WIDE, false>(a, tab, L, tri, graph, lane, w);
+  // A plan's launches read the graph bases as they are then: they may have been
+  // rewritten with a member past the tables.
+  if constexpr (BAT) {
+    if (large) small_walk<N, R, BAT, LAB, WIDE, true>(a, tab, L, tri, graph, lane, w);
   }
   if (BAT) tri.flush(a.gacc + (uint64_t)graph * 16, lane);
   else tri.flush(copy_of<LAB>(a.acc), lane);
 }
 
 // k_sw_small by the largest member: tables of 8 KB a wavefront in all (labelled
-// 16 KB), so that four workgroups fit a CU's LDS. The members that fit: 0 if k_sw_rest
-// takes the batch.
-int64_t small_table(int64_t nmax) { return nmax <= 4096 ? 4096 : nmax <= 8192 ? 8192 : nmax <= DIRECT_N ? DIRECT_N : 0; }
+// 16 KB), so that four workgroups fit a CU's LDS.
 template <bool BAT, bool LAB, bool WIDE, int WAVES>
 void launch_small_of(int64_t nmax, unsigned grid, const CountArgs& ca, hipStream_t s) {
-  if (small_table(nmax) == 4096) k_sw_small<4096, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
-  else if (small_table(nmax) == 8192) k_sw_small<8192, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  if (nmax <= 4096) k_sw_small<4096, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
+  else if (nmax <= 8192) k_sw_small<8192, 4, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
   else k_sw_small<DIRECT_N, 2, BAT, LAB, WIDE, WAVES><<<grid, WAVES * 64, 0, s>>>(ca);
 }
 template <bool BAT, bool LAB, bool WIDE>
@@ -2255,7 +2288,7 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
     ALLOC(dense_items, nnz / TAB_MAX + nnz / CHUNK + 1);
   }
   const RowArgs ra{n, nnz, in.off, rank ? nullptr : key, rank ? zero + w_hist : nullptr, info, list, zero + w_mark,
-                   tile_row, err, 0, nullptr, nullptr, 0, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
+                   tile_row, err, 0, nullptr, nullptr, in.nbr, labelled ? (Cross*)(zero + w_cross) : nullptr};
   // (16 rows a thread: fewer atomics on the bucket counters; 4 while that
   // leaves fewer workgroups than four a CU. 2^26 vertices in 2^25 pairs: 6.02 ms
   // with 16, 6.60 with 4; 2^24, R-MAT: 42.3 and 42.2)
@@ -2398,7 +2431,7 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
   k_sw_zero<<<grid_of_work(z.zero_words, 1024, 2048), 256, 0, s>>>(zero, z.zero_words, nullptr);
   if (nv > 0) {
     const RowArgs ra{nv, nnz, in.off, key, nullptr, info, list, zero + z.w_mark, tile_row, err, graphs, vbase, grow,
-                     small_table(nmax), zero + z.w_cnt + 9, nullptr, nullptr};
+                     nullptr, nullptr};
     k_sw_rows<1><<<grid_of_work(nv, 256, INT32_MAX), 256, 0, s>>>(ra);
   }
   if (nv > 0 && nnz > 0) {
@@ -2423,11 +2456,6 @@ int sweep_batch(int32_t graphs, int64_t nv, const SweepIn& in, const int64_t* vb
       constexpr bool W = decltype(wide)::value;
       if (nmax <= DIRECT_N) {
         launch_small<true, false, W>(nmax, grid, waves, ca, s);
-        // A plan's launches read the graph bases as they are then: if they were
-        // rewritten with a member past these tables, k_sw_small leaves the batch to
-        // this one (else 3 us).
-        ca.window = 0;
-        k_sw_rest<false, true, false, W><<<grid, waves * 64, 0, s>>>(ca);
       } else {
         k_sw_items<true, false><<<grid_of_work(nv, 4096, 4096), 256, 0, s>>>(ca);
         if (low) k_sw_dense<true, false, W, DENSE_LOW><<<(unsigned)di.cus * 4, DENSE_THREADS / 4, 0, s>>>(ca);
