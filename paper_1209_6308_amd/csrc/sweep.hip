@@ -2391,8 +2391,13 @@ struct BatchSizes {
     };
     place(2 * SW_WORDS * SW_COPIES);  // acc first
     w_err = place(SW_ERRS);
-    w_cnt = place(10);
+    // Atomics on 64 bytes queue: a graph's triangle counters (8, 9, 11 .. 15) fall
+    // three and four into two such pieces when the first counter is 32 bytes into
+    // one (85 graphs of up to 455 vertices 92 us; at 48 bytes, two and five, 97; at 56
+    // 105; at 0, all seven, 112; 64 of up to 4,000: 190, 212, 219, 237).
+    w_cnt = place(20);
     w_gacc = place(32 * (int64_t)graphs);
+    static_assert((2 * SW_WORDS * SW_COPIES + SW_ERRS + 20) % 16 == 8, "see above");
     w_cross = place((ntiles + 1) * (int64_t)(sizeof(Cross) / 4));
     w_mark = place(ntiles * (OT / 32));
   }
