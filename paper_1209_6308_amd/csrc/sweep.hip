@@ -2312,10 +2312,10 @@ int sweep_census(const SweepIn& in, bool validate, bool labelled, unsigned long 
   CountArgs ca{n, nnz, ntiles, in.off, list, info, key, tile_row, {hub_items, mid_items, dense_items}, clk, zero + w_cnt, 0, 0, acc, err,
                nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   // N+ packed for the hubs: at most as many units as entries (two for two; half
-  // of all of them in a symmetric graph), whose byte offsets take 32 bits. Packing takes 10 us more than it saves up to 2 M
-  // entries (60,001 vertices, R-MAT: 322 -> 328 us); from there on it gains
-  // (6.3 M: 630 -> 619, 16 M: 1,242 -> 1,160 us, 33 M: 2.64 -> 2.35 ms). With
-  // fewer than two entries a vertex its scratch could pass the documented bound.
+  // of all of them in a symmetric graph), whose byte offsets take 32 bits. R-MAT, by
+  // entries, not packed / packed, us: 1.7 M 304 / 316, 3.4 M 434 / 441, 5.4 M 541 /
+  // 543, 7.6 M 690 / 672, 14.8 M 1,154 / 1,077, 31 M 2,338 / 2,053; 521 M 51.2 / 42.2
+  // ms. With fewer than two entries a vertex its scratch could pass the documented bound.
   const bool pack = rank && !labelled && nnz >= 2 * n && nnz >= PACK_MIN && nnz < (int64_t)1 << 29;
   if (pack) {
     ALLOC(ca.prow, n);

@@ -15,7 +15,7 @@
 //     RB | b). The w adjacent to both a and b before come from the shorter of the
 //     two rows searched in the longer; the others are among the changes of a or
 //     b. (Merging both rows of every changed pair took 6.5 of 8.2 ms per 100,000
-//     updates on 112 M entries, R-MAT; row sums, pairs and parts now 1.3 ms. Bound
+//     updates on 90 M entries, R-MAT; row sums, pairs and parts now 1.3 ms. Bound
 //     by the latency of the searches' dependent reads.)
 // The classes come from the 64-state table of the census (Fig. 5 step
 // 2.1.4.1). The null count stays C(n,3) minus the rest.
@@ -542,7 +542,7 @@ __global__ void k_new_offsets(UpdGraph g, const uint64_t* __restrict__ E, const 
 // follows), and between two of them the old entries move by one shift. A tile
 // of places finds its changed entries by two searches and stages them in LDS;
 // a thread writes four ids and their flag byte. (By old entry, with the flags as
-// bytes and a pass to pack them: 1.0 ms per 100,000 updates on 112 M entries;
+// bytes and a pass to pack them: 1.0 ms per 100,000 updates on 90 M entries;
 // now 0.28.)
 constexpr int CT = 4096, CSTAGE = 1024;
 __global__ void __launch_bounds__(UT) k_upd_copy(UpdGraph g, const uint64_t* __restrict__ E,
